@@ -45,6 +45,8 @@ ALGO_BYTES = {
         "velocity_line_x": 16,   # read sigma, v1, b; write v1
         "velocity_line_z": 16,   # read sigma, v3, b; write v3
         "velocity_stress_x": 20,  # read sigma, v1, b; write v1 and T = d(v1 new)/dx
+        "stress_tile_xz": 20,    # read v1, v3, sigma, K; write sigma
+        "velocity_tile_xz": 24,  # read sigma, v1, v3, b; write v1, v3
     },
     1: {  # elastic stress passes: x stores d1 v1, d1 v2, d1 v3 (read v, write T: 8 B each);
           # y stores d2 v2, d2 v3 (8 B each) and adds mu (d2 v1 + T) to sigma12 (read v1,
@@ -55,6 +57,10 @@ ALGO_BYTES = {
           # sigma_i3, T, v_i, b; write v_i: 20 B)
         "stress_line_x": 24 / 3, "stress_line_y": 36 / 3, "stress_line_z": 84 / 3,
         "velocity_line_x": 8, "velocity_line_y": 12, "velocity_line_z": 20,
+        # tile schedule: three z derivatives stored per launch (read, write: 8 B each); the
+        # stress tiles read v, T (12 B each), 6 sigma, lambda, mu, lambda+2mu and write 6
+        # sigma; the velocity tiles read s11 s12 s22 s13 s23, T, v, b and write v
+        "stress_store_z": 24, "velocity_store_z": 24, "stress_tile_xy": 84, "velocity_tile_xy": 60,
     },
 }
 STEP_BYTES = {0: 44, 1: 120}   # compulsory bytes per cell-step (whole step)

@@ -89,17 +89,19 @@ typedef int32_t loss_status;
 
 /* desc.flags */
 #define LOSS_FLAG_NO_GRAPH 1   /* launch every step eagerly instead of replaying a hipGraph */
-#define LOSS_FLAG_NO_FUSE_X 2  /* acoustic: keep the x velocity pass and the next step's x
+#define LOSS_FLAG_NO_FUSE_X 2  /* acoustic line passes: keep the x velocity pass and the next step's x
                                   stress pass in separate kernels (by default one kernel
                                   runs both when a whole x line fits one workgroup and
                                   there are no body forces or velocity receivers) */
-#define LOSS_FLAG_LINE_PASSES 4 /* elastic: one kernel per derivative along one axis (18 per
-                                  step) instead of the plane schedule (per sub-flow: the z
-                                  derivatives of its inputs, then one pass that solves the x
-                                  and y lines of each patch tile of a plane from LDS and
-                                  updates every output once); the plane schedule applies to
-                                  x and y patches of at most 64 intervals without the
-                                  absorbing layer */
+#define LOSS_FLAG_LINE_PASSES 4 /* one kernel per derivative along one axis instead of the tile
+                                  schedule (acoustic: one kernel per sub-flow, its x and z
+                                  derivatives and the update; elastic, per sub-flow: one
+                                  kernel stores the z derivatives of its inputs, one takes
+                                  the x and y derivatives and updates every output).  The
+                                  tile schedule applies to halos of at most 20 nodes and
+                                  fields of one shot below 2^30 elements; grids of many
+                                  small tiles (patches of less than about 24 intervals)
+                                  keep the line passes unless asked (loss_set_shape) */
 
 typedef struct {
     int32_t physics;      /* LOSS_ACOUSTIC (ndim 2) or LOSS_ELASTIC (ndim 3) */
@@ -271,9 +273,9 @@ loss_status loss_adjoint(loss_sim *sim, const double *residual, int32_t param, d
  * wave (16, 32 or 64 x-columns; the rest of the wave's lanes take further chunks of the
  * same lines) and the nodes per lane (8 or 16), and for elastic grids the shape of the y
  * store passes apart (the axis's own, 64 or 32 columns with 8 nodes per lane); each
- * candidate timed over `trial_steps` steps, the fastest kept.  Elastic grids
- * that admit the plane schedule (LOSS_FLAG_LINE_PASSES) have it timed against the line
- * passes and the faster one kept.  A shape or schedule changes only how the carries of
+ * candidate timed over `trial_steps` steps, the fastest kept.  Grids that admit the tile
+ * schedule (LOSS_FLAG_LINE_PASSES) have it timed against the line passes and the faster
+ * one kept.  A shape or schedule changes only how the carries of
  * the scan are grouped and the order in which derivative terms are summed
  * (rounding-level differences).  Wavefields, traces and the step counter are restored
  * afterwards. */
@@ -282,14 +284,14 @@ loss_status loss_autotune(loss_sim *sim, int32_t trial_steps);
 /* The launch shape in use along `axis`: for x, 100 * lines per wave + nodes per lane
  * (lines per wave 0 = automatic: 16, 8, 4 or 2 where the kernel applies, as long as
  * that leaves 8192 waves; 1 = one unit per lane group); for y and z,
- * 100 * columns per wave + nodes per lane (0 = automatic choice); axis 3: the elastic
- * schedule in use (0 plane passes, 1 line passes); axes 4 and 5: the shape of the y and
+ * 100 * columns per wave + nodes per lane (0 = automatic choice); axis 3: the
+ * schedule in use (0 tile passes, 1 line passes); axes 4 and 5: the shape of the y and
  * z store passes (passes that only store a derivative), 0 when they take the axis's. */
 loss_status loss_autotune_choice(loss_sim *sim, int32_t axis, int32_t *cw);
 
 /* Set the launch shape along `axis` in the encoding of loss_autotune_choice
  * (x: 100 * {0, 1, 2, 4, 8, 16} + {4, 8, 16}; y/z: 100 * {8, 16, 32, 64} + {8, 16};
- * 0 = automatic; axis 3: 0 plane schedule where it applies, 1 line passes; axes 4, 5:
+ * 0 = automatic; axis 3: 0 tile schedule where it applies, 1 line passes; axes 4, 5:
  * the y / z store passes, 100 * {8, 16, 32, 64} + {8, 16}, 0 = the axis's shape).
  * LOSS_EINVAL for any other value. */
 loss_status loss_set_shape(loss_sim *sim, int32_t axis, int32_t shape);

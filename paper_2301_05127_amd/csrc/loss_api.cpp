@@ -13,6 +13,7 @@
 
 #include "../../include/loss.h"
 #include "loss_internal.h"
+#include "tile_index.h"
 
 using namespace loss;
 
@@ -49,13 +50,13 @@ struct RecHost {
 enum KClass {
     KC_STRESS_X, KC_STRESS_Y, KC_STRESS_Z, KC_VEL_X, KC_VEL_Y, KC_VEL_Z, KC_SOURCE, KC_RECEIVER,
     KC_ADVANCE, KC_ADJ_SOLVE, KC_ADJ_GATHER, KC_GRAD, KC_VEL_STRESS_X, KC_ADJ_X, KC_ADJ_XX, KC_STRESS_XY,
-    KC_VEL_XY, KC_COUNT
+    KC_VEL_XY, KC_STRESS_Z3, KC_VEL_Z3, KC_STRESS_TILE, KC_VEL_TILE, KC_COUNT
 };
 const char *kKClassName[KC_COUNT] = {
     "stress_line_x", "stress_line_y", "stress_line_z", "velocity_line_x", "velocity_line_y",
     "velocity_line_z", "source_inject", "receiver_record", "step_advance", "adjoint_line_solve",
     "adjoint_gather", "gradient_accumulate", "velocity_stress_x", "adjoint_line_x", "adjoint_line_x_pair",
-    "stress_plane_xy", "velocity_plane_xy"};
+    "stress_tile_xy", "velocity_tile_xy", "stress_store_z", "velocity_store_z", "stress_tile_xz", "velocity_tile_xz"};
 
 }  // namespace
 
@@ -130,8 +131,19 @@ struct loss_sim {
     int4 *d_rcol = nullptr;
     int *d_rrow = nullptr;
     int64_t *d_rtoff = nullptr;
-    // elastic schedule: 0 plane passes where they apply, 1 line passes (autotune's choice)
-    int elastic_schedule = 0;
+    // schedule: 0 tile passes where they apply, 1 line passes (the caller's or the
+    // autotuner's choice), -1 automatic (tile_pays)
+    int schedule = -1;
+    bool tile_pays = false;
+    // tables of the tile passes per axis (x: along_x form; y, z: rows form)
+    bool tile_built = false;
+    TileAxis tax[3]{};
+    int tile_nw[3] = {0, 0, 0};    // waves a workgroup needs along the rows of y, z
+    std::vector<int> tile_sb[3];   // piece ends
+    int64_t *d_step2 = nullptr;    // the step counter between the two kernels of an acoustic tile step
+    // receivers ordered by the tile that updates their node
+    RecDev *d_trec_vel = nullptr, *d_trec_str = nullptr;
+    int *d_trb_vel = nullptr, *d_trb_str = nullptr;
     // adjoint
     float *ckpt = nullptr;         // [nseg][nf fields][S][shot_stride] fused states
     int64_t ck_every = 0, ck_steps = 0, ck_nseg = 0;
@@ -372,89 +384,194 @@ loss_status record(loss_sim *s, const RecDev *rec0, int nrec0, float w0, int acc
     return timed_end(s, KC_RECEIVER);
 }
 
-// ---- elastic plane schedule ------------------------------------------------------
-// Per stage: three z passes store the z derivatives T of the stage's inputs, then the
-// plane kernel adds the x and y derivatives from LDS tiles and updates every output
-// once (see plane_xy.hip).  Used for elastic runs without the absorbing layer whose x
-// and y patches are at most kPlaneMaxM long, unless the line-pass schedule is asked for.
-bool plane_ok(const loss_sim *s)
+// ---- tile schedule -----------------------------------------------------------------
+// Acoustic: one kernel per sub-flow (x and z together).  Elastic, per sub-flow: one kernel
+// stores the z derivatives of its inputs, one takes the x and y derivatives and updates
+// every output.  Applies unless the halo is wider than the tile window or the line passes
+// are asked for; the automatic choice also leaves out grids of many small tiles.
+bool tile_ok(const loss_sim *s)
 {
-    return s->d.physics == LOSS_ELASTIC && !s->pml_mem && !(s->d.flags & LOSS_FLAG_LINE_PASSES) &&
-           s->elastic_schedule != 1 && s->d.patch[0] <= kPlaneMaxM && s->d.patch[1] <= kPlaneMaxM &&
-           s->d.halo <= kPlaneMaxHalo;
+    return s->tile_built && (s->schedule == 0 || (s->schedule < 0 && s->tile_pays)) &&
+           !(s->d.flags & LOSS_FLAG_LINE_PASSES);
 }
 
-PlaneArgs plane_args(const loss_sim *s)
+TileArgs tile_args(const loss_sim *s)
 {
-    PlaneArgs p{};
-    p.S = s->S;
-    p.nx = s->nx; p.ny = s->ny; p.nz = s->nz;
-    p.pitch = s->pitch; p.plane = s->plane; p.shot_stride = s->shot_stride;
-    p.ax = s->axd[0];
-    p.ay = s->axd[1];
-    p.lam = s->med[0]; p.mu = s->med[1]; p.l2m = s->med[2]; p.b = s->med[3];
-    for (int i = 0; i < 3; ++i) p.T[i] = s->tmp[i];
-    return p;
+    TileArgs t{};
+    const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
+    t.S = s->S;
+    t.nx = s->nx;
+    t.row_axis = ra;
+    t.nrow = ra == 1 ? s->ny : s->nz;
+    t.nother = ra == 1 ? s->nz : 1;
+    t.rstride = ra == 1 ? s->pitch : s->plane;
+    t.ostride = ra == 1 ? s->plane : 0;
+    t.shot_stride = s->shot_stride;
+    t.nw = s->tile_nw[ra];
+    t.x = s->tax[0];
+    t.r = s->tax[ra];
+    t.x.pml_w = s->axd[0].pml_w;
+    t.r.pml_w = s->axd[ra].pml_w;
+    t.fields = s->d_fields;
+    return t;
 }
 
-loss_status run_plane(loss_sim *s, int kc, int mode, const PlaneArgs &p)
+// index of kPmlFrac; any other value is a programming error of this file
+int pml_frac_index(float frac)
+{
+    for (int i = 0; i < 3; ++i)
+        if (frac == kPmlFrac[i]) return i;
+    std::fprintf(stderr, "loss: absorbing layer asked for an untabulated step fraction %g\n", (double)frac);
+    std::abort();
+}
+
+void tile_layer(const loss_sim *s, TileArgs &t, float frac, bool store)
+{
+    if (!s->pml_mem) return;
+    const size_t fi = pml_frac_index(frac);
+    t.pml_mem = s->pml_mem;
+    t.pml_stride = field_elems(s);
+    t.px = s->pml_tab[0] + fi * (s->d.n[0] + 1);
+    t.pr = s->pml_tab[t.row_axis] + fi * (s->d.n[t.row_axis] + 1);
+    t.pml_store = store ? 1 : 0;
+}
+
+void tile_sources(const loss_sim *s, TileArgs &t, int time_offset, bool forces)
+{
+    if (s->nsrc == 0) return;
+    t.src = s->d_src;
+    t.src_begin = s->d_src_begin;
+    t.wpool = s->d_wpool;
+    t.wavpool = s->d_wavpool;
+    t.src_time_offset = time_offset;
+    t.src_scale = forces ? 1.f : (float)s->d.dt;
+}
+
+void tile_receivers(const loss_sim *s, TileArgs &t, bool vel)
+{
+    if (s->d.trace_len == 0) return;
+    t.rec_begin = vel ? s->d_trb_vel : s->d_trb_str;
+    t.rec = vel ? s->d_trec_vel : s->d_trec_str;
+    t.traces = s->traces;
+    t.trace_len = s->d.trace_len;
+}
+
+loss_status run_tile(loss_sim *s, int kc, int mode, const TileArgs &t)
 {
     loss_status r = timed_begin(s);
     if (r) return r;
-    const hipError_t e = launch_plane_xy(mode, p, s->st);
-    if (e != hipSuccess) return fail(LOSS_EHIP, std::string("plane kernel launch: ") + hipGetErrorString(e));
+    const hipError_t e = launch_tile(mode, t, s->st);
+    if (e != hipSuccess) return fail(LOSS_EHIP, std::string("tile kernel launch: ") + hipGetErrorString(e));
     return timed_end(s, kc);
 }
 
-// z derivatives of three fields into tmp[0..2] (the first kernel of a step when pending)
-loss_status z_stores(loss_sim *s, int kc, const float *const *in)
+// z derivatives of three fields into tmp[0..2] (the first kernel of a step when pending);
+// with the layer the stretched derivatives, memory variables var0 + 3 i
+loss_status tile_z3(loss_sim *s, int kc, const float *const *in, int var0, float frac, bool store)
 {
+    TileZArgs z{};
+    z.nf = 3;
+    z.S = s->S;
+    z.nx = s->nx;
+    z.ny = s->ny;
+    z.pitch = s->pitch;
+    z.plane = s->plane;
+    z.shot_stride = s->shot_stride;
+    z.nw = s->tile_nw[2];
+    z.r = s->tax[2];
+    z.r.pml_w = s->axd[2].pml_w;
     for (int i = 0; i < 3; ++i) {
-        LineArgs z = base_args(s, 2);
-        z.in = in[i];
-        z.out[0] = s->tmp[i];
-        loss_status r = run_line(s, kc, 2, SOLVE_D1, EPI_STORE, z);
-        if (r) return r;
+        z.in[i] = in[i];
+        z.out[i] = s->tmp[i];
+        z.pml_mem[i] = pml_var(s, var0 + 3 * i);
     }
-    return LOSS_OK;
+    if (s->pml_mem) z.pr = s->pml_tab[2] + (size_t)pml_frac_index(frac) * (s->d.n[2] + 1);
+    z.pml_store = store ? 1 : 0;
+    if (s->pending_inc) {
+        z.step_inc = s->d_step;
+        s->pending_inc = false;
+    }
+    loss_status r = timed_begin(s);
+    if (r) return r;
+    const hipError_t e = launch_tile_z(z, s->st);
+    if (e != hipSuccess) return fail(LOSS_EHIP, std::string("z store launch: ") + hipGetErrorString(e));
+    return timed_end(s, kc);
 }
 
-// stress sub-flow B(dt): T_i = d3 v_i, then the plane pass over the six stresses
-loss_status stress_stage_planes(loss_sim *s)
+// stress sub-flow B(dt); `in_step`: part of a step (sources, receivers, step counter)
+loss_status stress_stage_tiles(loss_sim *s, float *keep)
 {
     float *const *F = s->f.data();
+    loss_status r;
+    TileArgs t = tile_args(s);
+    t.keep = keep;
+    t.keep_stride = field_elems(s);
+    tile_layer(s, t, 1.f, true);
+    tile_sources(s, t, -1, false);
+    tile_receivers(s, t, false);
+    if (s->d.physics == LOSS_ACOUSTIC) {
+        t.in[0] = F[LOSS_F_V1];
+        t.in[1] = F[LOSS_F_V3];
+        t.out[0] = F[LOSS_F_SIGMA];
+        t.c0 = s->med[0];
+        t.alpha = -1.f;
+        t.step_in = s->d_step;
+        t.step_add = s->pending_inc ? 1 : 0;
+        if (s->pending_inc) t.step_out = s->d_step2;
+        s->pending_inc = false;
+        return run_tile(s, KC_STRESS_TILE, TILE_AC_STRESS, t);
+    }
     const float *v[3] = {F[LOSS_F_EV1], F[LOSS_F_EV2], F[LOSS_F_EV3]};
-    loss_status r = z_stores(s, KC_STRESS_Z, v);
-    if (r) return r;
-    PlaneArgs p = plane_args(s);
-    for (int i = 0; i < 3; ++i) p.in[i] = v[i];
+    if ((r = tile_z3(s, KC_STRESS_Z3, v, 9 + 2, 1.f, true))) return r;
     const int outs[6] = {LOSS_F_S11, LOSS_F_S22, LOSS_F_S33, LOSS_F_S12, LOSS_F_S13, LOSS_F_S23};
-    for (int i = 0; i < 6; ++i) p.out[i] = F[outs[i]];
-    p.alpha = 1.f;
-    p.src = base_args(s, 0);
-    const int fid[3] = {LOSS_F_S11, LOSS_F_S22, LOSS_F_S33};
-    attach_sources(s, p.src, -1, fid, 3, false);
-    return run_plane(s, KC_STRESS_XY, 0, p);
+    for (int i = 0; i < 3; ++i) { t.in[i] = v[i]; t.T[i] = s->tmp[i]; }
+    for (int i = 0; i < 6; ++i) t.out[i] = F[outs[i]];
+    t.c0 = s->med[2];
+    t.c1 = s->med[0];
+    t.c2 = s->med[1];
+    t.alpha = 1.f;
+    t.step_in = s->d_step;
+    return run_tile(s, KC_STRESS_XY, TILE_EL_STRESS, t);
 }
 
-// velocity sub-flow over frac * dt: T_i = d3 sigma_i3, then the plane pass over v
-loss_status velocity_stage_planes(loss_sim *s, float frac, float *const *vel, bool with_forces)
+// velocity sub-flow over frac * dt: vel = base + increment (base null: in place).
+// `in_step`: part of a step (forces, receivers, step counter).
+loss_status velocity_stage_tiles(loss_sim *s, float frac, float *const *vel, const float *const *base, bool in_step,
+                                 float *keep)
 {
     float *const *F = s->f.data();
-    const float *t3[3] = {F[LOSS_F_S13], F[LOSS_F_S23], F[LOSS_F_S33]};
-    loss_status r = z_stores(s, KC_VEL_Z, t3);
-    if (r) return r;
-    PlaneArgs p = plane_args(s);
-    const int ins[5] = {LOSS_F_S11, LOSS_F_S12, LOSS_F_S22, LOSS_F_S13, LOSS_F_S23};
-    for (int i = 0; i < 5; ++i) p.in[i] = F[ins[i]];
-    for (int i = 0; i < 3; ++i) p.out[i] = vel[i];
-    p.alpha = frac;
-    p.src = base_args(s, 0);
-    if (with_forces) {
-        const int fid[3] = {LOSS_F_EV1, LOSS_F_EV2, LOSS_F_EV3};
-        attach_sources(s, p.src, 0, fid, 3, true);
+    loss_status r;
+    TileArgs t = tile_args(s);
+    t.keep = keep;
+    t.keep_stride = field_elems(s);
+    t.c0 = s->med.back();
+    tile_layer(s, t, frac, base == nullptr);
+    if (in_step) {
+        tile_sources(s, t, 0, true);
+        tile_receivers(s, t, true);
     }
-    return run_plane(s, KC_VEL_XY, 1, p);
+    const int nv = s->d.physics == LOSS_ACOUSTIC ? 2 : 3;
+    for (int i = 0; i < nv; ++i) {
+        t.out[i] = vel[i];
+        t.base[i] = base ? base[i] : vel[i];
+    }
+    if (s->d.physics == LOSS_ACOUSTIC) {
+        t.in[0] = F[LOSS_F_SIGMA];
+        t.alpha = -frac;
+        if (in_step) {
+            t.step_in = s->d_step2;
+            t.step_out = s->d_step;
+        }
+        return run_tile(s, KC_VEL_TILE, TILE_AC_VEL, t);
+    }
+    const float *t3[3] = {F[LOSS_F_S13], F[LOSS_F_S23], F[LOSS_F_S33]};
+    if ((r = tile_z3(s, KC_VEL_Z3, t3, 2, frac, base == nullptr))) return r;
+    const int ins[5] = {LOSS_F_S11, LOSS_F_S12, LOSS_F_S22, LOSS_F_S13, LOSS_F_S23};
+    for (int i = 0; i < 5; ++i) t.in[i] = F[ins[i]];
+    for (int i = 0; i < 3; ++i) t.T[i] = s->tmp[i];
+    t.alpha = frac;
+    if (in_step) t.step_in = s->d_step;
+    return run_tile(s, KC_VEL_XY, TILE_EL_VEL, t);
 }
 
 // ---- velocity sub-flow (A) over frac * dt with the stress frozen -------------
@@ -466,6 +583,7 @@ loss_status velocity_stage(loss_sim *s, float frac, float *const *vel, const flo
 {
     const float *b = s->med.back();
     loss_status r;
+    if (tile_ok(s)) return velocity_stage_tiles(s, frac, vel, base, with_forces, div_store);
     if (s->d.physics == LOSS_ACOUSTIC) {
         const float *sig = s->f[LOSS_F_SIGMA];
         for (int c = 0; c < 2; ++c) {
@@ -493,7 +611,6 @@ loss_status velocity_stage(loss_sim *s, float frac, float *const *vel, const flo
     static const int sidx[3][3] = {{LOSS_F_S11, LOSS_F_S12, LOSS_F_S13},
                                    {LOSS_F_S12, LOSS_F_S22, LOSS_F_S23},
                                    {LOSS_F_S13, LOSS_F_S23, LOSS_F_S33}};
-    if (!base && !div_store && plane_ok(s)) return velocity_stage_planes(s, frac, vel, with_forces);
     if (!base) {
         // T = d_x sigma_{i1} (stored), T += d_y sigma_{i2}, v_i += frac b (T + d_z sigma_{i3})
         for (int i = 0; i < 3; ++i) {
@@ -622,6 +739,7 @@ loss_status acoustic_velocity_stress_x(loss_sim *s)
 // line fits one block.
 bool fused_x_ok(loss_sim *s)
 {
+    if (tile_ok(s)) return false;
     if (s->d.physics != LOSS_ACOUSTIC || s->nrec_vel > 0 || (s->d.flags & LOSS_FLAG_NO_FUSE_X)) return false;
     for (const auto &shot : s->src)
         for (const SrcHost &h : shot)
@@ -633,12 +751,12 @@ bool fused_x_ok(loss_sim *s)
 loss_status stress_stage(loss_sim *s, float *div_store, int64_t div_shot_stride)
 {
     loss_status r;
+    if (tile_ok(s)) return stress_stage_tiles(s, div_store);
     if (s->d.physics == LOSS_ACOUSTIC) {
         // T = d v1/dx ; sigma -= dt K (T + d v3/dz)
         if ((r = acoustic_stress_x(s))) return r;
         return acoustic_stress_z(s, div_store, div_shot_stride);
     }
-    if (!div_store && plane_ok(s)) return stress_stage_planes(s);
     float *const *F = s->f.data();
     const float *lam = s->med[0], *mu = s->med[1], *l2m = s->med[2];
     // normal components: T1 = d1 v1 and T2 = d2 v2 stored, then the z pass updates all
@@ -907,6 +1025,40 @@ loss_status upload_receivers(loss_sim *s)
         HIPCHK(hipMemcpy(s->d_rrow, rrow.data(), rrow.size() * sizeof(int), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(s->d_rtoff, rtoff.data(), rtoff.size() * sizeof(int64_t), hipMemcpyHostToDevice));
     }
+    // the same receivers ordered by the tile whose kernel updates their node
+    auto by_tile = [&](const std::vector<RecDev> &list, RecDev **drec, int **dbeg) -> loss_status {
+        if (*drec) { s->release(*drec); *drec = nullptr; }
+        if (*dbeg) { s->release(*dbeg); *dbeg = nullptr; }
+        if (list.empty() || !s->tile_built) return LOSS_OK;
+        const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
+        const int nother = ra == 1 ? s->nz : 1;
+        auto piece = [&](int axis, int node) {   // a piece owns its first node; the last one node N too
+            const std::vector<int> &b = s->tile_sb[axis];
+            return std::min((int)(std::upper_bound(b.begin(), b.end(), node) - b.begin()) - 1, (int)b.size() - 2);
+        };
+        const int ntx = (int)s->tile_sb[0].size() - 1, ntr = (int)s->tile_sb[ra].size() - 1;
+        std::vector<std::pair<int64_t, int>> key(list.size());
+        for (size_t k = 0; k < list.size(); ++k) {
+            const int64_t z = list[k].node / s->plane, rem = list[k].node - z * s->plane;
+            const int y = (int)(rem / s->pitch), x = (int)(rem - (int64_t)y * s->pitch);
+            const int row = ra == 1 ? y : (int)z, o = ra == 1 ? (int)z : 0;
+            key[k] = {(((int64_t)list[k].shot * nother + o) * ntr + piece(ra, row)) * ntx + piece(0, x), (int)k};
+        }
+        std::sort(key.begin(), key.end());
+        std::vector<RecDev> sorted(list.size());
+        std::vector<int> beg((size_t)s->S * nother * ntr * ntx + 1, 0);
+        for (size_t k = 0; k < key.size(); ++k) {
+            sorted[k] = list[key[k].second];
+            beg[key[k].first + 1]++;
+        }
+        for (size_t k = 1; k < beg.size(); ++k) beg[k] += beg[k - 1];
+        loss_status q;
+        if ((q = s->alloc(drec, sorted.size())) || (q = s->alloc(dbeg, beg.size()))) return q;
+        HIPCHK(hipMemcpy(*drec, sorted.data(), sorted.size() * sizeof(RecDev), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(*dbeg, beg.data(), beg.size() * sizeof(int), hipMemcpyHostToDevice));
+        return LOSS_OK;
+    };
+    if ((r = by_tile(vel, &s->d_trec_vel, &s->d_trb_vel)) || (r = by_tile(str, &s->d_trec_str, &s->d_trb_str))) return r;
     s->trace_total = off;
     if ((r = s->alloc(&s->traces, std::max<int64_t>(off, 1)))) return r;
     HIPCHK(hipMemsetAsync(s->traces, 0, sizeof(double) * std::max<int64_t>(off, 1), s->st));
@@ -1008,15 +1160,16 @@ loss_status one_step(loss_sim *s, float *div_store, int64_t div_shot_stride)
     if ((r = stress_stage(s, div_store, div_shot_stride))) return r;
     // stress receivers not recorded by the stress kernel, and the first half of the
     // velocity receivers
+    const bool tiles = tile_ok(s);   // the tile kernels record the receivers of what they update
     const int nstr = s->d_rcol ? 0 : s->nrec_str;
-    if ((r = record(s, s->d_rec_str, nstr, 1.0f, 0, s->d_rec_vel, s->nrec_vel, 0.5f, 0))) return r;
+    if (!tiles && (r = record(s, s->d_rec_str, nstr, 1.0f, 0, s->d_rec_vel, s->nrec_vel, 0.5f, 0))) return r;
     std::vector<float *> vel;
     if (s->d.physics == LOSS_ACOUSTIC) vel = {s->f[LOSS_F_V1], s->f[LOSS_F_V3]};
     else vel = {s->f[LOSS_F_EV1], s->f[LOSS_F_EV2], s->f[LOSS_F_EV3]};
     float *vdiv = (div_store && s->d.physics == LOSS_ELASTIC && s->strain_slots == 9)
                       ? div_store + 6 * field_elems(s) : nullptr;
     if ((r = velocity_stage(s, 1.0f, vel.data(), nullptr, true, vdiv, div_shot_stride))) return r;
-    if ((r = record(s, s->d_rec_vel, s->nrec_vel, 0.5f, 1))) return r;
+    if (!tiles && (r = record(s, s->d_rec_vel, s->nrec_vel, 0.5f, 1))) return r;
     return LOSS_OK;
 }
 
@@ -1264,6 +1417,56 @@ loss_status upload_axis(loss_sim *s, int axis)
     return LOSS_OK;
 }
 
+// Tables of the tile passes; a grid they do not apply to keeps the line passes.
+loss_status upload_tiles(loss_sim *s)
+{
+    if (s->shot_stride >= (int64_t(1) << 30)) return LOSS_OK;   // 32-bit byte offsets within a shot's field
+    std::vector<char> blob;   // every table, uploaded at once
+    size_t off[3][6] = {};
+    for (int axis = 0; axis < 3; ++axis) {
+        if (axis == 1 && s->d.ndim == 2) continue;
+        TileHost h;
+        if (!build_tile(s->axh[axis], axis == 0, h).empty()) return LOSS_OK;
+        auto put = [&](const auto &v) {   // offset of a table in the blob, 16-byte aligned
+            const size_t o = (blob.size() + 15) / 16 * 16;
+            blob.resize(o + v.size() * sizeof(v[0]));
+            std::memcpy(blob.data() + o, v.data(), v.size() * sizeof(v[0]));
+            return o;
+        };
+        const size_t o[6] = {put(h.piece), put(h.halo_node), put(h.ends), put(h.halo_c), put(h.chunk), put(h.lanes)};
+        std::copy(o, o + 6, off[axis]);
+        TileAxis &t = s->tax[axis];
+        t.N = s->axh[axis].N;
+        t.nsub = h.nsub;
+        t.periodic = s->d.end_mode == LOSS_END_PERIODIC;
+        s->tile_nw[axis] = (h.max_m + kTileC - 1) / kTileC;
+        s->tile_sb[axis] = h.sb;
+    }
+    char *d = nullptr;
+    loss_status r = s->alloc(&d, blob.size());
+    if (r) return r;
+    HIPCHK(hipMemcpy(d, blob.data(), blob.size(), hipMemcpyHostToDevice));
+    for (int axis = 0; axis < 3; ++axis) {
+        TileAxis &t = s->tax[axis];
+        t.piece = (const int4 *)(d + off[axis][0]);
+        t.halo_node = (const int *)(d + off[axis][1]);
+        t.ends = (const float4 *)(d + off[axis][2]);
+        t.halo_c = (const float2 *)(d + off[axis][3]);
+        t.chunk = (const TileChunk *)(d + off[axis][4]);
+        t.lanes = (const float4 *)(d + off[axis][5]);
+    }
+    s->tile_built = true;
+    // A tile costs its latency however few nodes it holds.  Measured (us per step, tile
+    // against line passes at their default shapes): acoustic 1025^2 x 8 shots, patches of 16
+    // (256 nodes a tile, 33 k tiles) 397 / 166, of 24 200 / 170, of 32 140 / 142, of 64
+    // 106 / 120; elastic 257^3, patches of 16 (70 k tiles) 2134 / 2082, of 32 976 / 1620;
+    // 129^3, patches of 8 989 / 493, of 16 (9 k tiles) 255 / 410; 129^2, patches of 16 18 / 36.
+    const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
+    const int64_t tiles = (int64_t)s->S * (ra == 1 ? s->nz : 1) * s->tax[0].nsub * s->tax[ra].nsub;
+    const int64_t per_tile = (int64_t)s->nx * (ra == 1 ? s->ny : s->nz) / ((int64_t)s->tax[0].nsub * s->tax[ra].nsub);
+    s->tile_pays = tiles < 12000 || per_tile >= 600;
+    return LOSS_OK;
+}
 
 // Elastic adjoint of the fused schedule that loss_forward_ckpt ran.  Forward step n:
 //   B: sigma += (dt lambda) tr(e) I + 2 (dt mu) e, strains e of u^n; stress receivers
@@ -1490,7 +1693,10 @@ loss_status loss_create(const loss_desc *desc, void *hip_stream, loss_sim **out)
     s->nx = (int)d.n[0] + 1;
     s->ny = d.ndim == 3 ? (int)d.n[1] + 1 : 1;
     s->nz = (int)d.n[2] + 1;
-    s->pitch = ((int64_t)s->nx + 3) / 4 * 4;
+    // rows start on 64-byte boundaries (a wave's row of 64 floats then covers whole sectors),
+    // unless that padding would take a field over the size limit below
+    s->pitch = ((int64_t)s->nx + 15) / 16 * 16;
+    if (s->pitch * s->ny * s->nz >= (int64_t(1) << 31)) s->pitch = ((int64_t)s->nx + 3) / 4 * 4;
     s->plane = s->pitch * s->ny;
     s->shot_stride = s->plane * s->nz;
     s->nodes = (int64_t)s->nx * s->ny * s->nz;
@@ -1535,7 +1741,7 @@ loss_status loss_create(const loss_desc *desc, void *hip_stream, loss_sim **out)
     for (int i = 0; i < nmed; ++i)
         if ((r = s->alloc(&s->med[i], s->shot_stride))) return bail(r);
     if ((r = s->alloc(&s->d_fields, s->nf)) || (r = s->alloc(&s->d_tmpfields, s->nf)) ||
-        (r = s->alloc(&s->d_step, 1)) || (r = s->alloc(&s->d_bad, 1)))
+        (r = s->alloc(&s->d_step, 1)) || (r = s->alloc(&s->d_step2, 1)) || (r = s->alloc(&s->d_bad, 1)))
         return bail(r);
     if (hipHostMalloc((void **)&s->h_bad, sizeof(int), 0) != hipSuccess) {
         s->h_bad = nullptr;
@@ -1548,6 +1754,7 @@ loss_status loss_create(const loss_desc *desc, void *hip_stream, loss_sim **out)
         if (a == 1 && d.ndim == 2) continue;
         if ((r = upload_axis(s, a))) return bail(r);
     }
+    if ((r = upload_tiles(s))) return bail(r);
     if (hipMemcpy(s->d_fields, s->f.data(), sizeof(float *) * s->nf, hipMemcpyHostToDevice) != hipSuccess)
         return bail(fail(LOSS_EHIP, "pointer table upload"));
     if (hipEventCreate(&s->ev0) != hipSuccess || hipEventCreate(&s->ev1) != hipSuccess)
@@ -1998,10 +2205,10 @@ loss_status loss_autotune(loss_sim *s, int32_t trial_steps)
         return LOSS_OK;
     };
     float t_line = 0.f;
-    // the line-pass schedule (every axis), then for elastic grids that admit it the
-    // plane schedule (its line kernels run along z only); the faster schedule is kept
-    const int sched0 = s->elastic_schedule;
-    s->elastic_schedule = 1;
+    // the line-pass schedule (every axis), then the tile schedule where it applies; the
+    // faster schedule is kept
+    const int sched0 = s->schedule;
+    s->schedule = 1;
     // elastic: the y axis is timed with its store passes held at 64 columns, then the
     // store passes' own shape is chosen
     if (s->d.physics == LOSS_ELASTIC) {
@@ -2028,21 +2235,13 @@ loss_status loss_autotune(loss_sim *s, int32_t trial_steps)
         s->css[1] = bestc.second;
         t_line = std::min(t_line, best);
     }
-    s->elastic_schedule = sched0;
-    if (s->d.physics == LOSS_ELASTIC) {
-        s->elastic_schedule = 0;
-        if (plane_ok(s)) {
-            const int cw2 = s->cw[2], cs2 = s->cs[2];
-            float t_plane = 0.f;
-            if ((r = tune_axis(2, t_plane))) return r;
-            if (t_plane > t_line) {
-                s->elastic_schedule = 1;
-                s->cw[2] = cw2;
-                s->cs[2] = cs2;
-            }
-        } else {
-            s->elastic_schedule = sched0;
-        }
+    s->schedule = 0;
+    if (tile_ok(s)) {
+        float t_tile = 0.f;
+        if ((r = trial(t_tile))) return r;
+        if (t_tile > t_line) s->schedule = 1;
+    } else {
+        s->schedule = sched0;
     }
     // restore
     for (int f = 0; f < s->nf; ++f)
@@ -2075,8 +2274,8 @@ loss_status loss_set_shape(loss_sim *s, int32_t axis, int32_t shape)
         return LOSS_OK;
     }
     if (s && axis == 3) {
-        if (shape != 0 && shape != 1) return fail(LOSS_EINVAL, "schedule must be 0 (plane) or 1 (line passes)");
-        s->elastic_schedule = shape;
+        if (shape != 0 && shape != 1) return fail(LOSS_EINVAL, "schedule must be 0 (tile passes) or 1 (line passes)");
+        s->schedule = shape;
         drop_graph(s);
         return LOSS_OK;
     }
@@ -2102,7 +2301,7 @@ loss_status loss_autotune_choice(loss_sim *s, int32_t axis, int32_t *cw)
 {
     if (!s || !cw || axis < 0 || axis > 5) return fail(LOSS_EINVAL, "bad argument");
     if (axis == 3) {
-        *cw = plane_ok(s) ? 0 : 1;
+        *cw = tile_ok(s) ? 0 : 1;
         return LOSS_OK;
     }
     if (axis > 3) {

@@ -60,6 +60,24 @@ struct AxisHost {
 // Build the tables; returns an empty string on success, else the reason.
 std::string build_axis(AxisHost &ax, int N, double h, int M, int halo, int end_mode);
 
+// Tables of the tile passes (tile.hip) along one axis.  The patches are cut into pieces of
+// at most kTileM intervals; where a cut falls inside a patch the slope there is the row of
+// the patch's own derivative operator as taps (its entries decay by 0.27 per node; those
+// below kTapTol of the stencil weight are left out), so a piece is solved like a patch.
+constexpr double kTapTol = 0x1p-34;
+struct TileHost {
+    int nsub = 0, max_m = 0;
+    std::vector<int> sb, bh;            // [nsub+1] piece ends, taps on either side of each (0: natural end)
+    std::vector<int> piece;             // [nsub][4] {s, e, taps of s, taps of e}
+    std::vector<float> taps;            // [nsub+1][kTapW]
+    std::vector<float> ends;            // [nsub][4] closing row: w_e = iE E - imE y_{e-1}; natural end weight
+    std::vector<int> halo_node;         // [nsub][kTapW] grid node of each halo entry
+    std::vector<float> halo_c;          // [nsub][kTapW][2] its taps of the start and the closing junction
+    std::vector<float> chunk;           // [nsub][kTileWaves][kChunkF] rows form: see TileChunk
+    std::vector<float> lanes;           // [nsub][16][kLaneF] x form: see XLane (tile.hip)
+};
+std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t);
+
 // A node whose column of G^T is not the plain interior form: its stencil column and
 // the transposed PMBC rows reaching it (gather of the adjoint x pass).
 struct SpecialCol {
@@ -111,7 +129,18 @@ enum SolveKind : int {
     SOLVE_T1 = 2,         // adjoint phase 1: y = T^{-T} z on patch interiors
 };
 
-struct SrcDev;
+struct SrcDev {
+    int shot, kind, field0, nfield;   // fields field0 .. field0+nfield-1 (consecutive ids)
+    int x0, y0, z0, bx, by, bz;       // footprint box (nodes)
+    int64_t w_off, wav_off;           // offsets into the weight / wavelet pools
+    int nt;
+    int force;                        // 1: scale by b (body force), 0: stress rate
+};
+struct RecDev {
+    int shot, comp;
+    int64_t node;                     // padded node offset within a shot field
+    int64_t trace_off;                // offset of sample 0 in the trace pool
+};
 
 struct LineArgs {
     const float *in;
@@ -162,34 +191,96 @@ struct LineArgs {
     int pml_store;
 };
 
-// Elastic plane pass (plane_xy.hip): one workgroup per (shot, z plane, patch tile of
-// the x-y plane).  The tile's nodes sit in LDS; its x lines and y lines are solved from
-// there (PMBC taps outside the tile from global memory), and the epilogue combines the
-// x and y derivatives of every input with the z derivatives T stored by the z passes.
-//   stress (mode 0): in = v1, v2, v3; out = s11, s22, s33, s12, s13, s23;
-//     sigma_ii += (l2m) d_i v_i + (lam)(sum of the other two), sigma_ij += (mu)(d_i v_j + d_j v_i)
-//     with d3 v_i = T_i; explosive sources on the normal stresses.
-//   velocity (mode 1): in = s11, s12, s22, s13, s23; out = v1, v2, v3;
-//     v_i += alpha (b) (d1 sigma_i1 + d2 sigma_i2 + T_i) with T_i = d3 sigma_i3; body forces.
-// Media hold dt lambda, dt mu, dt (lambda + 2 mu), dt b.  Patch lengths along x and y
-// must be at most kPlaneMaxM and the halo at most kPlaneMaxHalo (the tile and its taps
-// sit in LDS).
-constexpr int kPlaneMaxM = 64;
-constexpr int kPlaneMaxHalo = 12;
-
-struct PlaneArgs {
-    const float *in[5];
-    const float *T[3];
-    float *out[6];
-    const float *lam, *mu, *l2m, *b;
-    float alpha;
-    int S, nx, ny, nz;
-    int64_t pitch, plane, shot_stride;
-    AxisDev ax, ay;
-    LineArgs src;          // source fields of the epilogue (src, src_begin, pools, d_step, out_field, ...)
+// Tile passes (tile.hip): one workgroup per (shot, plane, tile), a tile being one piece of
+// the x axis times one piece of a strided axis (the rows: y of an elastic grid, z of a 2-D
+// acoustic one).  It takes the derivatives along x and along the rows that a sub-flow needs
+// and updates the sub-flow's outputs in one epilogue; the elastic passes read the z
+// derivatives T of the stage from the stored z pass.
+enum TileMode : int {
+    TILE_EL_STRESS = 0,   // in v1 v2 v3, T d3 v_i; out s11 s22 s33 s12 s13 s23; keep e11 e22 e33 g12 g13 g23
+    TILE_EL_VEL = 1,      // in s11 s12 s22 s13 s23, T d3 s_i3; out v1 v2 v3; keep the three drives
+    TILE_AC_STRESS = 2,   // in v1 v3; out sigma; keep d1 v1 + d3 v3
+    TILE_AC_VEL = 3,      // in sigma; out v1 v3
 };
 
-hipError_t launch_plane_xy(int mode, const PlaneArgs &a, hipStream_t st);
+// One chunk (kTileC rows) of a piece, rows form: the rows' factors and taps, and the two
+// carries as sums over the chunks' B and W, the slope at the start (ph) and the closing
+// right-hand side (E)
+struct TileChunk {
+    float P[8];                 // products of nf from the chunk's first row on
+    float fB[8];                // carry into the elimination
+    float zB[8], zW[8];         // carry into the back substitution
+    float fph, zph, zE, pad0;
+    float nf[8], sc[8], fi[8], g[8];
+    float ts[8], te[8];         // taps of the start and the closing junction
+    float any_ts, any_te, pad1, pad2;
+};
+constexpr int kChunkF = sizeof(TileChunk) / 4;
+constexpr int kLaneF = 44;
+
+struct TileAxis {
+    int N, nsub, periodic, pml_w;
+    const int4 *piece;
+    const float4 *ends, *lanes;
+    const TileChunk *chunk;
+    const int *halo_node;
+    const float2 *halo_c;
+};
+
+struct TileArgs {
+    const float *in[5];
+    const float *T[3];
+    const float *base[3];      // velocity passes: out = base + increment (base = out in place)
+    float *out[6];
+    float *keep;               // optional stores of the derivatives, keep_stride apart
+    int64_t keep_stride;
+    const float *c0, *c1, *c2; // media times dt: l2m, lambda, mu / b / K
+    float alpha;
+    int S, nx, nrow, nother;   // nodes along x and the rows; planes per shot
+    int64_t rstride, ostride, shot_stride;
+    int row_axis;              // 1 or 2
+    int nw;                    // waves per workgroup: kTileC rows each
+    TileAxis x, r;
+    // step counter: the value of the running step is *step_in + step_add; stored by one thread
+    // into step_out (never the location other workgroups of this kernel read)
+    const int64_t *step_in;
+    int64_t *step_out;
+    int step_add;
+    const SrcDev *src;
+    const int *src_begin;
+    const float *wpool, *wavpool;
+    int src_time_offset;
+    float src_scale;
+    // receivers of the updated fields by tile: entries rec_begin[tile] .. of rec; velocity
+    // passes record half of the old and half of the new value
+    const int *rec_begin;
+    const RecDev *rec;
+    const float *const *fields;
+    double *traces;
+    int64_t trace_len;
+    // absorbing layer: variable k of the layer at pml_mem + k * pml_stride, flow tables
+    float *pml_mem;
+    int64_t pml_stride;
+    const float4 *px, *pr;
+    int pml_store;
+};
+hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st);
+
+// z derivatives of up to three fields stored in one launch (the strided solve of the tile
+// passes alone)
+struct TileZArgs {
+    const float *in[3];
+    float *out[3];
+    int nf, S, nx, ny;
+    int64_t pitch, plane, shot_stride;
+    int nw;
+    TileAxis r;
+    int64_t *step_inc;
+    float *pml_mem[3];
+    const float4 *pr;
+    int pml_store;
+};
+hipError_t launch_tile_z(const TileZArgs &a, hipStream_t st);
 
 // Launch helpers (kernels.hip).  axis: 0 = x (contiguous), 1 = y, 2 = z.
 hipError_t launch_line(int axis, int solve, int epi, const LineArgs &a, hipStream_t st);
@@ -208,18 +299,6 @@ hipError_t launch_adj_xx(const LineArgs &a, const float *coef2, float *out2, flo
 int line_xx_threads(const LineArgs &a);
 hipError_t launch_line_xx(const LineArgs &a, float *Tout, float *pml_mem_t, hipStream_t st);
 
-struct SrcDev {
-    int shot, kind, field0, nfield;   // fields field0 .. field0+nfield-1 (consecutive ids)
-    int x0, y0, z0, bx, by, bz;       // footprint box (nodes)
-    int64_t w_off, wav_off;           // offsets into the weight / wavelet pools
-    int nt;
-    int force;                        // 1: scale by b (body force), 0: stress rate
-};
-struct RecDev {
-    int shot, comp;
-    int64_t node;                     // padded node offset within a shot field
-    int64_t trace_off;                // offset of sample 0 in the trace pool
-};
 // One node that receives trace residuals in the adjoint: the receivers at that node of
 // that shot and field are entries first .. first + count - 1 of a trace-offset list, in
 // receiver order (so the injection needs no atomics and sums in a fixed order).

@@ -1,5 +1,5 @@
-// Index arithmetic of the elastic plane pass (plane_xy.hip), usable from host code so
-// that a CPU check can enumerate every index the kernel forms for a given geometry.
+// Index arithmetic of windows over a patch tile of an x-y plane (the tile's nodes and its
+// PMBC taps), usable from host code; tests/plane_index_check.cpp enumerates it.
 #pragma once
 
 #if defined(__HIPCC__)

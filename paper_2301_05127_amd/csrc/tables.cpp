@@ -13,8 +13,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 
 #include "loss_internal.h"
+#include "tile_index.h"
 
 namespace loss {
 namespace {
@@ -262,6 +264,244 @@ std::string build_axis(AxisHost &ax, int N, double h, int M, int halo, int end_m
             ax.reach = std::max(ax.reach, forward_reach(*f, s, e, kReachTol));
         for (const std::vector<double> *g : {&g1, &gT, &g2})
             ax.reach = std::max(ax.reach, backward_reach(*g, s, e, kReachTol));
+    }
+    return std::string();
+}
+
+namespace {
+
+// Row J of the derivative operator of the patch [s, e] of an axis as a tap row: z with
+// T^T z = e_J on the patch, then z^T G.  J is far enough inside the patch for the end
+// rows' own right-hand sides (the PMBC slopes) to enter below the tolerance.
+void interior_slope_row(const AxisHost &ax, int s, int e, int J, std::vector<double> &row)
+{
+    const int n = e - s + 1;
+    std::vector<double> cp(n), z(n, 0.0);
+    z[J - s] = 1.0;
+    // Thomas on T^T: sub-diagonal sup[i-1], super-diagonal sub[i+1]
+    double den = ax.diag[s];
+    cp[0] = (n > 1 ? ax.sub[s + 1] : 0.0) / den;
+    z[0] /= den;
+    for (int i = 1; i < n; ++i) {
+        const double lo = ax.sup[s + i - 1];
+        den = ax.diag[s + i] - lo * cp[i - 1];
+        cp[i] = (i + 1 < n ? ax.sub[s + i + 1] : 0.0) / den;
+        z[i] = (z[i] - lo * z[i - 1]) / den;
+    }
+    for (int i = n - 2; i >= 0; --i) z[i] -= cp[i] * z[i + 1];
+    row.assign(n, 0.0);
+    for (int i = 0; i < n; ++i) {
+        if (i > 0) row[i - 1] += z[i] * ax.cm[s + i];
+        row[i] += z[i] * ax.c0[s + i];
+        if (i + 1 < n) row[i + 1] += z[i] * ax.cp[s + i];
+    }
+}
+
+}  // namespace
+
+std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t)
+{
+    t = TileHost();
+    const int N = ax.N;
+    if (ax.halo > kTileHalo) return "halo wider than the tile window";
+    const double s3 = 3.0 / ax.h;
+    auto boundary = [&](int J, int s, int e) {
+        const size_t o = t.taps.size();
+        t.taps.resize(o + kTapW, 0.f);
+        t.sb.push_back(J);
+        if (ax.slot[J] >= 0) {
+            t.bh.push_back(ax.halo);
+            for (int k = 0; k < 2 * ax.halo + 1; ++k)
+                t.taps[o + k] = (float)ax.tap_c[(size_t)ax.slot[J] * (2 * ax.halo + 1) + k];
+        } else if (ax.kind[J] != ROW_INTERIOR) {
+            t.bh.push_back(0);
+        } else {
+            std::vector<double> row;
+            interior_slope_row(ax, s, e, J, row);
+            int H = kTileHalo;
+            auto mag = [&](int d) {
+                const int a = J - d - s, b = J + d - s;
+                return std::max(a >= 0 ? std::fabs(row[a]) : 0.0, b <= e - s ? std::fabs(row[b]) : 0.0);
+            };
+            while (H > 1 && mag(H) <= kTapTol * s3) --H;
+            t.bh.push_back(H);
+            for (int d = -H; d <= H; ++d)
+                if (J + d >= s && J + d <= e) t.taps[o + H + d] = (float)row[J + d - s];
+        }
+    };
+    for (int l = 0; l < ax.p; ++l) {
+        const int s = l * ax.M, e = std::min(s + ax.M, N), m = e - s;
+        // along x the closing node of the line takes a lane of the last piece; the cuts there
+        // fall on multiples of 16 nodes, so that a tile's rows start on 64-byte boundaries
+        // where the patches do (a row start inside a 64-byte sector costs a partial write)
+        const int cap = along_x && e == N ? kTileM - 1 : kTileM;
+        const int n = (m + cap - 1) / cap;
+        std::vector<int> cut(n + 1);
+        for (int i = 0; i <= n; ++i) cut[i] = (int)((int64_t)i * m / n);
+        if (along_x) {
+            std::vector<int> al = cut;
+            bool ok = true;
+            for (int i = 1; i < n; ++i) al[i] = (cut[i] + 8) / 16 * 16;
+            for (int i = 0; i < n; ++i) ok = ok && al[i + 1] > al[i] && al[i + 1] - al[i] <= (i == n - 1 ? cap : kTileM);
+            // taps at a cut need its distance to the patch ends (kTileHalo) as an equal cut has it
+            if (ok && (n == 1 || (al[1] > kTileHalo && m - al[n - 1] > kTileHalo))) cut = al;
+        }
+        for (int i = 0; i < n; ++i) boundary(s + cut[i], s, e);
+        if (e == N) boundary(N, s, e);
+    }
+    t.nsub = (int)t.sb.size() - 1;
+    for (int b = 0; b < t.nsub; ++b) {
+        const int s = t.sb[b], e = t.sb[b + 1], m = e - s;
+        for (int v : {s, e, t.bh[b], t.bh[b + 1]}) t.piece.push_back(v);
+        t.max_m = std::max(t.max_m, m);
+        // elimination rows of the piece: y_i = nf y_{i-1} + sc (u_{i+1} - u_{i-1}),
+        // w_i = fi y_i + g w_{i+1}; a junction row takes the slope as its carry, rows past
+        // the piece pass the carries on
+        struct Row { double nf, sc, fi, g; };
+        std::vector<Row> r(kTileM, Row{1.0, 0.0, 0.0, 1.0});
+        double d = 0.0, sup = 0.0;
+        for (int i = 0; i < m; ++i) {
+            if (i == 0) {
+                const bool nat = ax.kind[s] == ROW_NATURAL_L;
+                d = nat ? 2.0 : 1.0;
+                sup = nat ? 1.0 : 0.0;
+                r[0] = nat ? Row{0.0, s3, 0.5, -0.5} : Row{1.0, 0.0, 1.0, 0.0};
+            } else {
+                const double mi = 1.0 / d;
+                d = 4.0 - mi * sup;
+                sup = 1.0;
+                r[i] = Row{-mi, s3, 1.0 / d, -1.0 / d};
+            }
+        }
+        double iE = 1.0, imE = 0.0, sE = 0.0;
+        if (ax.kind[e] == ROW_NATURAL_R) {
+            const double mi = 1.0 / d, de = 2.0 - mi * sup;
+            iE = 1.0 / de;
+            imE = mi / de;
+            sE = s3;
+        }
+        for (float v : {(float)iE, (float)imE, (float)sE, 0.f}) t.ends.push_back(v);
+        // taps of the two junctions by the piece's own rows and by its halo entries
+        const Piece p = make_piece(s, e, t.bh[b], t.bh[b + 1]);
+        const float *cs = &t.taps[(size_t)b * kTapW], *ce = cs + kTapW;
+        auto tap = [&](const float *c, int H, int J, int k) {
+            const int d = k - (J - H);
+            return d >= 0 && d <= 2 * H ? c[d] : 0.f;
+        };
+        for (int i = 0; i < kTapW; ++i) {
+            const bool in = i < halo_count(p);
+            const int k = in ? halo_pos(p, i) : e;
+            t.halo_node.push_back(line_node(k, N, ax.end_mode == 2));
+            t.halo_c.push_back(in ? tap(cs, p.hs, s, k) : 0.f);
+            t.halo_c.push_back(in ? tap(ce, p.he, e, k) : 0.f);
+        }
+        // strided passes: the carries of the chunks of kTileC rows as sums over the chunks'
+        // own results.  B_j: chunk j eliminated from a zero carry; W_j: its back
+        // substitution from zero carries; ph: the start junction's slope; E: the closing
+        // row's right-hand side.  Vectors over (B_0.., W_0.., ph, E).
+        constexpr int nw = kTileWaves, nv = 2 * nw + 2;
+        typedef std::vector<double> V;
+        const int nch = (m + kTileC - 1) / kTileC;
+        std::vector<V> yin(nw + 1, V(nv, 0.0)), win(nw, V(nv, 0.0));
+        std::vector<double> A(nw, 1.0), Q(nw, 1.0), R(nw, 0.0);
+        yin[0][2 * nw] = 1.0;
+        for (int w = 0; w < nch; ++w) {
+            double back[kTileC];
+            for (int c = 0; c < kTileC; ++c) {
+                A[w] *= r[w * kTileC + c].nf;
+                back[c] = A[w];
+                Q[w] *= r[w * kTileC + c].g;
+            }
+            for (int c = kTileC - 1; c >= 0; --c) {
+                const Row &q = r[w * kTileC + c];
+                R[w] = q.fi * back[c] + q.g * R[w];
+            }
+            for (int k = 0; k < nv; ++k) yin[w + 1][k] = A[w] * yin[w][k];
+            yin[w + 1][w] += 1.0;
+        }
+        for (int k = 0; k < nv; ++k) win[nch - 1][k] = -imE * yin[nch][k];
+        win[nch - 1][2 * nw + 1] += iE;
+        for (int w = nch - 2; w >= 0; --w) {
+            for (int k = 0; k < nv; ++k) win[w][k] = R[w + 1] * yin[w + 1][k] + Q[w + 1] * win[w + 1][k];
+            win[w][nw + w + 1] += 1.0;
+        }
+        for (int w = 0; w < nw; ++w) {
+            double a = 1.0;
+            const bool on = w < nch;
+            const Row *q = &r[w * kTileC];
+            for (int c = 0; c < kTileC; ++c) { a *= q[c].nf; t.chunk.push_back(on ? (float)a : 0.f); }
+            for (int j = 0; j < nw; ++j) t.chunk.push_back(on ? (float)yin[w][j] : 0.f);
+            for (int j = 0; j < nw; ++j) t.chunk.push_back(on ? (float)win[w][j] : 0.f);
+            for (int j = 0; j < nw; ++j) t.chunk.push_back(on ? (float)win[w][nw + j] : 0.f);
+            for (double v : {yin[w][2 * nw], win[w][2 * nw], win[w][2 * nw + 1], 0.0}) t.chunk.push_back(on ? (float)v : 0.f);
+            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].nf);
+            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].sc);
+            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].fi);
+            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].g);
+            bool any[2] = {false, false};
+            for (int k = 0; k < 2; ++k)
+                for (int c = 0; c < kTileC; ++c) {
+                    const int i = s + w * kTileC + c;
+                    const float v = i >= e ? 0.f : (k ? tap(ce, p.he, e, i) : tap(cs, p.hs, s, i));
+                    any[k] = any[k] || v != 0.f;
+                    t.chunk.push_back(v);
+                }
+            for (float v : {any[0] ? 1.f : 0.f, any[1] ? 1.f : 0.f, 0.f, 0.f}) t.chunk.push_back(v);
+        }
+        // x pass: 16 lanes of four nodes.  The carries are composed in three doubling steps
+        // whose multipliers do not depend on the data: lane 0 absorbs the slope, the
+        // closing lane and those after it the closing value.
+        constexpr int nl = kTileM / 4;
+        const int kc = (m - 1) / 4;
+        std::vector<double> a1(nl), b1(nl), qt(nl);
+        double a0 = 0.0;
+        for (int k = 0; k < nl; ++k) {
+            double a = 1.0, q = 1.0;
+            for (int c = 0; c < 4; ++c) { a *= r[4 * k + c].nf; q *= r[4 * k + c].g; }
+            if (k == 0) a0 = a;
+            a1[k] = k == 0 ? 0.0 : a;
+            qt[k] = q;
+            b1[k] = k >= kc ? 0.0 : q;
+        }
+        auto up = [&](const std::vector<double> &v, int k, int w) {   // product over lanes k, k-1, .. k-w+1
+            double p = 1.0;
+            for (int i = 0; i < w; ++i) p *= k - i >= 0 ? v[k - i] : 0.0;
+            return p;
+        };
+        auto dn = [&](const std::vector<double> &v, int k, int w) {
+            double p = 1.0;
+            for (int i = 0; i < w; ++i) p *= k + i < nl ? v[k + i] : 0.0;
+            return p;
+        };
+        for (int k = 0; k < nl; ++k) {
+            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].nf);
+            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].sc);
+            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].fi);
+            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].g);
+            double a = 1.0;
+            for (int c = 0; c < 4; ++c) { a *= r[4 * k + c].nf; t.lanes.push_back((float)a); }
+            for (double v : {a1[k], up(a1, k, 2), up(a1, k, 4), k == 0 ? a0 : 0.0}) t.lanes.push_back((float)v);
+            for (double v : {b1[k], dn(b1, k, 2), dn(b1, k, 4), k == kc ? qt[k] : (k > kc ? 1.0 : 0.0)})
+                t.lanes.push_back((float)v);
+            // taps k, k + 16, k + 32 of the two junctions and their places in the LDS row
+            for (int j = 0; j < 2; ++j) {
+                const int H = j ? p.he : p.hs, d0 = j ? m - p.he : -p.hs;
+                float cf[3];
+                int pos[3];
+                for (int h = 0; h < 3; ++h) {
+                    const int i = k + 16 * h;
+                    const bool in = i <= 2 * H;
+                    cf[h] = in ? (j ? ce : cs)[i] : 0.f;
+                    pos[h] = 4 * tap_slot(p, d0 + (in ? i : 0));
+                }
+                for (float v : {cf[0], cf[1], cf[2], 0.f}) t.lanes.push_back(v);
+                for (int v : {pos[0], pos[1], pos[2], 0}) {   // byte offsets, as bits
+                    float f;
+                    std::memcpy(&f, &v, 4);
+                    t.lanes.push_back(f);
+                }
+            }
+        }
     }
     return std::string();
 }

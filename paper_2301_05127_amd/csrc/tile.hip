@@ -1,0 +1,905 @@
+// Tile passes (gfx950): the derivatives of a sub-flow along x and along one strided axis
+// ("rows": y of an elastic grid, z of a 2-D acoustic one) in one kernel, combined with the
+// update of the sub-flow's outputs (paper Sec. 2: the velocity-stress systems; Sec. 3.3:
+// the Strang sub-flows), and the z derivatives an elastic stage needs beforehand.
+//
+// Why: the passes are bound by HBM.  One pass per derivative has to park the partial sums
+// in full-size temporaries; taking two axes of a stage together leaves
+//   acoustic, bytes per node and step: 60 (three line kernels) -> 44 (two tile kernels),
+//   elastic: 264 (18 line kernels) -> 192 (two z stores of three fields, two tile kernels).
+//
+// A tile is a piece of at most 64 intervals of x times a piece of at most 64 intervals of
+// the rows (patches longer than that are cut, TileHost).  A wave owns 8 consecutive rows,
+// lane = column, so every row index, factor and carry coefficient along the rows is
+// wave-uniform (scalar loads, SGPR operands) and every global access is one 256-byte row.
+//
+// The factors do not depend on the data, so neither do the multipliers of the carries:
+//  * rows: each chunk of 8 rows eliminates and back-substitutes from zero carries and
+//    publishes the two end values (B, W) and its share of the junction slopes' tap sums;
+//    after ONE barrier every wave forms its two carries as sums over the chunks with
+//    coefficients from the table (FP64 on the host), where composing the maps chunk by
+//    chunk takes two barriers and the maps' multipliers through LDS.
+//  * x: the wave's rows pass through LDS once (each wave its own rows, no barrier), 16 lanes
+//    of four nodes solve a row, four rows at a time; the carries are composed by three
+//    doubling steps of one DPP move and one FMA each.
+// The tap sums along the rows come from the rows a wave holds and from the halo rows,
+// which are dealt to the waves of the workgroup.
+//
+// Measured (us per step, line passes -> tiles): elastic 513^3 8350 -> 6340, 257^3 x 2
+// shots 2190 -> 1655, 65^3 155 -> 63; acoustic 129^2 40 -> 22.  513^3: stress tiles 2637 us
+// (4.3 TB/s of the compulsory bytes), velocity tiles 2061 (3.9), z stores 820 (4.0); a 1 GiB
+// copy reaches 5.2 TB/s.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "line_device.h"
+#include "loss_internal.h"
+#include "tile_index.h"
+
+namespace loss {
+
+namespace {
+
+constexpr int kHaloPre = 4;     // halo rows per wave and field loaded ahead of the solve
+
+// orders the LDS accesses of a wave's lanes among each other (the wave runs in lockstep;
+// this keeps the compiler from moving them across)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// sum over the 16 lanes of a DPP row, in every lane
+__device__ __forceinline__ float row_sum(float v)
+{
+    auto ror = [](float x, auto dc) {
+        constexpr int D = decltype(dc)::value;
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + D, 0xF, 0xF, true));
+    };
+    v += ror(v, std::integral_constant<int, 8>{});
+    v += ror(v, std::integral_constant<int, 4>{});
+    v += ror(v, std::integral_constant<int, 2>{});
+    v += ror(v, std::integral_constant<int, 1>{});
+    return v;
+}
+
+__device__ __forceinline__ Piece piece_of(const TileAxis &t, int i)
+{
+    const int4 p = t.piece[i];
+    return make_piece(p.x, p.y, p.z, p.w);
+}
+
+// ---- rows ------------------------------------------------------------------------
+// One wave's chunk of one field: rows q .. q + 7 of a piece, u[0 .. 9] = rows q - 1 .. q + 8.
+
+// eliminated rows from a zero carry, B and W of the chunk
+__device__ __forceinline__ void rows_local(const TileChunk &t, const float (&u)[kTileC + 2], float (&y)[kTileC],
+                                           float &B, float &W)
+{
+    float v = 0.f;
+#pragma unroll
+    for (int c = 0; c < kTileC; ++c) {
+        v = fmaf(t.nf[c], v, t.sc[c] * (u[c + 2] - u[c]));
+        y[c] = v;
+    }
+    B = v;
+    v = 0.f;
+#pragma unroll
+    for (int c = kTileC - 1; c >= 0; --c) v = fmaf(t.g[c], v, t.fi[c] * y[c]);
+    W = v;
+}
+
+// the wave's share of the tap sums of the piece's two junctions, from its own rows
+__device__ __forceinline__ void taps_own(const TileChunk &t, const float (&u)[kTileC + 2], float &ps, float &pe)
+{
+    if (t.any_ts != 0.f) {          // uniform
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) ps = fmaf(t.ts[c], u[c + 1], ps);
+    }
+    if (t.any_te != 0.f) {
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) pe = fmaf(t.te[c], u[c + 1], pe);
+    }
+}
+
+// A wave publishes B, W, ps, pe of each field into its own row buffer once its x solves are
+// done (4 * 64 floats per field, at most three fields: below kTileC * kRowPitch).
+constexpr int kWaveLds = kTileC * kRowPitch;
+static_assert(3 * 4 * 64 <= kWaveLds, "exchange area");
+
+__device__ __forceinline__ void rows_publish(float *ex, int lane, float B, float W, float ps, float pe)
+{
+    ex[lane] = B;
+    ex[64 + lane] = W;
+    ex[128 + lane] = ps;
+    ex[192 + lane] = pe;
+}
+
+// the chunk's derivative from its carries; returns the carry from below (the value at the
+// closing row for the last chunk)
+template <int STRIDE>
+__device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex, int nw, int lane, float (&y)[kTileC])
+{
+    float ph = 0.f, pe = 0.f, yin = 0.f, win = 0.f;
+#pragma unroll
+    for (int j = 0; j < kTileWaves; ++j) {
+        if (j < nw) {   // uniform
+            const float *e = ex + j * STRIDE + lane;
+            const float B = e[0], W = e[64];
+            ph += e[128];
+            pe += e[192];
+            yin = fmaf(t.fB[j], B, yin);
+            win = fmaf(t.zB[j], B, win);
+            win = fmaf(t.zW[j], W, win);
+        }
+    }
+    yin = fmaf(t.fph, ph, yin);
+    win = fmaf(t.zph, ph, win);
+    win = fmaf(t.zE, pe, win);
+    float v = win;
+#pragma unroll
+    for (int c = kTileC - 1; c >= 0; --c) {
+        v = fmaf(t.g[c], v, t.fi[c] * fmaf(t.P[c], yin, y[c]));
+        y[c] = v;
+    }
+    return win;
+}
+
+// ---- x ----------------------------------------------------------------------------
+// What depends on the lane only: factors of its four nodes, carry multipliers, taps.
+// Solve rows of the piece in LDS (row r at L + r * kRowPitch) by 16 lanes each: the
+// derivative of the piece's nodes replaces them, and that of the line's last node follows
+// when the piece closes the line.  The lane's table entry (factors of its four nodes, carry
+// multipliers, taps k, k + 16, k + 32 of the two junctions and their places in the row) is
+// read from LDS as it is needed: kept in registers over the fields it would take 44.
+struct XPiece {
+    float4 end;
+    int m, kc;
+    bool last, wide;         // closes the line; taps beyond the first 32 of a junction
+};
+
+__device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, float *L, int k)
+{
+    __builtin_amdgcn_sched_barrier(0);   // one row group at a time: interleaved they spill
+    const float4 cs = t[7], os = t[8], ce = t[9], oe = t[10];
+    auto at = [&](float o) {        // the table holds byte offsets
+        return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(L) + __float_as_int(o));
+    };
+    float ph = cs.x * at(os.x), pe = ce.x * at(oe.x);
+    ph = fmaf(cs.y, at(os.y), ph);
+    pe = fmaf(ce.y, at(oe.y), pe);
+    if (p.wide) {                   // uniform
+        ph = fmaf(cs.z, at(os.z), ph);
+        pe = fmaf(ce.z, at(oe.z), pe);
+    }
+    ph = row_sum(ph);
+    pe = row_sum(pe);
+    if (p.last) pe = fmaf(p.end.z, L[kRowOwn + p.m] - L[kRowOwn + p.m - 1], pe);
+    __builtin_amdgcn_sched_barrier(0);
+    const float4 u = ld4(L + kRowOwn + 4 * k);
+    const float uE = L[kRowRight];
+    const float ul = row_shift_up_fill<1>(u.w, u.x);
+    const float ur = row_shift_down_fill<1>(u.x, uE);
+    const float4 nf = t[0], sc = t[1], P = t[4], a = t[5];
+    float y0 = sc.x * (u.y - ul);
+    float y1 = fmaf(nf.y, y0, sc.y * (u.z - u.x));
+    float y2 = fmaf(nf.z, y1, sc.z * (u.w - u.y));
+    float y3 = fmaf(nf.w, y2, sc.w * (ur - u.z));
+    float B = fmaf(a.w, ph, y3);
+    B = fmaf(a.x, row_shift_up_fill<1>(B, 0.f), B);
+    B = fmaf(a.y, row_shift_up_fill<2>(B, 0.f), B);
+    B = fmaf(a.z, row_shift_up_fill<4>(B, 0.f), B);
+    const float yin = row_shift_up_fill<1>(B, ph);
+    y0 = fmaf(P.x, yin, y0);
+    y1 = fmaf(P.y, yin, y1);
+    y2 = fmaf(P.z, yin, y2);
+    y3 = fmaf(P.w, yin, y3);
+    float we = fmaf(-p.end.y, y3, p.end.x * pe);   // of the closing lane
+    we = __shfl(we, p.kc, 16);
+    __builtin_amdgcn_sched_barrier(0);
+    const float4 fi = t[2], g = t[3], b = t[6];
+    const float t0 = fi.x * y0, t1 = fi.y * y1, t2 = fi.z * y2, t3 = fi.w * y3;
+    float W = fmaf(g.z, t3, t2);
+    W = fmaf(g.y, W, t1);
+    W = fmaf(g.x, W, t0);
+    W = fmaf(b.w, we, W);
+    W = fmaf(b.x, row_shift_down_fill<1>(W, 0.f), W);
+    W = fmaf(b.y, row_shift_down_fill<2>(W, 0.f), W);
+    W = fmaf(b.z, row_shift_down_fill<4>(W, 0.f), W);
+    const float win = row_shift_down_fill<1>(W, we);
+    float4 r;
+    r.w = fmaf(g.w, win, t3);
+    r.z = fmaf(g.z, r.w, t2);
+    r.y = fmaf(g.y, r.z, t1);
+    r.x = fmaf(g.x, r.y, t0);
+    st4(L + kRowOwn + 4 * k, r);
+    if (p.last) {
+        wave_sync();
+        if (k == 0) L[kRowOwn + p.m] = we;
+    }
+}
+
+template <int MODE>
+struct Traits;
+template <>
+struct Traits<TILE_EL_STRESS> {   // v1 v2 v3
+    static constexpr int NF = 3;
+    static constexpr bool xs(int f) { return true; }
+    static constexpr bool ys(int f) { return true; }
+    static constexpr int px(int f) { return 9 + 3 * f; }        // layer variable of d1 v_f, d2 v_f
+    static constexpr int py(int f) { return 9 + 3 * f + 1; }
+};
+template <>
+struct Traits<TILE_EL_VEL> {      // s11 s12 s22 s13 s23
+    static constexpr int NF = 5;
+    static constexpr bool xs(int f) { return f == 0 || f == 1 || f == 3; }
+    static constexpr bool ys(int f) { return f == 1 || f == 2 || f == 4; }
+    static constexpr int px(int f) { return f == 0 ? 0 : (f == 1 ? 3 : 6); }
+    static constexpr int py(int f) { return f == 1 ? 1 : (f == 2 ? 4 : 7); }
+};
+template <>
+struct Traits<TILE_AC_STRESS> {   // v1 v3
+    static constexpr int NF = 2;
+    static constexpr bool xs(int f) { return f == 0; }
+    static constexpr bool ys(int f) { return f == 1; }
+    static constexpr int px(int f) { return 2; }
+    static constexpr int py(int f) { return 3; }
+};
+template <>
+struct Traits<TILE_AC_VEL> {      // sigma
+    static constexpr int NF = 1;
+    static constexpr bool xs(int f) { return true; }
+    static constexpr bool ys(int f) { return true; }
+    static constexpr int px(int f) { return 0; }
+    static constexpr int py(int f) { return 1; }
+};
+
+template <int MODE>
+constexpr int rows_slot(int f)
+{
+    int n = 0;
+    for (int i = 0; i < f; ++i) n += Traits<MODE>::ys(i) ? 1 : 0;
+    return n;
+}
+
+// Where the tile lives: element of node (0, 0) of its plane in a field (of its shot) and in
+// a media array (uniform), the lane's column (clamped into the piece) and its byte offset,
+// whether the lane owns a node, the bytes per row.
+struct Place {
+    int64_t fb, mb;
+    int shot, o;
+    int xc;
+    bool act;
+    unsigned vx, rs4;
+};
+
+// Node access through buffer descriptors: scalar base, scalar row offset, the lane's column
+// offset: one instruction and no address arithmetic per access, and one register for the
+// addresses of every row and array (64-bit addresses formed per access were half of the
+// kernels' vector instructions).  Offsets are 32-bit bytes: a field of one shot stays below
+// 2^30 elements.
+typedef __amdgpu_buffer_rsrc_t Buf;
+__device__ __forceinline__ Buf buf(const float *p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, -1, 0x00020000);
+}
+__device__ __forceinline__ float ld(Buf b, unsigned row, unsigned col)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)col, (int)row, 0));
+}
+__device__ __forceinline__ void st(Buf b, unsigned row, unsigned col, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), b, (int)col, (int)row, 0);
+}
+
+// Sum of the source terms of field fid (a component of the outputs) over the R rows from
+// row q on, as the update adds them.
+template <int R>
+__device__ __forceinline__ void source_add(const TileArgs &a, const Place &pl, int64_t n, int fid, int q,
+                                           float (&add)[R])
+{
+#pragma unroll
+    for (int c = 0; c < R; ++c) add[c] = 0.f;
+    const int k1 = a.src_begin[pl.shot + 1];
+    for (int k = a.src_begin[pl.shot]; k < k1; ++k) {
+        const SrcDev &sd = a.src[k];
+        if (fid < sd.field0 || fid >= sd.field0 + sd.nfield) continue;
+        const int64_t ns = n + a.src_time_offset;
+        if (ns < 0 || ns >= sd.nt) continue;
+        const int r0 = a.row_axis == 1 ? sd.y0 : sd.z0, nr = a.row_axis == 1 ? sd.by : sd.bz;
+        const int oo = a.row_axis == 1 ? pl.o - sd.z0 : 0, no = a.row_axis == 1 ? sd.bz : 1;
+        if ((unsigned)oo >= (unsigned)no) continue;
+        const float amp = a.src_scale * a.wavpool[sd.wav_off + ns];
+        const unsigned ix = (unsigned)(pl.xc - sd.x0);
+        const float *w = a.wpool + sd.w_off + (int64_t)oo * nr * sd.bx;
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            const unsigned ir = (unsigned)(q + c - r0);
+            if (ir < (unsigned)nr && ix < (unsigned)sd.bx) {
+                float v = amp * w[ir * (unsigned)sd.bx + ix];
+                if (sd.force) v *= ld(buf(a.c0 + pl.mb), (unsigned)(q + c) * pl.rs4, pl.vx);
+                add[c] += v;
+            }
+        }
+    }
+}
+
+// The layer's sub-flow on one derivative of R rows: D becomes the effective derivative and
+// the memory variable advances.  Along x the table entry is the lane's, along the rows the row's.
+template <int R, bool ALONG_X>
+__device__ __forceinline__ void layer_flow(const TileArgs &a, const Place &pl, int var, int q, int nrow,
+                                           float (&D)[R])
+{
+    const Buf m = buf(a.pml_mem + var * a.pml_stride + pl.fb);
+    const TileAxis &ax = ALONG_X ? a.x : a.r;
+    auto band = [&](int j) { return j < ax.pml_w || j > ax.N - ax.pml_w; };
+    if (!pl.act || (ALONG_X && !band(pl.xc))) return;
+    const float4 tx = ALONG_X ? a.px[pl.xc] : make_float4(0.f, 0.f, 0.f, 0.f);
+    float psi[R];
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+        psi[c] = 0.f;
+        if (c < nrow && (ALONG_X || band(q + c))) psi[c] = ld(m, (unsigned)(q + c) * pl.rs4, pl.vx);
+    }
+#pragma unroll
+    for (int c = 0; c < R; ++c)
+        if (c < nrow && (ALONG_X || band(q + c))) {
+            const float4 t = ALONG_X ? tx : a.pr[q + c];
+            float psi1;
+            D[c] = pml_flow(t, D[c], psi[c], &psi1);
+            if (a.pml_store) st(m, (unsigned)(q + c) * pl.rs4, pl.vx, psi1);
+        }
+}
+
+// What the update of a row takes: the sums of x and row derivatives per output.
+//   elastic stress: d1 v1, d2 v2, d2 v1 + d1 v2, d1 v3, d2 v3; elastic velocity:
+//   d1 s_i1 + d2 s_i2; acoustic stress: d1 v1 + d3 v3; acoustic velocity: d1 sigma, d3 sigma
+template <int MODE>
+struct Sums;
+template <>
+struct Sums<TILE_EL_STRESS> { static constexpr int N = 5; };
+template <>
+struct Sums<TILE_EL_VEL> { static constexpr int N = 3; };
+template <>
+struct Sums<TILE_AC_STRESS> { static constexpr int N = 1; };
+template <>
+struct Sums<TILE_AC_VEL> { static constexpr int N = 2; };
+
+template <int MODE, int R>
+__device__ __forceinline__ void make_sums(const float (&dx)[Traits<MODE>::NF][R], const float (&dy)[Traits<MODE>::NF][R],
+                                          float (&e)[Sums<MODE>::N][R])
+{
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+        if constexpr (MODE == TILE_EL_STRESS) {
+            e[0][c] = dx[0][c];
+            e[1][c] = dy[1][c];
+            e[2][c] = dy[0][c] + dx[1][c];
+            e[3][c] = dx[2][c];
+            e[4][c] = dy[2][c];
+        } else if constexpr (MODE == TILE_EL_VEL) {
+            e[0][c] = dx[0][c] + dy[1][c];
+            e[1][c] = dx[1][c] + dy[2][c];
+            e[2][c] = dx[3][c] + dy[4][c];
+        } else if constexpr (MODE == TILE_AC_STRESS) {
+            e[0][c] = dy[1][c] + dx[0][c];
+        } else {
+            e[0][c] = dx[0][c];
+            e[1][c] = dy[0][c];
+        }
+    }
+}
+
+// Update of the R rows from row q on, lane = column.  FULL: all R rows belong to the piece
+// and no source reaches the tile (nearly all waves); else the first nrow rows, with the
+// sources when srcs is set.  KEEP: the derivatives are stored too.  pre: the operands of the
+// acoustic passes, read with the fields.
+template <int MODE>
+constexpr bool kEarly = MODE == TILE_AC_STRESS || MODE == TILE_AC_VEL;
+
+template <int MODE, int R, bool FULL, bool KEEP, bool PRE>
+__device__ __forceinline__ void tile_update(const TileArgs &a, const Place &pl, int64_t n, int q, int nrow, bool srcs,
+                                            const float (&e)[Sums<MODE>::N][R], const float (&pre)[3][R])
+{
+    if (!pl.act) return;
+    auto row = [&](int c) { return FULL || c < nrow; };
+    auto get = [&](const float *p, int c) { return ld(buf(p + pl.fb), (unsigned)(q + c) * pl.rs4, pl.vx); };
+    auto med = [&](const float *p, int c) { return ld(buf(p + pl.mb), (unsigned)(q + c) * pl.rs4, pl.vx); };
+    auto put = [&](float *p, int c, float v) { st(buf(p + pl.fb), (unsigned)(q + c) * pl.rs4, pl.vx, v); };
+    auto keep = [&](int k, int c, float v) {
+        if (KEEP) put(a.keep + k * a.keep_stride, c, v);
+    };
+    float add[R];
+#pragma unroll
+    for (int c = 0; c < R; ++c) add[c] = 0.f;
+    if constexpr (MODE == TILE_EL_STRESS) {
+        if (!FULL && srcs) source_add<R>(a, pl, n, 3, q, add);   // stress sources act on the normal stresses alike
+        constexpr int G = R < 4 ? R : 4;   // rows whose operands are in flight together
+#pragma unroll
+        for (int h = 0; h < R; h += G) {
+            float s[3][G], t3[G], l2m[G], lam[G];
+#pragma unroll
+            for (int c = 0; c < G; ++c)
+                if (row(h + c)) {
+                    t3[c] = get(a.T[2], h + c);
+                    l2m[c] = med(a.c0, h + c);
+                    lam[c] = med(a.c1, h + c);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) s[i][c] = get(a.out[i], h + c);
+                }
+#pragma unroll
+            for (int c = 0; c < G; ++c)
+                if (row(h + c)) {
+                    const float d[3] = {e[0][h + c], e[1][h + c], t3[c]};
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const float other = i == 0 ? d[1] + d[2] : (i == 1 ? d[0] + d[2] : d[0] + d[1]);
+                        float v = fmaf(l2m[c], d[i], lam[c] * other) + s[i][c];
+                        if (!FULL) v += add[h + c];
+                        put(a.out[i], h + c, v);
+                        keep(i, h + c, d[i]);
+                    }
+                }
+        }
+#pragma unroll
+        for (int h = 0; h < R; h += G) {
+            float s[3][G], t1[G], t2[G], mu[G];
+#pragma unroll
+            for (int c = 0; c < G; ++c)
+                if (row(h + c)) {
+                    t1[c] = get(a.T[0], h + c);
+                    t2[c] = get(a.T[1], h + c);
+                    mu[c] = med(a.c2, h + c);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) s[i][c] = get(a.out[3 + i], h + c);
+                }
+#pragma unroll
+            for (int c = 0; c < G; ++c)
+                if (row(h + c)) {
+                    const float gs[3] = {e[2][h + c], t1[c] + e[3][h + c], t2[c] + e[4][h + c]};
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        put(a.out[3 + i], h + c, fmaf(mu[c], gs[i], s[i][c]));
+                        keep(3 + i, h + c, gs[i]);
+                    }
+                }
+        }
+    } else if constexpr (MODE == TILE_EL_VEL) {
+        float b[R], v[3][R], t[3][R];
+#pragma unroll
+        for (int c = 0; c < R; ++c)
+            if (row(c)) {
+                b[c] = med(a.c0, c);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    v[i][c] = get(a.base[i], c);
+                    t[i][c] = get(a.T[i], c);
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            if (!FULL && srcs) source_add<R>(a, pl, n, i, q, add);
+#pragma unroll
+            for (int c = 0; c < R; ++c)
+                if (row(c)) {
+                    const float dr = e[i][c] + t[i][c];
+                    float r = fmaf(a.alpha * b[c], dr, v[i][c]);
+                    if (!FULL) r += add[c];
+                    put(a.out[i], c, r);
+                    keep(i, c, dr);
+                }
+        }
+    } else if constexpr (MODE == TILE_AC_STRESS) {
+        float s[R], K[R];
+#pragma unroll
+        for (int c = 0; c < R; ++c)
+            if (row(c)) {
+                s[c] = PRE ? pre[0][c] : get(a.out[0], c);
+                K[c] = PRE ? pre[1][c] : med(a.c0, c);
+            }
+        if (!FULL && srcs) source_add<R>(a, pl, n, 0, q, add);
+#pragma unroll
+        for (int c = 0; c < R; ++c)
+            if (row(c)) {
+                float v = fmaf(a.alpha * K[c], e[0][c], s[c]);
+                if (!FULL) v += add[c];
+                put(a.out[0], c, v);
+                keep(0, c, e[0][c]);
+            }
+    } else {
+        float v1[R], v3[R], b[R], add3[R];
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            add3[c] = 0.f;
+            if (row(c)) {
+                b[c] = PRE ? pre[0][c] : med(a.c0, c);
+                v1[c] = PRE ? pre[1][c] : get(a.base[0], c);
+                v3[c] = PRE ? pre[2][c] : get(a.base[1], c);
+            }
+        }
+        if (!FULL && srcs) {
+            source_add<R>(a, pl, n, 1, q, add);    // field ids of v1, v3
+            source_add<R>(a, pl, n, 2, q, add3);
+        }
+#pragma unroll
+        for (int c = 0; c < R; ++c)
+            if (row(c)) {
+                float p = fmaf(a.alpha * b[c], e[0][c], v1[c]), r = fmaf(a.alpha * b[c], e[1][c], v3[c]);
+                if (!FULL) {
+                    p += add[c];
+                    r += add3[c];
+                }
+                put(a.out[0], c, p);
+                put(a.out[1], c, r);
+            }
+    }
+}
+
+// does a source of the shot reach the tile?
+__device__ __forceinline__ bool tile_has_source(const TileArgs &a, int shot, int o, const Piece &px, const Piece &pr)
+{
+    const int k1 = a.src_begin[shot + 1];
+    for (int k = a.src_begin[shot]; k < k1; ++k) {
+        const SrcDev &sd = a.src[k];
+        const int r0 = a.row_axis == 1 ? sd.y0 : sd.z0, nr = a.row_axis == 1 ? sd.by : sd.bz;
+        const bool ho = a.row_axis == 1 ? (o >= sd.z0 && o < sd.z0 + sd.bz) : true;
+        if (ho && px.e >= sd.x0 && px.s < sd.x0 + sd.bx && pr.e >= r0 && pr.s < r0 + nr) return true;
+    }
+    return false;
+}
+
+template <int MODE, bool KEEP>
+__global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nreal)
+{
+    using T = Traits<MODE>;
+    constexpr int NF = T::NF;
+    __shared__ float4 tab4[16 * (kLaneF / 4)];                // x lanes' table of the piece
+    __shared__ float4 lds4[kTileWaves * kWaveLds / 4];
+    float *lds = reinterpret_cast<float *>(lds4);
+    // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs; each XCD gets a
+    // contiguous range of tiles (x fastest), so neighbours' halos meet in one L2
+    const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    if (lin >= nreal) return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int ntx = a.x.nsub, ntr = a.r.nsub;
+    const int plane = lin / (ntx * ntr), tile = lin - plane * (ntx * ntr);
+    const int lr = tile / ntx, lx = tile - lr * ntx;
+    Place pl;
+    pl.shot = plane / a.nother;
+    pl.o = plane - pl.shot * a.nother;
+    pl.mb = pl.o * a.ostride;
+    pl.fb = pl.shot * a.shot_stride + pl.mb;
+    const Piece px = piece_of(a.x, lx), pr = piece_of(a.r, lr);
+    const bool lastx = px.e == a.x.N, lastr = pr.e == a.r.N;
+    pl.xc = min(px.s + lane, px.e);
+    pl.act = lane < px.m + (lastx ? 1 : 0);
+
+    const int64_t n = a.step_in ? *a.step_in + a.step_add : 0;
+    if (a.step_out && blockIdx.x == 0 && threadIdx.x == 0) *a.step_out = n;
+    int rec0 = 0, rec1 = 0;
+    if (a.rec_begin && n >= 1 && n <= a.trace_len) {
+        rec0 = a.rec_begin[lin];
+        rec1 = a.rec_begin[lin + 1];
+    }
+    if ((MODE == TILE_EL_VEL || MODE == TILE_AC_VEL) && rec1 > rec0) {   // half of the old value
+        for (int k = rec0 + (int)threadIdx.x; k < rec1; k += blockDim.x) {
+            const RecDev rd = a.rec[k];
+            a.traces[rd.trace_off + n - 1] = 0.5 * (double)a.fields[rd.comp][rd.shot * a.shot_stride + rd.node];
+        }
+        __syncthreads();
+    }
+
+    const int q = pr.s + w * kTileC;
+    const int nown = min(max(pr.e - q, 0), kTileC);           // rows of the piece in this wave
+    const bool clos = lastr && nown > 0 && q + kTileC >= pr.e;  // this wave also updates row N
+    float *L = lds + w * kWaveLds;
+    pl.vx = 4u * pl.xc;
+    pl.rs4 = 4u * (unsigned)a.rstride;
+
+    // ---- loads ---------------------------------------------------------------------
+    // rows past the piece repeat its closing row (their factors ignore them)
+    float u[NF][kTileC + 2], yh[NF][kHaloPre], xh[NF][6];
+    const int nhx = halo_count(px), nhr = halo_count(pr);
+    const int *hn = a.r.halo_node + (size_t)lr * kTapW;
+    const float2 *hc = a.r.halo_c + (size_t)lr * kTapW;
+    // x halo: entries 0 .. 31 of two rows per load, entries 32 .. 40 (wide taps) of four
+    const bool wide = nhx > 32;
+    const int hi = min(lane & 31, nhx - 1), hj = min(32 + (lane & 15), nhx - 1);
+    const unsigned hcol = 4u * line_node(halo_pos(px, hi), a.x.N, a.x.periodic);
+    auto load = [&](int f) {
+        const Buf in = buf(a.in[f] + pl.fb);
+#pragma unroll
+        for (int c = 0; c < kTileC + 2; ++c)
+            if (T::ys(f) || (c > 0 && c <= kTileC))
+                u[f][c] = ld(in, (unsigned)max(min(q - 1 + c, pr.e), 0) * pl.rs4, pl.vx);
+        if (T::xs(f)) {
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                xh[f][h] = ld(in, 0, (unsigned)min(q + 2 * h + (lane >> 5), pr.e) * pl.rs4 + hcol);
+            if (wide) {
+                const unsigned wcol = 4u * line_node(halo_pos(px, hj), a.x.N, a.x.periodic);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    xh[f][4 + h] = ld(in, 0, (unsigned)min(q + 4 * h + (lane >> 4), pr.e) * pl.rs4 + wcol);
+            }
+        }
+    };
+    auto load_halo = [&](int f) {   // entries past the halo's count repeat row e with zero taps
+#pragma unroll
+        for (int h = 0; h < kHaloPre; ++h) yh[f][h] = ld(buf(a.in[f] + pl.fb), (unsigned)hn[w + h * a.nw] * pl.rs4, pl.vx);
+    };
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+        if (T::xs(f)) load(f);
+    float pre[3][kTileC];
+    if constexpr (kEarly<MODE>) {
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) {
+            const unsigned ro = (unsigned)min(q + c, pr.e) * pl.rs4;
+            if constexpr (MODE == TILE_AC_STRESS) {
+                pre[0][c] = ld(buf(a.out[0] + pl.fb), ro, pl.vx);
+                pre[1][c] = ld(buf(a.c0 + pl.mb), ro, pl.vx);
+            } else {
+                pre[0][c] = ld(buf(a.c0 + pl.mb), ro, pl.vx);
+                pre[1][c] = ld(buf(a.base[0] + pl.fb), ro, pl.vx);
+                pre[2][c] = ld(buf(a.base[1] + pl.fb), ro, pl.vx);
+            }
+        }
+    }
+    {
+        const float4 *tg = a.x.lanes + (size_t)lx * 16 * (kLaneF / 4);
+        for (int i = threadIdx.x; i < 16 * (kLaneF / 4); i += blockDim.x) tab4[i] = tg[i];
+    }
+    const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
+    const float rend = a.r.ends[lr].z;
+    const int k16 = lane & 15;
+    const float4 *xt = tab4 + k16 * (kLaneF / 4);
+    XPiece xp;
+    xp.end = a.x.ends[lx];
+    xp.m = px.m;
+    xp.kc = (px.m - 1) >> 2;
+    xp.last = lastx;
+    xp.wide = max(px.hs, px.he) > 15;
+    const bool hits = a.src && tile_has_source(a, pl.shot, pl.o, px, pr);
+    __syncthreads();                                          // the lanes' table
+
+    // ---- x: the wave's rows through LDS -------------------------------------------------
+    float dx[NF][kTileC], dy[NF][kTileC], dxn[NF][1], dyn[NF][1];
+    float *L16 = L + (lane >> 4) * kRowPitch;
+    float *Lh = L + (lane >> 5) * kRowPitch + halo_slot(px, hi), *Lw = L + (lane >> 4) * kRowPitch + halo_slot(px, hj);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        if (T::xs(f) && nown > 0) {
+            wave_sync();
+#pragma unroll
+            for (int c = 0; c < kTileC; ++c) L[c * kRowPitch + kRowOwn + lane] = u[f][c + 1];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) Lh[2 * h * kRowPitch] = xh[f][h];
+            if (wide) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) Lw[4 * h * kRowPitch] = xh[f][4 + h];
+            }
+            wave_sync();
+#pragma unroll
+            for (int it = 0; it < kTileC / 4; ++it) x_row(xp, xt, L16 + 4 * it * kRowPitch, k16);
+            wave_sync();
+#pragma unroll
+            for (int c = 0; c < kTileC; ++c) dx[f][c] = L[c * kRowPitch + kRowOwn + lane];
+            if (clos) {                   // row N of the line's last piece
+                const Buf in = buf(a.in[f] + pl.fb);
+                const float un = ld(in, (unsigned)pr.e * pl.rs4, pl.vx);
+                const int i = min(lane, nhx - 1);
+                const float xn = ld(in, (unsigned)pr.e * pl.rs4, 4u * line_node(halo_pos(px, i), a.x.N, a.x.periodic));
+                wave_sync();
+                L[kRowOwn + lane] = un;
+                L[halo_slot(px, i)] = xn;
+                wave_sync();
+                x_row(xp, xt, L16, k16);
+                wave_sync();
+                dxn[f][0] = L[kRowOwn + lane];
+            }
+        }
+        if (f == 0) {                     // what the rows alone need, in flight during the x solves
+#pragma unroll
+            for (int g = 0; g < NF; ++g) {
+                if (!T::xs(g)) load(g);
+                if (T::ys(g)) load_halo(g);
+            }
+        }
+    }
+
+    // ---- rows: local elimination, shares of the tap sums ------------------------------
+    wave_sync();
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+        if (T::ys(f)) {
+            float B, W, ps = 0.f, pe = 0.f;
+            rows_local(rt, u[f], dy[f], B, W);
+            taps_own(rt, u[f], ps, pe);
+            auto halo = [&](int i, float v) {
+                const float2 c = hc[i];
+                ps = fmaf(c.x, v, ps);
+                pe = fmaf(c.y, v, pe);
+            };
+#pragma unroll
+            for (int h = 0; h < kHaloPre; ++h) halo(w + h * a.nw, yh[f][h]);
+            for (int i = w + kHaloPre * a.nw; i < nhr; i += a.nw)     // few waves, wide taps
+                halo(i, ld(buf(a.in[f] + pl.fb), (unsigned)hn[i] * pl.rs4, pl.vx));
+            if (clos) {
+                // natural end: the closing row's difference (rend is 0 on a junction)
+                float ue = 0.f, ul = 0.f;
+#pragma unroll
+                for (int c = 0; c < kTileC; ++c)
+                    if (c == nown - 1) { ul = u[f][c + 1]; ue = u[f][c + 2]; }
+                pe = fmaf(rend, ue - ul, pe);
+            }
+            rows_publish(L + rows_slot<MODE>(f) * 256, lane, B, W, ps, pe);
+        }
+    __syncthreads();
+    if (nown > 0) {
+        const bool band = a.pml_mem && (px.s < a.x.pml_w || px.e > a.x.N - a.x.pml_w || pr.s < a.r.pml_w ||
+                                        pr.e > a.r.N - a.r.pml_w);
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            if (T::ys(f))
+                dyn[f][0] = rows_finish<kWaveLds>(rt, lds + rows_slot<MODE>(f) * 256, a.nw, lane, dy[f]);
+        if (band) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                if (T::xs(f)) layer_flow<kTileC, true>(a, pl, T::px(f), q, nown, dx[f]);
+                if (T::ys(f)) layer_flow<kTileC, false>(a, pl, T::py(f), q, nown, dy[f]);
+                if (clos) {
+                    if (T::xs(f)) layer_flow<1, true>(a, pl, T::px(f), pr.e, 1, dxn[f]);
+                    if (T::ys(f)) layer_flow<1, false>(a, pl, T::py(f), pr.e, 1, dyn[f]);
+                }
+            }
+        }
+        float e[Sums<MODE>::N][kTileC], en[Sums<MODE>::N][1];
+        make_sums<MODE, kTileC>(dx, dy, e);
+        constexpr bool PRE = kEarly<MODE>;
+        const bool full = !hits && nown == kTileC;
+        if (full) tile_update<MODE, kTileC, true, KEEP, PRE>(a, pl, n, q, kTileC, false, e, pre);
+        else tile_update<MODE, kTileC, false, KEEP, PRE>(a, pl, n, q, nown, hits, e, pre);
+        if (clos) {
+            make_sums<MODE, 1>(dxn, dyn, en);
+            const float none[3][1] = {};
+            tile_update<MODE, 1, false, KEEP, false>(a, pl, n, pr.e, 1, hits, en, none);
+        }
+    }
+    if (rec1 > rec0) {   // uniform across the workgroup
+        __syncthreads();
+        for (int k = rec0 + (int)threadIdx.x; k < rec1; k += blockDim.x) {
+            const RecDev rd = a.rec[k];
+            const double v = (double)a.fields[rd.comp][rd.shot * a.shot_stride + rd.node];
+            double *t = a.traces + rd.trace_off + n - 1;
+            if (MODE == TILE_EL_VEL || MODE == TILE_AC_VEL) *t += 0.5 * v;
+            else *t = v;
+        }
+    }
+}
+
+// ---- z derivatives of an elastic stage ------------------------------------------------
+// One workgroup per (field, shot, 64 flattened columns of an x-y plane, piece of z).
+__global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int ncg, int nreal)
+{
+    __shared__ float ex[kTileWaves * 256];
+    const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    if (a.step_inc && blockIdx.x == 0 && threadIdx.x == 0) *a.step_inc += 1;
+    if (lin >= nreal) return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int per = ncg * a.r.nsub;                 // workgroups of one field of one shot
+    const int fs = lin / per, rem = lin - fs * per;
+    const int lr = rem / ncg, cg = rem - lr * ncg;
+    const int f = fs / a.S, shot = fs - f * a.S;
+    const float *in = (f == 0 ? a.in[0] : (f == 1 ? a.in[1] : a.in[2])) + shot * a.shot_stride;
+    float *out = (f == 0 ? a.out[0] : (f == 1 ? a.out[1] : a.out[2])) + shot * a.shot_stride;
+    float *mem = f == 0 ? a.pml_mem[0] : (f == 1 ? a.pml_mem[1] : a.pml_mem[2]);
+    const Piece p = piece_of(a.r, lr);
+    const bool lastr = p.e == a.r.N;
+    const unsigned rs4 = 4u * (unsigned)a.plane;
+    // columns past the plane are clamped; columns of the row padding are solved and not stored
+    const unsigned xc = (unsigned)min((int64_t)cg * 64 + lane, a.plane - 1);
+    const bool act = (int64_t)cg * 64 + lane < a.plane && (int)(xc % (unsigned)a.pitch) < a.nx;
+    const unsigned vx = 4u * xc;
+    const int q = p.s + w * kTileC;
+    const int nown = min(max(p.e - q, 0), kTileC);
+    const bool clos = lastr && nown > 0 && q + kTileC >= p.e;
+    const int nh = halo_count(p);
+    const int *hn = a.r.halo_node + (size_t)lr * kTapW;
+    const float2 *hc = a.r.halo_c + (size_t)lr * kTapW;
+    const Buf bin = buf(in);
+    float u[kTileC + 2], yh[kHaloPre], y[kTileC];
+#pragma unroll
+    for (int c = 0; c < kTileC + 2; ++c) u[c] = ld(bin, (unsigned)max(min(q - 1 + c, p.e), 0) * rs4, vx);
+#pragma unroll
+    for (int h = 0; h < kHaloPre; ++h) yh[h] = ld(bin, (unsigned)hn[w + h * a.nw] * rs4, vx);
+    const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
+    float B, W, ps = 0.f, pe = 0.f;
+    rows_local(rt, u, y, B, W);
+    taps_own(rt, u, ps, pe);
+    auto halo = [&](int i, float v) {
+        const float2 c = hc[i];
+        ps = fmaf(c.x, v, ps);
+        pe = fmaf(c.y, v, pe);
+    };
+#pragma unroll
+    for (int h = 0; h < kHaloPre; ++h) halo(w + h * a.nw, yh[h]);
+    for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) halo(i, ld(bin, (unsigned)hn[i] * rs4, vx));
+    if (clos) {
+        float ue = 0.f, ul = 0.f;
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c)
+            if (c == nown - 1) { ul = u[c + 1]; ue = u[c + 2]; }
+        pe = fmaf(a.r.ends[lr].z, ue - ul, pe);
+    }
+    rows_publish(ex + w * 256, lane, B, W, ps, pe);
+    __syncthreads();
+    if (nown == 0) return;
+    float we = rows_finish<256>(rt, ex, a.nw, lane, y);
+    if (!act) return;
+    const Buf bout = buf(out);
+    if (mem) {
+        const Buf m = buf(mem + shot * a.shot_stride);
+        const int N = a.r.N, pw = a.r.pml_w;
+        float psi[kTileC];
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) {
+            psi[c] = 0.f;
+            if (c < nown && (q + c < pw || q + c > N - pw)) psi[c] = ld(m, (unsigned)(q + c) * rs4, vx);
+        }
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c)
+            if (c < nown && (q + c < pw || q + c > N - pw)) {
+                float psi1;
+                y[c] = pml_flow(a.pr[q + c], y[c], psi[c], &psi1);
+                if (a.pml_store) st(m, (unsigned)(q + c) * rs4, vx, psi1);
+            }
+        if (clos && pw > 0) {
+            float psi1;
+            we = pml_flow(a.pr[N], we, ld(m, (unsigned)N * rs4, vx), &psi1);
+            if (a.pml_store) st(m, (unsigned)N * rs4, vx, psi1);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < kTileC; ++c)
+        if (c < nown) st(bout, (unsigned)(q + c) * rs4, vx, y[c]);
+    if (clos) st(bout, (unsigned)p.e * rs4, vx, we);
+}
+
+}  // namespace
+
+hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st)
+{
+    if (a.nw < 1 || a.nw > kTileWaves) return hipErrorInvalidValue;
+    const int64_t nreal = (int64_t)a.S * a.nother * a.x.nsub * a.r.nsub;
+    if (nreal < 1 || nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
+    const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
+    const int threads = 64 * a.nw, nr = (int)nreal;
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, threads, 0, st, a, nr); };
+    const bool keep = a.keep != nullptr;
+    switch (mode) {
+    case TILE_EL_STRESS: keep ? go(k_tile<TILE_EL_STRESS, true>) : go(k_tile<TILE_EL_STRESS, false>); break;
+    case TILE_EL_VEL: keep ? go(k_tile<TILE_EL_VEL, true>) : go(k_tile<TILE_EL_VEL, false>); break;
+    case TILE_AC_STRESS: keep ? go(k_tile<TILE_AC_STRESS, true>) : go(k_tile<TILE_AC_STRESS, false>); break;
+    case TILE_AC_VEL: go(k_tile<TILE_AC_VEL, false>); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_z(const TileZArgs &a, hipStream_t st)
+{
+    if (a.nw < 1 || a.nw > kTileWaves || a.nf < 1 || a.nf > 3) return hipErrorInvalidValue;
+    const int64_t ncg = (a.plane + 63) / 64;
+    const int64_t nreal = (int64_t)a.nf * a.S * ncg * a.r.nsub;
+    if (nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
+    const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
+    hipLaunchKernelGGL(k_tile_z, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal);
+    return hipGetLastError();
+}
+
+}  // namespace loss

@@ -331,9 +331,9 @@ class Simulation:
 
     # ---- launch-shape autotuning ----------------------------------------------------
     def autotune(self, trial_steps=5):
-        """Pick the fastest launch shape of the line kernels (and, elastic, the faster of
-        the plane and line-pass schedules); returns the choice per axis (loss_set_shape
-        encoding), then, when elastic, the schedule (0 plane, 1 line passes) and the
+        """Pick the fastest launch shape of the line kernels and the faster of the tile and
+        line-pass schedules; returns the choice per axis (loss_set_shape
+        encoding), then, when elastic, the schedule (0 tile, 1 line passes) and the
         shapes of the y and z store passes (0: the axis's)."""
         _check(lib().loss_autotune(self._h, int(trial_steps)))
         out = []
@@ -344,8 +344,8 @@ class Simulation:
         return out
 
     def set_shape(self, shapes):
-        """Set the launch shape per axis (see loss_set_shape; a fourth entry is the elastic
-        schedule, 0 plane passes, 1 line passes, a fifth and sixth the shapes of the y and
+        """Set the launch shape per axis (see loss_set_shape; a fourth entry is the
+        schedule, 0 tile passes, 1 line passes, a fifth and sixth the shapes of the y and
         z store passes); None entries are skipped."""
         for axis, v in enumerate(shapes):
             if v is None or (axis == 1 and self.grid["ndim"] == 2):
