@@ -220,8 +220,9 @@ loss_status loss_deriv(loss_sim *sim, int32_t axis, int32_t order, const float *
 /* For callers that cannot allocate device memory (code under stream capture, tight
  * serving loops, harnesses that forbid hipMalloc): loss_deriv on device arrays
  * (in, out: batch dense fields on the simulation's device, x fastest) that allocates
- * nothing.  Instead of the handle's temporaries its kernels stage the padded fields
- * in a library-static device array of LOSS_STATIC_SCRATCH_FLOATS floats (3 slots;
+ * nothing.  Where the kernels cannot work on the caller's arrays (in and out overlap, a halo
+ * above 20 nodes, the transpose on a periodic axis or with patches shorter than the halo),
+ * they stage the padded fields, instead of in the handle's temporaries, in a library-static device array of LOSS_STATIC_SCRATCH_FLOATS floats (3 slots;
  * each GPU the library runs on holds its copy until the process ends), a slot's worth
  * of fields per pass (loss_create looks up the array's address on its device, which
  * is when the runtime sets the array up).  The work is queued on the simulation's stream (call loss_sync

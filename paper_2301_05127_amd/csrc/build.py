@@ -18,7 +18,7 @@ PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 OUT = os.path.join(PKG, "libloss.so")
 BUILD_DIR = os.path.join(ROOT, "_build", "libloss")
-SOURCES = ["kernels.hip", "tile.hip", "adjoint_elastic.hip", "adjoint_layer.hip", "energy.hip", "tables.cpp",
+SOURCES = ["kernels.hip", "tile.hip", "tile_axis.hip", "adjoint_elastic.hip", "adjoint_layer.hip", "energy.hip", "tables.cpp",
            "loss_api.cpp"]
 ARCH = os.environ.get("LOSS_OFFLOAD_ARCH", "gfx950")
 

@@ -138,6 +138,7 @@ struct loss_sim {
     // tables of the tile passes per axis (x: along_x form; y, z: rows form)
     bool tile_built = false;
     TileAxis tax[3]{};
+    TileAxis top[3][3]{};          // the same for each operator (TileOp) and axis; nsub 0: not applicable
     int tile_nw[3] = {0, 0, 0};    // waves a workgroup needs along the rows of y, z
     std::vector<int> tile_sb[3];   // piece ends
     int64_t *d_step2 = nullptr;    // the step counter between the two kernels of an acoustic tile step
@@ -315,6 +316,36 @@ loss_status adj_deriv(loss_sim *s, int axis, const float *in, const float *in_co
         const hipError_t e = launch_adj_x(epi, x, s->st);
         if (e != hipSuccess) return fail(LOSS_EHIP, std::string("adjoint x: ") + hipGetErrorString(e));
         return timed_end(s, KC_ADJ_X);
+    }
+    if (axis != 0 && s->top[TILE_DT][axis].nsub > 0 && (epi == EPI_STORE || epi == EPI_AXPY)) {
+        // solve, junction rows and gather in one kernel
+        AxisArgs x{};
+        x.in = in;
+        x.coef = in_coef;
+        x.out = out;
+        x.alpha = alpha;
+        x.accumulate = epi == EPI_AXPY;
+        x.t = s->top[TILE_DT][axis];
+        x.nw = s->tile_nw[axis];
+        x.s1 = s->shot_stride;
+        if (axis == 1) {
+            x.n1 = s->nz;
+            x.s0 = x.m0 = s->plane;
+            x.stride = s->pitch;
+            x.ncol = s->nx;
+        } else {
+            x.n1 = 1;
+            x.stride = s->plane;
+            x.ncol = s->plane;
+            x.pitch = (int)s->pitch;
+            x.nx = s->nx;
+        }
+        x.n_outer = (int64_t)nshots * x.n1;
+        loss_status r = timed_begin(s);
+        if (r) return r;
+        const hipError_t e = launch_axis_rows(TILE_DT, x, s->st);
+        if (e != hipSuccess) return fail(LOSS_EHIP, std::string("adjoint rows: ") + hipGetErrorString(e));
+        return timed_end(s, KC_ADJ_SOLVE);
     }
     LineArgs a = base_args(s, axis);
     a.S = nshots;
@@ -1369,39 +1400,29 @@ loss_status upload_axis(loss_sim *s, int axis)
         sc.row = j;
         spec.push_back(sc);
     }
-    unsigned *dplain;
-    SpecialCol *dspec;
-    float4 *dadjw;
     std::copy(h.tap_c.begin(), h.tap_c.end(), tc.begin());
-    float4 *dlu, *drc, *dluT, *dlu2;
-    float2 *dlu2c, *dlum, *dlum2;
-    int *dti, *dgn;
-    float *dtc, *dgc;
-    loss_status r;
-    if ((r = s->alloc(&dlu, n)) || (r = s->alloc(&drc, n)) || (r = s->alloc(&dluT, np)) ||
-        (r = s->alloc(&dlu2, n)) || (r = s->alloc(&dlu2c, n)) || (r = s->alloc(&dlum, np)) ||
-        (r = s->alloc(&dlum2, np)) ||
-        (r = s->alloc(&dti, std::max<size_t>(1, h.tap_idx.size()))) ||
-        (r = s->alloc(&dtc, tc.size())) ||
-        (r = s->alloc(&dgn, h.g_node.size())) || (r = s->alloc(&dgc, gc.size())) || (r = s->alloc(&dadjw, n)) ||
-        (r = s->alloc(&dplain, plain.size())) || (r = s->alloc(&dspec, std::max<size_t>(1, spec.size()))))
-        return r;
-    if (!spec.empty())
-        HIPCHK(hipMemcpy(dspec, spec.data(), spec.size() * sizeof(SpecialCol), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dplain, plain.data(), plain.size() * sizeof(unsigned), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dlu, lu.data(), n * sizeof(float4), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(drc, rc.data(), n * sizeof(float4), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dluT, luT.data(), np * sizeof(float4), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dlu2, lu2.data(), n * sizeof(float4), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dlu2c, lu2c.data(), n * sizeof(float2), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dlum, lum.data(), np * sizeof(float2), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dlum2, lum2.data(), np * sizeof(float2), hipMemcpyHostToDevice));
-    if (!h.tap_idx.empty())
-        HIPCHK(hipMemcpy(dti, h.tap_idx.data(), h.tap_idx.size() * sizeof(int), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dtc, tc.data(), tc.size() * sizeof(float), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dgn, h.g_node.data(), h.g_node.size() * sizeof(int), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dadjw, adjw.data(), n * sizeof(float4), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(dgc, gc.data(), gc.size() * sizeof(float), hipMemcpyHostToDevice));
+    // one allocation and one copy for the axis's tables
+    std::vector<char> blob;
+    auto put = [&](const auto &v, size_t least = 0) {
+        const size_t o = (blob.size() + 255) / 256 * 256;
+        blob.resize(o + std::max(v.size(), least) * sizeof(v[0]));
+        if (!v.empty()) std::memcpy(blob.data() + o, v.data(), v.size() * sizeof(v[0]));
+        return o;
+    };
+    const size_t olu = put(lu), orc = put(rc), oluT = put(luT), olu2 = put(lu2), olu2c = put(lu2c), olum = put(lum),
+                 olum2 = put(lum2), oti = put(h.tap_idx, 1), otc = put(tc), ogn = put(h.g_node), ogc = put(gc),
+                 oadjw = put(adjw), oplain = put(plain), ospec = put(spec, 1);
+    char *dev = nullptr;
+    loss_status r = s->alloc(&dev, blob.size());
+    if (r) return r;
+    HIPCHK(hipMemcpy(dev, blob.data(), blob.size(), hipMemcpyHostToDevice));
+    float4 *dlu = (float4 *)(dev + olu), *drc = (float4 *)(dev + orc), *dluT = (float4 *)(dev + oluT),
+           *dlu2 = (float4 *)(dev + olu2), *dadjw = (float4 *)(dev + oadjw);
+    float2 *dlu2c = (float2 *)(dev + olu2c), *dlum = (float2 *)(dev + olum), *dlum2 = (float2 *)(dev + olum2);
+    int *dti = (int *)(dev + oti), *dgn = (int *)(dev + ogn);
+    float *dtc = (float *)(dev + otc), *dgc = (float *)(dev + ogc);
+    unsigned *dplain = (unsigned *)(dev + oplain);
+    SpecialCol *dspec = (SpecialCol *)(dev + ospec);
     AxisDev &d = s->axd[axis];
     d.N = h.N; d.M = h.M; d.p = h.p; d.ntap = 2 * h.halo + 1; d.h = (float)h.h;
     d.s3 = (float)(3.0 / h.h);
@@ -1422,39 +1443,53 @@ loss_status upload_tiles(loss_sim *s)
 {
     if (s->shot_stride >= (int64_t(1) << 30)) return LOSS_OK;   // 32-bit byte offsets within a shot's field
     std::vector<char> blob;   // every table, uploaded at once
-    size_t off[3][6] = {};
+    size_t off[3][3][6] = {};
     for (int axis = 0; axis < 3; ++axis) {
         if (axis == 1 && s->d.ndim == 2) continue;
-        TileHost h;
-        if (!build_tile(s->axh[axis], axis == 0, h).empty()) return LOSS_OK;
-        auto put = [&](const auto &v) {   // offset of a table in the blob, 16-byte aligned
-            const size_t o = (blob.size() + 15) / 16 * 16;
-            blob.resize(o + v.size() * sizeof(v[0]));
-            std::memcpy(blob.data() + o, v.data(), v.size() * sizeof(v[0]));
-            return o;
-        };
-        const size_t o[6] = {put(h.piece), put(h.halo_node), put(h.ends), put(h.halo_c), put(h.chunk), put(h.lanes)};
-        std::copy(o, o + 6, off[axis]);
-        TileAxis &t = s->tax[axis];
-        t.N = s->axh[axis].N;
-        t.nsub = h.nsub;
-        t.periodic = s->d.end_mode == LOSS_END_PERIODIC;
-        s->tile_nw[axis] = (h.max_m + kTileC - 1) / kTileC;
-        s->tile_sb[axis] = h.sb;
+        for (int op : {TILE_D1, TILE_D2, TILE_DT}) {
+            TileHost h;
+            if (!build_tile(s->axh[axis], axis == 0, op, h).empty()) {
+                if (op != TILE_DT) return LOSS_OK;
+                continue;
+            }
+            auto put = [&](const auto &v) {   // offset of a table in the blob, 16-byte aligned
+                const size_t o = (blob.size() + 15) / 16 * 16;
+                blob.resize(o + v.size() * sizeof(v[0]));
+                std::memcpy(blob.data() + o, v.data(), v.size() * sizeof(v[0]));
+                return o;
+            };
+            size_t *o = off[op][axis];
+            o[0] = put(h.piece);
+            o[1] = put(h.halo_node);
+            o[2] = put(h.ends);
+            o[3] = put(h.halo_c);
+            if (axis > 0) o[4] = put(h.chunk);
+            else o[5] = put(h.lanes);
+            TileAxis &t = s->top[op][axis];
+            t.N = s->axh[axis].N;
+            t.nsub = h.nsub;
+            t.periodic = s->d.end_mode == LOSS_END_PERIODIC;
+            t.s3 = (float)(3.0 / s->d.h[axis]);
+            s->tile_nw[axis] = (h.max_m + kTileC - 1) / kTileC;
+            s->tile_sb[axis] = h.sb;
+        }
     }
     char *d = nullptr;
     loss_status r = s->alloc(&d, blob.size());
     if (r) return r;
     HIPCHK(hipMemcpy(d, blob.data(), blob.size(), hipMemcpyHostToDevice));
-    for (int axis = 0; axis < 3; ++axis) {
-        TileAxis &t = s->tax[axis];
-        t.piece = (const int4 *)(d + off[axis][0]);
-        t.halo_node = (const int *)(d + off[axis][1]);
-        t.ends = (const float4 *)(d + off[axis][2]);
-        t.halo_c = (const float2 *)(d + off[axis][3]);
-        t.chunk = (const TileChunk *)(d + off[axis][4]);
-        t.lanes = (const float4 *)(d + off[axis][5]);
-    }
+    for (int axis = 0; axis < 3; ++axis)
+        for (int op = 0; op < 3; ++op) {
+            TileAxis &t = s->top[op][axis];
+            const size_t *o = off[op][axis];
+            t.piece = (const int4 *)(d + o[0]);
+            t.halo_node = (const int *)(d + o[1]);
+            t.ends = (const TileEnds *)(d + o[2]);
+            t.halo_c = (const float2 *)(d + o[3]);
+            t.chunk = (const TileChunk *)(d + o[4]);
+            t.lanes = (const float4 *)(d + o[5]);
+        }
+    for (int axis = 0; axis < 3; ++axis) s->tax[axis] = s->top[TILE_D1][axis];
     s->tile_built = true;
     // A tile costs its latency however few nodes it holds.  Measured (us per step, tile
     // against line passes at their default shapes): acoustic 1025^2 x 8 shots, patches of 16
@@ -1466,6 +1501,48 @@ loss_status upload_tiles(loss_sim *s)
     const int64_t per_tile = (int64_t)s->nx * (ra == 1 ? s->ny : s->nz) / ((int64_t)s->tax[0].nsub * s->tax[ra].nsub);
     s->tile_pays = tiles < 12000 || per_tile >= 600;
     return LOSS_OK;
+}
+
+// loss_deriv straight from and to dense device fields, the whole batch in one launch; false
+// in *done where it does not apply (no tile tables for the operator, fields of 2^30 nodes or
+// more, arrays that overlap: the caller then stages the fields).
+loss_status deriv_direct(loss_sim *s, int axis, int order, const float *in, float *out, int64_t batch, bool *done)
+{
+    const int op = order == 1 ? TILE_D1 : (order == 2 ? TILE_D2 : TILE_DT);
+    const uintptr_t a0 = (uintptr_t)in, b0 = (uintptr_t)out, len = sizeof(float) * (uintptr_t)(batch * s->nodes);
+    *done = s->tile_built && s->top[op][axis].nsub > 0 && s->nodes < (int64_t(1) << 30) &&
+            (a0 + len <= b0 || b0 + len <= a0) && ((a0 | b0) & 3) == 0;
+    if (!*done) return LOSS_OK;
+    AxisArgs x{};
+    x.in = in;
+    x.out = out;
+    x.t = s->top[op][axis];
+    x.nw = s->tile_nw[axis];
+    x.n1 = 1;
+    x.s1 = s->nodes;
+    const int64_t plane = (int64_t)s->nx * s->ny;
+    if (axis == 0) {
+        x.n_outer = batch * s->ny * s->nz;
+        x.s0 = s->nx;
+    } else if (axis == 1) {
+        x.n_outer = batch * s->nz;
+        x.s1 = plane;
+        x.stride = s->nx;
+        x.ncol = s->nx;
+    } else {
+        x.n_outer = batch;
+        x.stride = plane;
+        x.ncol = plane;
+    }
+    loss_status r = timed_begin(s);
+    if (r) return r;
+    const hipError_t e = axis == 0 ? launch_axis_x(op, x, s->st) : launch_axis_rows(op, x, s->st);
+    if (e == hipErrorInvalidValue) {   // more workgroups than a launch takes: staged, S fields at a time
+        *done = false;
+        return LOSS_OK;
+    }
+    if (e != hipSuccess) return fail(LOSS_EHIP, std::string("derivative launch: ") + hipGetErrorString(e));
+    return timed_end(s, KC_VEL_X + axis);
 }
 
 // Elastic adjoint of the fused schedule that loss_forward_ckpt ran.  Forward step n:
@@ -1694,9 +1771,14 @@ loss_status loss_create(const loss_desc *desc, void *hip_stream, loss_sim **out)
     s->ny = d.ndim == 3 ? (int)d.n[1] + 1 : 1;
     s->nz = (int)d.n[2] + 1;
     // rows start on 64-byte boundaries (a wave's row of 64 floats then covers whole sectors),
-    // unless that padding would take a field over the size limit below
+    // unless that padding would take a field over the size limit below or that of the static
+    // scratch
     s->pitch = ((int64_t)s->nx + 15) / 16 * 16;
-    if (s->pitch * s->ny * s->nz >= (int64_t(1) << 31)) s->pitch = ((int64_t)s->nx + 3) / 4 * 4;
+    {
+        const int64_t p4 = ((int64_t)s->nx + 3) / 4 * 4, rows = (int64_t)s->ny * s->nz;
+        auto over = [&](int64_t limit) { return s->pitch * rows > limit && p4 * rows <= limit; };
+        if (over((int64_t(1) << 31) - 1) || over(kStaticSlot)) s->pitch = p4;
+    }
     s->plane = s->pitch * s->ny;
     s->shot_stride = s->plane * s->nz;
     s->nodes = (int64_t)s->nx * s->ny * s->nz;
@@ -2026,8 +2108,24 @@ loss_status loss_deriv(loss_sim *s, int32_t axis, int32_t order, const float *in
     const int64_t dense = s->nodes;
     loss_status r = unfuse_in_place(s);
     if (r) return r;
+    if (mem == LOSS_MEM_DEVICE) {
+        bool done = false;
+        if ((r = deriv_direct(s, axis, order, in, out, batch, &done)) || done) return r;
+    }
     for (int64_t b0 = 0; b0 < batch; b0 += s->S) {
         const int64_t nb = std::min<int64_t>(s->S, batch - b0);
+        if (mem == LOSS_MEM_HOST) {
+            // through dense device copies of the chunk in the temporaries (each holds S padded
+            // fields or more)
+            bool done = false;
+            HIPCHK(hipMemcpyAsync(s->tmp[1], in + b0 * dense, sizeof(float) * dense * nb, hipMemcpyHostToDevice, s->st));
+            if ((r = deriv_direct(s, axis, order, s->tmp[1], s->tmp[2], nb, &done))) return r;
+            if (done) {
+                HIPCHK(hipMemcpyAsync(out + b0 * dense, s->tmp[2], sizeof(float) * dense * nb, hipMemcpyDeviceToHost, s->st));
+                HIPCHK(hipStreamSynchronize(s->st));
+                continue;
+            }
+        }
         if ((r = copy_field_in(s, s->tmp[1], in + b0 * dense, mem, nb))) return r;
         if (order == -1) {
             if ((r = adj_deriv(s, axis, s->tmp[1], nullptr, s->tmp[2], 1.f, EPI_STORE, s->tmp[0], (int)nb)))
@@ -2061,6 +2159,8 @@ loss_status loss_deriv_static(loss_sim *s, int32_t axis, int32_t order, const fl
     float *base = nullptr;
     loss_status r = static_scratch(&base);
     if (r) return r;
+    bool done = false;
+    if ((r = deriv_direct(s, axis, order, in, out, batch, &done)) || done) return r;
     float *pin = base, *pout = base + kStaticSlot, *Y = base + 2 * kStaticSlot;
     const int64_t dense = s->nodes;
     const int64_t chunk = kStaticSlot / s->shot_stride;   // fields per pass through the scratch

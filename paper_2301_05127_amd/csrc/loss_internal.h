@@ -65,18 +65,19 @@ std::string build_axis(AxisHost &ax, int N, double h, int M, int halo, int end_m
 // the patch's own derivative operator as taps (its entries decay by 0.27 per node; those
 // below kTapTol of the stencil weight are left out), so a piece is solved like a patch.
 constexpr double kTapTol = 0x1p-34;
+enum TileOp : int { TILE_D1 = 0, TILE_D2 = 1, TILE_DT = 2 };   // slopes, moments, the transpose of the slopes
 struct TileHost {
     int nsub = 0, max_m = 0;
-    std::vector<int> sb, bh;            // [nsub+1] piece ends, taps on either side of each (0: natural end)
+    std::vector<int> sb;                // [nsub+1] piece ends
     std::vector<int> piece;             // [nsub][4] {s, e, taps of s, taps of e}
-    std::vector<float> taps;            // [nsub+1][kTapW]
-    std::vector<float> ends;            // [nsub][4] closing row: w_e = iE E - imE y_{e-1}; natural end weight
+    std::vector<float> ends;            // [nsub][8] closing row, see TileEnds
     std::vector<int> halo_node;         // [nsub][kTapW] grid node of each halo entry
-    std::vector<float> halo_c;          // [nsub][kTapW][2] its taps of the start and the closing junction
-    std::vector<float> chunk;           // [nsub][kTileWaves][kChunkF] rows form: see TileChunk
-    std::vector<float> lanes;           // [nsub][16][kLaneF] x form: see XLane (tile.hip)
+    std::vector<float> halo_c;          // [nsub][kTapW][2] its taps of the start and the closing right-hand side
+    std::vector<float> chunk;           // [nsub][kTileWaves][kChunkF] rows form, see TileChunk
+    std::vector<float> lanes;           // [nsub][16][kLaneF] x form: see x_row (tile.hip)
 };
-std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t);
+// `op` of TileOp; an error where the tile passes do not apply.
+std::string build_tile(const AxisHost &ax, bool along_x, int op, TileHost &t);
 
 // A node whose column of G^T is not the plain interior form: its stencil column and
 // the transposed PMBC rows reaching it (gather of the adjoint x pass).
@@ -204,24 +205,36 @@ enum TileMode : int {
 };
 
 // One chunk (kTileC rows) of a piece, rows form: the rows' factors and taps, and the two
-// carries as sums over the chunks' B and W, the slope at the start (ph) and the closing
-// right-hand side (E)
+// carries as sums over the chunks' B and W, the value at the start (ph) and the closing
+// right-hand side (E); transposed: the solution at the row before the chunk likewise (p*),
+// and what each row takes from the junction values y_s, y_e
 struct TileChunk {
     float P[8];                 // products of nf from the chunk's first row on
     float fB[8];                // carry into the elimination
     float zB[8], zW[8];         // carry into the back substitution
-    float fph, zph, zE, pad0;
+    float fph, zph, zE, pE;
     float nf[8], sc[8], fi[8], g[8];
-    float ts[8], te[8];         // taps of the start and the closing junction
-    float any_ts, any_te, pad1, pad2;
+    float ts[8], te[8];         // taps of the start and the closing right-hand side
+    float any_ts, any_te, any_cs, any_ce;
+    float cs[8], ce[8];
+    float pB[8], pW[8];
 };
 constexpr int kChunkF = sizeof(TileChunk) / 4;
-constexpr int kLaneF = 44;
+constexpr int kLaneF = 52;
+// Closing row of a piece: w_e = iE E - imE y_{e-1}.  sE: weight of u_e - u_{e-1} in E
+// (slopes: natural end; moments: Hermite row); transposed: 1 at a natural end.
+// cs, ce: moments: sums of the two tap rows; transposed: the transposed taps of y_s and y_e at
+// the closing node.  m1: transposed: weight of y_s in place of y_{s-1} (-1 at a natural end).
+struct TileEnds {
+    float iE, imE, sE, pad0, cs, ce, m1, pad1;
+};
 
 struct TileAxis {
     int N, nsub, periodic, pml_w;
+    float s3;              // 3/h
     const int4 *piece;
-    const float4 *ends, *lanes;
+    const TileEnds *ends;
+    const float4 *lanes;
     const TileChunk *chunk;
     const int *halo_node;
     const float2 *halo_c;
@@ -265,6 +278,27 @@ struct TileArgs {
     int pml_store;
 };
 hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st);
+
+// One operator (TileOp) along one axis of many fields, tile_axis.hip: out = op(coef in), or
+// out += alpha op(coef in) (transposed slopes).  Outer index o of n_outer: element
+// (o / n1) * s1 + (o % n1) * s0 of in and out, (o % n1) * m0 of coef; along the axis
+// `stride` elements per node.  Rows form: ncol consecutive columns per outer index, those
+// with column % pitch >= nx left alone when pitch is set.  x form (stride 1): one line each.
+struct AxisArgs {
+    const float *in, *coef;
+    float *out;
+    float alpha;
+    int accumulate;
+    int64_t n_outer;
+    int n1;
+    int64_t s1, s0, m0, stride;
+    int64_t ncol;
+    int pitch, nx;
+    int nw;
+    TileAxis t;
+};
+hipError_t launch_axis_rows(int op, const AxisArgs &a, hipStream_t st);
+hipError_t launch_axis_x(int op, const AxisArgs &a, hipStream_t st);
 
 // z derivatives of up to three fields stored in one launch (the strided solve of the tile
 // passes alone)

@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 
 #include "loss_internal.h"
 #include "tile_index.h"
@@ -270,63 +271,109 @@ std::string build_axis(AxisHost &ax, int N, double h, int M, int halo, int end_m
 
 namespace {
 
-// Row J of the derivative operator of the patch [s, e] of an axis as a tap row: z with
-// T^T z = e_J on the patch, then z^T G.  J is far enough inside the patch for the end
-// rows' own right-hand sides (the PMBC slopes) to enter below the tolerance.
-void interior_slope_row(const AxisHost &ax, int s, int e, int J, std::vector<double> &row)
+// Row J of the order-1 or order-2 derivative operator of the patch [s, e] of an axis as a
+// tap row: z with T^T z = e_J on the patch (T the slope or the moment system), then z^T G.
+// J is far enough inside the patch for the end rows' own right-hand sides to enter below
+// the tolerance.
+void interior_row(const AxisHost &ax, int order, int s, int e, int J, std::vector<double> &row)
 {
     const int n = e - s + 1;
+    std::vector<double> diag(n, 4.0), sub(n, 1.0), sup(n, 1.0);
+    for (int i : {0, n - 1}) {
+        const int k = i ? e : s;
+        const bool nat = ax.kind[k] == ROW_NATURAL_L || ax.kind[k] == ROW_NATURAL_R;
+        diag[i] = order == 1 ? (nat ? 2.0 : 1.0) : (nat ? 1.0 : 2.0);
+        if (order == 1 ? !nat : nat) sub[i] = sup[i] = 0.0;   // identity row
+    }
     std::vector<double> cp(n), z(n, 0.0);
     z[J - s] = 1.0;
     // Thomas on T^T: sub-diagonal sup[i-1], super-diagonal sub[i+1]
-    double den = ax.diag[s];
-    cp[0] = (n > 1 ? ax.sub[s + 1] : 0.0) / den;
+    double den = diag[0];
+    cp[0] = (n > 1 ? sub[1] : 0.0) / den;
     z[0] /= den;
     for (int i = 1; i < n; ++i) {
-        const double lo = ax.sup[s + i - 1];
-        den = ax.diag[s + i] - lo * cp[i - 1];
-        cp[i] = (i + 1 < n ? ax.sub[s + i + 1] : 0.0) / den;
+        const double lo = sup[i - 1];
+        den = diag[i] - lo * cp[i - 1];
+        cp[i] = (i + 1 < n ? sub[i + 1] : 0.0) / den;
         z[i] = (z[i] - lo * z[i - 1]) / den;
     }
     for (int i = n - 2; i >= 0; --i) z[i] -= cp[i] * z[i + 1];
     row.assign(n, 0.0);
-    for (int i = 0; i < n; ++i) {
-        if (i > 0) row[i - 1] += z[i] * ax.cm[s + i];
-        row[i] += z[i] * ax.c0[s + i];
-        if (i + 1 < n) row[i + 1] += z[i] * ax.cp[s + i];
+    const double w1 = 3.0 / ax.h, w2 = 6.0 / (ax.h * ax.h);
+    for (int i = 1; i + 1 < n; ++i) {
+        row[i - 1] += z[i] * (order == 1 ? -w1 : w2);
+        row[i] += z[i] * (order == 1 ? 0.0 : -2.0 * w2);
+        row[i + 1] += z[i] * (order == 1 ? w1 : w2);
     }
+}
+
+// Elimination rows of a piece: y_i = nf y_{i-1} + sc (right-hand side), w_i = fi y_i + g
+// w_{i+1}; rows past the piece pass the carries on.
+struct Row {
+    double nf = 1.0, sc = 0.0, fi = 0.0, g = 1.0;
+};
+
+typedef std::vector<double> V;
+
+// First (at_end false) or last (true) row of the inverse of a piece's interior system of
+// T^T: [1 4 1] rows s+1 .. e-1, and the rows of a natural end.  row[k] belongs to node lo + k.
+void interior_inverse_end(const AxisHost &ax, int s, int e, bool at_end, int &lo, std::vector<double> &row)
+{
+    lo = ax.kind[s] == ROW_NATURAL_L ? s : s + 1;
+    const int hi = ax.kind[e] == ROW_NATURAL_R ? e : e - 1;
+    const int n = hi - lo + 1;
+    row.assign(std::max(n, 0), 0.0);
+    if (n < 1) return;
+    auto diag = [&](int i) { return lo + i == s || lo + i == e ? 2.0 : 4.0; };
+    std::vector<double> cp(n);
+    row[at_end ? n - 1 : 0] = 1.0;
+    double den = diag(0);
+    cp[0] = 1.0 / den;
+    row[0] /= den;
+    for (int i = 1; i < n; ++i) {
+        den = diag(i) - cp[i - 1];
+        cp[i] = 1.0 / den;
+        row[i] = (row[i] - row[i - 1]) / den;
+    }
+    for (int i = n - 2; i >= 0; --i) row[i] -= cp[i] * row[i + 1];
 }
 
 }  // namespace
 
-std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t)
+std::string build_tile(const AxisHost &ax, bool along_x, int op, TileHost &t)
 {
     t = TileHost();
     const int N = ax.N;
     if (ax.halo > kTileHalo) return "halo wider than the tile window";
-    const double s3 = 3.0 / ax.h;
+    const double s3 = 3.0 / ax.h, w2 = 6.0 / (ax.h * ax.h);
+    const int nt = 2 * ax.halo + 1;
+    // ---- pieces and the tap rows of their ends (order-1 slopes; order 2 of a cut) ----------
+    std::vector<int> sb, bh;
+    std::vector<double> taps;
+    std::vector<char> real;             // a junction or an end of the method's patches
     auto boundary = [&](int J, int s, int e) {
-        const size_t o = t.taps.size();
-        t.taps.resize(o + kTapW, 0.f);
-        t.sb.push_back(J);
+        const size_t o = taps.size();
+        taps.resize(o + kTapW, 0.0);
+        sb.push_back(J);
+        real.push_back(1);
         if (ax.slot[J] >= 0) {
-            t.bh.push_back(ax.halo);
-            for (int k = 0; k < 2 * ax.halo + 1; ++k)
-                t.taps[o + k] = (float)ax.tap_c[(size_t)ax.slot[J] * (2 * ax.halo + 1) + k];
+            bh.push_back(ax.halo);
+            for (int k = 0; k < nt; ++k) taps[o + k] = ax.tap_c[(size_t)ax.slot[J] * nt + k];
         } else if (ax.kind[J] != ROW_INTERIOR) {
-            t.bh.push_back(0);
+            bh.push_back(0);
         } else {
+            real.back() = 0;
             std::vector<double> row;
-            interior_slope_row(ax, s, e, J, row);
+            interior_row(ax, op == TILE_D2 ? 2 : 1, s, e, J, row);
             int H = kTileHalo;
             auto mag = [&](int d) {
                 const int a = J - d - s, b = J + d - s;
                 return std::max(a >= 0 ? std::fabs(row[a]) : 0.0, b <= e - s ? std::fabs(row[b]) : 0.0);
             };
-            while (H > 1 && mag(H) <= kTapTol * s3) --H;
-            t.bh.push_back(H);
+            while (H > 1 && mag(H) <= kTapTol * (op == TILE_D2 ? w2 : s3)) --H;
+            bh.push_back(H);
             for (int d = -H; d <= H; ++d)
-                if (J + d >= s && J + d <= e) t.taps[o + H + d] = (float)row[J + d - s];
+                if (J + d >= s && J + d <= e) taps[o + H + d] = row[J + d - s];
         }
     };
     for (int l = 0; l < ax.p; ++l) {
@@ -349,62 +396,148 @@ std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t)
         for (int i = 0; i < n; ++i) boundary(s + cut[i], s, e);
         if (e == N) boundary(N, s, e);
     }
-    t.nsub = (int)t.sb.size() - 1;
+    t.sb = sb;
+    t.nsub = (int)sb.size() - 1;
+    if (op == TILE_DT) {
+        if (ax.end_mode == 2) return "transposed taps wrap around a periodic line";
+        // a node takes the transposed taps of its own piece's two ends only
+        for (int b = 0; b <= t.nsub; ++b)
+            if (bh[b] > 0 && ((b > 0 && sb[b] - bh[b] < sb[b - 1] && b > 1) ||
+                              (b < t.nsub && sb[b] + bh[b] > sb[b + 1] && b + 1 < t.nsub)))
+                return "transposed taps reach past the neighbouring piece";
+    }
     for (int b = 0; b < t.nsub; ++b) {
-        const int s = t.sb[b], e = t.sb[b + 1], m = e - s;
-        for (int v : {s, e, t.bh[b], t.bh[b + 1]}) t.piece.push_back(v);
+        const int s = sb[b], e = sb[b + 1], m = e - s;
         t.max_m = std::max(t.max_m, m);
-        // elimination rows of the piece: y_i = nf y_{i-1} + sc (u_{i+1} - u_{i-1}),
-        // w_i = fi y_i + g w_{i+1}; a junction row takes the slope as its carry, rows past
-        // the piece pass the carries on
-        struct Row { double nf, sc, fi, g; };
-        std::vector<Row> r(kTileM, Row{1.0, 0.0, 0.0, 1.0});
-        double d = 0.0, sup = 0.0;
-        for (int i = 0; i < m; ++i) {
-            if (i == 0) {
-                const bool nat = ax.kind[s] == ROW_NATURAL_L;
-                d = nat ? 2.0 : 1.0;
-                sup = nat ? 1.0 : 0.0;
-                r[0] = nat ? Row{0.0, s3, 0.5, -0.5} : Row{1.0, 0.0, 1.0, 0.0};
-            } else {
-                const double mi = 1.0 / d;
-                d = 4.0 - mi * sup;
-                sup = 1.0;
-                r[i] = Row{-mi, s3, 1.0 / d, -1.0 / d};
-            }
-        }
-        double iE = 1.0, imE = 0.0, sE = 0.0;
-        if (ax.kind[e] == ROW_NATURAL_R) {
-            const double mi = 1.0 / d, de = 2.0 - mi * sup;
-            iE = 1.0 / de;
-            imE = mi / de;
-            sE = s3;
-        }
-        for (float v : {(float)iE, (float)imE, (float)sE, 0.f}) t.ends.push_back(v);
-        // taps of the two junctions by the piece's own rows and by its halo entries
-        const Piece p = make_piece(s, e, t.bh[b], t.bh[b + 1]);
-        const float *cs = &t.taps[(size_t)b * kTapW], *ce = cs + kTapW;
-        auto tap = [&](const float *c, int H, int J, int k) {
+        const bool nat_s = ax.kind[s] == ROW_NATURAL_L, nat_e = ax.kind[e] == ROW_NATURAL_R;
+        const double *cs = &taps[(size_t)b * kTapW], *ce = cs + kTapW;
+        auto tap = [](const double *c, int H, int J, int k) {
             const int d = k - (J - H);
-            return d >= 0 && d <= 2 * H ? c[d] : 0.f;
+            return d >= 0 && d <= 2 * H ? c[d] : 0.0;
         };
+        // taps of the start and the closing right-hand side at node k, and how far they reach
+        // outside the piece
+        int hs = bh[b], he = bh[b + 1];
+        std::function<double(int)> tap_s = [&](int k) { return tap(cs, hs, s, k); };
+        std::function<double(int)> tap_e = [&](int k) { return tap(ce, he, e, k); };
+        std::vector<Row> r(kTileM);
+        double iE = 1.0, imE = 0.0, sE = 0.0, endc = 0.0, endd = 0.0;
+        double d = 0.0, sup = 0.0;
+        V as, ae;                       // TILE_DT: transposed-system taps of y_s, y_e by node offset
+        if (op == TILE_D1) {
+            for (int i = 0; i < m; ++i) {
+                if (i == 0) {           // junction: the slope is the carry; natural end row
+                    d = nat_s ? 2.0 : 1.0;
+                    sup = nat_s ? 1.0 : 0.0;
+                    r[0] = nat_s ? Row{0.0, s3, 0.5, -0.5} : Row{1.0, 0.0, 1.0, 0.0};
+                } else {
+                    const double mi = 1.0 / d;
+                    d = 4.0 - mi * sup;
+                    sup = 1.0;
+                    r[i] = Row{-mi, s3, 1.0 / d, -1.0 / d};
+                }
+            }
+            if (nat_e) {
+                const double mi = 1.0 / d, de = 2.0 - mi * sup;
+                iE = 1.0 / de;
+                imE = mi / de;
+                sE = s3;
+            }
+        } else if (op == TILE_D2) {
+            // moments: Hermite rows at a junction (the slope enters the first row with -6/h,
+            // the closing one with 6/h), zero at a natural end, the tapped moment at a cut
+            for (int i = 0; i < m; ++i) {
+                if (i == 0) {
+                    const bool herm = real[b] && !nat_s;
+                    d = herm ? 2.0 : 1.0;
+                    sup = herm ? 1.0 : 0.0;
+                    r[0] = herm ? Row{-6.0 / ax.h, w2, 0.5, -0.5} : Row{nat_s ? 0.0 : 1.0, 0.0, 1.0, 0.0};
+                } else {
+                    const double mi = 1.0 / d;
+                    d = 4.0 - mi * sup;
+                    sup = 1.0;
+                    r[i] = Row{-mi, w2, 1.0 / d, -1.0 / d};
+                }
+            }
+            if (nat_e) {
+                iE = 0.0;
+            } else if (real[b + 1]) {
+                const double mi = 1.0 / d, de = 2.0 - mi * sup;
+                iE = 1.0 / de;
+                imE = mi / de;
+                sE = -w2;
+                tap_e = [&](int k) { return 6.0 / ax.h * tap(ce, he, e, k); };
+            }
+            for (int k = s - kTileHalo; k <= s + kTileHalo; ++k) endc += tap_s(k);
+            for (int k = e - kTileHalo; k <= e + kTileHalo; ++k) endd += tap_e(k);
+        } else {
+            // T^T on the piece's interior rows; the junction rows follow from the neighbouring
+            // interior values: y_J = z_J - y_{J-1} - y_{J+1}, here as taps
+            for (int i = nat_s ? 0 : 1; i < m; ++i) {
+                const bool first = i == (nat_s ? 0 : 1);
+                const double mi = first ? 0.0 : 1.0 / d;
+                d = first ? (nat_s ? 2.0 : 4.0) : 4.0 - mi;
+                r[i] = Row{-mi, 1.0, 1.0 / d, -1.0 / d};
+            }
+            if (!nat_s) r[0] = Row{0.0, 0.0, 0.0, 0.0};
+            iE = 0.0;
+            if (nat_e) {
+                const bool any = m > (nat_s ? 0 : 1);
+                const double mi = any ? 1.0 / d : 0.0, de = 2.0 - mi;
+                iE = 1.0 / de;
+                imE = mi / de;
+            }
+            auto end_taps = [&](int J, V &a) {      // a[kTileHalo + offset]
+                a.assign(2 * kTileHalo + 1, 0.0);
+                a[kTileHalo] = 1.0;
+                const int j = J == s ? b : b + 1;
+                int reach = 0;
+                for (int side = 0; side < 2; ++side) {
+                    const int p = side ? j : j - 1; // the piece right or left of J
+                    if (p < 0 || p >= t.nsub) continue;
+                    int lo;
+                    std::vector<double> row;
+                    interior_inverse_end(ax, sb[p], sb[p + 1], side == 0, lo, row);
+                    for (int k = 0; k < (int)row.size(); ++k) {
+                        const int off = lo + k - J;
+                        if (std::abs(off) <= kTileHalo && std::fabs(row[k]) > kTapTol) {
+                            a[kTileHalo + off] -= row[k];
+                            reach = std::max(reach, std::abs(off));
+                        }
+                    }
+                }
+                return reach;
+            };
+            hs = he = 0;
+            if (!nat_s) hs = end_taps(s, as);
+            if (!nat_e) he = end_taps(e, ae);
+            tap_s = [&](int k) { return !nat_s && std::abs(k - s) <= kTileHalo ? as[kTileHalo + k - s] : 0.0; };
+            tap_e = [&](int k) { return nat_e ? (k == e ? 1.0 : 0.0)
+                                              : (std::abs(k - e) <= kTileHalo ? ae[kTileHalo + k - e] : 0.0); };
+            sE = nat_e ? 1.0 : 0.0;
+            endc = tap(cs, bh[b], s, e);            // transposed PMBC taps at the closing node
+            endd = nat_e ? 0.0 : tap(ce, bh[b + 1], e, e);
+        }
+        const Piece p = make_piece(s, e, hs, he);
+        for (int v : {s, e, hs, he}) t.piece.push_back(v);
+        for (double v : {iE, imE, sE, 0.0, endc, endd, nat_s ? -1.0 : 0.0, 0.0}) t.ends.push_back((float)v);
         for (int i = 0; i < kTapW; ++i) {
             const bool in = i < halo_count(p);
             const int k = in ? halo_pos(p, i) : e;
             t.halo_node.push_back(line_node(k, N, ax.end_mode == 2));
-            t.halo_c.push_back(in ? tap(cs, p.hs, s, k) : 0.f);
-            t.halo_c.push_back(in ? tap(ce, p.he, e, k) : 0.f);
+            const bool real_node = ax.end_mode == 2 || (k >= 0 && k <= N);
+            t.halo_c.push_back(in && real_node ? (float)tap_s(k) : 0.f);
+            t.halo_c.push_back(in && real_node ? (float)tap_e(k) : 0.f);
         }
         // strided passes: the carries of the chunks of kTileC rows as sums over the chunks'
         // own results.  B_j: chunk j eliminated from a zero carry; W_j: its back
-        // substitution from zero carries; ph: the start junction's slope; E: the closing
+        // substitution from zero carries; ph: the start junction's value; E: the closing
         // row's right-hand side.  Vectors over (B_0.., W_0.., ph, E).
         constexpr int nw = kTileWaves, nv = 2 * nw + 2;
-        typedef std::vector<double> V;
         const int nch = (m + kTileC - 1) / kTileC;
-        std::vector<V> yin(nw + 1, V(nv, 0.0)), win(nw, V(nv, 0.0));
+        std::vector<V> yin(nw + 1, V(nv, 0.0)), win(nw, V(nv, 0.0)), prev(nw, V(nv, 0.0));
         std::vector<double> A(nw, 1.0), Q(nw, 1.0), R(nw, 0.0);
-        yin[0][2 * nw] = 1.0;
+        if (op != TILE_DT) yin[0][2 * nw] = 1.0;
         for (int w = 0; w < nch; ++w) {
             double back[kTileC];
             for (int c = 0; c < kTileC; ++c) {
@@ -425,28 +558,49 @@ std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t)
             for (int k = 0; k < nv; ++k) win[w][k] = R[w + 1] * yin[w + 1][k] + Q[w + 1] * win[w + 1][k];
             win[w][nw + w + 1] += 1.0;
         }
+        for (int w = 1; w < nch; ++w) {             // the solution at the row before chunk w
+            const Row &q = r[w * kTileC - 1];
+            for (int k = 0; k < nv; ++k) prev[w][k] = q.fi * yin[w][k] + q.g * win[w - 1][k];
+        }
+        auto push = [&](std::vector<float> &v, double x) { v.push_back((float)x); };
         for (int w = 0; w < nw; ++w) {
-            double a = 1.0;
             const bool on = w < nch;
             const Row *q = &r[w * kTileC];
-            for (int c = 0; c < kTileC; ++c) { a *= q[c].nf; t.chunk.push_back(on ? (float)a : 0.f); }
-            for (int j = 0; j < nw; ++j) t.chunk.push_back(on ? (float)yin[w][j] : 0.f);
-            for (int j = 0; j < nw; ++j) t.chunk.push_back(on ? (float)win[w][j] : 0.f);
-            for (int j = 0; j < nw; ++j) t.chunk.push_back(on ? (float)win[w][nw + j] : 0.f);
-            for (double v : {yin[w][2 * nw], win[w][2 * nw], win[w][2 * nw + 1], 0.0}) t.chunk.push_back(on ? (float)v : 0.f);
-            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].nf);
-            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].sc);
-            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].fi);
-            for (int c = 0; c < kTileC; ++c) t.chunk.push_back((float)q[c].g);
+            double a = 1.0;
+            for (int c = 0; c < kTileC; ++c) { a *= q[c].nf; push(t.chunk, on ? a : 0.0); }
+            for (int j = 0; j < nw; ++j) push(t.chunk, on ? yin[w][j] : 0.0);
+            for (int j = 0; j < nw; ++j) push(t.chunk, on ? win[w][j] : 0.0);
+            for (int j = 0; j < nw; ++j) push(t.chunk, on ? win[w][nw + j] : 0.0);
+            for (double v : {yin[w][2 * nw], win[w][2 * nw], win[w][2 * nw + 1], prev[w][2 * nw + 1]})
+                push(t.chunk, on ? v : 0.0);
+            for (int c = 0; c < kTileC; ++c) push(t.chunk, q[c].nf);
+            for (int c = 0; c < kTileC; ++c) push(t.chunk, q[c].sc);
+            for (int c = 0; c < kTileC; ++c) push(t.chunk, q[c].fi);
+            for (int c = 0; c < kTileC; ++c) push(t.chunk, q[c].g);
             bool any[2] = {false, false};
             for (int k = 0; k < 2; ++k)
                 for (int c = 0; c < kTileC; ++c) {
                     const int i = s + w * kTileC + c;
-                    const float v = i >= e ? 0.f : (k ? tap(ce, p.he, e, i) : tap(cs, p.hs, s, i));
-                    any[k] = any[k] || v != 0.f;
-                    t.chunk.push_back(v);
+                    const double v = i >= e ? 0.0 : (k ? tap_e(i) : tap_s(i));
+                    any[k] = any[k] || v != 0.0;
+                    push(t.chunk, v);
                 }
-            for (float v : {any[0] ? 1.f : 0.f, any[1] ? 1.f : 0.f, 0.f, 0.f}) t.chunk.push_back(v);
+            for (int k = 0; k < 2; ++k) push(t.chunk, any[k] ? 1.0 : 0.0);
+            // transposed: what the row takes from y_s and y_e
+            bool anyc[2] = {false, false};
+            float cc[2][kTileC];
+            for (int k = 0; k < 2; ++k)
+                for (int c = 0; c < kTileC; ++c) {
+                    const int i = s + w * kTileC + c;
+                    const double v = op != TILE_DT || i >= e ? 0.0 : (k ? tap(ce, bh[b + 1], e, i) : tap(cs, bh[b], s, i));
+                    cc[k][c] = (float)v;
+                    anyc[k] = anyc[k] || v != 0.0;
+                }
+            for (int k = 0; k < 2; ++k) push(t.chunk, anyc[k] ? 1.0 : 0.0);
+            for (int k = 0; k < 2; ++k)
+                for (int c = 0; c < kTileC; ++c) t.chunk.push_back(cc[k][c]);
+            for (int j = 0; j < nw; ++j) push(t.chunk, prev[w][j]);
+            for (int j = 0; j < nw; ++j) push(t.chunk, prev[w][nw + j]);
         }
         // x pass: 16 lanes of four nodes.  The carries are composed in three doubling steps
         // whose multipliers do not depend on the data: lane 0 absorbs the slope, the
@@ -474,16 +628,15 @@ std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t)
             return p;
         };
         for (int k = 0; k < nl; ++k) {
-            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].nf);
-            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].sc);
-            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].fi);
-            for (int c = 0; c < 4; ++c) t.lanes.push_back((float)r[4 * k + c].g);
+            for (int c = 0; c < 4; ++c) push(t.lanes, r[4 * k + c].nf);
+            for (int c = 0; c < 4; ++c) push(t.lanes, r[4 * k + c].sc);
+            for (int c = 0; c < 4; ++c) push(t.lanes, r[4 * k + c].fi);
+            for (int c = 0; c < 4; ++c) push(t.lanes, r[4 * k + c].g);
             double a = 1.0;
-            for (int c = 0; c < 4; ++c) { a *= r[4 * k + c].nf; t.lanes.push_back((float)a); }
-            for (double v : {a1[k], up(a1, k, 2), up(a1, k, 4), k == 0 ? a0 : 0.0}) t.lanes.push_back((float)v);
-            for (double v : {b1[k], dn(b1, k, 2), dn(b1, k, 4), k == kc ? qt[k] : (k > kc ? 1.0 : 0.0)})
-                t.lanes.push_back((float)v);
-            // taps k, k + 16, k + 32 of the two junctions and their places in the LDS row
+            for (int c = 0; c < 4; ++c) { a *= r[4 * k + c].nf; push(t.lanes, a); }
+            for (double v : {a1[k], up(a1, k, 2), up(a1, k, 4), k == 0 ? a0 : 0.0}) push(t.lanes, v);
+            for (double v : {b1[k], dn(b1, k, 2), dn(b1, k, 4), k == kc ? qt[k] : (k > kc ? 1.0 : 0.0)}) push(t.lanes, v);
+            // taps k, k + 16, k + 32 of the two right-hand sides and their places in the LDS row
             for (int j = 0; j < 2; ++j) {
                 const int H = j ? p.he : p.hs, d0 = j ? m - p.he : -p.hs;
                 float cf[3];
@@ -491,7 +644,9 @@ std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t)
                 for (int h = 0; h < 3; ++h) {
                     const int i = k + 16 * h;
                     const bool in = i <= 2 * H;
-                    cf[h] = in ? (j ? ce : cs)[i] : 0.f;
+                    const int node = s + d0 + i;
+                    const bool real_node = ax.end_mode == 2 || (node >= 0 && node <= N);
+                    cf[h] = in && real_node ? (float)(j ? tap_e(node) : tap_s(node)) : 0.f;
                     pos[h] = 4 * tap_slot(p, d0 + (in ? i : 0));
                 }
                 for (float v : {cf[0], cf[1], cf[2], 0.f}) t.lanes.push_back(v);
@@ -501,6 +656,11 @@ std::string build_tile(const AxisHost &ax, bool along_x, TileHost &t)
                     t.lanes.push_back(f);
                 }
             }
+            for (int j = 0; j < 2; ++j)             // transposed: what the node takes from y_s, y_e
+                for (int c = 0; c < 4; ++c) {
+                    const int i = s + 4 * k + c;
+                    push(t.lanes, op != TILE_DT || i >= e ? 0.0 : (j ? tap(ce, bh[b + 1], e, i) : tap(cs, bh[b], s, i)));
+                }
         }
     }
     return std::string();

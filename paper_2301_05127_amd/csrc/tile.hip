@@ -33,193 +33,11 @@
 
 #include <algorithm>
 
-#include "line_device.h"
-#include "loss_internal.h"
-#include "tile_index.h"
+#include "tile_device.h"
 
 namespace loss {
 
 namespace {
-
-constexpr int kHaloPre = 4;     // halo rows per wave and field loaded ahead of the solve
-
-// orders the LDS accesses of a wave's lanes among each other (the wave runs in lockstep;
-// this keeps the compiler from moving them across)
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// sum over the 16 lanes of a DPP row, in every lane
-__device__ __forceinline__ float row_sum(float v)
-{
-    auto ror = [](float x, auto dc) {
-        constexpr int D = decltype(dc)::value;
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + D, 0xF, 0xF, true));
-    };
-    v += ror(v, std::integral_constant<int, 8>{});
-    v += ror(v, std::integral_constant<int, 4>{});
-    v += ror(v, std::integral_constant<int, 2>{});
-    v += ror(v, std::integral_constant<int, 1>{});
-    return v;
-}
-
-__device__ __forceinline__ Piece piece_of(const TileAxis &t, int i)
-{
-    const int4 p = t.piece[i];
-    return make_piece(p.x, p.y, p.z, p.w);
-}
-
-// ---- rows ------------------------------------------------------------------------
-// One wave's chunk of one field: rows q .. q + 7 of a piece, u[0 .. 9] = rows q - 1 .. q + 8.
-
-// eliminated rows from a zero carry, B and W of the chunk
-__device__ __forceinline__ void rows_local(const TileChunk &t, const float (&u)[kTileC + 2], float (&y)[kTileC],
-                                           float &B, float &W)
-{
-    float v = 0.f;
-#pragma unroll
-    for (int c = 0; c < kTileC; ++c) {
-        v = fmaf(t.nf[c], v, t.sc[c] * (u[c + 2] - u[c]));
-        y[c] = v;
-    }
-    B = v;
-    v = 0.f;
-#pragma unroll
-    for (int c = kTileC - 1; c >= 0; --c) v = fmaf(t.g[c], v, t.fi[c] * y[c]);
-    W = v;
-}
-
-// the wave's share of the tap sums of the piece's two junctions, from its own rows
-__device__ __forceinline__ void taps_own(const TileChunk &t, const float (&u)[kTileC + 2], float &ps, float &pe)
-{
-    if (t.any_ts != 0.f) {          // uniform
-#pragma unroll
-        for (int c = 0; c < kTileC; ++c) ps = fmaf(t.ts[c], u[c + 1], ps);
-    }
-    if (t.any_te != 0.f) {
-#pragma unroll
-        for (int c = 0; c < kTileC; ++c) pe = fmaf(t.te[c], u[c + 1], pe);
-    }
-}
-
-// A wave publishes B, W, ps, pe of each field into its own row buffer once its x solves are
-// done (4 * 64 floats per field, at most three fields: below kTileC * kRowPitch).
-constexpr int kWaveLds = kTileC * kRowPitch;
-static_assert(3 * 4 * 64 <= kWaveLds, "exchange area");
-
-__device__ __forceinline__ void rows_publish(float *ex, int lane, float B, float W, float ps, float pe)
-{
-    ex[lane] = B;
-    ex[64 + lane] = W;
-    ex[128 + lane] = ps;
-    ex[192 + lane] = pe;
-}
-
-// the chunk's derivative from its carries; returns the carry from below (the value at the
-// closing row for the last chunk)
-template <int STRIDE>
-__device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex, int nw, int lane, float (&y)[kTileC])
-{
-    float ph = 0.f, pe = 0.f, yin = 0.f, win = 0.f;
-#pragma unroll
-    for (int j = 0; j < kTileWaves; ++j) {
-        if (j < nw) {   // uniform
-            const float *e = ex + j * STRIDE + lane;
-            const float B = e[0], W = e[64];
-            ph += e[128];
-            pe += e[192];
-            yin = fmaf(t.fB[j], B, yin);
-            win = fmaf(t.zB[j], B, win);
-            win = fmaf(t.zW[j], W, win);
-        }
-    }
-    yin = fmaf(t.fph, ph, yin);
-    win = fmaf(t.zph, ph, win);
-    win = fmaf(t.zE, pe, win);
-    float v = win;
-#pragma unroll
-    for (int c = kTileC - 1; c >= 0; --c) {
-        v = fmaf(t.g[c], v, t.fi[c] * fmaf(t.P[c], yin, y[c]));
-        y[c] = v;
-    }
-    return win;
-}
-
-// ---- x ----------------------------------------------------------------------------
-// What depends on the lane only: factors of its four nodes, carry multipliers, taps.
-// Solve rows of the piece in LDS (row r at L + r * kRowPitch) by 16 lanes each: the
-// derivative of the piece's nodes replaces them, and that of the line's last node follows
-// when the piece closes the line.  The lane's table entry (factors of its four nodes, carry
-// multipliers, taps k, k + 16, k + 32 of the two junctions and their places in the row) is
-// read from LDS as it is needed: kept in registers over the fields it would take 44.
-struct XPiece {
-    float4 end;
-    int m, kc;
-    bool last, wide;         // closes the line; taps beyond the first 32 of a junction
-};
-
-__device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, float *L, int k)
-{
-    __builtin_amdgcn_sched_barrier(0);   // one row group at a time: interleaved they spill
-    const float4 cs = t[7], os = t[8], ce = t[9], oe = t[10];
-    auto at = [&](float o) {        // the table holds byte offsets
-        return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(L) + __float_as_int(o));
-    };
-    float ph = cs.x * at(os.x), pe = ce.x * at(oe.x);
-    ph = fmaf(cs.y, at(os.y), ph);
-    pe = fmaf(ce.y, at(oe.y), pe);
-    if (p.wide) {                   // uniform
-        ph = fmaf(cs.z, at(os.z), ph);
-        pe = fmaf(ce.z, at(oe.z), pe);
-    }
-    ph = row_sum(ph);
-    pe = row_sum(pe);
-    if (p.last) pe = fmaf(p.end.z, L[kRowOwn + p.m] - L[kRowOwn + p.m - 1], pe);
-    __builtin_amdgcn_sched_barrier(0);
-    const float4 u = ld4(L + kRowOwn + 4 * k);
-    const float uE = L[kRowRight];
-    const float ul = row_shift_up_fill<1>(u.w, u.x);
-    const float ur = row_shift_down_fill<1>(u.x, uE);
-    const float4 nf = t[0], sc = t[1], P = t[4], a = t[5];
-    float y0 = sc.x * (u.y - ul);
-    float y1 = fmaf(nf.y, y0, sc.y * (u.z - u.x));
-    float y2 = fmaf(nf.z, y1, sc.z * (u.w - u.y));
-    float y3 = fmaf(nf.w, y2, sc.w * (ur - u.z));
-    float B = fmaf(a.w, ph, y3);
-    B = fmaf(a.x, row_shift_up_fill<1>(B, 0.f), B);
-    B = fmaf(a.y, row_shift_up_fill<2>(B, 0.f), B);
-    B = fmaf(a.z, row_shift_up_fill<4>(B, 0.f), B);
-    const float yin = row_shift_up_fill<1>(B, ph);
-    y0 = fmaf(P.x, yin, y0);
-    y1 = fmaf(P.y, yin, y1);
-    y2 = fmaf(P.z, yin, y2);
-    y3 = fmaf(P.w, yin, y3);
-    float we = fmaf(-p.end.y, y3, p.end.x * pe);   // of the closing lane
-    we = __shfl(we, p.kc, 16);
-    __builtin_amdgcn_sched_barrier(0);
-    const float4 fi = t[2], g = t[3], b = t[6];
-    const float t0 = fi.x * y0, t1 = fi.y * y1, t2 = fi.z * y2, t3 = fi.w * y3;
-    float W = fmaf(g.z, t3, t2);
-    W = fmaf(g.y, W, t1);
-    W = fmaf(g.x, W, t0);
-    W = fmaf(b.w, we, W);
-    W = fmaf(b.x, row_shift_down_fill<1>(W, 0.f), W);
-    W = fmaf(b.y, row_shift_down_fill<2>(W, 0.f), W);
-    W = fmaf(b.z, row_shift_down_fill<4>(W, 0.f), W);
-    const float win = row_shift_down_fill<1>(W, we);
-    float4 r;
-    r.w = fmaf(g.w, win, t3);
-    r.z = fmaf(g.z, r.w, t2);
-    r.y = fmaf(g.y, r.z, t1);
-    r.x = fmaf(g.x, r.y, t0);
-    st4(L + kRowOwn + 4 * k, r);
-    if (p.last) {
-        wave_sync();
-        if (k == 0) L[kRowOwn + p.m] = we;
-    }
-}
 
 template <int MODE>
 struct Traits;
@@ -262,36 +80,6 @@ constexpr int rows_slot(int f)
     int n = 0;
     for (int i = 0; i < f; ++i) n += Traits<MODE>::ys(i) ? 1 : 0;
     return n;
-}
-
-// Where the tile lives: element of node (0, 0) of its plane in a field (of its shot) and in
-// a media array (uniform), the lane's column (clamped into the piece) and its byte offset,
-// whether the lane owns a node, the bytes per row.
-struct Place {
-    int64_t fb, mb;
-    int shot, o;
-    int xc;
-    bool act;
-    unsigned vx, rs4;
-};
-
-// Node access through buffer descriptors: scalar base, scalar row offset, the lane's column
-// offset: one instruction and no address arithmetic per access, and one register for the
-// addresses of every row and array (64-bit addresses formed per access were half of the
-// kernels' vector instructions).  Offsets are 32-bit bytes: a field of one shot stays below
-// 2^30 elements.
-typedef __amdgpu_buffer_rsrc_t Buf;
-__device__ __forceinline__ Buf buf(const float *p)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, -1, 0x00020000);
-}
-__device__ __forceinline__ float ld(Buf b, unsigned row, unsigned col)
-{
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)col, (int)row, 0));
-}
-__device__ __forceinline__ void st(Buf b, unsigned row, unsigned col, float v)
-{
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), b, (int)col, (int)row, 0);
 }
 
 // Sum of the source terms of field fid (a component of the outputs) over the R rows from
@@ -654,12 +442,14 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
         for (int i = threadIdx.x; i < 16 * (kLaneF / 4); i += blockDim.x) tab4[i] = tg[i];
     }
     const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
-    const float rend = a.r.ends[lr].z;
+    const float rend = a.r.ends[lr].sE;
     const int k16 = lane & 15;
     const float4 *xt = tab4 + k16 * (kLaneF / 4);
     XPiece xp;
     xp.end = a.x.ends[lx];
+    xp.s3 = a.x.s3;
     xp.m = px.m;
+    xp.hs = px.hs;
     xp.kc = (px.m - 1) >> 2;
     xp.last = lastx;
     xp.wide = max(px.hs, px.he) > 15;
@@ -684,7 +474,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
             }
             wave_sync();
 #pragma unroll
-            for (int it = 0; it < kTileC / 4; ++it) x_row(xp, xt, L16 + 4 * it * kRowPitch, k16);
+            for (int it = 0; it < kTileC / 4; ++it) x_row<TILE_D1>(xp, xt, L16 + 4 * it * kRowPitch, k16);
             wave_sync();
 #pragma unroll
             for (int c = 0; c < kTileC; ++c) dx[f][c] = L[c * kRowPitch + kRowOwn + lane];
@@ -697,7 +487,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
                 L[kRowOwn + lane] = un;
                 L[halo_slot(px, i)] = xn;
                 wave_sync();
-                x_row(xp, xt, L16, k16);
+                x_row<TILE_D1>(xp, xt, L16, k16);
                 wave_sync();
                 dxn[f][0] = L[kRowOwn + lane];
             }
@@ -717,8 +507,8 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
     for (int f = 0; f < NF; ++f)
         if (T::ys(f)) {
             float B, W, ps = 0.f, pe = 0.f;
-            rows_local(rt, u[f], dy[f], B, W);
-            taps_own(rt, u[f], ps, pe);
+            rows_local<TILE_D1>(rt, u[f], dy[f], B, W);
+            taps_own<TILE_D1>(rt, u[f], 0.f, 0.f, ps, pe);
             auto halo = [&](int i, float v) {
                 const float2 c = hc[i];
                 ps = fmaf(c.x, v, ps);
@@ -745,7 +535,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
 #pragma unroll
         for (int f = 0; f < NF; ++f)
             if (T::ys(f))
-                dyn[f][0] = rows_finish<kWaveLds>(rt, lds + rows_slot<MODE>(f) * 256, a.nw, lane, dy[f]);
+                dyn[f][0] = rows_finish<kWaveLds, TILE_D1>(rt, lds + rows_slot<MODE>(f) * 256, a.nw, lane, dy[f]);
         if (band) {
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
@@ -819,8 +609,8 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     for (int h = 0; h < kHaloPre; ++h) yh[h] = ld(bin, (unsigned)hn[w + h * a.nw] * rs4, vx);
     const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
     float B, W, ps = 0.f, pe = 0.f;
-    rows_local(rt, u, y, B, W);
-    taps_own(rt, u, ps, pe);
+    rows_local<TILE_D1>(rt, u, y, B, W);
+    taps_own<TILE_D1>(rt, u, 0.f, 0.f, ps, pe);
     auto halo = [&](int i, float v) {
         const float2 c = hc[i];
         ps = fmaf(c.x, v, ps);
@@ -834,12 +624,12 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
 #pragma unroll
         for (int c = 0; c < kTileC; ++c)
             if (c == nown - 1) { ul = u[c + 1]; ue = u[c + 2]; }
-        pe = fmaf(a.r.ends[lr].z, ue - ul, pe);
+        pe = fmaf(a.r.ends[lr].sE, ue - ul, pe);
     }
     rows_publish(ex + w * 256, lane, B, W, ps, pe);
     __syncthreads();
     if (nown == 0) return;
-    float we = rows_finish<256>(rt, ex, a.nw, lane, y);
+    float we = rows_finish<256, TILE_D1>(rt, ex, a.nw, lane, y);
     if (!act) return;
     const Buf bout = buf(out);
     if (mem) {

@@ -1,0 +1,318 @@
+// Device building blocks of the tile passes (tile.hip) and of the single-axis passes built
+// the same way (tile_axis.hip): node access through buffer descriptors, the solve along the
+// rows by chunks whose carries are sums with tabulated coefficients, and the solve of a row
+// of x by 16 lanes.  OP is one of TileOp: slopes, moments, transposed slopes.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "line_device.h"
+#include "loss_internal.h"
+#include "tile_index.h"
+
+namespace loss {
+
+namespace {
+
+// Where the tile lives: element of node (0, 0) of its plane in a field (of its shot) and in
+// a media array (uniform), the lane's column (clamped into the piece) and its byte offset,
+// whether the lane owns a node, the bytes per row.
+struct Place {
+    int64_t fb, mb;
+    int shot, o;
+    int xc;
+    bool act;
+    unsigned vx, rs4;
+};
+
+// Node access through buffer descriptors: scalar base, scalar row offset, the lane's column
+// offset: one instruction and no address arithmetic per access, and one register for the
+// addresses of every row and array (64-bit addresses formed per access were half of the
+// kernels' vector instructions).  Offsets are 32-bit bytes: a field of one shot stays below
+// 2^30 elements.
+typedef __amdgpu_buffer_rsrc_t Buf;
+__device__ __forceinline__ Buf buf(const float *p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, -1, 0x00020000);
+}
+__device__ __forceinline__ float ld(Buf b, unsigned row, unsigned col)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)col, (int)row, 0));
+}
+__device__ __forceinline__ void st(Buf b, unsigned row, unsigned col, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), b, (int)col, (int)row, 0);
+}
+
+constexpr int kHaloPre = 4;     // halo rows per wave and field loaded ahead of the solve
+
+// orders the LDS accesses of a wave's lanes among each other (the wave runs in lockstep;
+// this keeps the compiler from moving them across)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// sum over the 16 lanes of a DPP row, in every lane
+__device__ __forceinline__ float row_sum(float v)
+{
+    auto ror = [](float x, auto dc) {
+        constexpr int D = decltype(dc)::value;
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + D, 0xF, 0xF, true));
+    };
+    v += ror(v, std::integral_constant<int, 8>{});
+    v += ror(v, std::integral_constant<int, 4>{});
+    v += ror(v, std::integral_constant<int, 2>{});
+    v += ror(v, std::integral_constant<int, 1>{});
+    return v;
+}
+
+__device__ __forceinline__ Piece piece_of(const TileAxis &t, int i)
+{
+    const int4 p = t.piece[i];
+    return make_piece(p.x, p.y, p.z, p.w);
+}
+
+// ---- rows ------------------------------------------------------------------------
+// One wave's chunk of one field: rows q .. q + 7 of a piece, u[0 .. 9] = rows q - 1 .. q + 8.
+
+// right-hand side of row c before its weight sc
+template <int OP>
+__device__ __forceinline__ float row_rhs(const float (&u)[kTileC + 2], int c)
+{
+    if constexpr (OP == TILE_D1) return u[c + 2] - u[c];
+    else if constexpr (OP == TILE_D2) return (u[c + 2] - u[c + 1]) - (u[c + 1] - u[c]);
+    else return u[c + 1];
+}
+
+// eliminated rows from a zero carry, B and W of the chunk
+template <int OP>
+__device__ __forceinline__ void rows_local(const TileChunk &t, const float (&u)[kTileC + 2], float (&y)[kTileC],
+                                           float &B, float &W)
+{
+    float v = 0.f;
+#pragma unroll
+    for (int c = 0; c < kTileC; ++c) {
+        v = fmaf(t.nf[c], v, t.sc[c] * row_rhs<OP>(u, c));
+        y[c] = v;
+    }
+    B = v;
+    v = 0.f;
+#pragma unroll
+    for (int c = kTileC - 1; c >= 0; --c) v = fmaf(t.g[c], v, t.fi[c] * y[c]);
+    W = v;
+}
+
+// the wave's share of the two tap sums from its own rows; moments take the differences from
+// the junction's own value (us, ue), whose share is added once: the taps cancel to the
+// second difference of the field
+template <int OP>
+__device__ __forceinline__ void taps_own(const TileChunk &t, const float (&u)[kTileC + 2], float us, float ue, float &ps,
+                                         float &pe)
+{
+    if (t.any_ts != 0.f) {          // uniform
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) ps = fmaf(t.ts[c], OP == TILE_D2 ? u[c + 1] - us : u[c + 1], ps);
+    }
+    if (t.any_te != 0.f) {
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) pe = fmaf(t.te[c], OP == TILE_D2 ? u[c + 1] - ue : u[c + 1], pe);
+    }
+}
+
+// A wave publishes B, W, ps, pe of each field into its own row buffer once its x solves are
+// done (4 * 64 floats per field, at most three fields: below kTileC * kRowPitch).
+constexpr int kWaveLds = kTileC * kRowPitch;
+static_assert(3 * 4 * 64 <= kWaveLds, "exchange area");
+
+__device__ __forceinline__ void rows_publish(float *ex, int lane, float B, float W, float ps, float pe)
+{
+    ex[lane] = B;
+    ex[64 + lane] = W;
+    ex[128 + lane] = ps;
+    ex[192 + lane] = pe;
+}
+
+// The chunk's rows from its carries; returns the carry from below (the value at the closing
+// row for the last chunk).  Transposed slopes: the rows of G^T y from the solution y, its
+// neighbours and the junction values y_s = ph, y_e = pe; the taps left of the piece alone,
+// which the waves publish after their four sums, give y at the row before it (`first`: the
+// piece's first chunk); dn = the value at the closing node.
+template <int STRIDE, int OP>
+__device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex, int nw, int lane, float (&y)[kTileC],
+                                             const TileEnds *end = nullptr, float s3 = 0.f, bool first = false,
+                                             int nown = 0, float *dn = nullptr)
+{
+    float ph = 0.f, pe = 0.f, yin = 0.f, win = 0.f, prev = 0.f;
+#pragma unroll
+    for (int j = 0; j < kTileWaves; ++j) {
+        if (j < nw) {   // uniform
+            const float *e = ex + j * STRIDE + lane;
+            const float B = e[0], W = e[64];
+            ph += e[128];
+            pe += e[192];
+            yin = fmaf(t.fB[j], B, yin);
+            win = fmaf(t.zB[j], B, win);
+            win = fmaf(t.zW[j], W, win);
+            if constexpr (OP == TILE_DT) {
+                prev = fmaf(t.pB[j], B, prev);
+                prev = fmaf(t.pW[j], W, prev);
+            }
+        }
+    }
+    if constexpr (OP != TILE_DT) {
+        yin = fmaf(t.fph, ph, yin);
+        win = fmaf(t.zph, ph, win);
+    }
+    win = fmaf(t.zE, pe, win);
+    float v = win;
+#pragma unroll
+    for (int c = kTileC - 1; c >= 0; --c) {
+        v = fmaf(t.g[c], v, t.fi[c] * fmaf(t.P[c], yin, y[c]));
+        y[c] = v;
+    }
+    if constexpr (OP == TILE_DT) {
+        prev = fmaf(t.pE, pe, prev);
+        if (first) {                // the row before the piece; a natural end mirrors y_0
+            prev = 0.f;
+            for (int j = 0; j < nw; ++j) prev -= ex[j * STRIDE + 256 + lane];
+            if (end->m1 != 0.f) prev = -y[0];
+        }
+        float wl = 0.f;
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c)
+            if (c == nown - 1) wl = y[c];
+        *dn = fmaf(s3, fmaf(end->sE, win, wl), fmaf(end->cs, ph, end->ce * pe));
+        float lo = prev;
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) {
+            const float own = y[c];
+            float r = s3 * (lo - (c < kTileC - 1 ? y[c < kTileC - 1 ? c + 1 : c] : win));
+            lo = own;
+            y[c] = r;
+        }
+        if (t.any_cs != 0.f) {
+#pragma unroll
+            for (int c = 0; c < kTileC; ++c) y[c] = fmaf(t.cs[c], ph, y[c]);
+        }
+        if (t.any_ce != 0.f) {
+#pragma unroll
+            for (int c = 0; c < kTileC; ++c) y[c] = fmaf(t.ce[c], pe, y[c]);
+        }
+    }
+    return win;
+}
+
+// ---- x ----------------------------------------------------------------------------
+// What depends on the lane only: factors of its four nodes, carry multipliers, taps.
+// Solve rows of the piece in LDS (row r at L + r * kRowPitch) by 16 lanes each: the
+// derivative of the piece's nodes replaces them, and that of the line's last node follows
+// when the piece closes the line.  The lane's table entry (factors of its four nodes, carry
+// multipliers, taps k, k + 16, k + 32 of the two junctions and their places in the row) is
+// read from LDS as it is needed: kept in registers over the fields it would take 44.
+struct XPiece {
+    TileEnds end;
+    float s3;
+    int m, kc, hs;
+    bool last, wide;         // closes the line; taps beyond the first 32 of a junction
+};
+
+template <int OP>
+__device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, float *L, int k)
+{
+    __builtin_amdgcn_sched_barrier(0);   // one row group at a time: interleaved they spill
+    const float4 cs = t[7], os = t[8], ce = t[9], oe = t[10];
+    auto at = [&](float o) {        // the table holds byte offsets
+        return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(L) + __float_as_int(o));
+    };
+    // transposed: the taps left of the piece alone give y at the node before it
+    float pl = 0.f;
+    if constexpr (OP == TILE_DT) {
+        if (k < p.hs) pl = cs.x * at(os.x);
+        if (k + 16 < p.hs) pl = fmaf(cs.y, at(os.y), pl);
+        pl = row_sum(pl);
+    }
+    const float us = OP == TILE_D2 ? L[kRowOwn] : 0.f, ue = OP == TILE_D2 ? L[kRowRight] : 0.f;
+    float ph = cs.x * (at(os.x) - us), pe = ce.x * (at(oe.x) - ue);
+    ph = fmaf(cs.y, at(os.y) - us, ph);
+    pe = fmaf(ce.y, at(oe.y) - ue, pe);
+    if (p.wide) {                   // uniform
+        ph = fmaf(cs.z, at(os.z) - us, ph);
+        pe = fmaf(ce.z, at(oe.z) - ue, pe);
+    }
+    ph = row_sum(ph);
+    pe = row_sum(pe);
+    if constexpr (OP == TILE_D2) {
+        ph = fmaf(p.end.cs, us, ph);
+        pe = fmaf(p.end.ce, ue, pe);
+    }
+    if (OP != TILE_DT && p.end.sE != 0.f) pe = fmaf(p.end.sE, L[kRowOwn + p.m] - L[kRowOwn + p.m - 1], pe);
+    __builtin_amdgcn_sched_barrier(0);
+    const float4 u = ld4(L + kRowOwn + 4 * k);
+    const float uE = L[kRowRight];
+    const float ul = row_shift_up_fill<1>(u.w, u.x);
+    const float ur = row_shift_down_fill<1>(u.x, uE);
+    const float4 nf = t[0], sc = t[1], P = t[4], a = t[5];
+    auto rhs = [](float lo, float own, float hi) {
+        if constexpr (OP == TILE_D1) return hi - lo;
+        else if constexpr (OP == TILE_D2) return (hi - own) - (own - lo);
+        else return own;
+    };
+    float y0 = sc.x * rhs(ul, u.x, u.y);
+    float y1 = fmaf(nf.y, y0, sc.y * rhs(u.x, u.y, u.z));
+    float y2 = fmaf(nf.z, y1, sc.z * rhs(u.y, u.z, u.w));
+    float y3 = fmaf(nf.w, y2, sc.w * rhs(u.z, u.w, ur));
+    float B = fmaf(a.w, ph, y3);
+    B = fmaf(a.x, row_shift_up_fill<1>(B, 0.f), B);
+    B = fmaf(a.y, row_shift_up_fill<2>(B, 0.f), B);
+    B = fmaf(a.z, row_shift_up_fill<4>(B, 0.f), B);
+    const float yin = row_shift_up_fill<1>(B, ph);
+    y0 = fmaf(P.x, yin, y0);
+    y1 = fmaf(P.y, yin, y1);
+    y2 = fmaf(P.z, yin, y2);
+    y3 = fmaf(P.w, yin, y3);
+    float we = fmaf(-p.end.imE, y3, p.end.iE * pe);   // of the closing lane
+    we = __shfl(we, p.kc, 16);
+    __builtin_amdgcn_sched_barrier(0);
+    const float4 fi = t[2], g = t[3], b = t[6];
+    const float t0 = fi.x * y0, t1 = fi.y * y1, t2 = fi.z * y2, t3 = fi.w * y3;
+    float W = fmaf(g.z, t3, t2);
+    W = fmaf(g.y, W, t1);
+    W = fmaf(g.x, W, t0);
+    W = fmaf(b.w, we, W);
+    W = fmaf(b.x, row_shift_down_fill<1>(W, 0.f), W);
+    W = fmaf(b.y, row_shift_down_fill<2>(W, 0.f), W);
+    W = fmaf(b.z, row_shift_down_fill<4>(W, 0.f), W);
+    const float win = row_shift_down_fill<1>(W, we);
+    float4 r;
+    r.w = fmaf(g.w, win, t3);
+    r.z = fmaf(g.z, r.w, t2);
+    r.y = fmaf(g.y, r.z, t1);
+    r.x = fmaf(g.x, r.y, t0);
+    float dn = we;                  // the closing node
+    if constexpr (OP == TILE_DT) {
+        const float4 c1 = t[11], c2 = t[12];
+        const int cc = (p.m - 1) & 3;
+        const float wl = __shfl(cc == 0 ? r.x : (cc == 1 ? r.y : (cc == 2 ? r.z : r.w)), p.kc, 16);
+        dn = fmaf(p.s3, fmaf(p.end.sE, we, wl), fmaf(p.end.cs, ph, p.end.ce * pe));
+        const float before = p.end.m1 != 0.f ? -r.x : -pl;   // a natural end mirrors y_0
+        const float lo = row_shift_up_fill<1>(r.w, before);
+        const float hi = row_shift_down_fill<1>(r.x, we);
+        float4 o;
+        o.x = fmaf(p.s3, lo - r.y, fmaf(c1.x, ph, c2.x * pe));
+        o.y = fmaf(p.s3, r.x - r.z, fmaf(c1.y, ph, c2.y * pe));
+        o.z = fmaf(p.s3, r.y - r.w, fmaf(c1.z, ph, c2.z * pe));
+        o.w = fmaf(p.s3, r.z - hi, fmaf(c1.w, ph, c2.w * pe));
+        r = o;
+    }
+    st4(L + kRowOwn + 4 * k, r);
+    if (p.last) {
+        wave_sync();
+        if (k == 0) L[kRowOwn + p.m] = dn;
+    }
+}
+
+}  // namespace
+
+}  // namespace loss

@@ -1,6 +1,6 @@
 """CPU check of the tile passes (paper Sec. 3.1-3.2: patch systems with PMBC junctions):
-every index their kernels form along an axis, and the two solves as the kernels evaluate
-them in FP32 against the patch systems in FP64 (tests/tile_check.cpp)."""
+every index their kernels form along an axis, and the two solves of the slopes, the moments
+and the transposed slopes as the kernels evaluate them in FP32 against the patch systems in FP64 (tests/tile_check.cpp)."""
 import os
 import subprocess
 
@@ -25,9 +25,17 @@ def checker(tmp_path_factory):
     return exe
 
 
+@pytest.mark.parametrize("op", [0, 1, 2])
 @pytest.mark.parametrize("axis", AXES, ids=["N%d_M%d_h%d_e%d" % a for a in AXES])
-def test_tile_tables_and_indices(checker, axis):
-    out = subprocess.run([checker] + [str(v) for v in axis], capture_output=True, text=True)
-    assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout
-    # FP32 rounding of a diagonally dominant system (condition at most 3) on white noise
-    assert max(float(v) for v in out.stdout.split()[1:]) < 2e-6, out.stdout
+def test_tile_tables_and_indices(checker, axis, op):
+    out = subprocess.run([checker] + [str(v) for v in axis + (op,)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    N, M, halo, end = axis
+    if out.stdout.startswith("unsupported"):
+        # the transposed taps of a junction may reach the two pieces it separates only
+        assert op == 2 and (end == 2 or halo > min(M, N % M or M)), out.stdout
+        return
+    assert out.stdout.startswith("ok"), out.stdout
+    # FP32 rounding of diagonally dominant systems (condition at most 3) on white noise
+    tol = 5e-6 if op == 1 else 2e-6
+    assert max(float(v) for v in out.stdout.split()[1:]) < tol, out.stdout
