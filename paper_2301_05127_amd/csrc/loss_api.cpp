@@ -144,7 +144,9 @@ struct loss_sim {
     int64_t *d_step2 = nullptr;    // the step counter between the two kernels of an acoustic tile step
     // receivers ordered by the tile that updates their node
     RecDev *d_trec_vel = nullptr, *d_trec_str = nullptr;
-    int *d_trb_vel = nullptr, *d_trb_str = nullptr;
+    int2 *d_info_vel = nullptr, *d_info_str = nullptr;   // TileArgs::info of the two passes
+    std::vector<SrcDev> src_dev;                         // as uploaded
+    bool info_dirty = false;       // sources or receivers changed since the tables of the tiles
     // adjoint
     float *ckpt = nullptr;         // [nseg][nf fields][S][shot_stride] fused states
     int64_t ck_every = 0, ck_steps = 0, ck_nseg = 0;
@@ -480,8 +482,7 @@ void tile_sources(const loss_sim *s, TileArgs &t, int time_offset, bool forces)
 
 void tile_receivers(const loss_sim *s, TileArgs &t, bool vel)
 {
-    if (s->d.trace_len == 0) return;
-    t.rec_begin = vel ? s->d_trb_vel : s->d_trb_str;
+    t.info = vel ? s->d_info_vel : s->d_info_str;
     t.rec = vel ? s->d_trec_vel : s->d_trec_str;
     t.traces = s->traces;
     t.trace_len = s->d.trace_len;
@@ -939,6 +940,7 @@ loss_status upload_sources(loss_sim *s)
     if (s->d_wpool) { s->release(s->d_wpool); s->d_wpool = nullptr; }
     if (s->d_wavpool) { s->release(s->d_wavpool); s->d_wavpool = nullptr; }
     s->nsrc = (int)sd.size();
+    s->src_dev = sd;
     if (s->nsrc) {
         loss_status r;
         if ((r = s->alloc(&s->d_src, sd.size()))) return r;
@@ -1056,44 +1058,70 @@ loss_status upload_receivers(loss_sim *s)
         HIPCHK(hipMemcpy(s->d_rrow, rrow.data(), rrow.size() * sizeof(int), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(s->d_rtoff, rtoff.data(), rtoff.size() * sizeof(int64_t), hipMemcpyHostToDevice));
     }
-    // the same receivers ordered by the tile whose kernel updates their node
-    auto by_tile = [&](const std::vector<RecDev> &list, RecDev **drec, int **dbeg) -> loss_status {
-        if (*drec) { s->release(*drec); *drec = nullptr; }
-        if (*dbeg) { s->release(*dbeg); *dbeg = nullptr; }
-        if (list.empty() || !s->tile_built) return LOSS_OK;
-        const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
-        const int nother = ra == 1 ? s->nz : 1;
-        auto piece = [&](int axis, int node) {   // a piece owns its first node; the last one node N too
-            const std::vector<int> &b = s->tile_sb[axis];
-            return std::min((int)(std::upper_bound(b.begin(), b.end(), node) - b.begin()) - 1, (int)b.size() - 2);
-        };
-        const int ntx = (int)s->tile_sb[0].size() - 1, ntr = (int)s->tile_sb[ra].size() - 1;
-        std::vector<std::pair<int64_t, int>> key(list.size());
-        for (size_t k = 0; k < list.size(); ++k) {
-            const int64_t z = list[k].node / s->plane, rem = list[k].node - z * s->plane;
-            const int y = (int)(rem / s->pitch), x = (int)(rem - (int64_t)y * s->pitch);
-            const int row = ra == 1 ? y : (int)z, o = ra == 1 ? (int)z : 0;
-            key[k] = {(((int64_t)list[k].shot * nother + o) * ntr + piece(ra, row)) * ntx + piece(0, x), (int)k};
-        }
-        std::sort(key.begin(), key.end());
-        std::vector<RecDev> sorted(list.size());
-        std::vector<int> beg((size_t)s->S * nother * ntr * ntx + 1, 0);
-        for (size_t k = 0; k < key.size(); ++k) {
-            sorted[k] = list[key[k].second];
-            beg[key[k].first + 1]++;
-        }
-        for (size_t k = 1; k < beg.size(); ++k) beg[k] += beg[k - 1];
-        loss_status q;
-        if ((q = s->alloc(drec, sorted.size())) || (q = s->alloc(dbeg, beg.size()))) return q;
-        HIPCHK(hipMemcpy(*drec, sorted.data(), sorted.size() * sizeof(RecDev), hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(*dbeg, beg.data(), beg.size() * sizeof(int), hipMemcpyHostToDevice));
-        return LOSS_OK;
-    };
-    if ((r = by_tile(vel, &s->d_trec_vel, &s->d_trb_vel)) || (r = by_tile(str, &s->d_trec_str, &s->d_trb_str))) return r;
     s->trace_total = off;
     if ((r = s->alloc(&s->traces, std::max<int64_t>(off, 1)))) return r;
     HIPCHK(hipMemsetAsync(s->traces, 0, sizeof(double) * std::max<int64_t>(off, 1), s->st));
     s->rec_dirty = false;
+    s->info_dirty = true;
+    return LOSS_OK;
+}
+
+// What the tile kernels of a step find at a tile: its receivers (ordered by tile) and
+// whether a source reaches it, for the stress and the velocity pass.
+loss_status upload_tile_info(loss_sim *s)
+{
+    const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
+    const int nother = ra == 1 ? s->nz : 1;
+    auto piece = [&](int axis, int node) {   // a piece owns its first node; the last one node N too
+        const std::vector<int> &b = s->tile_sb[axis];
+        return std::max(0, std::min((int)(std::upper_bound(b.begin(), b.end(), node) - b.begin()) - 1, (int)b.size() - 2));
+    };
+    const int ntx = (int)s->tile_sb[0].size() - 1, ntr = (int)s->tile_sb[ra].size() - 1;
+    auto tile = [&](int64_t shot, int o, int lr, int lx) { return ((shot * nother + o) * ntr + lr) * ntx + lx; };
+    for (int vel = 0; vel < 2; ++vel) {
+        RecDev **drec = vel ? &s->d_trec_vel : &s->d_trec_str;
+        int2 **dinfo = vel ? &s->d_info_vel : &s->d_info_str;
+        if (*drec) { s->release(*drec); *drec = nullptr; }
+        if (*dinfo) { s->release(*dinfo); *dinfo = nullptr; }
+        std::vector<std::pair<int64_t, RecDev>> list;
+        for (int shot = 0; shot < s->S && s->d.trace_len > 0; ++shot) {
+            const RecHost &rh = s->rec[shot];
+            if (is_velocity(s, rh.comp) != (vel != 0)) continue;
+            for (size_t k = 0; k + 2 < rh.idx.size(); k += 3) {
+                const int x = rh.idx[k], y = rh.idx[k + 1], z = rh.idx[k + 2];
+                RecDev d{};
+                d.shot = shot;
+                d.comp = rh.comp;
+                d.node = (int64_t)z * s->plane + (int64_t)y * s->pitch + x;
+                d.trace_off = s->rec_off[shot] + (int64_t)(k / 3) * s->d.trace_len;
+                list.push_back({tile(shot, ra == 1 ? z : 0, piece(ra, ra == 1 ? y : z), piece(0, x)), d});
+            }
+        }
+        bool any = !list.empty();
+        for (const SrcDev &d : s->src_dev) any = any || (d.force != 0) == (vel != 0);
+        if (!any || !s->tile_built) continue;
+        std::stable_sort(list.begin(), list.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+        std::vector<RecDev> rec;
+        std::vector<int2> info((size_t)s->S * nother * ntr * ntx, make_int2(0, 0));
+        for (const auto &e : list) {
+            int2 &i = info[e.first];
+            if (i.y == 0) i.x = (int)rec.size();
+            i.y += 2;
+            rec.push_back(e.second);
+        }
+        for (const SrcDev &d : s->src_dev) {
+            if ((d.force != 0) != (vel != 0)) continue;
+            const int r0 = ra == 1 ? d.y0 : d.z0, nr = ra == 1 ? d.by : d.bz;
+            const int o0 = ra == 1 ? d.z0 : 0, no = ra == 1 ? d.bz : 1;
+            for (int o = o0; o < o0 + no; ++o)
+                for (int lr = piece(ra, r0); lr <= piece(ra, r0 + nr - 1); ++lr)
+                    for (int lx = piece(0, d.x0); lx <= piece(0, d.x0 + d.bx - 1); ++lx) info[tile(d.shot, o, lr, lx)].y |= 1;
+        }
+        loss_status r;
+        if ((r = s->alloc(drec, rec.size())) || (r = s->alloc(dinfo, info.size()))) return r;
+        if (!rec.empty()) HIPCHK(hipMemcpy(*drec, rec.data(), rec.size() * sizeof(RecDev), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(*dinfo, info.data(), info.size() * sizeof(int2), hipMemcpyHostToDevice));
+    }
     return LOSS_OK;
 }
 
@@ -1241,8 +1269,11 @@ loss_status ensure_ready(loss_sim *s)
 {
     if (!s->media_set) return fail(LOSS_ESTATE, "loss_set_media must be called first");
     loss_status r;
+    s->info_dirty = s->info_dirty || s->src_dirty || s->rec_dirty;
     if ((r = upload_sources(s))) return r;
     if ((r = upload_receivers(s))) return r;
+    if (s->info_dirty && (r = upload_tile_info(s))) return r;
+    s->info_dirty = false;
     return LOSS_OK;
 }
 

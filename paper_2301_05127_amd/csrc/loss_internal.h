@@ -264,9 +264,10 @@ struct TileArgs {
     const float *wpool, *wavpool;
     int src_time_offset;
     float src_scale;
-    // receivers of the updated fields by tile: entries rec_begin[tile] .. of rec; velocity
-    // passes record half of the old and half of the new value
-    const int *rec_begin;
+    // per tile {first entry of rec, 2 * entries + (a source reaches the tile)}, null: none of
+    // either.  rec: receivers of the updated fields; velocity passes record half of the old
+    // and half of the new value
+    const int2 *info;
     const RecDev *rec;
     const float *const *fields;
     double *traces;

@@ -25,10 +25,14 @@
 // The tap sums along the rows come from the rows a wave holds and from the halo rows,
 // which are dealt to the waves of the workgroup.
 //
-// Measured (us per step, line passes -> tiles): elastic 513^3 8350 -> 6340, 257^3 x 2
-// shots 2190 -> 1655, 65^3 155 -> 63; acoustic 129^2 40 -> 22.  513^3: stress tiles 2637 us
-// (4.3 TB/s of the compulsory bytes), velocity tiles 2061 (3.9), z stores 820 (4.0); a 1 GiB
-// copy reaches 5.2 TB/s.
+// Measured (us per step, line passes -> tiles): elastic 513^3 8350 -> 6210, 257^3 x 2
+// shots 2190 -> 1650, 65^3 155 -> 59; acoustic 2049^2 78 -> 62, 129^2 40 -> 21.  513^3: stress
+// tiles 2575 us (4.4 TB/s of the compulsory bytes), velocity tiles 2019 (4.0), z stores 818
+// (4.0); a 1 GiB copy reaches 5.2 TB/s.
+//
+// What a tile does before its first field load counts: a per-tile word says whether it has
+// receivers or a source (each tile walking the sources and the receivers' ranges, behind a
+// read of the step counter: acoustic 2049^2 31.9 + 37.2 -> 28.4 + 32.0 us with the next).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -182,14 +186,10 @@ __device__ __forceinline__ void make_sums(const float (&dx)[Traits<MODE>::NF][R]
 
 // Update of the R rows from row q on, lane = column.  FULL: all R rows belong to the piece
 // and no source reaches the tile (nearly all waves); else the first nrow rows, with the
-// sources when srcs is set.  KEEP: the derivatives are stored too.  pre: the operands of the
-// acoustic passes, read with the fields.
-template <int MODE>
-constexpr bool kEarly = MODE == TILE_AC_STRESS || MODE == TILE_AC_VEL;
-
-template <int MODE, int R, bool FULL, bool KEEP, bool PRE>
+// sources when srcs is set.  KEEP: the derivatives are stored too. 
+template <int MODE, int R, bool FULL, bool KEEP>
 __device__ __forceinline__ void tile_update(const TileArgs &a, const Place &pl, int64_t n, int q, int nrow, bool srcs,
-                                            const float (&e)[Sums<MODE>::N][R], const float (&pre)[3][R])
+                                            const float (&e)[Sums<MODE>::N][R])
 {
     if (!pl.act) return;
     auto row = [&](int c) { return FULL || c < nrow; };
@@ -284,8 +284,8 @@ __device__ __forceinline__ void tile_update(const TileArgs &a, const Place &pl, 
 #pragma unroll
         for (int c = 0; c < R; ++c)
             if (row(c)) {
-                s[c] = PRE ? pre[0][c] : get(a.out[0], c);
-                K[c] = PRE ? pre[1][c] : med(a.c0, c);
+                s[c] = get(a.out[0], c);
+                K[c] = med(a.c0, c);
             }
         if (!FULL && srcs) source_add<R>(a, pl, n, 0, q, add);
 #pragma unroll
@@ -302,9 +302,9 @@ __device__ __forceinline__ void tile_update(const TileArgs &a, const Place &pl, 
         for (int c = 0; c < R; ++c) {
             add3[c] = 0.f;
             if (row(c)) {
-                b[c] = PRE ? pre[0][c] : med(a.c0, c);
-                v1[c] = PRE ? pre[1][c] : get(a.base[0], c);
-                v3[c] = PRE ? pre[2][c] : get(a.base[1], c);
+                b[c] = med(a.c0, c);
+                v1[c] = get(a.base[0], c);
+                v3[c] = get(a.base[1], c);
             }
         }
         if (!FULL && srcs) {
@@ -325,21 +325,15 @@ __device__ __forceinline__ void tile_update(const TileArgs &a, const Place &pl, 
     }
 }
 
-// does a source of the shot reach the tile?
-__device__ __forceinline__ bool tile_has_source(const TileArgs &a, int shot, int o, const Piece &px, const Piece &pr)
-{
-    const int k1 = a.src_begin[shot + 1];
-    for (int k = a.src_begin[shot]; k < k1; ++k) {
-        const SrcDev &sd = a.src[k];
-        const int r0 = a.row_axis == 1 ? sd.y0 : sd.z0, nr = a.row_axis == 1 ? sd.by : sd.bz;
-        const bool ho = a.row_axis == 1 ? (o >= sd.z0 && o < sd.z0 + sd.bz) : true;
-        if (ho && px.e >= sd.x0 && px.s < sd.x0 + sd.bx && pr.e >= r0 && pr.s < r0 + nr) return true;
-    }
-    return false;
-}
+// Waves per SIMD (registers): the elastic kernels hold three fields and their sums (121-123
+// VGPRs: two workgroups per CU), the acoustic ones fit three (80 VGPRs).  Measured: acoustic
+// 2049^2 29.4 + 37.2 us at two workgroups, 29.2 + 34.5 at three, 31.0 + 44.3 at four (spills);
+// reading the updated arrays with the fields instead of after the solves 33.3 + 39.5.
+template <int MODE>
+constexpr int kTileWavesPerSimd = MODE == TILE_AC_STRESS || MODE == TILE_AC_VEL ? 6 : 4;
 
 template <int MODE, bool KEEP>
-__global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nreal)
+__global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_tile(TileArgs a, int nreal)
 {
     using T = Traits<MODE>;
     constexpr int NF = T::NF;
@@ -365,15 +359,22 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
     pl.xc = min(px.s + lane, px.e);
     pl.act = lane < px.m + (lastx ? 1 : 0);
 
-    const int64_t n = a.step_in ? *a.step_in + a.step_add : 0;
-    if (a.step_out && blockIdx.x == 0 && threadIdx.x == 0) *a.step_out = n;
-    int rec0 = 0, rec1 = 0;
-    if (a.rec_begin && n >= 1 && n <= a.trace_len) {
-        rec0 = a.rec_begin[lin];
-        rec1 = a.rec_begin[lin + 1];
+    // receivers of the tile and whether a source reaches it; nearly all tiles have neither,
+    // and only the others wait for the step counter
+    int rec0 = 0, nrec = 0;
+    bool hits = false;
+    if (a.info) {
+        const int2 ti = a.info[lin];
+        rec0 = ti.x;
+        nrec = ti.y >> 1;
+        hits = a.src && (ti.y & 1);
     }
-    if ((MODE == TILE_EL_VEL || MODE == TILE_AC_VEL) && rec1 > rec0) {   // half of the old value
-        for (int k = rec0 + (int)threadIdx.x; k < rec1; k += blockDim.x) {
+    int64_t n = 0;
+    if (nrec > 0 || hits) n = *a.step_in + a.step_add;
+    if (a.step_out && blockIdx.x == 0 && threadIdx.x == 0) *a.step_out = *a.step_in + a.step_add;
+    if (n < 1 || n > a.trace_len) nrec = 0;
+    if ((MODE == TILE_EL_VEL || MODE == TILE_AC_VEL) && nrec > 0) {   // half of the old value
+        for (int k = rec0 + (int)threadIdx.x; k < rec0 + nrec; k += blockDim.x) {
             const RecDev rd = a.rec[k];
             a.traces[rd.trace_off + n - 1] = 0.5 * (double)a.fields[rd.comp][rd.shot * a.shot_stride + rd.node];
         }
@@ -388,6 +389,10 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
     pl.rs4 = 4u * (unsigned)a.rstride;
 
     // ---- loads ---------------------------------------------------------------------
+    // the x table first: the barrier it needs then does not wait for the fields
+    constexpr int kTab = 16 * (kLaneF / 4);
+    const float4 *tabg = a.x.lanes + (size_t)lx * kTab;
+    const float4 tab_reg = tabg[min((int)threadIdx.x, kTab - 1)];
     // rows past the piece repeat its closing row (their factors ignore them)
     float u[NF][kTileC + 2], yh[NF][kHaloPre], xh[NF][6];
     const int nhx = halo_count(px), nhr = halo_count(pr);
@@ -422,25 +427,6 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
 #pragma unroll
     for (int f = 0; f < NF; ++f)
         if (T::xs(f)) load(f);
-    float pre[3][kTileC];
-    if constexpr (kEarly<MODE>) {
-#pragma unroll
-        for (int c = 0; c < kTileC; ++c) {
-            const unsigned ro = (unsigned)min(q + c, pr.e) * pl.rs4;
-            if constexpr (MODE == TILE_AC_STRESS) {
-                pre[0][c] = ld(buf(a.out[0] + pl.fb), ro, pl.vx);
-                pre[1][c] = ld(buf(a.c0 + pl.mb), ro, pl.vx);
-            } else {
-                pre[0][c] = ld(buf(a.c0 + pl.mb), ro, pl.vx);
-                pre[1][c] = ld(buf(a.base[0] + pl.fb), ro, pl.vx);
-                pre[2][c] = ld(buf(a.base[1] + pl.fb), ro, pl.vx);
-            }
-        }
-    }
-    {
-        const float4 *tg = a.x.lanes + (size_t)lx * 16 * (kLaneF / 4);
-        for (int i = threadIdx.x; i < 16 * (kLaneF / 4); i += blockDim.x) tab4[i] = tg[i];
-    }
     const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
     const float rend = a.r.ends[lr].sE;
     const int k16 = lane & 15;
@@ -453,7 +439,8 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
     xp.kc = (px.m - 1) >> 2;
     xp.last = lastx;
     xp.wide = max(px.hs, px.he) > 15;
-    const bool hits = a.src && tile_has_source(a, pl.shot, pl.o, px, pr);
+    if ((int)threadIdx.x < kTab) tab4[threadIdx.x] = tab_reg;
+    for (int i = threadIdx.x + blockDim.x; i < kTab; i += blockDim.x) tab4[i] = tabg[i];   // fewer than four waves
     __syncthreads();                                          // the lanes' table
 
     // ---- x: the wave's rows through LDS -------------------------------------------------
@@ -549,19 +536,16 @@ __global__ void __launch_bounds__(kTileWaves * 64, 4) k_tile(TileArgs a, int nre
         }
         float e[Sums<MODE>::N][kTileC], en[Sums<MODE>::N][1];
         make_sums<MODE, kTileC>(dx, dy, e);
-        constexpr bool PRE = kEarly<MODE>;
-        const bool full = !hits && nown == kTileC;
-        if (full) tile_update<MODE, kTileC, true, KEEP, PRE>(a, pl, n, q, kTileC, false, e, pre);
-        else tile_update<MODE, kTileC, false, KEEP, PRE>(a, pl, n, q, nown, hits, e, pre);
+        if (!hits && nown == kTileC) tile_update<MODE, kTileC, true, KEEP>(a, pl, 0, q, kTileC, false, e);
+        else tile_update<MODE, kTileC, false, KEEP>(a, pl, n, q, nown, hits, e);
         if (clos) {
             make_sums<MODE, 1>(dxn, dyn, en);
-            const float none[3][1] = {};
-            tile_update<MODE, 1, false, KEEP, false>(a, pl, n, pr.e, 1, hits, en, none);
+            tile_update<MODE, 1, false, KEEP>(a, pl, n, pr.e, 1, hits, en);
         }
     }
-    if (rec1 > rec0) {   // uniform across the workgroup
+    if (nrec > 0) {   // uniform across the workgroup
         __syncthreads();
-        for (int k = rec0 + (int)threadIdx.x; k < rec1; k += blockDim.x) {
+        for (int k = rec0 + (int)threadIdx.x; k < rec0 + nrec; k += blockDim.x) {
             const RecDev rd = a.rec[k];
             const double v = (double)a.fields[rd.comp][rd.shot * a.shot_stride + rd.node];
             double *t = a.traces + rd.trace_off + n - 1;
