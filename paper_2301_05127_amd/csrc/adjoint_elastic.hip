@@ -47,20 +47,38 @@ __global__ void k_el_normal_operand(float *__restrict__ w, const float *__restri
 // dJ/dmu     += dt (2 sum_k e_kk sbar_kk + sum_{i<j} g_ij sbar_ij), summed over shots in
 // FP64.  e: six strain fields (e11, e22, e33, g12, g13, g23) of the state B was applied
 // to; sb: the six stress bars (11, 22, 33, 12, 13, 23).  g: two padded accumulators.
+// W: the bars are in registers here, so the operands of the transposed stress sub-flow are
+// formed on the way (24 bytes written; one pass per operand read the bars again, five or two
+// fields at a time).
 struct Six {
     const float *p[6];
 };
+struct SixOut {
+    float *p[6];
+};
 
-__global__ void k_el_grad_accum(double *__restrict__ gl, double *__restrict__ gm, Six e, Six sb, double dt,
-                                int nx, int64_t pitch, int64_t per_shot, int S, int64_t total_one_shot)
+template <bool W>
+__global__ void k_el_grad_accum(double *__restrict__ gl, double *__restrict__ gm, Six e, Six sb, SixOut w,
+                                const float *__restrict__ l2m, const float *__restrict__ lam,
+                                const float *__restrict__ mu, double dt, int nx, int64_t pitch, int64_t per_shot,
+                                int S, int64_t total_one_shot)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total_one_shot) return;
     int64_t so, p;
     if (!valid_node(i, nx, pitch, per_shot, 1, &so, &p)) return;
     double al = 0.0, am = 0.0;
+    const float ml = W ? l2m[p] : 0.f, la = W ? lam[p] : 0.f, m = W ? mu[p] : 0.f;
     for (int s = 0; s < S; ++s) {
         const int64_t q = (int64_t)s * per_shot + p;
+        if (W) {
+            const float s0 = sb.p[0][q], s1 = sb.p[1][q], s2 = sb.p[2][q];
+            w.p[0][q] = fmaf(ml, s0, la * (s1 + s2));
+            w.p[1][q] = fmaf(ml, s1, la * (s0 + s2));
+            w.p[2][q] = fmaf(ml, s2, la * (s0 + s1));
+#pragma unroll
+            for (int k = 3; k < 6; ++k) w.p[k][q] = m * sb.p[k][q];
+        }
         const double e11 = e.p[0][q], e22 = e.p[1][q], e33 = e.p[2][q];
         const double b11 = sb.p[0][q], b22 = sb.p[1][q], b33 = sb.p[2][q];
         al += (e11 + e22 + e33) * (b11 + b22 + b33);
@@ -159,13 +177,22 @@ hipError_t launch_el_normal_operand(float *w, const float *s11, const float *s22
 }
 
 hipError_t launch_el_grad_accum(double *gl, double *gm, const float *const *strain, const float *const *sbar,
-                                double dt, int nx, int64_t pitch, int64_t per_shot, int S, hipStream_t st)
+                                float *const *w, const float *l2m, const float *lam, const float *mu, double dt,
+                                int nx, int64_t pitch, int64_t per_shot, int S, hipStream_t st)
 {
     Six e, sb;
-    for (int k = 0; k < 6; ++k) { e.p[k] = strain[k]; sb.p[k] = sbar[k]; }
+    SixOut o{};
+    for (int k = 0; k < 6; ++k) {
+        e.p[k] = strain[k];
+        sb.p[k] = sbar[k];
+        if (w) o.p[k] = w[k];
+    }
     const int64_t total = (per_shot / pitch) * nx;
     const unsigned blocks = (unsigned)((total + 255) / 256);
-    hipLaunchKernelGGL(k_el_grad_accum, blocks, 256, 0, st, gl, gm, e, sb, dt, nx, pitch, per_shot, S, total);
+    auto go = [&](auto k) {
+        hipLaunchKernelGGL(k, blocks, 256, 0, st, gl, gm, e, sb, o, l2m, lam, mu, dt, nx, pitch, per_shot, S, total);
+    };
+    w ? go(k_el_grad_accum<true>) : go(k_el_grad_accum<false>);
     return hipGetLastError();
 }
 

@@ -50,13 +50,15 @@ struct RecHost {
 enum KClass {
     KC_STRESS_X, KC_STRESS_Y, KC_STRESS_Z, KC_VEL_X, KC_VEL_Y, KC_VEL_Z, KC_SOURCE, KC_RECEIVER,
     KC_ADVANCE, KC_ADJ_SOLVE, KC_ADJ_GATHER, KC_GRAD, KC_VEL_STRESS_X, KC_ADJ_X, KC_ADJ_XX, KC_STRESS_XY,
-    KC_VEL_XY, KC_STRESS_Z3, KC_VEL_Z3, KC_STRESS_TILE, KC_VEL_TILE, KC_COUNT
+    KC_VEL_XY, KC_STRESS_Z3, KC_VEL_Z3, KC_STRESS_TILE, KC_VEL_TILE,
+    KC_ADJ_TILE, KC_ADJ_Z3, KC_COUNT
 };
 const char *kKClassName[KC_COUNT] = {
     "stress_line_x", "stress_line_y", "stress_line_z", "velocity_line_x", "velocity_line_y",
     "velocity_line_z", "source_inject", "receiver_record", "step_advance", "adjoint_line_solve",
     "adjoint_gather", "gradient_accumulate", "velocity_stress_x", "adjoint_line_x", "adjoint_line_x_pair",
-    "stress_tile_xy", "velocity_tile_xy", "stress_store_z", "velocity_store_z", "stress_tile_xz", "velocity_tile_xz"};
+    "stress_tile_xy", "velocity_tile_xy", "stress_store_z", "velocity_store_z", "stress_tile_xz", "velocity_tile_xz",
+    "adjoint_tile", "adjoint_store_z"};
 
 }  // namespace
 
@@ -155,7 +157,8 @@ struct loss_sim {
     int strain_slots = 6;          // elastic: strains, then the three velocity drives if 9
     int divstore_slots = 0;        // slots per step divstore was allocated with
     float *adj[4] = {nullptr, nullptr, nullptr, nullptr};   // lambda, mu1, mu3, Y scratch
-    float *adj_el[11] = {};        // elastic: the 9 field bars (field order), Y scratch, operand
+    float *adj_el[15] = {};        // elastic: the 9 field bars (field order), Y scratch, operand (tile passes:
+                                   // six operands, the last four allocated with them)
     float *adj_pml[5] = {};        // acoustic with the layer: the 4 memory-variable bars, operand
     float *adj_pml_el[19] = {};    // elastic with the layer: the 18 memory-variable bars, operand
     int ck_fields = 0;             // fields per checkpoint (the state, and the layer's variables)
@@ -525,7 +528,7 @@ loss_status tile_z3(loss_sim *s, int kc, const float *const *in, int var0, float
     }
     loss_status r = timed_begin(s);
     if (r) return r;
-    const hipError_t e = launch_tile_z(z, s->st);
+    const hipError_t e = launch_tile_z(TILE_D1, z, s->st);
     if (e != hipSuccess) return fail(LOSS_EHIP, std::string("z store launch: ") + hipGetErrorString(e));
     return timed_end(s, kc);
 }
@@ -1576,6 +1579,56 @@ loss_status deriv_direct(loss_sim *s, int axis, int order, const float *in, floa
     return timed_end(s, KC_VEL_X + axis);
 }
 
+// Whether the transposed passes run as tiles: as the forward ones do, without the layer (its
+// flow stands between a bar and its derivative), where the transposed tables exist.
+bool tile_adjoint_ok(const loss_sim *s)
+{
+    if (!tile_ok(s) || s->pml_mem) return false;
+    for (int axis = 0; axis < 3; ++axis)
+        if (!(axis == 1 && s->d.ndim == 2) && s->top[TILE_DT][axis].nsub == 0) return false;
+    return true;
+}
+
+// One transposed pass: x and row derivatives of in (times coef) added to out.
+loss_status adj_tile(loss_sim *s, int mode, const float *const *in, int nin, const float *coef, float *const *out,
+                     int nout, float alpha)
+{
+    TileArgs t = tile_args(s);
+    t.x = s->top[TILE_DT][0];
+    t.r = s->top[TILE_DT][t.row_axis];
+    for (int i = 0; i < nin; ++i) t.in[i] = in[i];
+    for (int i = 0; i < nout; ++i) t.out[i] = out[i];
+    for (int i = 0; i < 3; ++i) t.T[i] = s->tmp[i];
+    t.c0 = coef;
+    t.alpha = alpha;
+    return run_tile(s, KC_ADJ_TILE, mode, t);
+}
+
+// transposed z derivatives of three fields (times coef) into tmp[0..2]
+loss_status adj_tile_z3(loss_sim *s, const float *const *in, const float *coef)
+{
+    TileZArgs z{};
+    z.nf = 3;
+    z.S = s->S;
+    z.nx = s->nx;
+    z.ny = s->ny;
+    z.pitch = s->pitch;
+    z.plane = s->plane;
+    z.shot_stride = s->shot_stride;
+    z.nw = s->tile_nw[2];
+    z.r = s->top[TILE_DT][2];
+    z.coef = coef;
+    for (int i = 0; i < 3; ++i) {
+        z.in[i] = in[i];
+        z.out[i] = s->tmp[i];
+    }
+    loss_status r = timed_begin(s);
+    if (r) return r;
+    const hipError_t e = launch_tile_z(TILE_DT, z, s->st);
+    if (e != hipSuccess) return fail(LOSS_EHIP, std::string("adjoint z launch: ") + hipGetErrorString(e));
+    return timed_end(s, KC_ADJ_Z3);
+}
+
 // Elastic adjoint of the fused schedule that loss_forward_ckpt ran.  Forward step n:
 //   B: sigma += (dt lambda) tr(e) I + 2 (dt mu) e, strains e of u^n; stress receivers
 //      record sigma, velocity receivers half of u^n (the half-step-ahead state);
@@ -1628,6 +1681,16 @@ loss_status elastic_adjoint(loss_sim *s, const double *residual, int32_t param, 
             if (launch_fill(s->adj_pml_el[k], fe, 0.f, s->st) != hipSuccess) return fail(LOSS_EHIP, "fill");
     }
     HIPCHK(hipMemsetAsync(s->grad_pad, 0, sizeof(double) * 3 * ss, s->st));
+    // tile passes: six operands of the transposed stress sub-flow (without room for them the
+    // passes run one by one)
+    bool tiles = tile_adjoint_ok(s);
+    for (int k = 11; tiles && k < 15; ++k)
+        if (!s->adj_el[k] && s->alloc(&s->adj_el[k], fe)) tiles = false;
+    if (!tiles) {
+        for (int k = 11; k < 15; ++k)
+            if (s->adj_el[k]) { s->release(s->adj_el[k]); s->adj_el[k] = nullptr; }
+        (void)hipGetLastError();   // a refused allocation is no error of the launches that follow
+    }
     double *gb = s->grad_pad + 2 * ss;
     float *const *A = s->adj_el;
     float *Y = s->adj_el[9], *Wop = s->adj_el[10];
@@ -1690,7 +1753,13 @@ loss_status elastic_adjoint(loss_sim *s, const double *residual, int32_t param, 
                 if (e != hipSuccess) return fail(LOSS_EHIP, hipGetErrorString(e));
                 if ((r = timed_end(s, KC_GRAD))) return r;
             }
-            for (int i = 0; i < 3; ++i)
+            if (tiles) {
+                const float *ub[3] = {A[LOSS_F_EV1], A[LOSS_F_EV2], A[LOSS_F_EV3]};
+                float *sb[6] = {A[LOSS_F_S11], A[LOSS_F_S22], A[LOSS_F_S33], A[LOSS_F_S12], A[LOSS_F_S13],
+                                A[LOSS_F_S23]};
+                if ((r = adj_tile_z3(s, ub, b)) || (r = adj_tile(s, TILE_EL_VEL_T, ub, 3, b, sb, 6, 1.f))) return r;
+            }
+            for (int i = 0; i < 3 && !tiles; ++i)
                 for (int j = 0; j < 3; ++j)
                     if ((r = pass_t(j, A[LOSS_F_EV1 + i], b, 3 * i + j, A[sidx[i][j]]))) return r;
             if ((r = inject_res(false, n, 1.f))) return r;
@@ -1698,10 +1767,18 @@ loss_status elastic_adjoint(loss_sim *s, const double *residual, int32_t param, 
             const float *strain[6];
             for (int q = 0; q < 6; ++q) strain[q] = s->divstore + (k * slots + q) * fe;
             if ((r = timed_begin(s))) return r;
-            hipError_t e = launch_el_grad_accum(s->grad_pad, s->grad_pad + ss, strain, sbar, s->d.dt, s->nx,
-                                                s->pitch, ss, S, s->st);
+            hipError_t e = launch_el_grad_accum(s->grad_pad, s->grad_pad + ss, strain, sbar, tiles ? s->adj_el + 9 : nullptr,
+                                                l2m, lam, mu, s->d.dt, s->nx, s->pitch, ss, S, s->st);
             if (e != hipSuccess) return fail(LOSS_EHIP, hipGetErrorString(e));
             if ((r = timed_end(s, KC_GRAD))) return r;
+            if (tiles) {
+                float *const *w = s->adj_el + 9;   // 11 22 33 12 13 23
+                const float *wz[3] = {w[4], w[5], w[2]}, *wi[5] = {w[0], w[3], w[1], w[4], w[5]};
+                float *ub[3] = {A[LOSS_F_EV1], A[LOSS_F_EV2], A[LOSS_F_EV3]};
+                if ((r = adj_tile_z3(s, wz, nullptr)) || (r = adj_tile(s, TILE_EL_STRESS_T, wi, 5, nullptr, ub, 3, 1.f)))
+                    return r;
+                continue;
+            }
             for (int kk = 0; kk < 3; ++kk) {
                 e = launch_el_normal_operand(Wop, A[LOSS_F_S11], A[LOSS_F_S22], A[LOSS_F_S33], l2m, lam, kk, s->nx,
                                              s->pitch, ss, S, s->st);
@@ -2551,6 +2628,26 @@ loss_status loss_adjoint(loss_sim *s, const double *residual, int32_t param, dou
                 if ((r = timed_end(s, KC_GRAD))) return r;
                 if ((r = pass_t(2, lam, K, 3, mu3))) return r;
                 if ((r = pass_t(0, lam, K, 2, mu1))) return r;
+            }
+            continue;
+        }
+        if (tile_adjoint_ok(s)) {
+            // lambda^{n+1} += -dt (Dx^T(b mu1) + Dz^T(b mu3)) and the residual; dJ/dK += -dt
+            // lambda^{n+1} div u^n; mu^n = mu^{n+1} - dt D^T(K lambda^{n+1})
+            const float *mu[2] = {mu1, mu3}, *la[1] = {lam};
+            float *mu_out[2] = {mu1, mu3}, *la_out[1] = {lam};
+            for (int64_t k = nc - 1; k >= 0; --k) {
+                const int64_t n = n0 + k;
+                if ((r = adj_tile(s, TILE_AC_VEL_T, mu, 2, b, la_out, 1, -1.f))) return r;
+                if ((r = timed_begin(s))) return r;
+                hipError_t e = launch_res_gather(s->d_tgt_str, s->ntgt_str, s->d_toff_str, nullptr, lam, ss, s->res_dev,
+                                                 n, 1.f, s->st);
+                if (e != hipSuccess) return fail(LOSS_EHIP, hipGetErrorString(e));
+                if ((r = timed_end(s, KC_RECEIVER)) || (r = timed_begin(s))) return r;
+                e = launch_grad_accum(s->grad_pad, lam, s->divstore + k * fe, -dt, (int)S, ss, ss, s->st);
+                if (e != hipSuccess) return fail(LOSS_EHIP, hipGetErrorString(e));
+                if ((r = timed_end(s, KC_GRAD))) return r;
+                if ((r = adj_tile(s, TILE_AC_STRESS_T, la, 1, K, mu_out, 2, -1.f))) return r;
             }
             continue;
         }

@@ -202,6 +202,12 @@ enum TileMode : int {
     TILE_EL_VEL = 1,      // in s11 s12 s22 s13 s23, T d3 s_i3; out v1 v2 v3; keep the three drives
     TILE_AC_STRESS = 2,   // in v1 v3; out sigma; keep d1 v1 + d3 v3
     TILE_AC_VEL = 3,      // in sigma; out v1 v3
+    // transposes (adjoint), derivatives transposed slopes; no media in the update, c0: the
+    // coefficient of the inputs (uniform over shots)
+    TILE_EL_VEL_T = 4,    // in c0 u1 u2 u3 (bars), T Dt3 (c0 u_i); out += bars of s11 s22 s33 s12 s13 s23
+    TILE_EL_STRESS_T = 5, // in w11 w12 w22 w13 w23, T Dt3 w_i3; out += bars of v1 v2 v3
+    TILE_AC_VEL_T = 6,    // in c0 v1 v3 (bars); out += alpha (bar of sigma)
+    TILE_AC_STRESS_T = 7, // in c0 sigma (bar); out += alpha (bars of v1 v3)
 };
 
 // One chunk (kTileC rows) of a piece, rows form: the rows' factors and taps, and the two
@@ -301,10 +307,11 @@ struct AxisArgs {
 hipError_t launch_axis_rows(int op, const AxisArgs &a, hipStream_t st);
 hipError_t launch_axis_x(int op, const AxisArgs &a, hipStream_t st);
 
-// z derivatives of up to three fields stored in one launch (the strided solve of the tile
+// z derivatives (slopes, or transposed slopes) of up to three fields stored in one launch (the strided solve of the tile
 // passes alone)
 struct TileZArgs {
     const float *in[3];
+    const float *coef;         // transposed slopes: coefficient of the inputs, or null
     float *out[3];
     int nf, S, nx, ny;
     int64_t pitch, plane, shot_stride;
@@ -315,7 +322,7 @@ struct TileZArgs {
     const float4 *pr;
     int pml_store;
 };
-hipError_t launch_tile_z(const TileZArgs &a, hipStream_t st);
+hipError_t launch_tile_z(int op, const TileZArgs &a, hipStream_t st);   // TILE_D1 or TILE_DT
 
 // Launch helpers (kernels.hip).  axis: 0 = x (contiguous), 1 = y, 2 = z.
 hipError_t launch_line(int axis, int solve, int epi, const LineArgs &a, hipStream_t st);
@@ -352,8 +359,11 @@ hipError_t launch_pml_adj_operand(float *w, const float *f, const float *coef, f
 hipError_t launch_el_normal_operand(float *w, const float *s11, const float *s22, const float *s33,
                                     const float *l2m, const float *lam, int k, int nx, int64_t pitch,
                                     int64_t per_shot, int S, hipStream_t st);
+// w (or null): the six operands of the transposed stress sub-flow are written too, w_kk as above,
+// w_ij = mu sbar_ij (11, 22, 33, 12, 13, 23)
 hipError_t launch_el_grad_accum(double *gl, double *gm, const float *const *strain, const float *const *sbar,
-                                double dt, int nx, int64_t pitch, int64_t per_shot, int S, hipStream_t st);
+                                float *const *w, const float *l2m, const float *lam, const float *mu, double dt,
+                                int nx, int64_t pitch, int64_t per_shot, int S, hipStream_t st);
 hipError_t launch_el_grad_unpad(const double *gl, const double *gm, const double *gb, double *g, int nx,
                                 int64_t pitch, const float *vp, const float *vs, const float *rho, int mode,
                                 int64_t nodes, hipStream_t st);

@@ -33,6 +33,11 @@
 // What a tile does before its first field load counts: a per-tile word says whether it has
 // receivers or a source (each tile walking the sources and the receivers' ranges, behind a
 // read of the step counter: acoustic 2049^2 31.9 + 37.2 -> 28.4 + 32.0 us with the next).
+//
+// The adjoints' reverse steps run the same way with transposed slopes (TILE_*_T): x and row
+// parts of D^T in one kernel, bytes per node and reverse step acoustic 68 -> 44, elastic
+// 312 -> 216 and 20 launches fewer.  Measured (us per reverse step, without the gradient's
+// sums): acoustic 64 x 1025^2 1165 -> 864, elastic 129^3 x 2 shots 540 -> 298.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,8 +50,13 @@ namespace {
 
 template <int MODE>
 struct Traits;
+struct Forward {
+    static constexpr int OP = TILE_D1;
+    static constexpr bool coef = false;           // inputs times c0
+};
 template <>
-struct Traits<TILE_EL_STRESS> {   // v1 v2 v3
+struct Traits<TILE_EL_STRESS> : Forward {   // v1 v2 v3
+    static constexpr int SHAPE = TILE_EL_STRESS;  // which derivatives of which inputs, and their sums
     static constexpr int NF = 3;
     static constexpr bool xs(int f) { return true; }
     static constexpr bool ys(int f) { return true; }
@@ -54,7 +64,8 @@ struct Traits<TILE_EL_STRESS> {   // v1 v2 v3
     static constexpr int py(int f) { return 9 + 3 * f + 1; }
 };
 template <>
-struct Traits<TILE_EL_VEL> {      // s11 s12 s22 s13 s23
+struct Traits<TILE_EL_VEL> : Forward {   // s11 s12 s22 s13 s23
+    static constexpr int SHAPE = TILE_EL_VEL;
     static constexpr int NF = 5;
     static constexpr bool xs(int f) { return f == 0 || f == 1 || f == 3; }
     static constexpr bool ys(int f) { return f == 1 || f == 2 || f == 4; }
@@ -62,7 +73,8 @@ struct Traits<TILE_EL_VEL> {      // s11 s12 s22 s13 s23
     static constexpr int py(int f) { return f == 1 ? 1 : (f == 2 ? 4 : 7); }
 };
 template <>
-struct Traits<TILE_AC_STRESS> {   // v1 v3
+struct Traits<TILE_AC_STRESS> : Forward {   // v1 v3
+    static constexpr int SHAPE = TILE_AC_STRESS;
     static constexpr int NF = 2;
     static constexpr bool xs(int f) { return f == 0; }
     static constexpr bool ys(int f) { return f == 1; }
@@ -70,12 +82,35 @@ struct Traits<TILE_AC_STRESS> {   // v1 v3
     static constexpr int py(int f) { return 3; }
 };
 template <>
-struct Traits<TILE_AC_VEL> {      // sigma
+struct Traits<TILE_AC_VEL> : Forward {   // sigma
+    static constexpr int SHAPE = TILE_AC_VEL;
     static constexpr int NF = 1;
     static constexpr bool xs(int f) { return true; }
     static constexpr bool ys(int f) { return true; }
     static constexpr int px(int f) { return 0; }
     static constexpr int py(int f) { return 1; }
+};
+
+// Transposes: the transpose of a velocity pass takes the derivatives that the stress pass
+// takes (sigma_ij bar += D_j^T (c0 u_i bar)) and the other way round.
+template <>
+struct Traits<TILE_EL_VEL_T> : Traits<TILE_EL_STRESS> {
+    static constexpr int OP = TILE_DT;
+    static constexpr bool coef = true;
+};
+template <>
+struct Traits<TILE_EL_STRESS_T> : Traits<TILE_EL_VEL> {
+    static constexpr int OP = TILE_DT;
+};
+template <>
+struct Traits<TILE_AC_VEL_T> : Traits<TILE_AC_STRESS> {
+    static constexpr int OP = TILE_DT;
+    static constexpr bool coef = true;
+};
+template <>
+struct Traits<TILE_AC_STRESS_T> : Traits<TILE_AC_VEL> {
+    static constexpr int OP = TILE_DT;
+    static constexpr bool coef = true;
 };
 
 template <int MODE>
@@ -85,6 +120,12 @@ constexpr int rows_slot(int f)
     for (int i = 0; i < f; ++i) n += Traits<MODE>::ys(i) ? 1 : 0;
     return n;
 }
+
+// floats a wave publishes per field of the rows, and its LDS: its rows of x, then those
+template <int OP>
+constexpr int kPublish = OP == TILE_DT ? 320 : 256;
+template <int MODE>
+constexpr int kModeLds = std::max(kWaveLds, rows_slot<MODE>(Traits<MODE>::NF) * kPublish<Traits<MODE>::OP>);
 
 // Sum of the source terms of field fid (a component of the outputs) over the R rows from
 // row q on, as the update adds them.
@@ -148,34 +189,38 @@ __device__ __forceinline__ void layer_flow(const TileArgs &a, const Place &pl, i
 // What the update of a row takes: the sums of x and row derivatives per output.
 //   elastic stress: d1 v1, d2 v2, d2 v1 + d1 v2, d1 v3, d2 v3; elastic velocity:
 //   d1 s_i1 + d2 s_i2; acoustic stress: d1 v1 + d3 v3; acoustic velocity: d1 sigma, d3 sigma
+template <int SHAPE>
+struct SumsOf;
+template <>
+struct SumsOf<TILE_EL_STRESS> { static constexpr int N = 5; };
+template <>
+struct SumsOf<TILE_EL_VEL> { static constexpr int N = 3; };
+template <>
+struct SumsOf<TILE_AC_STRESS> { static constexpr int N = 1; };
+template <>
+struct SumsOf<TILE_AC_VEL> { static constexpr int N = 2; };
+
 template <int MODE>
-struct Sums;
-template <>
-struct Sums<TILE_EL_STRESS> { static constexpr int N = 5; };
-template <>
-struct Sums<TILE_EL_VEL> { static constexpr int N = 3; };
-template <>
-struct Sums<TILE_AC_STRESS> { static constexpr int N = 1; };
-template <>
-struct Sums<TILE_AC_VEL> { static constexpr int N = 2; };
+using Sums = SumsOf<Traits<MODE>::SHAPE>;
 
 template <int MODE, int R>
 __device__ __forceinline__ void make_sums(const float (&dx)[Traits<MODE>::NF][R], const float (&dy)[Traits<MODE>::NF][R],
                                           float (&e)[Sums<MODE>::N][R])
 {
+    constexpr int SHAPE = Traits<MODE>::SHAPE;
 #pragma unroll
     for (int c = 0; c < R; ++c) {
-        if constexpr (MODE == TILE_EL_STRESS) {
+        if constexpr (SHAPE == TILE_EL_STRESS) {
             e[0][c] = dx[0][c];
             e[1][c] = dy[1][c];
             e[2][c] = dy[0][c] + dx[1][c];
             e[3][c] = dx[2][c];
             e[4][c] = dy[2][c];
-        } else if constexpr (MODE == TILE_EL_VEL) {
+        } else if constexpr (SHAPE == TILE_EL_VEL) {
             e[0][c] = dx[0][c] + dy[1][c];
             e[1][c] = dx[1][c] + dy[2][c];
             e[2][c] = dx[3][c] + dy[4][c];
-        } else if constexpr (MODE == TILE_AC_STRESS) {
+        } else if constexpr (SHAPE == TILE_AC_STRESS) {
             e[0][c] = dy[1][c] + dx[0][c];
         } else {
             e[0][c] = dx[0][c];
@@ -325,20 +370,64 @@ __device__ __forceinline__ void tile_update(const TileArgs &a, const Place &pl, 
     }
 }
 
+// The same for the transposes: the sums (and the stored z derivatives T) are added to the bars.
+template <int MODE, int R, bool FULL>
+__device__ __forceinline__ void tile_add(const TileArgs &a, const Place &pl, int q, int nrow,
+                                         const float (&e)[Sums<MODE>::N][R])
+{
+    if (!pl.act) return;
+    auto row = [&](int c) { return FULL || c < nrow; };
+    auto get = [&](const float *p, int c) { return ld(buf(p + pl.fb), (unsigned)(q + c) * pl.rs4, pl.vx); };
+    auto put = [&](float *p, int c, float v) { st(buf(p + pl.fb), (unsigned)(q + c) * pl.rs4, pl.vx, v); };
+    // output j += sum of e[x] (if any) and T[t] (if any), R rows in flight
+    auto add = [&](int j, int x, int t) {
+        float o[R], z[R];
+#pragma unroll
+        for (int c = 0; c < R; ++c)
+            if (row(c)) {
+                o[c] = get(a.out[j], c);
+                if (t >= 0) z[c] = get(a.T[t], c);
+            }
+#pragma unroll
+        for (int c = 0; c < R; ++c)
+            if (row(c)) {
+                const float d = x < 0 ? z[c] : (t < 0 ? e[x < 0 ? 0 : x][c] : e[x < 0 ? 0 : x][c] + z[c]);
+                put(a.out[j], c, fmaf(a.alpha, d, o[c]));
+            }
+    };
+    if constexpr (MODE == TILE_EL_VEL_T) {
+        add(0, 0, -1);
+        add(1, 1, -1);
+        add(2, -1, 2);
+        add(3, 2, -1);
+        add(4, 3, 0);
+        add(5, 4, 1);
+    } else if constexpr (MODE == TILE_EL_STRESS_T) {
+        add(0, 0, 0);
+        add(1, 1, 1);
+        add(2, 2, 2);
+    } else if constexpr (MODE == TILE_AC_VEL_T) {
+        add(0, 0, -1);
+    } else {
+        add(0, 0, -1);
+        add(1, 1, -1);
+    }
+}
+
 // Waves per SIMD (registers): the elastic kernels hold three fields and their sums (121-123
 // VGPRs: two workgroups per CU), the acoustic ones fit three (80 VGPRs).  Measured: acoustic
 // 2049^2 29.4 + 37.2 us at two workgroups, 29.2 + 34.5 at three, 31.0 + 44.3 at four (spills);
 // reading the updated arrays with the fields instead of after the solves 33.3 + 39.5.
 template <int MODE>
-constexpr int kTileWavesPerSimd = MODE == TILE_AC_STRESS || MODE == TILE_AC_VEL ? 6 : 4;
+constexpr int kTileWavesPerSimd = Traits<MODE>::SHAPE == TILE_AC_STRESS || Traits<MODE>::SHAPE == TILE_AC_VEL ? 6 : 4;
 
 template <int MODE, bool KEEP>
 __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_tile(TileArgs a, int nreal)
 {
     using T = Traits<MODE>;
-    constexpr int NF = T::NF;
+    constexpr int NF = T::NF, OP = T::OP, kLds = kModeLds<MODE>, kEx = kPublish<OP>;
     __shared__ float4 tab4[16 * (kLaneF / 4)];                // x lanes' table of the piece
-    __shared__ float4 lds4[kTileWaves * kWaveLds / 4];
+    __shared__ float4 lds4[kTileWaves * kLds / 4];
     float *lds = reinterpret_cast<float *>(lds4);
     // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs; each XCD gets a
     // contiguous range of tiles (x fastest), so neighbours' halos meet in one L2
@@ -384,7 +473,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
     const int q = pr.s + w * kTileC;
     const int nown = min(max(pr.e - q, 0), kTileC);           // rows of the piece in this wave
     const bool clos = lastr && nown > 0 && q + kTileC >= pr.e;  // this wave also updates row N
-    float *L = lds + w * kWaveLds;
+    float *L = lds + w * kLds;
     pl.vx = 4u * pl.xc;
     pl.rs4 = 4u * (unsigned)a.rstride;
 
@@ -406,7 +495,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
         const Buf in = buf(a.in[f] + pl.fb);
 #pragma unroll
         for (int c = 0; c < kTileC + 2; ++c)
-            if (T::ys(f) || (c > 0 && c <= kTileC))
+            if ((T::ys(f) && OP == TILE_D1) || (c > 0 && c <= kTileC))
                 u[f][c] = ld(in, (unsigned)max(min(q - 1 + c, pr.e), 0) * pl.rs4, pl.vx);
         if (T::xs(f)) {
 #pragma unroll
@@ -420,13 +509,37 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             }
         }
     };
+    const Buf cf = buf(T::coef ? a.c0 + pl.mb : a.in[0]);
+    auto scale = [&](int f) {       // inputs times their coefficient
+#pragma unroll
+        for (int c = 1; c <= kTileC; ++c) u[f][c] *= ld(cf, (unsigned)max(min(q - 1 + c, pr.e), 0) * pl.rs4, pl.vx);
+        if (T::xs(f)) {
+#pragma unroll
+            for (int h = 0; h < 4; ++h) xh[f][h] *= ld(cf, 0, (unsigned)min(q + 2 * h + (lane >> 5), pr.e) * pl.rs4 + hcol);
+            if (wide) {
+                const unsigned wcol = 4u * line_node(halo_pos(px, hj), a.x.N, a.x.periodic);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    xh[f][4 + h] *= ld(cf, 0, (unsigned)min(q + 4 * h + (lane >> 4), pr.e) * pl.rs4 + wcol);
+            }
+        }
+    };
     auto load_halo = [&](int f) {   // entries past the halo's count repeat row e with zero taps
 #pragma unroll
-        for (int h = 0; h < kHaloPre; ++h) yh[f][h] = ld(buf(a.in[f] + pl.fb), (unsigned)hn[w + h * a.nw] * pl.rs4, pl.vx);
+        for (int h = 0; h < kHaloPre; ++h) {
+            const unsigned r = (unsigned)hn[w + h * a.nw] * pl.rs4;
+            yh[f][h] = ld(buf(a.in[f] + pl.fb), r, pl.vx);
+            if (T::coef) yh[f][h] *= ld(cf, r, pl.vx);
+        }
     };
 #pragma unroll
     for (int f = 0; f < NF; ++f)
         if (T::xs(f)) load(f);
+    if (T::coef) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            if (T::xs(f)) scale(f);
+    }
     const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
     const float rend = a.r.ends[lr].sE;
     const int k16 = lane & 15;
@@ -461,20 +574,25 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             }
             wave_sync();
 #pragma unroll
-            for (int it = 0; it < kTileC / 4; ++it) x_row<TILE_D1>(xp, xt, L16 + 4 * it * kRowPitch, k16);
+            for (int it = 0; it < kTileC / 4; ++it) x_row<OP>(xp, xt, L16 + 4 * it * kRowPitch, k16);
             wave_sync();
 #pragma unroll
             for (int c = 0; c < kTileC; ++c) dx[f][c] = L[c * kRowPitch + kRowOwn + lane];
             if (clos) {                   // row N of the line's last piece
                 const Buf in = buf(a.in[f] + pl.fb);
-                const float un = ld(in, (unsigned)pr.e * pl.rs4, pl.vx);
+                float un = ld(in, (unsigned)pr.e * pl.rs4, pl.vx);
                 const int i = min(lane, nhx - 1);
-                const float xn = ld(in, (unsigned)pr.e * pl.rs4, 4u * line_node(halo_pos(px, i), a.x.N, a.x.periodic));
+                const unsigned xi = 4u * line_node(halo_pos(px, i), a.x.N, a.x.periodic);
+                float xn = ld(in, (unsigned)pr.e * pl.rs4, xi);
+                if (T::coef) {
+                    un *= ld(cf, (unsigned)pr.e * pl.rs4, pl.vx);
+                    xn *= ld(cf, (unsigned)pr.e * pl.rs4, xi);
+                }
                 wave_sync();
                 L[kRowOwn + lane] = un;
                 L[halo_slot(px, i)] = xn;
                 wave_sync();
-                x_row<TILE_D1>(xp, xt, L16, k16);
+                x_row<OP>(xp, xt, L16, k16);
                 wave_sync();
                 dxn[f][0] = L[kRowOwn + lane];
             }
@@ -482,7 +600,10 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
         if (f == 0) {                     // what the rows alone need, in flight during the x solves
 #pragma unroll
             for (int g = 0; g < NF; ++g) {
-                if (!T::xs(g)) load(g);
+                if (!T::xs(g)) {
+                    load(g);
+                    if (T::coef) scale(g);
+                }
                 if (T::ys(g)) load_halo(g);
             }
         }
@@ -493,19 +614,22 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
 #pragma unroll
     for (int f = 0; f < NF; ++f)
         if (T::ys(f)) {
-            float B, W, ps = 0.f, pe = 0.f;
-            rows_local<TILE_D1>(rt, u[f], dy[f], B, W);
-            taps_own<TILE_D1>(rt, u[f], 0.f, 0.f, ps, pe);
+            float B, W, ps = 0.f, pe = 0.f, pt = 0.f;
+            if (OP == TILE_DT) u[f][0] = u[f][kTileC + 1] = 0.f;
+            rows_local<OP>(rt, u[f], dy[f], B, W);
+            taps_own<OP>(rt, u[f], 0.f, 0.f, ps, pe);
             auto halo = [&](int i, float v) {
                 const float2 c = hc[i];
                 ps = fmaf(c.x, v, ps);
                 pe = fmaf(c.y, v, pe);
+                if (OP == TILE_DT && i < pr.hl) pt = fmaf(c.x, v, pt);
             };
 #pragma unroll
             for (int h = 0; h < kHaloPre; ++h) halo(w + h * a.nw, yh[f][h]);
             for (int i = w + kHaloPre * a.nw; i < nhr; i += a.nw)     // few waves, wide taps
-                halo(i, ld(buf(a.in[f] + pl.fb), (unsigned)hn[i] * pl.rs4, pl.vx));
-            if (clos) {
+                halo(i, ld(buf(a.in[f] + pl.fb), (unsigned)hn[i] * pl.rs4, pl.vx) *
+                            (T::coef ? ld(cf, (unsigned)hn[i] * pl.rs4, pl.vx) : 1.f));
+            if (OP == TILE_D1 && clos) {
                 // natural end: the closing row's difference (rend is 0 on a junction)
                 float ue = 0.f, ul = 0.f;
 #pragma unroll
@@ -513,7 +637,8 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
                     if (c == nown - 1) { ul = u[f][c + 1]; ue = u[f][c + 2]; }
                 pe = fmaf(rend, ue - ul, pe);
             }
-            rows_publish(L + rows_slot<MODE>(f) * 256, lane, B, W, ps, pe);
+            rows_publish(L + rows_slot<MODE>(f) * kEx, lane, B, W, ps, pe);
+            if (OP == TILE_DT) L[rows_slot<MODE>(f) * kEx + 256 + lane] = pt;
         }
     __syncthreads();
     if (nown > 0) {
@@ -521,8 +646,11 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
                                         pr.e > a.r.N - a.r.pml_w);
 #pragma unroll
         for (int f = 0; f < NF; ++f)
-            if (T::ys(f))
-                dyn[f][0] = rows_finish<kWaveLds, TILE_D1>(rt, lds + rows_slot<MODE>(f) * 256, a.nw, lane, dy[f]);
+            if (T::ys(f)) {
+                const float we = rows_finish<kLds, OP>(rt, lds + rows_slot<MODE>(f) * kEx, a.nw, lane, dy[f],
+                                                       &a.r.ends[lr], a.r.s3, w == 0, nown, &dyn[f][0]);
+                if (OP == TILE_D1) dyn[f][0] = we;
+            }
         if (band) {
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
@@ -536,11 +664,17 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
         }
         float e[Sums<MODE>::N][kTileC], en[Sums<MODE>::N][1];
         make_sums<MODE, kTileC>(dx, dy, e);
-        if (!hits && nown == kTileC) tile_update<MODE, kTileC, true, KEEP>(a, pl, 0, q, kTileC, false, e);
-        else tile_update<MODE, kTileC, false, KEEP>(a, pl, n, q, nown, hits, e);
+        if constexpr (OP == TILE_DT) {
+            if (nown == kTileC) tile_add<MODE, kTileC, true>(a, pl, q, kTileC, e);
+            else tile_add<MODE, kTileC, false>(a, pl, q, nown, e);
+        } else {
+            if (!hits && nown == kTileC) tile_update<MODE, kTileC, true, KEEP>(a, pl, 0, q, kTileC, false, e);
+            else tile_update<MODE, kTileC, false, KEEP>(a, pl, n, q, nown, hits, e);
+        }
         if (clos) {
             make_sums<MODE, 1>(dxn, dyn, en);
-            tile_update<MODE, 1, false, KEEP>(a, pl, n, pr.e, 1, hits, en);
+            if constexpr (OP == TILE_DT) tile_add<MODE, 1, true>(a, pl, pr.e, 1, en);
+            else tile_update<MODE, 1, false, KEEP>(a, pl, n, pr.e, 1, hits, en);
         }
     }
     if (nrec > 0) {   // uniform across the workgroup
@@ -556,16 +690,19 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
 }
 
 // ---- z derivatives of an elastic stage ------------------------------------------------
-// One workgroup per (field, shot, 64 flattened columns of an x-y plane, piece of z).  The
-// pieces of kZGroup neighbouring column groups follow each other: the rows that a piece
+// One workgroup per (field, shot, 64 flattened columns of an x-y plane, piece of z); the
+// transposes of the adjoint likewise.  The pieces of kZGroup neighbouring column groups follow each other: the rows that a piece
 // takes from its neighbours are in the XCD's L2 then, and the groups' rows still make runs
 // of 8 KiB.  Measured, groups of a whole plane -> of 32: 513^3 818 -> 770 us (4.2 TB/s),
 // 184 x 142 x 211 with layers 59 -> 56, 257^3 x 2 and 65^3 the same; 4, 8 and 16 groups lie
 // between on 257^3 (206, 206, 204 us; 32: 200).
 constexpr int kZGroup = 32;
+
+template <int OP>
 __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int ncg, int nreal)
 {
-    __shared__ float ex[kTileWaves * 256];
+    constexpr int kEx = kPublish<OP>;
+    __shared__ float ex[kTileWaves * kEx];
     const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
     if (a.step_inc && blockIdx.x == 0 && threadIdx.x == 0) *a.step_inc += 1;
     if (lin >= nreal) return;
@@ -594,37 +731,47 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     const int *hn = a.r.halo_node + (size_t)lr * kTapW;
     const float2 *hc = a.r.halo_c + (size_t)lr * kTapW;
     const Buf bin = buf(in);
+    const bool has_c = OP == TILE_DT && a.coef != nullptr;    // uniform
+    const Buf cf = buf(has_c ? a.coef : in);
+    auto get = [&](int r) {
+        const float v = ld(bin, (unsigned)r * rs4, vx);
+        return has_c ? v * ld(cf, (unsigned)r * rs4, vx) : v;
+    };
     float u[kTileC + 2], yh[kHaloPre], y[kTileC];
 #pragma unroll
-    for (int c = 0; c < kTileC + 2; ++c) u[c] = ld(bin, (unsigned)max(min(q - 1 + c, p.e), 0) * rs4, vx);
+    for (int c = 0; c < kTileC + 2; ++c) u[c] = get(max(min(q - 1 + c, p.e), 0));
 #pragma unroll
-    for (int h = 0; h < kHaloPre; ++h) yh[h] = ld(bin, (unsigned)hn[w + h * a.nw] * rs4, vx);
+    for (int h = 0; h < kHaloPre; ++h) yh[h] = get(hn[w + h * a.nw]);
     const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
-    float B, W, ps = 0.f, pe = 0.f;
-    rows_local<TILE_D1>(rt, u, y, B, W);
-    taps_own<TILE_D1>(rt, u, 0.f, 0.f, ps, pe);
+    float B, W, ps = 0.f, pe = 0.f, pl = 0.f;
+    rows_local<OP>(rt, u, y, B, W);
+    taps_own<OP>(rt, u, 0.f, 0.f, ps, pe);
     auto halo = [&](int i, float v) {
         const float2 c = hc[i];
         ps = fmaf(c.x, v, ps);
         pe = fmaf(c.y, v, pe);
+        if (OP == TILE_DT && i < p.hl) pl = fmaf(c.x, v, pl);
     };
 #pragma unroll
     for (int h = 0; h < kHaloPre; ++h) halo(w + h * a.nw, yh[h]);
-    for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) halo(i, ld(bin, (unsigned)hn[i] * rs4, vx));
-    if (clos) {
+    for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) halo(i, get(hn[i]));
+    if (OP == TILE_D1 && clos) {
         float ue = 0.f, ul = 0.f;
 #pragma unroll
         for (int c = 0; c < kTileC; ++c)
             if (c == nown - 1) { ul = u[c + 1]; ue = u[c + 2]; }
         pe = fmaf(a.r.ends[lr].sE, ue - ul, pe);
     }
-    rows_publish(ex + w * 256, lane, B, W, ps, pe);
+    rows_publish(ex + w * kEx, lane, B, W, ps, pe);
+    if (OP == TILE_DT) ex[w * kEx + 256 + lane] = pl;
     __syncthreads();
     if (nown == 0) return;
-    float we = rows_finish<256, TILE_D1>(rt, ex, a.nw, lane, y);
+    float dn = 0.f;
+    float we = rows_finish<kEx, OP>(rt, ex, a.nw, lane, y, &a.r.ends[lr], a.r.s3, w == 0, nown, &dn);
+    if (OP == TILE_DT) we = dn;
     if (!act) return;
     const Buf bout = buf(out);
-    if (mem) {
+    if (OP == TILE_D1 && mem) {
         const Buf m = buf(mem + shot * a.shot_stride);
         const int N = a.r.N, pw = a.r.pml_w;
         float psi[kTileC];
@@ -668,19 +815,25 @@ hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st)
     case TILE_EL_VEL: keep ? go(k_tile<TILE_EL_VEL, true>) : go(k_tile<TILE_EL_VEL, false>); break;
     case TILE_AC_STRESS: keep ? go(k_tile<TILE_AC_STRESS, true>) : go(k_tile<TILE_AC_STRESS, false>); break;
     case TILE_AC_VEL: go(k_tile<TILE_AC_VEL, false>); break;
+    case TILE_EL_VEL_T: go(k_tile<TILE_EL_VEL_T, false>); break;
+    case TILE_EL_STRESS_T: go(k_tile<TILE_EL_STRESS_T, false>); break;
+    case TILE_AC_VEL_T: go(k_tile<TILE_AC_VEL_T, false>); break;
+    case TILE_AC_STRESS_T: go(k_tile<TILE_AC_STRESS_T, false>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_tile_z(const TileZArgs &a, hipStream_t st)
+hipError_t launch_tile_z(int op, const TileZArgs &a, hipStream_t st)
 {
     if (a.nw < 1 || a.nw > kTileWaves || a.nf < 1 || a.nf > 3) return hipErrorInvalidValue;
     const int64_t ncg = (a.plane + 63) / 64;
     const int64_t nreal = (int64_t)a.nf * a.S * ncg * a.r.nsub;
     if (nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
-    hipLaunchKernelGGL(k_tile_z, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal);
+    if (op == TILE_D1) hipLaunchKernelGGL(k_tile_z<TILE_D1>, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal);
+    else if (op == TILE_DT) hipLaunchKernelGGL(k_tile_z<TILE_DT>, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
