@@ -160,28 +160,36 @@ __device__ __forceinline__ void source_add(const TileArgs &a, const Place &pl, i
 }
 
 // The layer's sub-flow on one derivative of R rows: D becomes the effective derivative and
-// the memory variable advances.  Along x the table entry is the lane's, along the rows the row's.
-template <int R, bool ALONG_X>
-__device__ __forceinline__ void layer_flow(const TileArgs &a, const Place &pl, int var, int q, int nrow,
-                                           float (&D)[R])
+// the memory variable advances.  Along x the table entry is the lane's, along the rows the
+// row's.  The memory values are requested before the solve whose result they meet (x: of
+// the field, rows: before the barrier), and the rows' table entries before the first flow:
+// one flow after the other, each waiting for its row's entry and value, was half of a tile's
+// time in the layer (16 700 of 34 000 cycles, acoustic 1101 x 706).  184 x 142 x 211 with 16
+// layer nodes: stress tiles 248 -> 192 us, velocity tiles 212 -> 170.  Kernels of their own:
+// the values' registers and branches slowed those without a layer (z stores 204 -> 213 us).
+template <int R>
+__device__ __forceinline__ void layer_load(const TileArgs &a, const Place &pl, int var, int q, int last, bool on,
+                                           float (&psi)[R])
 {
     const Buf m = buf(a.pml_mem + var * a.pml_stride + pl.fb);
-    const TileAxis &ax = ALONG_X ? a.x : a.r;
-    auto band = [&](int j) { return j < ax.pml_w || j > ax.N - ax.pml_w; };
-    if (!pl.act || (ALONG_X && !band(pl.xc))) return;
-    const float4 tx = ALONG_X ? a.px[pl.xc] : make_float4(0.f, 0.f, 0.f, 0.f);
-    float psi[R];
+    if (!on) return;
 #pragma unroll
-    for (int c = 0; c < R; ++c) {
-        psi[c] = 0.f;
-        if (c < nrow && (ALONG_X || band(q + c))) psi[c] = ld(m, (unsigned)(q + c) * pl.rs4, pl.vx);
-    }
+    for (int c = 0; c < R; ++c) psi[c] = ld(m, (unsigned)min(q + c, last) * pl.rs4, pl.vx);
+}
+
+__device__ __forceinline__ bool layer_band(const TileAxis &ax, int j) { return j < ax.pml_w || j > ax.N - ax.pml_w; }
+
+template <int R, bool ALONG_X>
+__device__ __forceinline__ void layer_flow(const TileArgs &a, const Place &pl, int var, int q, int nrow, bool on,
+                                           float4 tx, const float4 (&tr)[R], const float (&psi)[R], float (&D)[R])
+{
+    const Buf m = buf(a.pml_mem + var * a.pml_stride + pl.fb);
+    if (!on) return;
 #pragma unroll
     for (int c = 0; c < R; ++c)
-        if (c < nrow && (ALONG_X || band(q + c))) {
-            const float4 t = ALONG_X ? tx : a.pr[q + c];
+        if (c < nrow && (ALONG_X || layer_band(a.r, q + c))) {
             float psi1;
-            D[c] = pml_flow(t, D[c], psi[c], &psi1);
+            D[c] = pml_flow(ALONG_X ? tx : tr[c], D[c], psi[c], &psi1);
             if (a.pml_store) st(m, (unsigned)(q + c) * pl.rs4, pl.vx, psi1);
         }
 }
@@ -421,7 +429,7 @@ __device__ __forceinline__ void tile_add(const TileArgs &a, const Place &pl, int
 template <int MODE>
 constexpr int kTileWavesPerSimd = Traits<MODE>::SHAPE == TILE_AC_STRESS || Traits<MODE>::SHAPE == TILE_AC_VEL ? 6 : 4;
 
-template <int MODE, bool KEEP>
+template <int MODE, bool KEEP, bool LAYER>
 __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_tile(TileArgs a, int nreal)
 {
     using T = Traits<MODE>;
@@ -557,12 +565,18 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
     __syncthreads();                                          // the lanes' table
 
     // ---- x: the wave's rows through LDS -------------------------------------------------
+    const bool xband = LAYER && (px.s < a.x.pml_w || px.e > a.x.N - a.x.pml_w);   // uniform
+    const bool xon = xband && pl.act && layer_band(a.x, pl.xc);
+    float4 xt4{};
+    if (xband) xt4 = a.px[pl.xc];
     float dx[NF][kTileC], dy[NF][kTileC], dxn[NF][1], dyn[NF][1];
     float *L16 = L + (lane >> 4) * kRowPitch;
     float *Lh = L + (lane >> 5) * kRowPitch + halo_slot(px, hi), *Lw = L + (lane >> 4) * kRowPitch + halo_slot(px, hj);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         if (T::xs(f) && nown > 0) {
+            float psi[kTileC];
+            if (xband) layer_load<kTileC>(a, pl, T::px(f), q, pr.e, xon, psi);
             wave_sync();
 #pragma unroll
             for (int c = 0; c < kTileC; ++c) L[c * kRowPitch + kRowOwn + lane] = u[f][c + 1];
@@ -578,6 +592,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             wave_sync();
 #pragma unroll
             for (int c = 0; c < kTileC; ++c) dx[f][c] = L[c * kRowPitch + kRowOwn + lane];
+            if (xband) layer_flow<kTileC, true>(a, pl, T::px(f), q, nown, xon, xt4, {}, psi, dx[f]);
             if (clos) {                   // row N of the line's last piece
                 const Buf in = buf(a.in[f] + pl.fb);
                 float un = ld(in, (unsigned)pr.e * pl.rs4, pl.vx);
@@ -595,6 +610,11 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
                 x_row<OP>(xp, xt, L16, k16);
                 wave_sync();
                 dxn[f][0] = L[kRowOwn + lane];
+                if (xband) {
+                    float p1[1];
+                    layer_load<1>(a, pl, T::px(f), pr.e, pr.e, xon, p1);
+                    layer_flow<1, true>(a, pl, T::px(f), pr.e, 1, xon, xt4, {}, p1, dxn[f]);
+                }
             }
         }
         if (f == 0) {                     // what the rows alone need, in flight during the x solves
@@ -640,10 +660,17 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             rows_publish(L + rows_slot<MODE>(f) * kEx, lane, B, W, ps, pe);
             if (OP == TILE_DT) L[rows_slot<MODE>(f) * kEx + 256 + lane] = pt;
         }
+    // the layer: the wave's memory values of the rows
+    const bool rband = LAYER && nown > 0 && (q < a.r.pml_w || min(q + kTileC, pr.e) > a.r.N - a.r.pml_w);   // uniform
+    const bool ron = rband && pl.act;
+    float psr[NF][kTileC];
+    if (rband) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            if (T::ys(f)) layer_load<kTileC>(a, pl, T::py(f), q, pr.e, ron, psr[f]);
+    }
     __syncthreads();
     if (nown > 0) {
-        const bool band = a.pml_mem && (px.s < a.x.pml_w || px.e > a.x.N - a.x.pml_w || pr.s < a.r.pml_w ||
-                                        pr.e > a.r.N - a.r.pml_w);
 #pragma unroll
         for (int f = 0; f < NF; ++f)
             if (T::ys(f)) {
@@ -651,16 +678,21 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
                                                        &a.r.ends[lr], a.r.s3, w == 0, nown, &dyn[f][0]);
                 if (OP == TILE_D1) dyn[f][0] = we;
             }
-        if (band) {
+        if (rband) {
+            float4 t[kTileC], t1[1];
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                if (T::xs(f)) layer_flow<kTileC, true>(a, pl, T::px(f), q, nown, dx[f]);
-                if (T::ys(f)) layer_flow<kTileC, false>(a, pl, T::py(f), q, nown, dy[f]);
-                if (clos) {
-                    if (T::xs(f)) layer_flow<1, true>(a, pl, T::px(f), pr.e, 1, dxn[f]);
-                    if (T::ys(f)) layer_flow<1, false>(a, pl, T::py(f), pr.e, 1, dyn[f]);
+            for (int c = 0; c < kTileC; ++c) t[c] = a.pr[min(q + c, a.r.N)];
+            t1[0] = a.pr[pr.e];
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                if (T::ys(f)) {
+                    layer_flow<kTileC, false>(a, pl, T::py(f), q, nown, ron, {}, t, psr[f], dy[f]);
+                    if (clos) {
+                        float p1[1];
+                        layer_load<1>(a, pl, T::py(f), pr.e, pr.e, ron, p1);
+                        layer_flow<1, false>(a, pl, T::py(f), pr.e, 1, ron, {}, t1, p1, dyn[f]);
+                    }
                 }
-            }
         }
         float e[Sums<MODE>::N][kTileC], en[Sums<MODE>::N][1];
         make_sums<MODE, kTileC>(dx, dy, e);
@@ -691,14 +723,14 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
 
 // ---- z derivatives of an elastic stage ------------------------------------------------
 // One workgroup per (field, shot, 64 flattened columns of an x-y plane, piece of z); the
-// transposes of the adjoint likewise.  The pieces of kZGroup neighbouring column groups follow each other: the rows that a piece
-// takes from its neighbours are in the XCD's L2 then, and the groups' rows still make runs
-// of 8 KiB.  Measured, groups of a whole plane -> of 32: 513^3 818 -> 770 us (4.2 TB/s),
-// 184 x 142 x 211 with layers 59 -> 56, 257^3 x 2 and 65^3 the same; 4, 8 and 16 groups lie
-// between on 257^3 (206, 206, 204 us; 32: 200).
+// transposes of the adjoint likewise.  The pieces of kZGroup neighbouring column groups
+// follow each other: the rows that a piece takes from its neighbours are in the XCD's L2
+// then, and the groups' rows still make runs of 8 KiB.  Measured, groups of a whole plane ->
+// of 32: 513^3 818 -> 770 us (4.2 TB/s), 184 x 142 x 211 with layers 59 -> 56, 257^3 x 2 and
+// 65^3 the same; 4, 8 and 16 groups lie between on 257^3 (206, 206, 204 us; 32: 200).
 constexpr int kZGroup = 32;
 
-template <int OP>
+template <int OP, bool LAYER>
 __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int ncg, int nreal)
 {
     constexpr int kEx = kPublish<OP>;
@@ -716,7 +748,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     const int f = fs / a.S, shot = fs - f * a.S;
     const float *in = (f == 0 ? a.in[0] : (f == 1 ? a.in[1] : a.in[2])) + shot * a.shot_stride;
     float *out = (f == 0 ? a.out[0] : (f == 1 ? a.out[1] : a.out[2])) + shot * a.shot_stride;
-    float *mem = f == 0 ? a.pml_mem[0] : (f == 1 ? a.pml_mem[1] : a.pml_mem[2]);
+    float *mem = !LAYER ? nullptr : f == 0 ? a.pml_mem[0] : (f == 1 ? a.pml_mem[1] : a.pml_mem[2]);
     const Piece p = piece_of(a.r, lr);
     const bool lastr = p.e == a.r.N;
     const unsigned rs4 = 4u * (unsigned)a.plane;
@@ -764,6 +796,15 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     }
     rows_publish(ex + w * kEx, lane, B, W, ps, pe);
     if (OP == TILE_DT) ex[w * kEx + 256 + lane] = pl;
+    // the layer's memory values of the wave's rows, requested before the barrier
+    const int pw = a.r.pml_w;
+    const bool band = LAYER && nown > 0 && (q < pw || min(q + kTileC, p.e) > a.r.N - pw);   // uniform
+    const Buf m = buf(band ? mem + shot * a.shot_stride : in);
+    float psi[kTileC];
+    if (band) {
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) psi[c] = ld(m, (unsigned)min(q + c, p.e) * rs4, vx);
+    }
     __syncthreads();
     if (nown == 0) return;
     float dn = 0.f;
@@ -771,20 +812,16 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     if (OP == TILE_DT) we = dn;
     if (!act) return;
     const Buf bout = buf(out);
-    if (OP == TILE_D1 && mem) {
-        const Buf m = buf(mem + shot * a.shot_stride);
-        const int N = a.r.N, pw = a.r.pml_w;
-        float psi[kTileC];
+    if (band) {
+        const int N = a.r.N;
+        float4 t[kTileC];
 #pragma unroll
-        for (int c = 0; c < kTileC; ++c) {
-            psi[c] = 0.f;
-            if (c < nown && (q + c < pw || q + c > N - pw)) psi[c] = ld(m, (unsigned)(q + c) * rs4, vx);
-        }
+        for (int c = 0; c < kTileC; ++c) t[c] = a.pr[min(q + c, N)];
 #pragma unroll
         for (int c = 0; c < kTileC; ++c)
             if (c < nown && (q + c < pw || q + c > N - pw)) {
                 float psi1;
-                y[c] = pml_flow(a.pr[q + c], y[c], psi[c], &psi1);
+                y[c] = pml_flow(t[c], y[c], psi[c], &psi1);
                 if (a.pml_store) st(m, (unsigned)(q + c) * rs4, vx, psi1);
             }
         if (clos && pw > 0) {
@@ -809,16 +846,26 @@ hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st)
     const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
     const int threads = 64 * a.nw, nr = (int)nreal;
     auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, threads, 0, st, a, nr); };
-    const bool keep = a.keep != nullptr;
+    const bool keep = a.keep != nullptr, layer = a.pml_mem != nullptr;
+    if (mode >= TILE_EL_VEL_T && (keep || layer)) return hipErrorInvalidValue;
     switch (mode) {
-    case TILE_EL_STRESS: keep ? go(k_tile<TILE_EL_STRESS, true>) : go(k_tile<TILE_EL_STRESS, false>); break;
-    case TILE_EL_VEL: keep ? go(k_tile<TILE_EL_VEL, true>) : go(k_tile<TILE_EL_VEL, false>); break;
-    case TILE_AC_STRESS: keep ? go(k_tile<TILE_AC_STRESS, true>) : go(k_tile<TILE_AC_STRESS, false>); break;
-    case TILE_AC_VEL: go(k_tile<TILE_AC_VEL, false>); break;
-    case TILE_EL_VEL_T: go(k_tile<TILE_EL_VEL_T, false>); break;
-    case TILE_EL_STRESS_T: go(k_tile<TILE_EL_STRESS_T, false>); break;
-    case TILE_AC_VEL_T: go(k_tile<TILE_AC_VEL_T, false>); break;
-    case TILE_AC_STRESS_T: go(k_tile<TILE_AC_STRESS_T, false>); break;
+    case TILE_EL_STRESS:
+        if (layer) keep ? go(k_tile<TILE_EL_STRESS, true, true>) : go(k_tile<TILE_EL_STRESS, false, true>);
+        else keep ? go(k_tile<TILE_EL_STRESS, true, false>) : go(k_tile<TILE_EL_STRESS, false, false>);
+        break;
+    case TILE_EL_VEL:
+        if (layer) keep ? go(k_tile<TILE_EL_VEL, true, true>) : go(k_tile<TILE_EL_VEL, false, true>);
+        else keep ? go(k_tile<TILE_EL_VEL, true, false>) : go(k_tile<TILE_EL_VEL, false, false>);
+        break;
+    case TILE_AC_STRESS:
+        if (layer) keep ? go(k_tile<TILE_AC_STRESS, true, true>) : go(k_tile<TILE_AC_STRESS, false, true>);
+        else keep ? go(k_tile<TILE_AC_STRESS, true, false>) : go(k_tile<TILE_AC_STRESS, false, false>);
+        break;
+    case TILE_AC_VEL: layer ? go(k_tile<TILE_AC_VEL, false, true>) : go(k_tile<TILE_AC_VEL, false, false>); break;
+    case TILE_EL_VEL_T: go(k_tile<TILE_EL_VEL_T, false, false>); break;
+    case TILE_EL_STRESS_T: go(k_tile<TILE_EL_STRESS_T, false, false>); break;
+    case TILE_AC_VEL_T: go(k_tile<TILE_AC_VEL_T, false, false>); break;
+    case TILE_AC_STRESS_T: go(k_tile<TILE_AC_STRESS_T, false, false>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -831,8 +878,10 @@ hipError_t launch_tile_z(int op, const TileZArgs &a, hipStream_t st)
     const int64_t nreal = (int64_t)a.nf * a.S * ncg * a.r.nsub;
     if (nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
-    if (op == TILE_D1) hipLaunchKernelGGL(k_tile_z<TILE_D1>, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal);
-    else if (op == TILE_DT) hipLaunchKernelGGL(k_tile_z<TILE_DT>, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal);
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
+    const bool layer = a.pml_mem[0] != nullptr;
+    if (op == TILE_D1) layer ? go(k_tile_z<TILE_D1, true>) : go(k_tile_z<TILE_D1, false>);
+    else if (op == TILE_DT && !layer) go(k_tile_z<TILE_DT, false>);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
