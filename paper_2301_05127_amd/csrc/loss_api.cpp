@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -141,7 +142,7 @@ struct loss_sim {
     bool tile_built = false;
     TileAxis tax[3]{};
     TileAxis top[3][3]{};          // the same for each operator (TileOp) and axis; nsub 0: not applicable
-    int tile_nw[3] = {0, 0, 0};    // waves a workgroup needs along the rows of y, z
+    TileAxis tdt[3]{};             // transposed slopes of the tile passes
     std::vector<int> tile_sb[3];   // piece ends
     int64_t *d_step2 = nullptr;    // the step counter between the two kernels of an acoustic tile step
     // receivers ordered by the tile that updates their node
@@ -331,7 +332,7 @@ loss_status adj_deriv(loss_sim *s, int axis, const float *in, const float *in_co
         x.alpha = alpha;
         x.accumulate = epi == EPI_AXPY;
         x.t = s->top[TILE_DT][axis];
-        x.nw = s->tile_nw[axis];
+        x.nw = x.t.nw;
         x.s1 = s->shot_stride;
         if (axis == 1) {
             x.n1 = s->nz;
@@ -443,9 +444,9 @@ TileArgs tile_args(const loss_sim *s)
     t.rstride = ra == 1 ? s->pitch : s->plane;
     t.ostride = ra == 1 ? s->plane : 0;
     t.shot_stride = s->shot_stride;
-    t.nw = s->tile_nw[ra];
     t.x = s->tax[0];
     t.r = s->tax[ra];
+    t.nw = t.r.nw;
     t.x.pml_w = s->axd[0].pml_w;
     t.r.pml_w = s->axd[ra].pml_w;
     t.fields = s->d_fields;
@@ -512,8 +513,8 @@ loss_status tile_z3(loss_sim *s, int kc, const float *const *in, int var0, float
     z.pitch = s->pitch;
     z.plane = s->plane;
     z.shot_stride = s->shot_stride;
-    z.nw = s->tile_nw[2];
     z.r = s->tax[2];
+    z.nw = z.r.nw;
     z.r.pml_w = s->axd[2].pml_w;
     for (int i = 0; i < 3; ++i) {
         z.in[i] = in[i];
@@ -1476,64 +1477,98 @@ loss_status upload_axis(loss_sim *s, int axis)
 loss_status upload_tiles(loss_sim *s)
 {
     if (s->shot_stride >= (int64_t(1) << 30)) return LOSS_OK;   // 32-bit byte offsets within a shot's field
+    // each operator and axis, with pieces between junctions and, where they may pay, across them
+    TileHost built[2][3][3];
+    const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
+    const int64_t planes = (int64_t)s->S * (ra == 1 ? s->nz : 1);
+    int64_t tiles[2] = {0, 0};
+    for (int k = 0; k < 2; ++k) {
+        for (int axis = 0; axis < 3; ++axis) {
+            if (axis == 1 && s->d.ndim == 2) continue;
+            if (k == 1 && tiles[0] <= 2500 && 2 * s->axh[axis].M > kTileM) continue;
+            for (int op : {TILE_D1, TILE_D2, TILE_DT}) {
+                TileHost h;
+                const std::string err = build_tile(s->axh[axis], axis == 0, op, k != 0, h);
+                if (err.empty()) built[k][op][axis] = std::move(h);   // else nsub stays 0
+                else if (k == 0 && op != TILE_DT) return LOSS_OK;
+            }
+        }
+        tiles[k] = planes * built[k][TILE_D1][0].nsub * built[k][TILE_D1][ra].nsub;
+    }
+    // Pieces across junctions hold more nodes, at a tap sum per junction inside.  Tile kernels:
+    // they pay when there are tiles enough and clearly fewer of them.  Measured (us per step,
+    // pieces between junctions / across): elastic 129^3, patches of 16 (8 k tiles) 248 / 148,
+    // of 24 (4.6 k) 170 / 158, of 32 (2 k) 124 / 140; 257^3, patches of 16 2072 / 906, of 48
+    // (9 k) 968 / 898; acoustic 8 x 1025^2, patches of 16 388 / 105, of 32 130 / 100, of 48
+    // (3.9 k) 104 / 102; 2049^2, patches of 48 (1.8 k) 59 / 65; 129^2, patches of 16 17 / 21;
+    // 16 x 1101 x 706 with layers, patches of 128 (1.1 times as many) 147 / 166.
+    const bool across = tiles[1] > 0 && tiles[0] > 2500 && 2 * tiles[0] >= 3 * tiles[1];
     std::vector<char> blob;   // every table, uploaded at once
-    size_t off[3][3][6] = {};
+    std::vector<std::pair<const TileHost *, size_t>> placed;
+    std::vector<std::pair<TileAxis *, size_t>> users;
+    auto put = [&](const auto &v) {   // offset of a table in the blob, 16-byte aligned
+        const size_t o = (blob.size() + 15) / 16 * 16;
+        blob.resize(o + v.size() * sizeof(v[0]));
+        std::memcpy(blob.data() + o, v.data(), v.size() * sizeof(v[0]));
+        return o;
+    };
+    std::vector<std::array<size_t, 7>> offs;
+    auto use = [&](TileAxis &t, const TileHost &h, int axis) {
+        t = TileAxis();
+        if (h.nsub == 0) return;
+        t.N = s->axh[axis].N;
+        t.nsub = h.nsub;
+        t.periodic = s->d.end_mode == LOSS_END_PERIODIC;
+        t.s3 = (float)(3.0 / s->d.h[axis]);
+        t.nw = (h.max_m + kTileC - 1) / kTileC;
+        for (size_t i = 3; i < h.piece.size(); i += 4) t.inside |= (h.piece[i] & 255) != 0;
+        size_t k = 0;
+        while (k < placed.size() && placed[k].first != &h) ++k;
+        if (k == placed.size()) {
+            placed.push_back({&h, offs.size()});
+            offs.push_back({put(h.piece), put(h.halo_node), put(h.ends), put(h.halo_c), axis > 0 ? put(h.chunk) : 0,
+                            axis > 0 ? 0 : put(h.lanes), axis > 0 ? 0 : put(h.lanes_in)});
+        }
+        users.push_back({&t, placed[k].second});
+    };
     for (int axis = 0; axis < 3; ++axis) {
         if (axis == 1 && s->d.ndim == 2) continue;
         for (int op : {TILE_D1, TILE_D2, TILE_DT}) {
-            TileHost h;
-            if (!build_tile(s->axh[axis], axis == 0, op, h).empty()) {
-                if (op != TILE_DT) return LOSS_OK;
-                continue;
-            }
-            auto put = [&](const auto &v) {   // offset of a table in the blob, 16-byte aligned
-                const size_t o = (blob.size() + 15) / 16 * 16;
-                blob.resize(o + v.size() * sizeof(v[0]));
-                std::memcpy(blob.data() + o, v.data(), v.size() * sizeof(v[0]));
-                return o;
-            };
-            size_t *o = off[op][axis];
-            o[0] = put(h.piece);
-            o[1] = put(h.halo_node);
-            o[2] = put(h.ends);
-            o[3] = put(h.halo_c);
-            if (axis > 0) o[4] = put(h.chunk);
-            else o[5] = put(h.lanes);
-            TileAxis &t = s->top[op][axis];
-            t.N = s->axh[axis].N;
-            t.nsub = h.nsub;
-            t.periodic = s->d.end_mode == LOSS_END_PERIODIC;
-            t.s3 = (float)(3.0 / s->d.h[axis]);
-            s->tile_nw[axis] = (h.max_m + kTileC - 1) / kTileC;
-            s->tile_sb[axis] = h.sb;
+            // one axis alone: columns fill the chip, and only short pieces (waves per workgroup) pay
+            const TileHost &b0 = built[0][op][axis], &b1 = built[1][op][axis];
+            const bool one = b1.nsub > 0 && (b0.nsub == 0 || b0.nsub >= 3 * b1.nsub);
+            use(s->top[op][axis], one ? b1 : b0, axis);
+            if (op == TILE_D2) continue;
+            const bool tile = axis == 0 || axis == ra;
+            const TileHost &h = (tile ? across && b1.nsub > 0 : one) ? b1 : b0;
+            use(op == TILE_D1 ? s->tax[axis] : s->tdt[axis], h, axis);
+            if (op == TILE_D1) s->tile_sb[axis] = h.sb;
         }
     }
     char *d = nullptr;
     loss_status r = s->alloc(&d, blob.size());
     if (r) return r;
     HIPCHK(hipMemcpy(d, blob.data(), blob.size(), hipMemcpyHostToDevice));
-    for (int axis = 0; axis < 3; ++axis)
-        for (int op = 0; op < 3; ++op) {
-            TileAxis &t = s->top[op][axis];
-            const size_t *o = off[op][axis];
-            t.piece = (const int4 *)(d + o[0]);
-            t.halo_node = (const int *)(d + o[1]);
-            t.ends = (const TileEnds *)(d + o[2]);
-            t.halo_c = (const float2 *)(d + o[3]);
-            t.chunk = (const TileChunk *)(d + o[4]);
-            t.lanes = (const float4 *)(d + o[5]);
-        }
-    for (int axis = 0; axis < 3; ++axis) s->tax[axis] = s->top[TILE_D1][axis];
+    for (const auto &u : users) {
+        TileAxis &t = *u.first;
+        const auto &o = offs[u.second];
+        t.piece = (const int4 *)(d + o[0]);
+        t.halo_node = (const int *)(d + o[1]);
+        t.ends = (const TileEnds *)(d + o[2]);
+        t.halo_c = (const float4 *)(d + o[3]);
+        t.chunk = (const TileChunk *)(d + o[4]);
+        t.lanes = (const float4 *)(d + o[5]);
+        t.lanes_in = (const float4 *)(d + o[6]);
+    }
     s->tile_built = true;
-    // A tile costs its latency however few nodes it holds.  Measured (us per step, tile
-    // against line passes at their default shapes): acoustic 1025^2 x 8 shots, patches of 16
-    // (256 nodes a tile, 33 k tiles) 397 / 166, of 24 200 / 170, of 32 140 / 142, of 64
-    // 106 / 120; elastic 257^3, patches of 16 (70 k tiles) 2134 / 2082, of 32 976 / 1620;
-    // 129^3, patches of 8 989 / 493, of 16 (9 k tiles) 255 / 410; 129^2, patches of 16 18 / 36.
-    const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
-    const int64_t tiles = (int64_t)s->S * (ra == 1 ? s->nz : 1) * s->tax[0].nsub * s->tax[ra].nsub;
-    const int64_t per_tile = (int64_t)s->nx * (ra == 1 ? s->ny : s->nz) / ((int64_t)s->tax[0].nsub * s->tax[ra].nsub);
-    s->tile_pays = tiles < 12000 || per_tile >= 600;
+    // A tile costs its latency however few nodes it holds: patches below kTileInGap, between
+    // whose junctions the pieces stay.  Measured (us per step, tile against line passes at
+    // their default shapes): elastic 129^3, tiles of 8 x 8 972 / 495, of 16 x 16 248 / 409;
+    // acoustic 1025^2 x 8 shots, tiles of 16 x 16 (256 nodes, 33 k tiles) 388 / 166, of 24 x 24
+    // 195 / 172, of 32 x 32 131 / 142.
+    const int64_t n = std::max<int64_t>(1, planes * s->tax[0].nsub * s->tax[ra].nsub);
+    const int64_t per_tile = planes * s->nx * (ra == 1 ? s->ny : s->nz) / n;
+    s->tile_pays = n < 12000 || per_tile >= 600;
     return LOSS_OK;
 }
 
@@ -1551,7 +1586,7 @@ loss_status deriv_direct(loss_sim *s, int axis, int order, const float *in, floa
     x.in = in;
     x.out = out;
     x.t = s->top[op][axis];
-    x.nw = s->tile_nw[axis];
+    x.nw = x.t.nw;
     x.n1 = 1;
     x.s1 = s->nodes;
     const int64_t plane = (int64_t)s->nx * s->ny;
@@ -1585,7 +1620,7 @@ bool tile_adjoint_ok(const loss_sim *s)
 {
     if (!tile_ok(s) || s->pml_mem) return false;
     for (int axis = 0; axis < 3; ++axis)
-        if (!(axis == 1 && s->d.ndim == 2) && s->top[TILE_DT][axis].nsub == 0) return false;
+        if (!(axis == 1 && s->d.ndim == 2) && s->tdt[axis].nsub == 0) return false;
     return true;
 }
 
@@ -1594,8 +1629,9 @@ loss_status adj_tile(loss_sim *s, int mode, const float *const *in, int nin, con
                      int nout, float alpha)
 {
     TileArgs t = tile_args(s);
-    t.x = s->top[TILE_DT][0];
-    t.r = s->top[TILE_DT][t.row_axis];
+    t.x = s->tdt[0];
+    t.r = s->tdt[t.row_axis];
+    t.nw = t.r.nw;
     for (int i = 0; i < nin; ++i) t.in[i] = in[i];
     for (int i = 0; i < nout; ++i) t.out[i] = out[i];
     for (int i = 0; i < 3; ++i) t.T[i] = s->tmp[i];
@@ -1615,8 +1651,8 @@ loss_status adj_tile_z3(loss_sim *s, const float *const *in, const float *coef)
     z.pitch = s->pitch;
     z.plane = s->plane;
     z.shot_stride = s->shot_stride;
-    z.nw = s->tile_nw[2];
-    z.r = s->top[TILE_DT][2];
+    z.r = s->tdt[2];
+    z.nw = z.r.nw;
     z.coef = coef;
     for (int i = 0; i < 3; ++i) {
         z.in[i] = in[i];

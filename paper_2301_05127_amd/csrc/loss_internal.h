@@ -69,15 +69,18 @@ enum TileOp : int { TILE_D1 = 0, TILE_D2 = 1, TILE_DT = 2 };   // slopes, moment
 struct TileHost {
     int nsub = 0, max_m = 0;
     std::vector<int> sb;                // [nsub+1] piece ends
-    std::vector<int> piece;             // [nsub][4] {s, e, taps of s, taps of e}
+    std::vector<int> piece;             // [nsub][4] see make_piece
     std::vector<float> ends;            // [nsub][8] closing row, see TileEnds
     std::vector<int> halo_node;         // [nsub][kTapW] grid node of each halo entry
-    std::vector<float> halo_c;          // [nsub][kTapW][2] its taps of the start and the closing right-hand side
+    std::vector<float> halo_c;          // [nsub][kTapW][4] its taps of the start, the end, the first and the
+                                        // last junction inside (one alone: the first)
     std::vector<float> chunk;           // [nsub][kTileWaves][kChunkF] rows form, see TileChunk
-    std::vector<float> lanes;           // [nsub][16][kLaneF] x form: see x_row (tile.hip)
+    std::vector<float> lanes;           // [nsub][16][kLaneF] x form: see x_row (tile_device.h)
+    std::vector<float> lanes_in;        // [nsub][16][kLaneInF] the same, junctions inside
 };
-// `op` of TileOp; an error where the tile passes do not apply.
-std::string build_tile(const AxisHost &ax, bool along_x, int op, TileHost &t);
+// `op` of TileOp, pieces across junctions or between them; an error where the tile passes do
+// not apply.
+std::string build_tile(const AxisHost &ax, bool along_x, int op, bool across, TileHost &t);
 
 // A node whose column of G^T is not the plain interior form: its stencil column and
 // the transposed PMBC rows reaching it (gather of the adjoint x pass).
@@ -211,28 +214,33 @@ enum TileMode : int {
 };
 
 // One chunk (kTileC rows) of a piece, rows form: the rows' factors and taps, and the two
-// carries as sums over the chunks' B and W, the value at the start (ph) and the closing
-// right-hand side (E); transposed: the solution at the row before the chunk likewise (p*),
-// and what each row takes from the junction values y_s, y_e
+// carries as sums over the chunks' B and W and the junctions' values around the chunk: p_l at or
+// before its first row, p_r after its last one, p_m inside (l, m, r: 0 the start, 1 the closing
+// right-hand side, 2 .. the junctions inside); transposed: the solution at the row before the
+// chunk likewise (p*), and what each row takes from the values of the piece's junctions
 struct TileChunk {
     float P[8];                 // products of nf from the chunk's first row on
     float fB[8];                // carry into the elimination
     float zB[8], zW[8];         // carry into the back substitution
-    float fph, zph, zE, pE;
+    float fph, zph, zE, pE;     // weights of p_l, of p_m (without one: p_l), of p_r
     float nf[8], sc[8], fi[8], g[8];
     float ts[8], te[8];         // taps of the start and the closing right-hand side
     float any_ts, any_te, any_cs, any_ce;
     float cs[8], ce[8];
     float pB[8], pW[8];
+    int l, m, r, any_in;        // m: -1 none; any_in: a row of the chunk is among the taps of a junction inside
+    float Q[8];                 // response of the rows' elimination to p_m
+    float tj[3][8], cj[3][8];   // taps of the junctions inside; transposed: weights of their values
 };
 constexpr int kChunkF = sizeof(TileChunk) / 4;
-constexpr int kLaneF = 52;
+constexpr int kLaneF = 52, kLaneInF = 44;
 // Closing row of a piece: w_e = iE E - imE y_{e-1}.  sE: weight of u_e - u_{e-1} in E
 // (slopes: natural end; moments: Hermite row); transposed: 1 at a natural end.
 // cs, ce: moments: sums of the two tap rows; transposed: the transposed taps of y_s and y_e at
-// the closing node.  m1: transposed: weight of y_s in place of y_{s-1} (-1 at a natural end).
+// the closing node; cj: and those of the last junction inside.  m1: transposed: weight of y_s in
+// place of y_{s-1} (-1 at a natural end).
 struct TileEnds {
-    float iE, imE, sE, pad0, cs, ce, m1, pad1;
+    float iE, imE, sE, cj, cs, ce, m1, pad1;
 };
 
 struct TileAxis {
@@ -240,10 +248,12 @@ struct TileAxis {
     float s3;              // 3/h
     const int4 *piece;
     const TileEnds *ends;
-    const float4 *lanes;
+    const float4 *lanes, *lanes_in;
     const TileChunk *chunk;
     const int *halo_node;
-    const float2 *halo_c;
+    const float4 *halo_c;
+    int nw;                // waves per workgroup (rows form)
+    int inside;            // some piece holds junctions inside
 };
 
 struct TileArgs {

@@ -9,7 +9,9 @@
 //   elastic: 264 (18 line kernels) -> 192 (two z stores of three fields, two tile kernels).
 //
 // A tile is a piece of at most 64 intervals of x times a piece of at most 64 intervals of
-// the rows (patches longer than that are cut, TileHost).  A wave owns 8 consecutive rows,
+// the rows: patches longer than that are cut, and pieces of short patches reach across up to
+// three junctions, whose slopes are tap sums like those of the ends and enter at their rows
+// (8 x 1025^2 acoustic, patches of 16: 388 us per step with tiles of 16 x 16 nodes -> 105).  A wave owns 8 consecutive rows,
 // lane = column, so every row index, factor and carry coefficient along the rows is
 // wave-uniform (scalar loads, SGPR operands) and every global access is one 256-byte row.
 //
@@ -121,11 +123,9 @@ constexpr int rows_slot(int f)
     return n;
 }
 
-// floats a wave publishes per field of the rows, and its LDS: its rows of x, then those
-template <int OP>
-constexpr int kPublish = OP == TILE_DT ? 320 : 256;
-template <int MODE>
-constexpr int kModeLds = std::max(kWaveLds, rows_slot<MODE>(Traits<MODE>::NF) * kPublish<Traits<MODE>::OP>);
+// floats of LDS of a wave: its rows of x, then what it publishes of each field
+template <int MODE, bool IN>
+constexpr int kModeLds = std::max(kWaveLds, rows_slot<MODE>(Traits<MODE>::NF) * kPublish<Traits<MODE>::OP, IN>);
 
 // Sum of the source terms of field fid (a component of the outputs) over the R rows from
 // row q on, as the update adds them.
@@ -429,12 +429,13 @@ __device__ __forceinline__ void tile_add(const TileArgs &a, const Place &pl, int
 template <int MODE>
 constexpr int kTileWavesPerSimd = Traits<MODE>::SHAPE == TILE_AC_STRESS || Traits<MODE>::SHAPE == TILE_AC_VEL ? 6 : 4;
 
-template <int MODE, bool KEEP, bool LAYER>
+template <int MODE, bool KEEP, bool LAYER, bool IN>
 __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_tile(TileArgs a, int nreal)
 {
     using T = Traits<MODE>;
-    constexpr int NF = T::NF, OP = T::OP, kLds = kModeLds<MODE>, kEx = kPublish<OP>;
+    constexpr int NF = T::NF, OP = T::OP, kLds = kModeLds<MODE, IN>, kEx = kPublish<OP, IN>;
     __shared__ float4 tab4[16 * (kLaneF / 4)];                // x lanes' table of the piece
+    __shared__ float4 tabi4[IN ? 16 * (kLaneInF / 4) : 1];    // the same, junctions inside
     __shared__ float4 lds4[kTileWaves * kLds / 4];
     float *lds = reinterpret_cast<float *>(lds4);
     // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs; each XCD gets a
@@ -494,7 +495,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
     float u[NF][kTileC + 2], yh[NF][kHaloPre], xh[NF][6];
     const int nhx = halo_count(px), nhr = halo_count(pr);
     const int *hn = a.r.halo_node + (size_t)lr * kTapW;
-    const float2 *hc = a.r.halo_c + (size_t)lr * kTapW;
+    const float4 *hc = a.r.halo_c + (size_t)lr * kTapW;
     // x halo: entries 0 .. 31 of two rows per load, entries 32 .. 40 (wide taps) of four
     const bool wide = nhx > 32;
     const int hi = min(lane & 31, nhx - 1), hj = min(32 + (lane & 15), nhx - 1);
@@ -552,16 +553,14 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
     const float rend = a.r.ends[lr].sE;
     const int k16 = lane & 15;
     const float4 *xt = tab4 + k16 * (kLaneF / 4);
-    XPiece xp;
-    xp.end = a.x.ends[lx];
-    xp.s3 = a.x.s3;
-    xp.m = px.m;
-    xp.hs = px.hs;
-    xp.kc = (px.m - 1) >> 2;
-    xp.last = lastx;
-    xp.wide = max(px.hs, px.he) > 15;
+    const float4 *xti = tabi4 + k16 * (kLaneInF / 4);
+    const XPiece xp = x_piece(a.x, px, lx);
     if ((int)threadIdx.x < kTab) tab4[threadIdx.x] = tab_reg;
     for (int i = threadIdx.x + blockDim.x; i < kTab; i += blockDim.x) tab4[i] = tabg[i];   // fewer than four waves
+    if (IN && px.ni > 0) {
+        constexpr int kTabIn = 16 * (kLaneInF / 4);
+        for (int i = threadIdx.x; i < kTabIn; i += blockDim.x) tabi4[i] = a.x.lanes_in[(size_t)lx * kTabIn + i];
+    }
     __syncthreads();                                          // the lanes' table
 
     // ---- x: the wave's rows through LDS -------------------------------------------------
@@ -588,7 +587,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             }
             wave_sync();
 #pragma unroll
-            for (int it = 0; it < kTileC / 4; ++it) x_row<OP>(xp, xt, L16 + 4 * it * kRowPitch, k16);
+            for (int it = 0; it < kTileC / 4; ++it) x_row<OP, IN>(xp, xt, xti, L16 + 4 * it * kRowPitch, k16);
             wave_sync();
 #pragma unroll
             for (int c = 0; c < kTileC; ++c) dx[f][c] = L[c * kRowPitch + kRowOwn + lane];
@@ -607,7 +606,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
                 L[kRowOwn + lane] = un;
                 L[halo_slot(px, i)] = xn;
                 wave_sync();
-                x_row<OP>(xp, xt, L16, k16);
+                x_row<OP, IN>(xp, xt, xti, L16, k16);
                 wave_sync();
                 dxn[f][0] = L[kRowOwn + lane];
                 if (xband) {
@@ -634,31 +633,27 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
 #pragma unroll
     for (int f = 0; f < NF; ++f)
         if (T::ys(f)) {
-            float B, W, ps = 0.f, pe = 0.f, pt = 0.f;
+            float B, W;
+            Taps tp;
             if (OP == TILE_DT) u[f][0] = u[f][kTileC + 1] = 0.f;
             rows_local<OP>(rt, u[f], dy[f], B, W);
-            taps_own<OP>(rt, u[f], 0.f, 0.f, ps, pe);
-            auto halo = [&](int i, float v) {
-                const float2 c = hc[i];
-                ps = fmaf(c.x, v, ps);
-                pe = fmaf(c.y, v, pe);
-                if (OP == TILE_DT && i < pr.hl) pt = fmaf(c.x, v, pt);
-            };
+            taps_own<OP, IN>(rt, u[f], 0.f, 0.f, tp);
 #pragma unroll
-            for (int h = 0; h < kHaloPre; ++h) halo(w + h * a.nw, yh[f][h]);
+            for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(pr, hc, w + h * a.nw, yh[f][h], 0.f, 0.f, tp);
             for (int i = w + kHaloPre * a.nw; i < nhr; i += a.nw)     // few waves, wide taps
-                halo(i, ld(buf(a.in[f] + pl.fb), (unsigned)hn[i] * pl.rs4, pl.vx) *
-                            (T::coef ? ld(cf, (unsigned)hn[i] * pl.rs4, pl.vx) : 1.f));
+                taps_halo<OP, IN>(pr, hc, i,
+                              ld(buf(a.in[f] + pl.fb), (unsigned)hn[i] * pl.rs4, pl.vx) *
+                                  (T::coef ? ld(cf, (unsigned)hn[i] * pl.rs4, pl.vx) : 1.f),
+                              0.f, 0.f, tp);
             if (OP == TILE_D1 && clos) {
                 // natural end: the closing row's difference (rend is 0 on a junction)
                 float ue = 0.f, ul = 0.f;
 #pragma unroll
                 for (int c = 0; c < kTileC; ++c)
                     if (c == nown - 1) { ul = u[f][c + 1]; ue = u[f][c + 2]; }
-                pe = fmaf(rend, ue - ul, pe);
+                tp.e = fmaf(rend, ue - ul, tp.e);
             }
-            rows_publish(L + rows_slot<MODE>(f) * kEx, lane, B, W, ps, pe);
-            if (OP == TILE_DT) L[rows_slot<MODE>(f) * kEx + 256 + lane] = pt;
+            rows_publish<OP, IN>(pr, L + rows_slot<MODE>(f) * kEx, lane, B, W, tp);
         }
     // the layer: the wave's memory values of the rows
     const bool rband = LAYER && nown > 0 && (q < a.r.pml_w || min(q + kTileC, pr.e) > a.r.N - a.r.pml_w);   // uniform
@@ -674,7 +669,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
 #pragma unroll
         for (int f = 0; f < NF; ++f)
             if (T::ys(f)) {
-                const float we = rows_finish<kLds, OP>(rt, lds + rows_slot<MODE>(f) * kEx, a.nw, lane, dy[f],
+                const float we = rows_finish<kLds, OP, IN>(pr, rt, lds + rows_slot<MODE>(f) * kEx, a.nw, lane, dy[f],
                                                        &a.r.ends[lr], a.r.s3, w == 0, nown, &dyn[f][0]);
                 if (OP == TILE_D1) dyn[f][0] = we;
             }
@@ -730,10 +725,10 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
 // 65^3 the same; 4, 8 and 16 groups lie between on 257^3 (206, 206, 204 us; 32: 200).
 constexpr int kZGroup = 32;
 
-template <int OP, bool LAYER>
+template <int OP, bool LAYER, bool IN>
 __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int ncg, int nreal)
 {
-    constexpr int kEx = kPublish<OP>;
+    constexpr int kEx = kPublish<OP, IN>;
     __shared__ float ex[kTileWaves * kEx];
     const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
     if (a.step_inc && blockIdx.x == 0 && threadIdx.x == 0) *a.step_inc += 1;
@@ -761,7 +756,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     const bool clos = lastr && nown > 0 && q + kTileC >= p.e;
     const int nh = halo_count(p);
     const int *hn = a.r.halo_node + (size_t)lr * kTapW;
-    const float2 *hc = a.r.halo_c + (size_t)lr * kTapW;
+    const float4 *hc = a.r.halo_c + (size_t)lr * kTapW;
     const Buf bin = buf(in);
     const bool has_c = OP == TILE_DT && a.coef != nullptr;    // uniform
     const Buf cf = buf(has_c ? a.coef : in);
@@ -775,27 +770,21 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
 #pragma unroll
     for (int h = 0; h < kHaloPre; ++h) yh[h] = get(hn[w + h * a.nw]);
     const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
-    float B, W, ps = 0.f, pe = 0.f, pl = 0.f;
+    float B, W;
+    Taps tp;
     rows_local<OP>(rt, u, y, B, W);
-    taps_own<OP>(rt, u, 0.f, 0.f, ps, pe);
-    auto halo = [&](int i, float v) {
-        const float2 c = hc[i];
-        ps = fmaf(c.x, v, ps);
-        pe = fmaf(c.y, v, pe);
-        if (OP == TILE_DT && i < p.hl) pl = fmaf(c.x, v, pl);
-    };
+    taps_own<OP, IN>(rt, u, 0.f, 0.f, tp);
 #pragma unroll
-    for (int h = 0; h < kHaloPre; ++h) halo(w + h * a.nw, yh[h]);
-    for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) halo(i, get(hn[i]));
+    for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(p, hc, w + h * a.nw, yh[h], 0.f, 0.f, tp);
+    for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) taps_halo<OP, IN>(p, hc, i, get(hn[i]), 0.f, 0.f, tp);
     if (OP == TILE_D1 && clos) {
         float ue = 0.f, ul = 0.f;
 #pragma unroll
         for (int c = 0; c < kTileC; ++c)
             if (c == nown - 1) { ul = u[c + 1]; ue = u[c + 2]; }
-        pe = fmaf(a.r.ends[lr].sE, ue - ul, pe);
+        tp.e = fmaf(a.r.ends[lr].sE, ue - ul, tp.e);
     }
-    rows_publish(ex + w * kEx, lane, B, W, ps, pe);
-    if (OP == TILE_DT) ex[w * kEx + 256 + lane] = pl;
+    rows_publish<OP, IN>(p, ex + w * kEx, lane, B, W, tp);
     // the layer's memory values of the wave's rows, requested before the barrier
     const int pw = a.r.pml_w;
     const bool band = LAYER && nown > 0 && (q < pw || min(q + kTileC, p.e) > a.r.N - pw);   // uniform
@@ -808,7 +797,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     __syncthreads();
     if (nown == 0) return;
     float dn = 0.f;
-    float we = rows_finish<kEx, OP>(rt, ex, a.nw, lane, y, &a.r.ends[lr], a.r.s3, w == 0, nown, &dn);
+    float we = rows_finish<kEx, OP, IN>(p, rt, ex, a.nw, lane, y, &a.r.ends[lr], a.r.s3, w == 0, nown, &dn);
     if (OP == TILE_DT) we = dn;
     if (!act) return;
     const Buf bout = buf(out);
@@ -848,26 +837,32 @@ hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st)
     auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, threads, 0, st, a, nr); };
     const bool keep = a.keep != nullptr, layer = a.pml_mem != nullptr;
     if (mode >= TILE_EL_VEL_T && (keep || layer)) return hipErrorInvalidValue;
-    switch (mode) {
-    case TILE_EL_STRESS:
-        if (layer) keep ? go(k_tile<TILE_EL_STRESS, true, true>) : go(k_tile<TILE_EL_STRESS, false, true>);
-        else keep ? go(k_tile<TILE_EL_STRESS, true, false>) : go(k_tile<TILE_EL_STRESS, false, false>);
-        break;
-    case TILE_EL_VEL:
-        if (layer) keep ? go(k_tile<TILE_EL_VEL, true, true>) : go(k_tile<TILE_EL_VEL, false, true>);
-        else keep ? go(k_tile<TILE_EL_VEL, true, false>) : go(k_tile<TILE_EL_VEL, false, false>);
-        break;
-    case TILE_AC_STRESS:
-        if (layer) keep ? go(k_tile<TILE_AC_STRESS, true, true>) : go(k_tile<TILE_AC_STRESS, false, true>);
-        else keep ? go(k_tile<TILE_AC_STRESS, true, false>) : go(k_tile<TILE_AC_STRESS, false, false>);
-        break;
-    case TILE_AC_VEL: layer ? go(k_tile<TILE_AC_VEL, false, true>) : go(k_tile<TILE_AC_VEL, false, false>); break;
-    case TILE_EL_VEL_T: go(k_tile<TILE_EL_VEL_T, false, false>); break;
-    case TILE_EL_STRESS_T: go(k_tile<TILE_EL_STRESS_T, false, false>); break;
-    case TILE_AC_VEL_T: go(k_tile<TILE_AC_VEL_T, false, false>); break;
-    case TILE_AC_STRESS_T: go(k_tile<TILE_AC_STRESS_T, false, false>); break;
-    default: return hipErrorInvalidValue;
-    }
+    auto pick = [&](auto in) {
+        constexpr bool IN = decltype(in)::value;
+        switch (mode) {
+        case TILE_EL_STRESS:
+            if (layer) keep ? go(k_tile<TILE_EL_STRESS, true, true, IN>) : go(k_tile<TILE_EL_STRESS, false, true, IN>);
+            else keep ? go(k_tile<TILE_EL_STRESS, true, false, IN>) : go(k_tile<TILE_EL_STRESS, false, false, IN>);
+            return true;
+        case TILE_EL_VEL:
+            if (layer) keep ? go(k_tile<TILE_EL_VEL, true, true, IN>) : go(k_tile<TILE_EL_VEL, false, true, IN>);
+            else keep ? go(k_tile<TILE_EL_VEL, true, false, IN>) : go(k_tile<TILE_EL_VEL, false, false, IN>);
+            return true;
+        case TILE_AC_STRESS:
+            if (layer) keep ? go(k_tile<TILE_AC_STRESS, true, true, IN>) : go(k_tile<TILE_AC_STRESS, false, true, IN>);
+            else keep ? go(k_tile<TILE_AC_STRESS, true, false, IN>) : go(k_tile<TILE_AC_STRESS, false, false, IN>);
+            return true;
+        case TILE_AC_VEL:
+            layer ? go(k_tile<TILE_AC_VEL, false, true, IN>) : go(k_tile<TILE_AC_VEL, false, false, IN>);
+            return true;
+        case TILE_EL_VEL_T: go(k_tile<TILE_EL_VEL_T, false, false, IN>); return true;
+        case TILE_EL_STRESS_T: go(k_tile<TILE_EL_STRESS_T, false, false, IN>); return true;
+        case TILE_AC_VEL_T: go(k_tile<TILE_AC_VEL_T, false, false, IN>); return true;
+        case TILE_AC_STRESS_T: go(k_tile<TILE_AC_STRESS_T, false, false, IN>); return true;
+        }
+        return false;
+    };
+    if (!(a.x.inside || a.r.inside ? pick(std::true_type{}) : pick(std::false_type{}))) return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -880,9 +875,13 @@ hipError_t launch_tile_z(int op, const TileZArgs &a, hipStream_t st)
     const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
     auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
     const bool layer = a.pml_mem[0] != nullptr;
-    if (op == TILE_D1) layer ? go(k_tile_z<TILE_D1, true>) : go(k_tile_z<TILE_D1, false>);
-    else if (op == TILE_DT && !layer) go(k_tile_z<TILE_DT, false>);
-    else return hipErrorInvalidValue;
+    if (!(op == TILE_D1 || (op == TILE_DT && !layer))) return hipErrorInvalidValue;
+    if (a.r.inside)
+        op == TILE_DT ? go(k_tile_z<TILE_DT, false, true>)
+                      : (layer ? go(k_tile_z<TILE_D1, true, true>) : go(k_tile_z<TILE_D1, false, true>));
+    else
+        op == TILE_DT ? go(k_tile_z<TILE_DT, false, false>)
+                      : (layer ? go(k_tile_z<TILE_D1, true, false>) : go(k_tile_z<TILE_D1, false, false>));
     return hipGetLastError();
 }
 

@@ -18,10 +18,10 @@ namespace loss {
 
 namespace {
 
-template <int OP>
+template <int OP, bool IN>
 __global__ void __launch_bounds__(kTileWaves * 64, 8) k_axis_rows(AxisArgs a, int ncg, int nreal)
 {
-    constexpr int kEx = OP == TILE_DT ? 320 : 256;            // floats a wave publishes
+    constexpr int kEx = kPublish<OP, IN>;
     __shared__ float ex[kTileWaves * kEx];
     // XCD-aware order: each XCD takes a contiguous range, columns fastest
     const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_axis_rows(AxisArgs a, in
     const bool clos = nown > 0 && q + kTileC >= p.e;          // holds the row before the closing one
     const int nh = halo_count(p);
     const int *hn = a.t.halo_node + (size_t)lr * kTapW;
-    const float2 *hc = a.t.halo_c + (size_t)lr * kTapW;
+    const float4 *hc = a.t.halo_c + (size_t)lr * kTapW;
     const Buf in = buf(a.in + fb), out = buf(a.out + fb);
     const bool has_c = OP == TILE_DT && a.coef != nullptr;    // uniform
     const Buf cf = buf(has_c ? a.coef + o0 * a.m0 : a.in);
@@ -72,35 +72,29 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_axis_rows(AxisArgs a, in
     }
     const TileChunk &rt = a.t.chunk[(size_t)lr * kTileWaves + w];
     const TileEnds end = a.t.ends[lr];
-    float B, W, ps = 0.f, pe = 0.f, pl = 0.f;
+    float B, W;
+    Taps tp;
     rows_local<OP>(rt, u, y, B, W);
-    taps_own<OP>(rt, u, us, ue, ps, pe);
-    auto halo = [&](int i, float v) {
-        const float2 c = hc[i];
-        ps = fmaf(c.x, v - us, ps);
-        pe = fmaf(c.y, v - ue, pe);
-        if (OP == TILE_DT && i < p.hl) pl = fmaf(c.x, v, pl);
-    };
+    taps_own<OP, IN>(rt, u, us, ue, tp);
 #pragma unroll
-    for (int h = 0; h < kHaloPre; ++h) halo(w + h * a.nw, yh[h]);
-    for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) halo(i, get(hn[i]));
+    for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(p, hc, w + h * a.nw, yh[h], us, ue, tp);
+    for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) taps_halo<OP, IN>(p, hc, i, get(hn[i]), us, ue, tp);
     if (OP == TILE_D2 && w == 0) {
-        ps = fmaf(end.cs, us, ps);
-        pe = fmaf(end.ce, ue, pe);
+        tp.s = fmaf(end.cs, us, tp.s);
+        tp.e = fmaf(end.ce, ue, tp.e);
     }
     if (OP != TILE_DT && clos) {
         float u1 = 0.f, u0 = 0.f;
 #pragma unroll
         for (int c = 0; c < kTileC; ++c)
             if (c == nown - 1) { u0 = u[c + 1]; u1 = u[c + 2]; }
-        pe = fmaf(end.sE, u1 - u0, pe);
+        tp.e = fmaf(end.sE, u1 - u0, tp.e);
     }
-    rows_publish(ex + w * kEx, lane, B, W, ps, pe);
-    if (OP == TILE_DT) ex[w * kEx + 256 + lane] = pl;
+    rows_publish<OP, IN>(p, ex + w * kEx, lane, B, W, tp);
     __syncthreads();
     if (nown == 0) return;
     float dn = 0.f;
-    const float we = rows_finish<kEx, OP>(rt, ex, a.nw, lane, y, &end, a.t.s3, w == 0, nown, &dn);
+    const float we = rows_finish<kEx, OP, IN>(p, rt, ex, a.nw, lane, y, &end, a.t.s3, w == 0, nown, &dn);
     if (OP != TILE_DT) dn = we;
     if (!act) return;
 #pragma unroll
@@ -119,10 +113,10 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_axis_rows(AxisArgs a, in
 // four waves of a workgroup the same piece of consecutive lines.
 constexpr int kXWaves = 4;
 
-template <int OP>
+template <int OP, bool IN>
 __global__ void __launch_bounds__(kXWaves * 64) k_axis_x(AxisArgs a, int ngrp, int nreal)
 {
-    __shared__ float4 tab4[16 * (kLaneF / 4)];
+    __shared__ float4 tab4[16 * (kLaneF / 4)], tabi4[IN ? 16 * (kLaneInF / 4) : 1];
     __shared__ float4 lds4[kXWaves * kWaveLds / 4];
     const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
     if (lin >= nreal) return;
@@ -154,14 +148,11 @@ __global__ void __launch_bounds__(kXWaves * 64) k_axis_x(AxisArgs a, int ngrp, i
     }
     const float4 *tg = a.t.lanes + (size_t)lx * 16 * (kLaneF / 4);
     for (int i = threadIdx.x; i < 16 * (kLaneF / 4); i += kXWaves * 64) tab4[i] = tg[i];
-    XPiece xp;
-    xp.end = a.t.ends[lx];
-    xp.s3 = a.t.s3;
-    xp.m = p.m;
-    xp.hs = p.hs;
-    xp.kc = (p.m - 1) >> 2;
-    xp.last = p.e == a.t.N;
-    xp.wide = max(p.hs, p.he) > 15;
+    if (IN && p.ni > 0) {
+        const float4 *ti = a.t.lanes_in + (size_t)lx * 16 * (kLaneInF / 4);
+        for (int i = threadIdx.x; i < 16 * (kLaneInF / 4); i += kXWaves * 64) tabi4[i] = ti[i];
+    }
+    const XPiece xp = x_piece(a.t, p, lx);
 #pragma unroll
     for (int c = 0; c < kTileC; ++c) L[c * kRowPitch + kRowOwn + lane] = u[c];
 #pragma unroll
@@ -174,7 +165,7 @@ __global__ void __launch_bounds__(kXWaves * 64) k_axis_x(AxisArgs a, int ngrp, i
     const int k = lane & 15;
 #pragma unroll
     for (int it = 0; it < kTileC / 4; ++it)
-        x_row<OP>(xp, tab4 + k * (kLaneF / 4), L + (4 * it + (lane >> 4)) * kRowPitch, k);
+        x_row<OP, IN>(xp, tab4 + k * (kLaneF / 4), tabi4 + k * (kLaneInF / 4), L + (4 * it + (lane >> 4)) * kRowPitch, k);
     wave_sync();
     if (lane >= p.m + (xp.last ? 1 : 0)) return;
 #pragma unroll
@@ -193,9 +184,9 @@ hipError_t launch_axis_rows(int op, const AxisArgs &a, hipStream_t st)
     const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
     auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
     switch (op) {
-    case TILE_D1: go(k_axis_rows<TILE_D1>); break;
-    case TILE_D2: go(k_axis_rows<TILE_D2>); break;
-    case TILE_DT: go(k_axis_rows<TILE_DT>); break;
+    case TILE_D1: a.t.inside ? go(k_axis_rows<TILE_D1, true>) : go(k_axis_rows<TILE_D1, false>); break;
+    case TILE_D2: go(k_axis_rows<TILE_D2, false>); break;
+    case TILE_DT: a.t.inside ? go(k_axis_rows<TILE_DT, true>) : go(k_axis_rows<TILE_DT, false>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -209,9 +200,9 @@ hipError_t launch_axis_x(int op, const AxisArgs &a, hipStream_t st)
     const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
     auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, kXWaves * 64, 0, st, a, (int)ngrp, (int)nreal); };
     switch (op) {
-    case TILE_D1: go(k_axis_x<TILE_D1>); break;
-    case TILE_D2: go(k_axis_x<TILE_D2>); break;
-    case TILE_DT: go(k_axis_x<TILE_DT>); break;
+    case TILE_D1: a.t.inside ? go(k_axis_x<TILE_D1, true>) : go(k_axis_x<TILE_D1, false>); break;
+    case TILE_D2: go(k_axis_x<TILE_D2, false>); break;
+    case TILE_DT: a.t.inside ? go(k_axis_x<TILE_DT, true>) : go(k_axis_x<TILE_DT, false>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -104,54 +104,91 @@ __device__ __forceinline__ void rows_local(const TileChunk &t, const float (&u)[
     W = v;
 }
 
-// the wave's share of the two tap sums from its own rows; moments take the differences from
-// the junction's own value (us, ue), whose share is added once: the taps cancel to the
-// second difference of the field
-template <int OP>
-__device__ __forceinline__ void taps_own(const TileChunk &t, const float (&u)[kTileC + 2], float us, float ue, float &ps,
-                                         float &pe)
+// IN: pieces may hold junctions inside.  Kernels of their own: the junctions' sums take
+// registers that the elastic kernels do not have to spare.
+
+// Shares of the tap sums: of the start, of the closing right-hand side, of the junctions inside.
+struct Taps {
+    float s = 0.f, e = 0.f, j[kTileIn] = {};
+    float l = 0.f;              // transposed: the taps left of the piece of its start alone
+};
+
+// from a wave's own rows; moments take the differences from the junction's own value (us, ue),
+// whose share is added once: the taps cancel to the second difference of the field
+template <int OP, bool IN>
+__device__ __forceinline__ void taps_own(const TileChunk &t, const float (&u)[kTileC + 2], float us, float ue, Taps &p)
 {
     if (t.any_ts != 0.f) {          // uniform
 #pragma unroll
-        for (int c = 0; c < kTileC; ++c) ps = fmaf(t.ts[c], OP == TILE_D2 ? u[c + 1] - us : u[c + 1], ps);
+        for (int c = 0; c < kTileC; ++c) p.s = fmaf(t.ts[c], OP == TILE_D2 ? u[c + 1] - us : u[c + 1], p.s);
     }
     if (t.any_te != 0.f) {
 #pragma unroll
-        for (int c = 0; c < kTileC; ++c) pe = fmaf(t.te[c], OP == TILE_D2 ? u[c + 1] - ue : u[c + 1], pe);
+        for (int c = 0; c < kTileC; ++c) p.e = fmaf(t.te[c], OP == TILE_D2 ? u[c + 1] - ue : u[c + 1], p.e);
+    }
+    if (IN && t.any_in) {
+#pragma unroll
+        for (int j = 0; j < kTileIn; ++j)
+#pragma unroll
+            for (int c = 0; c < kTileC; ++c) p.j[j] = fmaf(t.tj[j][c], u[c + 1], p.j[j]);
     }
 }
 
-// A wave publishes B, W, ps, pe of each field into its own row buffer once its x solves are
-// done (4 * 64 floats per field, at most three fields: below kTileC * kRowPitch).
-constexpr int kWaveLds = kTileC * kRowPitch;
-static_assert(3 * 4 * 64 <= kWaveLds, "exchange area");
+// from halo entry i of value v
+template <int OP, bool IN>
+__device__ __forceinline__ void taps_halo(const Piece &pc, const float4 *hc, int i, float v, float us, float ue, Taps &p)
+{
+    const float4 c = hc[i];
+    p.s = fmaf(c.x, v - us, p.s);
+    p.e = fmaf(c.y, v - ue, p.e);
+    if (IN && pc.ni > 0) {   // uniform
+        p.j[0] = fmaf(c.z, v, p.j[0]);
+        const float w = c.w * v;        // of the last one, when there are several
+#pragma unroll
+        for (int j = 1; j < kTileIn; ++j) p.j[j] += j == pc.ni - 1 ? w : 0.f;
+    }
+    if (OP == TILE_DT && i < pc.hl) p.l = fmaf(c.x, v, p.l);
+}
 
-__device__ __forceinline__ void rows_publish(float *ex, int lane, float B, float W, float ps, float pe)
+// A wave publishes B, W and its shares of each field into its own row buffer once its x solves
+// are done: kPublish floats per field.
+constexpr int kWaveLds = kTileC * kRowPitch;
+template <int OP, bool IN>
+constexpr int kPublish = 256 + (IN ? 64 * kTileIn : 0) + (OP == TILE_DT ? 64 : 0);
+
+template <int OP, bool IN>
+__device__ __forceinline__ void rows_publish(const Piece &pc, float *ex, int lane, float B, float W, const Taps &p)
 {
     ex[lane] = B;
     ex[64 + lane] = W;
-    ex[128 + lane] = ps;
-    ex[192 + lane] = pe;
+    ex[128 + lane] = p.s;
+    ex[192 + lane] = p.e;
+    if (IN && pc.ni > 0) {   // uniform
+#pragma unroll
+        for (int j = 0; j < kTileIn; ++j) ex[256 + 64 * j + lane] = p.j[j];
+    }
+    if (OP == TILE_DT) ex[kPublish<OP, IN> - 64 + lane] = p.l;
 }
 
 // The chunk's rows from its carries; returns the carry from below (the value at the closing
 // row for the last chunk).  Transposed slopes: the rows of G^T y from the solution y, its
-// neighbours and the junction values y_s = ph, y_e = pe; the taps left of the piece alone,
-// which the waves publish after their four sums, give y at the row before it (`first`: the
-// piece's first chunk); dn = the value at the closing node.
-template <int STRIDE, int OP>
-__device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex, int nw, int lane, float (&y)[kTileC],
-                                             const TileEnds *end = nullptr, float s3 = 0.f, bool first = false,
-                                             int nown = 0, float *dn = nullptr)
+// neighbours and the values y_J of the piece's junctions; the taps left of the piece alone
+// give y at the row before it (`first`: the piece's first chunk); dn = the value at the
+// closing node.
+template <int STRIDE, int OP, bool IN>
+__device__ __forceinline__ float rows_finish(const Piece &pc, const TileChunk &t, const float *ex, int nw, int lane,
+                                             float (&y)[kTileC], const TileEnds *end = nullptr, float s3 = 0.f,
+                                             bool first = false, int nown = 0, float *dn = nullptr)
 {
     float ph = 0.f, pe = 0.f, yin = 0.f, win = 0.f, prev = 0.f;
+    const int ol = IN ? 128 + 64 * t.l : 128, orr = IN ? 128 + 64 * t.r : 192;
 #pragma unroll
     for (int j = 0; j < kTileWaves; ++j) {
         if (j < nw) {   // uniform
             const float *e = ex + j * STRIDE + lane;
             const float B = e[0], W = e[64];
-            ph += e[128];
-            pe += e[192];
+            ph += e[ol];
+            pe += e[orr];
             yin = fmaf(t.fB[j], B, yin);
             win = fmaf(t.zB[j], B, win);
             win = fmaf(t.zW[j], W, win);
@@ -163,7 +200,14 @@ __device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex
     }
     if constexpr (OP != TILE_DT) {
         yin = fmaf(t.fph, ph, yin);
-        win = fmaf(t.zph, ph, win);
+        float pm = ph;
+        if (IN && OP == TILE_D1 && t.m >= 0) {    // uniform
+            pm = 0.f;
+            for (int j = 0; j < nw; ++j) pm += ex[j * STRIDE + lane + 128 + 64 * t.m];
+#pragma unroll
+            for (int c = 0; c < kTileC; ++c) y[c] = fmaf(t.Q[c], pm, y[c]);
+        }
+        win = fmaf(t.zph, pm, win);
     }
     win = fmaf(t.zE, pe, win);
     float v = win;
@@ -176,14 +220,14 @@ __device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex
         prev = fmaf(t.pE, pe, prev);
         if (first) {                // the row before the piece; a natural end mirrors y_0
             prev = 0.f;
-            for (int j = 0; j < nw; ++j) prev -= ex[j * STRIDE + 256 + lane];
+            for (int j = 0; j < nw; ++j) prev -= ex[j * STRIDE + kPublish<OP, IN> - 64 + lane];
             if (end->m1 != 0.f) prev = -y[0];
         }
         float wl = 0.f;
 #pragma unroll
         for (int c = 0; c < kTileC; ++c)
             if (c == nown - 1) wl = y[c];
-        *dn = fmaf(s3, fmaf(end->sE, win, wl), fmaf(end->cs, ph, end->ce * pe));
+        float d = fmaf(s3, fmaf(end->sE, win, wl), fmaf(end->cs, ph, end->ce * pe));
         float lo = prev;
 #pragma unroll
         for (int c = 0; c < kTileC; ++c) {
@@ -200,6 +244,18 @@ __device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex
 #pragma unroll
             for (int c = 0; c < kTileC; ++c) y[c] = fmaf(t.ce[c], pe, y[c]);
         }
+        if (IN && pc.ni > 0 && (t.any_in || end->cj != 0.f)) {   // uniform
+#pragma unroll
+            for (int k = 0; k < kTileIn; ++k)
+                if (k < pc.ni) {
+                    float pj = 0.f;
+                    for (int j = 0; j < nw; ++j) pj += ex[j * STRIDE + 256 + 64 * k + lane];
+#pragma unroll
+                    for (int c = 0; c < kTileC; ++c) y[c] = fmaf(t.cj[k][c], pj, y[c]);
+                    if (k == pc.ni - 1) d = fmaf(end->cj, pj, d);
+                }
+        }
+        *dn = d;
     }
     return win;
 }
@@ -210,16 +266,32 @@ __device__ __forceinline__ float rows_finish(const TileChunk &t, const float *ex
 // derivative of the piece's nodes replaces them, and that of the line's last node follows
 // when the piece closes the line.  The lane's table entry (factors of its four nodes, carry
 // multipliers, taps k, k + 16, k + 32 of the two junctions and their places in the row) is
-// read from LDS as it is needed: kept in registers over the fields it would take 44.
+// read from LDS as it is needed: kept in registers over the fields it would take 44.  ti: the
+// lane's entry for junctions inside the piece: a node that is one takes its tap sum as its row's
+// value (its factors are 0), and the transposed rows take the values by weights.
 struct XPiece {
     TileEnds end;
     float s3;
-    int m, kc, hs;
+    int m, kc, hs, ni;
     bool last, wide;         // closes the line; taps beyond the first 32 of a junction
 };
 
-template <int OP>
-__device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, float *L, int k)
+__device__ __forceinline__ XPiece x_piece(const TileAxis &t, const Piece &p, int lx)
+{
+    XPiece x;
+    x.end = t.ends[lx];
+    x.s3 = t.s3;
+    x.m = p.m;
+    x.hs = p.hs;
+    x.ni = p.ni;
+    x.kc = (p.m - 1) >> 2;
+    x.last = p.e == t.N;
+    x.wide = max(max(p.hs, p.he), p.hi) > 15;
+    return x;
+}
+
+template <int OP, bool IN>
+__device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const float4 *ti, float *L, int k)
 {
     __builtin_amdgcn_sched_barrier(0);   // one row group at a time: interleaved they spill
     const float4 cs = t[7], os = t[8], ce = t[9], oe = t[10];
@@ -247,6 +319,22 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, float *L
         ph = fmaf(p.end.cs, us, ph);
         pe = fmaf(p.end.ce, ue, pe);
     }
+    float pj[kTileIn], pm = 0.f;
+    if (IN && p.ni > 0) {   // uniform
+        const float4 own = ti[1];
+#pragma unroll
+        for (int j = 0; j < kTileIn; ++j) {
+            pj[j] = 0.f;
+            if (j < p.ni) {
+                const float4 c = ti[2 + 2 * j], o = ti[3 + 2 * j];
+                float v = c.x * at(o.x);
+                v = fmaf(c.y, at(o.y), v);
+                if (p.wide) v = fmaf(c.z, at(o.z), v);
+                pj[j] = row_sum(v);
+                if (OP == TILE_D1) pm = fmaf(j == 0 ? own.x : (j == 1 ? own.y : own.z), pj[j], pm);
+            }
+        }
+    }
     if (OP != TILE_DT && p.end.sE != 0.f) pe = fmaf(p.end.sE, L[kRowOwn + p.m] - L[kRowOwn + p.m - 1], pe);
     __builtin_amdgcn_sched_barrier(0);
     const float4 u = ld4(L + kRowOwn + 4 * k);
@@ -259,10 +347,18 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, float *L
         else if constexpr (OP == TILE_D2) return (hi - own) - (own - lo);
         else return own;
     };
-    float y0 = sc.x * rhs(ul, u.x, u.y);
-    float y1 = fmaf(nf.y, y0, sc.y * rhs(u.x, u.y, u.z));
-    float y2 = fmaf(nf.z, y1, sc.z * rhs(u.y, u.z, u.w));
-    float y3 = fmaf(nf.w, y2, sc.w * rhs(u.z, u.w, ur));
+    float y0 = sc.x * rhs(ul, u.x, u.y), y1 = sc.y * rhs(u.x, u.y, u.z);
+    float y2 = sc.z * rhs(u.y, u.z, u.w), y3 = sc.w * rhs(u.z, u.w, ur);
+    if (IN && OP == TILE_D1 && p.ni > 0) {
+        const float4 q = ti[0];
+        y0 = fmaf(q.x, pm, y0);
+        y1 = fmaf(q.y, pm, y1);
+        y2 = fmaf(q.z, pm, y2);
+        y3 = fmaf(q.w, pm, y3);
+    }
+    y1 = fmaf(nf.y, y0, y1);
+    y2 = fmaf(nf.z, y1, y2);
+    y3 = fmaf(nf.w, y2, y3);
     float B = fmaf(a.w, ph, y3);
     B = fmaf(a.x, row_shift_up_fill<1>(B, 0.f), B);
     B = fmaf(a.y, row_shift_up_fill<2>(B, 0.f), B);
@@ -304,6 +400,18 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, float *L
         o.y = fmaf(p.s3, r.x - r.z, fmaf(c1.y, ph, c2.y * pe));
         o.z = fmaf(p.s3, r.y - r.w, fmaf(c1.z, ph, c2.z * pe));
         o.w = fmaf(p.s3, r.z - hi, fmaf(c1.w, ph, c2.w * pe));
+        if (IN && p.ni > 0) {
+#pragma unroll
+            for (int j = 0; j < kTileIn; ++j)
+                if (j < p.ni) {
+                    const float4 c = ti[8 + j];
+                    o.x = fmaf(c.x, pj[j], o.x);
+                    o.y = fmaf(c.y, pj[j], o.y);
+                    o.z = fmaf(c.z, pj[j], o.z);
+                    o.w = fmaf(c.w, pj[j], o.w);
+                    if (j == p.ni - 1) dn = fmaf(p.end.cj, pj[j], dn);
+                }
+        }
         r = o;
     }
     st4(L + kRowOwn + 4 * k, r);

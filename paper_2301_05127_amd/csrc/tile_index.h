@@ -23,24 +23,34 @@ constexpr int kRowOwn = kTileHalo;
 constexpr int kRowRight = kRowOwn + kTileM;
 constexpr int kRowPitch = 112;    // = 48 mod 64: the four rows a wave solves at once start in different banks
 
+// a cut lies this far inside a patch: its row's weights beyond the patch ends are then below
+// 0.268^16 = 7e-10 of the others (FP32 rounding: 6e-8)
+constexpr int kCutGap = 16;
+constexpr int kTileIn = 3;        // junctions inside a piece, at most
+constexpr int kTileInGap = 8;     // nodes between them, at least: one per chunk of rows, one per lane
+
 // Window of one piece along an axis: nodes s .. e, hl nodes left of s and hr nodes right
-// of e that the taps of its two junctions reach.
+// of e that the taps of its junctions (the two ends and up to kTileIn inside) reach.
 struct Piece {
     int s, e, m;       // m = e - s
     int hs, he;        // taps on either side of the junction rows s and e (0: natural end)
     int hl, hr;
+    int ni, hi;        // junctions inside, taps on either side of them
 };
 
-LOSS_HD Piece make_piece(int s, int e, int hs, int he)
+// as the tables hold it: {s, e, hs | he << 8 | hl << 16 | hr << 24, ni | hi << 8}
+LOSS_HD Piece make_piece(int s, int e, int z, int w)
 {
     Piece p;
     p.s = s;
     p.e = e;
     p.m = e - s;
-    p.hs = hs;
-    p.he = he;
-    p.hl = hs > he - p.m ? hs : he - p.m;
-    p.hr = he > hs - p.m ? he : hs - p.m;
+    p.hs = z & 255;
+    p.he = (z >> 8) & 255;
+    p.hl = (z >> 16) & 255;
+    p.hr = (z >> 24) & 255;
+    p.ni = w & 255;
+    p.hi = w >> 8;
     return p;
 }
 

@@ -20,6 +20,7 @@ CASES = [
     (2, (96, 0, 96), (8, 8, 8), 20, 0, 1),       # transposed taps reach past the next patch: staged
     (2, (130, 0, 64), (65, 64, 32), 12, 1, 2),
     (2, (96, 0, 72), (48, 48, 24), 10, 2, 2),    # periodic: the transposed operator is staged
+    (2, (131, 0, 97), (16, 64, 8), 6, 0, 3),     # pieces across junctions
     (3, (33, 70, 66), (32, 35, 66), 6, 0, 2),
     (3, (66, 9, 17), (22, 9, 16), 8, 0, 4),
 ]

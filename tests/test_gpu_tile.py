@@ -26,6 +26,13 @@ ACOUSTIC = [
     ((150, 0, 128), (75, 64, 64), 9, 2, 0),      # periodic
     ((150, 0, 131), (96, 64, 40), 8, 0, 12),     # layer over tile edges
 ]
+# short patches and enough tiles: pieces across junctions
+ACROSS = [
+    # intervals, patches, halo, end mode, layer, copies of the shots
+    ((205, 0, 200), (8, 8, 8), 12, 0, 0, 3),     # three junctions inside; taps wider than a patch
+    ((193, 0, 210), (16, 16, 24), 5, 2, 0, 12),  # periodic; two inside and one
+    ((190, 0, 177), (24, 24, 8), 7, 1, 9, 7),    # the end stencil; a last patch of one interval; layer
+]
 
 
 def _src(kind, pos, f0, dt, nsteps):
@@ -34,13 +41,17 @@ def _src(kind, pos, f0, dt, nsteps):
             "wavelet": inputs.ricker(f0, 0.03, dt, nsteps + 1, 0.5 if kind < 2 else 0.0)}
 
 
-def _check(orc, w, layer, schedules=(0, 1)):
+def _check(orc, w, layer, schedules=(0, 1), copies=1):
     from paper_2301_05127_amd import loss
+    w["shots"] = w["shots"] * copies
     S = len(w["shots"])
     ac = w["physics"] == 0
     refs = []
     for s in range(S):
-        if layer:
+        first = next(k for k in range(S) if w["shots"][k] is w["shots"][s])
+        if first < s:                    # the same shot again
+            refs.append(refs[first])
+        elif layer:
             sh = w["shots"][s]
             lay = dict(width=layer, R=1e-6, kmax=1.5, f0=30.0, cmax=float(np.max(w["vp"])))
             kw = dict(sources=sh["sources"], receivers=sh["receivers"])
@@ -67,11 +78,15 @@ def _check(orc, w, layer, schedules=(0, 1)):
         sim.close()
 
 
-@pytest.mark.parametrize("geom", ACOUSTIC, ids=["x".join(map(str, g[0])) + "h%de%dl%d" % g[2:] for g in ACOUSTIC])
+def _ids(geoms):
+    return ["x".join(map(str, g[0])) + "h%de%dl%d" % g[2:5] for g in geoms]
+
+
+@pytest.mark.parametrize("geom", ACOUSTIC + ACROSS, ids=_ids(ACOUSTIC + ACROSS))
 def test_acoustic_tiles_match_oracle(orc, geom):
     require_gpu()
     from paper_2301_05127_amd import inputs
-    n, M, halo, end, layer = geom
+    n, M, halo, end, layer = geom[:5]
     announce("acoustic tiles %s" % (geom,))
     g = inputs.grid(2, n, (10.0, 10.0, 10.0), M, halo, end)
     shape = inputs.field_shape(g)
@@ -86,7 +101,7 @@ def test_acoustic_tiles_match_oracle(orc, geom):
              {"sources": [_src(2, (cx, 0.0, cz), 30.0, dt, nsteps)], "receivers": np.array(rec, np.int32),
               "rec_comp": 0}]
     w = _f32(dict(grid=g, physics=0, dt=dt, nsteps=nsteps, vp=vp, vs=None, rho=np.full(shape, 1000.0), shots=shots))
-    _check(orc, w, layer)
+    _check(orc, w, layer, copies=(geom + (1,))[5])
 
 
 ELASTIC = [
@@ -94,13 +109,17 @@ ELASTIC = [
     ((64, 64, 130), (64, 64, 128), 12, 0, 0),
     ((48, 41, 44), (20, 12, 9), 6, 0, 10),       # layer, rows that do not fill a wave
 ]
+ELASTIC_ACROSS = [
+    ((48, 41, 30), (8, 8, 8), 6, 0, 0, 2),
+    ((50, 40, 35), (8, 20, 12), 6, 0, 8, 2),
+]
 
 
-@pytest.mark.parametrize("geom", ELASTIC, ids=["x".join(map(str, g[0])) + "h%de%dl%d" % g[2:] for g in ELASTIC])
+@pytest.mark.parametrize("geom", ELASTIC + ELASTIC_ACROSS, ids=_ids(ELASTIC + ELASTIC_ACROSS))
 def test_elastic_tiles_match_oracle(orc, geom):
     require_gpu()
     from paper_2301_05127_amd import inputs
-    n, M, halo, end, layer = geom
+    n, M, halo, end, layer = geom[:5]
     announce("elastic tiles %s" % (geom,))
     g = inputs.grid(3, n, (10.0, 10.0, 10.0), M, halo, end)
     shape = inputs.field_shape(g)
@@ -112,4 +131,4 @@ def test_elastic_tiles_match_oracle(orc, geom):
              {"sources": [_src(3, c, 40.0, dt, nsteps)], "receivers": rec, "rec_comp": 7}]
     w = _f32(dict(grid=g, physics=1, dt=dt, nsteps=nsteps, vp=vp, vs=vp / np.sqrt(3.0), rho=310.0 * vp ** 0.25,
                   shots=shots))
-    _check(orc, w, layer)
+    _check(orc, w, layer, copies=(geom + (1,))[5])

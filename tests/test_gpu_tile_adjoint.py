@@ -22,11 +22,13 @@ ACOUSTIC = [
     ((65, 0, 64), (64, 64, 64), 6, 0),       # a last x piece of one interval
     ((70, 0, 65), (35, 64, 64), 6, 1),       # a last row piece of one interval; end stencil
     ((48, 0, 52), (24, 26, 26), 6, 2),       # periodic
+    ((205, 0, 200), (8, 64, 8), 6, 0, 6),    # pieces across junctions
 ]
 ELASTIC = [
     ((66, 18, 20), (66, 18, 20), 8, 0),      # cut x patch
     ((20, 66, 17), (20, 66, 16), 8, 0),      # cut rows; a last z piece of one interval
     ((17, 25, 22), (16, 12, 11), 5, 1),      # a last x piece and a last row piece of one interval
+    ((56, 48, 36), (8, 8, 9), 6, 0),         # pieces across junctions
 ]
 
 
@@ -34,15 +36,15 @@ ELASTIC = [
 def test_acoustic_tile_gradient_matches_oracle(orc, geom):
     require_gpu()
     from paper_2301_05127_amd import inputs, loss
-    n, M, halo, end = geom
+    n, M, halo, end = geom[:4]
     announce("acoustic tile gradient %s" % (geom,))
     g = inputs.grid(2, n, (10.0, 10.0, 10.0), M, halo, end)
     shape = inputs.field_shape(g)
-    dt, nsteps, S = 1e-3, 12, 2
+    dt, nsteps, S = 1e-3, 12, (geom + (2,))[4]
     vp = _f32(inputs.gaussian_random_field(shape, 10.0, 80.0, 5, 2000.0, 2400.0))
     rho = np.full(shape, 1000.0)
     rec = np.array([[ix, 0, iz] for iz in range(0, n[2] + 1, 4) for ix in range(0, n[0] + 1, 5)], np.int32)
-    shots = [{"sources": [{"kind": 0, "pos": (10.0 * (n[0] // 3) * (s + 1), 0.0, 10.0 * (n[2] // 2)), "spread": 300.0,
+    shots = [{"sources": [{"kind": 0, "pos": (10.0 * (n[0] // 3) * (s % 2 + 1), 0.0, 10.0 * (n[2] // 2)), "spread": 300.0,
                            "wavelet": _f32(inputs.ricker(40.0, 0.004, dt, nsteps + 1, 0.5))}],
               "receivers": rec, "rec_comp": 0} for s in range(S)]
     res = np.random.default_rng(3).standard_normal((S, len(rec), nsteps))
@@ -75,7 +77,7 @@ def test_elastic_tile_gradient_matches_oracle(orc, geom):
         return {"kind": kind, "pos": tuple(5.0 * v for v in n), "spread": 15.0,
                 "wavelet": _f32(inputs.ricker(50.0, 0.02, 1e-3, nsteps + 1, shift))}
 
-    rec = np.array([[ix, n[1] // 2, 6] for ix in range(3, n[0] - 2, 3)], np.int32)
+    rec = np.array([[ix, n[1] // 2, n[2] // 2 + 3] for ix in range(3, n[0] - 2, 3)], np.int32)
     w = dict(grid=g, physics=1, dt=1e-3, nsteps=nsteps, vp=vp, vs=vs, rho=rho,
              shots=[{"sources": [src(1, 0.5)], "receivers": rec, "rec_comp": 2},
                     {"sources": [src(3, 0.0)], "receivers": rec, "rec_comp": 6}])

@@ -4,7 +4,7 @@
 // solve) against the buffers' sizes, and evaluates the two solves as the kernels do (chunks
 // of rows with summed carries; 16 lanes of four nodes with doubling steps) in FP32 on a
 // random line, against the patch systems solved in FP64.
-// Usage: tile_check N M halo end_mode op.  Prints "ok" and the two relative errors, or
+// Usage: tile_check N M halo end_mode op across.  Prints "ok" and the two relative errors, or
 // "unsupported" where build_tile refuses the transposed operator.
 #include <cmath>
 #include <cstdio>
@@ -73,8 +73,8 @@ static V moments(const AxisHost &ax, const V &u)
 
 int main(int argc, char **argv)
 {
-    if (argc != 6) return 2;
-    const int N = atoi(argv[1]), M = atoi(argv[2]), halo = atoi(argv[3]), mode = atoi(argv[4]), op = atoi(argv[5]);
+    if (argc != 7) return 2;
+    const int N = atoi(argv[1]), M = atoi(argv[2]), halo = atoi(argv[3]), mode = atoi(argv[4]), op = atoi(argv[5]), across = atoi(argv[6]);
     const double h = 10.0;
     const int per = mode == 2;
     AxisHost ax;
@@ -99,8 +99,8 @@ int main(int argc, char **argv)
     double errs[2];
     for (int along_x = 0; along_x < 2; ++along_x) {
         TileHost t;
-        err = build_tile(ax, along_x != 0, op, t);
-        if (!err.empty()) { std::printf(op == 2 ? "unsupported\n" : "%s\n", err.c_str()); return op == 2 ? 0 : 1; }
+        err = build_tile(ax, along_x != 0, op, across != 0, t);
+        if (!err.empty()) { std::printf(op == 2 || across ? "unsupported %s\n" : "%s\n", err.c_str()); return op == 2 || across ? 0 : 1; }
         in("max_m", t.max_m, 1, kTileM + 1);
         std::vector<float> d(N + 1, NAN);
         for (int l = 0; l < t.nsub; ++l) {
@@ -109,12 +109,15 @@ int main(int argc, char **argv)
             const bool last = p.e == N;
             in("hl", p.hl, 0, kTileHalo + 1);
             in("hr", p.hr, 0, kTileHalo + 1);
+            in("ni", p.ni, 0, kTileIn + 1);
+            if (op == 1 || !across) in("ni", p.ni, 0, 1);
+            in("halo entries", halo_count(p), 1, kTapW + 1);
             in("m", p.m, 1, (along_x && last ? kTileM - 1 : kTileM) + 1);
             auto node = [&](int k) { const int n = line_node(k, N, per); in("node", n, 0, N + 1); return n; };
             TileEnds end;
             std::memcpy(&end, &t.ends[(size_t)l * 8], sizeof(end));
             const float us = op == 1 ? u[p.s] : 0.f, ue = op == 1 ? u[node(p.e)] : 0.f;   // moments: taps on differences
-            float ps = op == 1 ? end.cs * us : 0.f, pe = op == 1 ? end.ce * ue : 0.f, pl = 0.f;
+            float ps = op == 1 ? end.cs * us : 0.f, pe = op == 1 ? end.ce * ue : 0.f, pl = 0.f, pj[kTileIn] = {};
             if (!along_x) {
                 const int nw = (t.max_m + kTileC - 1) / kTileC;
                 const TileChunk *ch = (const TileChunk *)t.chunk.data() + (size_t)l * kTileWaves;
@@ -123,9 +126,13 @@ int main(int argc, char **argv)
                     const int k = t.halo_node[(size_t)l * kTapW + i];
                     in("halo node", k, 0, N + 1);
                     if (i < halo_count(p)) check(k == node(halo_pos(p, i)), "halo node", k, 0, N + 1);
-                    ps += t.halo_c[2 * ((size_t)l * kTapW + i)] * (u[k] - us);
-                    if (i < p.hl) pl += t.halo_c[2 * ((size_t)l * kTapW + i)] * u[k];
-                    pe += t.halo_c[2 * ((size_t)l * kTapW + i) + 1] * (u[k] - ue);
+                    const float *hc = &t.halo_c[4 * ((size_t)l * kTapW + i)];
+                    ps += hc[0] * (u[k] - us);
+                    if (i < p.hl) pl += hc[0] * u[k];
+                    pe += hc[1] * (u[k] - ue);
+                    if (p.ni > 0) pj[0] += hc[2] * u[k];
+                    if (p.ni > 1) pj[p.ni - 1] += hc[3] * u[k];
+                    else check(hc[3] == 0.f && (p.ni > 0 || hc[2] == 0.f), "halo tap", i, 0, 0);
                 }
                 for (int j = 0; j < nw; ++j) {
                     const int q = p.s + j * kTileC;
@@ -144,6 +151,10 @@ int main(int argc, char **argv)
                         y[j * kTileC + c] = v;
                         ps += ch[j].ts[c] * (uu[c + 1] - us);
                         pe += ch[j].te[c] * (uu[c + 1] - ue);
+                        for (int i = 0; i < kTileIn; ++i) {
+                            pj[i] += ch[j].tj[i][c] * uu[c + 1];
+                            check((i < p.ni && ch[j].any_in) || (ch[j].tj[i][c] == 0.f && ch[j].cj[i][c] == 0.f), "inside tap", i, 0, 0);
+                        }
                         if (op != 2 && q + c == p.e - 1) pe += end.sE * (uu[c + 2] - uu[c + 1]);
                     }
                     B[j] = v;
@@ -152,7 +163,12 @@ int main(int argc, char **argv)
                     W[j] = v;
                 }
                 for (int j = 0; j < nw && p.s + j * kTileC < p.e; ++j) {
-                    float yin = ch[j].fph * ps, win = ch[j].zph * ps + ch[j].zE * pe, prev = ch[j].pE * pe;
+                    in("junction", ch[j].l, 0, 2 + p.ni);
+                    in("junction", ch[j].r, 0, 2 + p.ni);
+                    in("junction", ch[j].m, -1, 2 + p.ni);
+                    auto jv = [&](int i) { return i == 0 ? ps : (i == 1 ? pe : pj[i - 2]); };
+                    const float vl = jv(ch[j].l), vm = ch[j].m >= 0 ? jv(ch[j].m) : vl, vr = jv(ch[j].r);
+                    float yin = ch[j].fph * vl, win = ch[j].zph * vm + ch[j].zE * vr, prev = ch[j].pE * pe;
                     for (int i = 0; i < nw; ++i) {
                         yin += ch[j].fB[i] * B[i];
                         win += ch[j].zB[i] * B[i] + ch[j].zW[i] * W[i];
@@ -161,7 +177,7 @@ int main(int argc, char **argv)
                     const int q = p.s + j * kTileC;
                     float v = win, w[kTileC];
                     for (int c = kTileC - 1; c >= 0; --c) {
-                        v = ch[j].g[c] * v + ch[j].fi[c] * (y[j * kTileC + c] + ch[j].P[c] * yin);
+                        v = ch[j].g[c] * v + ch[j].fi[c] * (y[j * kTileC + c] + (ch[j].m >= 0 ? ch[j].Q[c] * vm : 0.f) + ch[j].P[c] * yin);
                         w[c] = v;
                     }
                     if (op < 2) {
@@ -172,9 +188,11 @@ int main(int argc, char **argv)
                         for (int c = 0; c < kTileC && q + c < p.e; ++c) {
                             const float lo = c > 0 ? w[c - 1] : prev, hi = c < kTileC - 1 ? w[c + 1] : win;
                             d[q + c] = s3 * (lo - hi) + ch[j].cs[c] * ps + ch[j].ce[c] * pe;
+                            for (int i = 0; i < p.ni; ++i) d[q + c] += ch[j].cj[i][c] * pj[i];
                         }
                         if (last && q + kTileC >= p.e)
-                            d[N] = s3 * (w[p.e - 1 - q] + end.sE * win) + end.cs * ps + end.ce * pe;
+                            d[N] = s3 * (w[p.e - 1 - q] + end.sE * win) + end.cs * ps + end.ce * pe +
+                                   (p.ni > 0 ? end.cj * pj[p.ni - 1] : 0.f);
                     }
                 }
             } else {
@@ -198,6 +216,18 @@ int main(int argc, char **argv)
                         if (x[28 + i] != 0.f && k + 16 * i < p.hs) pl += x[28 + i] * L[os / 4];
                         if (x[36 + i] != 0.f) pe += x[36 + i] * (L[oe / 4] - ue);
                     }
+                const float *tin = &t.lanes_in[(size_t)l * 16 * kLaneInF];
+                for (int k = 0; k < 16; ++k)
+                    for (int j = 0; j < kTileIn; ++j)
+                        for (int i = 0; i < 3; ++i) {
+                            const float *x = tin + k * kLaneInF + 8 + 8 * j;
+                            int o;
+                            memcpy(&o, x + 4 + i, 4);
+                            in("tap place", o, 0, 4 * kRowPitch);
+                            check(j < p.ni || x[i] == 0.f, "inside tap", j, 0, 0);
+                            check(i < 2 || std::max(std::max(p.hs, p.he), p.hi) > 15 || x[i] == 0.f, "third tap", j, 0, 0);
+                            if (x[i] != 0.f) pj[j] += x[i] * L[o / 4];
+                        }
                 if (op != 2) pe += end.sE * (u[p.e] - u[p.e - 1]);
                 const int kc = (p.m - 1) / 4;
                 float y[16][4], B[16], W[16], tt[16][4], w[65];
@@ -208,7 +238,10 @@ int main(int argc, char **argv)
                         const int i = 4 * k + c;
                         const float own = L[kRowOwn + i];
                         const float lo = i > 0 ? L[kRowOwn + i - 1] : own, hi = i < 63 ? L[kRowOwn + i + 1] : L[kRowRight];
-                        v = x[c] * v + x[4 + c] * (op == 0 ? hi - lo : (op == 1 ? (hi - own) - (own - lo) : own));
+                        const float *xi = tin + k * kLaneInF;
+                        float pm = 0;
+                        for (int j = 0; j < kTileIn; ++j) pm += xi[4 + j] * pj[j];
+                        v = x[c] * v + xi[c] * pm + x[4 + c] * (op == 0 ? hi - lo : (op == 1 ? (hi - own) - (own - lo) : own));
                         y[k][c] = v;
                     }
                     B[k] = v + x[23] * ps;
@@ -253,8 +286,11 @@ int main(int argc, char **argv)
                     for (int i = 0; i < p.m; ++i) {
                         const float *x = tab + (i / 4) * kLaneF;
                         d[p.s + i] = s3 * ((i > 0 ? w[i - 1] : prev) - w[i + 1]) + x[44 + i % 4] * ps + x[48 + i % 4] * pe;
+                        for (int j = 0; j < p.ni; ++j) d[p.s + i] += tin[(i / 4) * kLaneInF + 32 + 4 * j + i % 4] * pj[j];
                     }
-                    if (last) d[N] = s3 * (w[p.m - 1] + end.sE * we) + end.cs * ps + end.ce * pe;
+                    if (last)
+                        d[N] = s3 * (w[p.m - 1] + end.sE * we) + end.cs * ps + end.ce * pe +
+                               (p.ni > 0 ? end.cj * pj[p.ni - 1] : 0.f);
                 }
             }
         }
