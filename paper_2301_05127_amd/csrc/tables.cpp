@@ -11,10 +11,12 @@
 // g_k = alpha (r^k + r^{N-k}), r = sqrt(3) - 2, from the two decaying homogeneous
 // solutions of the three-term recurrence.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <map>
 
 #include "loss_internal.h"
 #include "tile_index.h"
@@ -434,6 +436,7 @@ std::string build_tile(const AxisHost &ax, bool along_x, int op, bool across, Ti
     std::vector<int> sb, bh;
     std::vector<double> taps;
     std::vector<char> real;             // a junction or an end of the method's patches
+    std::map<std::array<int, 4>, std::vector<double>> rows;
     std::set_union(jn.begin(), jn.end(), t.sb.begin(), t.sb.end(), std::back_inserter(sb));
     for (int J : sb) {
         const size_t o = taps.size();
@@ -446,8 +449,14 @@ std::string build_tile(const AxisHost &ax, bool along_x, int op, bool across, Ti
             bh.push_back(0);
         } else {
             const int s = J / ax.M * ax.M, e = std::min(s + ax.M, N);
-            std::vector<double> row;
-            interior_row(ax, op == TILE_D2 ? 2 : 1, s, e, J, row);
+            // equal for equal patches
+            const std::array<int, 4> key = {J - s, e - s, ax.kind[s], ax.kind[e]};
+            auto known = rows.find(key);
+            if (known == rows.end()) {
+                known = rows.emplace(key, std::vector<double>()).first;
+                interior_row(ax, op == TILE_D2 ? 2 : 1, s, e, J, known->second);
+            }
+            const std::vector<double> &row = known->second;
             int H = kTileHalo;
             auto mag = [&](int d) {
                 const int a = J - d - s, b = J + d - s;

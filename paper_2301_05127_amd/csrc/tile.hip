@@ -11,9 +11,10 @@
 // A tile is a piece of at most 64 intervals of x times a piece of at most 64 intervals of
 // the rows: patches longer than that are cut, and pieces of short patches reach across up to
 // three junctions, whose slopes are tap sums like those of the ends and enter at their rows
-// (8 x 1025^2 acoustic, patches of 16: 388 us per step with tiles of 16 x 16 nodes -> 105).  A wave owns 8 consecutive rows,
-// lane = column, so every row index, factor and carry coefficient along the rows is
-// wave-uniform (scalar loads, SGPR operands) and every global access is one 256-byte row.
+// (8 x 1025^2 acoustic, patches of 16: 388 us per step with tiles of 16 x 16 nodes -> 105).
+// A wave owns 8 consecutive rows, lane = column, so every row index, factor and carry
+// coefficient along the rows is wave-uniform (scalar loads, SGPR operands) and every global
+// access is one 256-byte row.
 //
 // The factors do not depend on the data, so neither do the multipliers of the carries:
 //  * rows: each chunk of 8 rows eliminates and back-substitutes from zero carries and
@@ -114,6 +115,26 @@ struct Traits<TILE_AC_STRESS_T> : Traits<TILE_AC_VEL> {
     static constexpr int OP = TILE_DT;
     static constexpr bool coef = true;
 };
+
+// Workgroups are dealt round-robin to the 8 XCDs; each XCD gets runs of `chunk` tiles (x
+// fastest), so that neighbours' halos meet in one L2.  One run per XCD, except where elastic
+// tiles are few (they are in flight at nearly the same time: runs of whole rows, about 16
+// tiles, keep the XCDs' reads close together) and for the z derivatives.  Measured, one run per
+// XCD -> 16: elastic 65^3 1800 -> 1745 us a pass, gradient of 2 x 129^3 (1548 tiles) 39.8 -> 38.9
+// ms; z derivatives of 257^3 x 2 205 -> 200 us; but elastic 257^3 x 2 (12 850 tiles) 685 -> 700
+// us, acoustic 16 x 1101 x 706 with layers 7.65 -> 8.17 ms.  Shots of one tile next to each
+// other (the media read once) lose: 64 x 1025^2 382 -> 410 us a kernel.
+constexpr int kXcdChunk = 16;
+
+__device__ __forceinline__ int xcd_range() { return (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)); }
+__device__ __forceinline__ int xcd_order(int chunk)
+{
+    const int i = (int)(blockIdx.x >> 3), r = i / chunk;
+    return (r * 8 + (int)(blockIdx.x & 7)) * chunk + (i - r * chunk);
+}
+
+// workgroups of a launch: whole rounds of 8 chunks, those past the last tile return
+int64_t xcd_blocks(int64_t nreal, int chunk) { return (nreal + 8 * (int64_t)chunk - 1) / (8 * (int64_t)chunk) * 8 * chunk; }
 
 template <int MODE>
 constexpr int rows_slot(int f)
@@ -430,7 +451,7 @@ template <int MODE>
 constexpr int kTileWavesPerSimd = Traits<MODE>::SHAPE == TILE_AC_STRESS || Traits<MODE>::SHAPE == TILE_AC_VEL ? 6 : 4;
 
 template <int MODE, bool KEEP, bool LAYER, bool IN>
-__global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_tile(TileArgs a, int nreal)
+__global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_tile(TileArgs a, int nreal, int chunk)
 {
     using T = Traits<MODE>;
     constexpr int NF = T::NF, OP = T::OP, kLds = kModeLds<MODE, IN>, kEx = kPublish<OP, IN>;
@@ -438,9 +459,8 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
     __shared__ float4 tabi4[IN ? 16 * (kLaneInF / 4) : 1];    // the same, junctions inside
     __shared__ float4 lds4[kTileWaves * kLds / 4];
     float *lds = reinterpret_cast<float *>(lds4);
-    // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs; each XCD gets a
-    // contiguous range of tiles (x fastest), so neighbours' halos meet in one L2
-    const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    // (one run is left to the shifts: the division is 1 % of a 2049^2 acoustic step)
+    const int lin = NF < 3 ? xcd_range() : xcd_order(chunk);
     if (lin >= nreal) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -730,7 +750,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
 {
     constexpr int kEx = kPublish<OP, IN>;
     __shared__ float ex[kTileWaves * kEx];
-    const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    const int lin = xcd_order(kXcdChunk);
     if (a.step_inc && blockIdx.x == 0 && threadIdx.x == 0) *a.step_inc += 1;
     if (lin >= nreal) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -832,9 +852,13 @@ hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st)
     if (a.nw < 1 || a.nw > kTileWaves) return hipErrorInvalidValue;
     const int64_t nreal = (int64_t)a.S * a.nother * a.x.nsub * a.r.nsub;
     if (nreal < 1 || nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
+    const bool elastic = mode == TILE_EL_STRESS || mode == TILE_EL_VEL || mode == TILE_EL_VEL_T || mode == TILE_EL_STRESS_T;
+    const int chunk = elastic && nreal < 4096 ? a.x.nsub * std::max(1, (kXcdChunk + a.x.nsub / 2) / a.x.nsub)
+                                              : (int)((nreal + 7) / 8);
+    const int64_t blocks = xcd_blocks(nreal, chunk);
+    if (blocks >= 1ll << 31) return hipErrorInvalidValue;
     const int threads = 64 * a.nw, nr = (int)nreal;
-    auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, threads, 0, st, a, nr); };
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, (unsigned)blocks, threads, 0, st, a, nr, chunk); };
     const bool keep = a.keep != nullptr, layer = a.pml_mem != nullptr;
     if (mode >= TILE_EL_VEL_T && (keep || layer)) return hipErrorInvalidValue;
     auto pick = [&](auto in) {
@@ -872,8 +896,9 @@ hipError_t launch_tile_z(int op, const TileZArgs &a, hipStream_t st)
     const int64_t ncg = (a.plane + 63) / 64;
     const int64_t nreal = (int64_t)a.nf * a.S * ncg * a.r.nsub;
     if (nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
-    auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
+    const int64_t blocks = xcd_blocks(nreal, kXcdChunk);
+    if (blocks >= 1ll << 31) return hipErrorInvalidValue;
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, (unsigned)blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
     const bool layer = a.pml_mem[0] != nullptr;
     if (!(op == TILE_D1 || (op == TILE_DT && !layer))) return hipErrorInvalidValue;
     if (a.r.inside)
