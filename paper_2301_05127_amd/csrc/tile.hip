@@ -116,26 +116,6 @@ struct Traits<TILE_AC_STRESS_T> : Traits<TILE_AC_VEL> {
     static constexpr bool coef = true;
 };
 
-// Workgroups are dealt round-robin to the 8 XCDs; each XCD gets runs of `chunk` tiles (x
-// fastest), so that neighbours' halos meet in one L2.  One run per XCD, except where elastic
-// tiles are few (they are in flight at nearly the same time: runs of whole rows, about 16
-// tiles, keep the XCDs' reads close together) and for the z derivatives.  Measured, one run per
-// XCD -> 16: elastic 65^3 1800 -> 1745 us a pass, gradient of 2 x 129^3 (1548 tiles) 39.8 -> 38.9
-// ms; z derivatives of 257^3 x 2 205 -> 200 us; but elastic 257^3 x 2 (12 850 tiles) 685 -> 700
-// us, acoustic 16 x 1101 x 706 with layers 7.65 -> 8.17 ms.  Shots of one tile next to each
-// other (the media read once) lose: 64 x 1025^2 382 -> 410 us a kernel.
-constexpr int kXcdChunk = 16;
-
-__device__ __forceinline__ int xcd_range() { return (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)); }
-__device__ __forceinline__ int xcd_order(int chunk)
-{
-    const int i = (int)(blockIdx.x >> 3), r = i / chunk;
-    return (r * 8 + (int)(blockIdx.x & 7)) * chunk + (i - r * chunk);
-}
-
-// workgroups of a launch: whole rounds of 8 chunks, those past the last tile return
-int64_t xcd_blocks(int64_t nreal, int chunk) { return (nreal + 8 * (int64_t)chunk - 1) / (8 * (int64_t)chunk) * 8 * chunk; }
-
 template <int MODE>
 constexpr int rows_slot(int f)
 {

@@ -18,13 +18,12 @@ namespace loss {
 
 namespace {
 
-template <int OP, bool IN>
+template <int OP, bool IN, bool RUNS>
 __global__ void __launch_bounds__(kTileWaves * 64, 8) k_axis_rows(AxisArgs a, int ncg, int nreal)
 {
     constexpr int kEx = kPublish<OP, IN>;
     __shared__ float ex[kTileWaves * kEx];
-    // XCD-aware order: each XCD takes a contiguous range, columns fastest
-    const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    const int lin = RUNS ? xcd_order(kXcdChunk) : xcd_range();
     if (lin >= nreal) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -118,7 +117,7 @@ __global__ void __launch_bounds__(kXWaves * 64) k_axis_x(AxisArgs a, int ngrp, i
 {
     __shared__ float4 tab4[16 * (kLaneF / 4)], tabi4[IN ? 16 * (kLaneInF / 4) : 1];
     __shared__ float4 lds4[kXWaves * kWaveLds / 4];
-    const int lin = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    const int lin = xcd_range();
     if (lin >= nreal) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -181,14 +180,20 @@ hipError_t launch_axis_rows(int op, const AxisArgs &a, hipStream_t st)
     const int64_t ncg = (a.ncol + 63) / 64;
     const int64_t nreal = a.n_outer * ncg * a.t.nsub;
     if (nreal < 1 || nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
-    auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
-    switch (op) {
-    case TILE_D1: a.t.inside ? go(k_axis_rows<TILE_D1, true>) : go(k_axis_rows<TILE_D1, false>); break;
-    case TILE_D2: go(k_axis_rows<TILE_D2, false>); break;
-    case TILE_DT: a.t.inside ? go(k_axis_rows<TILE_DT, true>) : go(k_axis_rows<TILE_DT, false>); break;
-    default: return hipErrorInvalidValue;
-    }
+    const bool runs = ncg >= 64;   // see xcd_order
+    const int64_t blocks = xcd_blocks(nreal, runs ? kXcdChunk : 1);
+    if (blocks >= 1ll << 31) return hipErrorInvalidValue;
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, (unsigned)blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
+    auto pick = [&](auto r) {
+        constexpr bool R = decltype(r)::value;
+        switch (op) {
+        case TILE_D1: a.t.inside ? go(k_axis_rows<TILE_D1, true, R>) : go(k_axis_rows<TILE_D1, false, R>); return true;
+        case TILE_D2: go(k_axis_rows<TILE_D2, false, R>); return true;
+        case TILE_DT: a.t.inside ? go(k_axis_rows<TILE_DT, true, R>) : go(k_axis_rows<TILE_DT, false, R>); return true;
+        }
+        return false;
+    };
+    if (!(runs ? pick(std::true_type{}) : pick(std::false_type{}))) return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
