@@ -136,14 +136,17 @@ def cpu_baseline(w, nsteps, pml=0):
 
 def measured_traffic(workload_key, kernel):
     """HBM bytes per launch of `kernel` from the committed rocprofv3 summary of this
-    workload (profiles/line_kernels_<key>.md, FETCH_SIZE and WRITE_SIZE passes scaled by
-    a 1 GiB copy), or None when the summary was taken on other kernel sources."""
+    workload (profiles/tile_kernels_<key>.md or line_kernels_<key>.md, FETCH_SIZE and
+    WRITE_SIZE passes scaled by a 1 GiB copy), or None when the summary was taken on other
+    kernel sources."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", "line_kernels_%s.md" % workload_key)
-    src = os.path.join(ROOT, "paper_2301_05127_amd", "csrc", "kernels.hip")
+    tiles = "tile" in kernel or "store" in kernel
+    path = os.path.join(ROOT, "profiles", "%s_kernels_%s.md" % ("tile" if tiles else "line", workload_key))
+    src = [os.path.join(ROOT, "paper_2301_05127_amd", "csrc", f)
+           for f in (("tile.hip", "tile_device.h") if tiles else ("kernels.hip",))]
     if not os.path.exists(path):
         return None
-    sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
+    sha = hashlib.sha256(b"".join(open(f, "rb").read() for f in src)).hexdigest()
     for line in open(path):
         if line.startswith("bench-traffic "):
             _, h, js = line.split(" ", 2)
