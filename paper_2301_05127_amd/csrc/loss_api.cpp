@@ -350,8 +350,9 @@ loss_status adj_deriv(loss_sim *s, int axis, const float *in, const float *in_co
         loss_status r = timed_begin(s);
         if (r) return r;
         const hipError_t e = launch_axis_rows(TILE_DT, x, s->st);
-        if (e != hipSuccess) return fail(LOSS_EHIP, std::string("adjoint rows: ") + hipGetErrorString(e));
-        return timed_end(s, KC_ADJ_SOLVE);
+        if (e == hipSuccess) return timed_end(s, KC_ADJ_SOLVE);
+        if (e != hipErrorInvalidValue)   // else more workgroups than a launch takes: the passes below
+            return fail(LOSS_EHIP, std::string("adjoint rows: ") + hipGetErrorString(e));
     }
     LineArgs a = base_args(s, axis);
     a.S = nshots;
@@ -1569,6 +1570,13 @@ loss_status upload_tiles(loss_sim *s)
     const int64_t n = std::max<int64_t>(1, planes * s->tax[0].nsub * s->tax[ra].nsub);
     const int64_t per_tile = planes * s->nx * (ra == 1 ? s->ny : s->nz) / n;
     s->tile_pays = n < 12000 || per_tile >= 600;
+    // one launch of each kind has fewer than 2^32 threads, spare workgroups included; else the line passes
+    auto threads = [&](int64_t tiles, const TileAxis &t) { return (tiles + 4096) * 64 * t.nw; };
+    int64_t most = std::max(threads(n, s->tax[ra]), threads(planes * s->tdt[0].nsub * s->tdt[ra].nsub, s->tdt[ra]));
+    if (ra == 1)
+        for (const TileAxis *t : {&s->tax[2], &s->tdt[2]})
+            most = std::max(most, threads(3 * (int64_t)s->S * ((s->plane + 63) / 64) * t->nsub, *t));
+    if (most >= int64_t(1) << 32) s->tile_built = false;
     return LOSS_OK;
 }
 

@@ -836,7 +836,7 @@ hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t st)
     const int chunk = elastic && nreal < 4096 ? a.x.nsub * std::max(1, (kXcdChunk + a.x.nsub / 2) / a.x.nsub)
                                               : (int)((nreal + 7) / 8);
     const int64_t blocks = xcd_blocks(nreal, chunk);
-    if (blocks >= 1ll << 31) return hipErrorInvalidValue;
+    if (blocks * 64 * a.nw >= 1ll << 32) return hipErrorInvalidValue;   // threads of a launch
     const int threads = 64 * a.nw, nr = (int)nreal;
     auto go = [&](auto k) { hipLaunchKernelGGL(k, (unsigned)blocks, threads, 0, st, a, nr, chunk); };
     const bool keep = a.keep != nullptr, layer = a.pml_mem != nullptr;
@@ -877,7 +877,7 @@ hipError_t launch_tile_z(int op, const TileZArgs &a, hipStream_t st)
     const int64_t nreal = (int64_t)a.nf * a.S * ncg * a.r.nsub;
     if (nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
     const int64_t blocks = xcd_blocks(nreal, kXcdChunk);
-    if (blocks >= 1ll << 31) return hipErrorInvalidValue;
+    if (blocks * 64 * a.nw >= 1ll << 32) return hipErrorInvalidValue;   // threads of a launch
     auto go = [&](auto k) { hipLaunchKernelGGL(k, (unsigned)blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
     const bool layer = a.pml_mem[0] != nullptr;
     if (!(op == TILE_D1 || (op == TILE_DT && !layer))) return hipErrorInvalidValue;

@@ -182,7 +182,7 @@ hipError_t launch_axis_rows(int op, const AxisArgs &a, hipStream_t st)
     if (nreal < 1 || nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
     const bool runs = ncg >= 64;   // see xcd_order
     const int64_t blocks = xcd_blocks(nreal, runs ? kXcdChunk : 1);
-    if (blocks >= 1ll << 31) return hipErrorInvalidValue;
+    if (blocks * 64 * a.nw >= 1ll << 32) return hipErrorInvalidValue;   // threads of a launch
     auto go = [&](auto k) { hipLaunchKernelGGL(k, (unsigned)blocks, 64 * a.nw, 0, st, a, (int)ncg, (int)nreal); };
     auto pick = [&](auto r) {
         constexpr bool R = decltype(r)::value;
@@ -203,6 +203,7 @@ hipError_t launch_axis_x(int op, const AxisArgs &a, hipStream_t st)
     const int64_t nreal = ngrp * a.t.nsub;
     if (nreal < 1 || nreal >= (1ll << 31) - 8) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)((nreal + 7) / 8 * 8);
+    if ((int64_t)blocks * kXWaves * 64 >= 1ll << 32) return hipErrorInvalidValue;   // threads of a launch
     auto go = [&](auto k) { hipLaunchKernelGGL(k, blocks, kXWaves * 64, 0, st, a, (int)ngrp, (int)nreal); };
     switch (op) {
     case TILE_D1: a.t.inside ? go(k_axis_x<TILE_D1, true>) : go(k_axis_x<TILE_D1, false>); break;

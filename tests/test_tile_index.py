@@ -18,7 +18,7 @@ AXES = [(512, 64, 12, 0), (256, 64, 10, 0), (2048, 256, 12, 0), (1024, 128, 12, 
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def host_check(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("tile") / "tile_check")
     csrc = os.path.join(ROOT, "paper_2301_05127_amd", "csrc")
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", csrc,
@@ -29,8 +29,8 @@ def checker(tmp_path_factory):
 @pytest.mark.parametrize("across", [0, 1])
 @pytest.mark.parametrize("op", [0, 1, 2])
 @pytest.mark.parametrize("axis", AXES, ids=["N%d_M%d_h%d_e%d" % a for a in AXES])
-def test_tile_tables_and_indices(checker, axis, op, across):
-    out = subprocess.run([checker] + [str(v) for v in axis + (op, across)], capture_output=True, text=True)
+def test_tile_tables_and_indices(host_check, axis, op, across):
+    out = subprocess.run([host_check] + [str(v) for v in axis + (op, across)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
     N, M, halo, end = axis
     if across and (op == 1 or not 8 <= M < 64 or N <= M):
