@@ -28,10 +28,10 @@
 // The tap sums along the rows come from the rows a wave holds and from the halo rows,
 // which are dealt to the waves of the workgroup.
 //
-// Measured (us per step, line passes -> tiles): elastic 513^3 8350 -> 6210, 257^3 x 2
-// shots 2190 -> 1650, 65^3 155 -> 59; acoustic 2049^2 78 -> 62, 129^2 40 -> 21.  513^3: stress
-// tiles 2575 us (4.4 TB/s of the compulsory bytes), velocity tiles 2019 (4.0), z stores 818
-// (4.0); a 1 GiB copy reaches 5.2 TB/s.
+// Measured (us per step, line passes -> tiles): elastic 513^3 8150 -> 5860-6130, 257^3 x 2
+// shots 2190 -> 1650, 65^3 155 -> 58; acoustic 2049^2 78 -> 62, 129^2 40 -> 21.  513^3: stress
+// tiles 2400-2575 us (4.4-4.7 TB/s of the compulsory bytes), velocity tiles 1890-2019 (4.0-4.3),
+// z stores 740-785 (4.1-4.4); a 1 GiB copy reaches 5.2 TB/s.
 //
 // What a tile does before its first field load counts: a per-tile word says whether it has
 // receivers or a source (each tile walking the sources and the receivers' ranges, behind a
