@@ -946,6 +946,7 @@ loss_status upload_sources(loss_sim *s)
     if (s->d_wavpool) { s->release(s->d_wavpool); s->d_wavpool = nullptr; }
     s->nsrc = (int)sd.size();
     s->src_dev = sd;
+    s->info_dirty = true;
     if (s->nsrc) {
         loss_status r;
         if ((r = s->alloc(&s->d_src, sd.size()))) return r;
@@ -967,6 +968,10 @@ bool is_velocity(const loss_sim *s, int field)
     return field <= LOSS_F_EV3;
 }
 
+loss_status upload_tile_info(loss_sim *s);
+
+// With the traces' new layout goes everything that points into it, the tables of the tiles
+// too: a recompute of the adjoint launches whatever is uploaded.
 loss_status upload_receivers(loss_sim *s)
 {
     if (!s->rec_dirty) return LOSS_OK;
@@ -1068,7 +1073,7 @@ loss_status upload_receivers(loss_sim *s)
     HIPCHK(hipMemsetAsync(s->traces, 0, sizeof(double) * std::max<int64_t>(off, 1), s->st));
     s->rec_dirty = false;
     s->info_dirty = true;
-    return LOSS_OK;
+    return upload_tile_info(s);
 }
 
 // What the tile kernels of a step find at a tile: its receivers (ordered by tile) and
@@ -1127,6 +1132,7 @@ loss_status upload_tile_info(loss_sim *s)
         if (!rec.empty()) HIPCHK(hipMemcpy(*drec, rec.data(), rec.size() * sizeof(RecDev), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(*dinfo, info.data(), info.size() * sizeof(int2), hipMemcpyHostToDevice));
     }
+    s->info_dirty = false;
     return LOSS_OK;
 }
 
@@ -1274,11 +1280,9 @@ loss_status ensure_ready(loss_sim *s)
 {
     if (!s->media_set) return fail(LOSS_ESTATE, "loss_set_media must be called first");
     loss_status r;
-    s->info_dirty = s->info_dirty || s->src_dirty || s->rec_dirty;
     if ((r = upload_sources(s))) return r;
     if ((r = upload_receivers(s))) return r;
     if (s->info_dirty && (r = upload_tile_info(s))) return r;
-    s->info_dirty = false;
     return LOSS_OK;
 }
 

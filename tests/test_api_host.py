@@ -1,0 +1,31 @@
+"""CPU check of the host side of the C ABI (include/loss.h): the calls run against stand-ins
+for the HIP runtime and the kernels (tests/api_check.cpp), which check every copy, every
+receiver and every trace sample a launch is given against the sizes of the allocations."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def api_check(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("api") / "api_check")
+    csrc = os.path.join(ROOT, "paper_2301_05127_amd", "csrc")
+    subprocess.check_call(["g++", "-O1", "-w", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                           "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(ROOT, "tests", "api_check.cpp"),
+                           os.path.join(csrc, "tables.cpp"), "-o", exe])
+
+    def run(*args):
+        out = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True, timeout=100)
+        assert out.returncode == 0 and out.stdout.endswith("ok\n"), (args, out.returncode, out.stdout, out.stderr)
+        return out.stdout.splitlines()[:-1]
+    return run
+
+
+@pytest.mark.parametrize("physics", [0, 1])
+def test_receivers_exchanged_before_the_adjoint(api_check, physics):
+    """The adjoint's recompute records into the traces that exist then: the tiles' receiver
+    tables go with them when loss_get_traces has laid them out anew."""
+    api_check("exchanged_receivers", physics)
