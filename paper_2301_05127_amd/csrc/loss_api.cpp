@@ -999,6 +999,7 @@ loss_status upload_receivers(loss_sim *s)
     if (s->d_rrow) { s->release(s->d_rrow); s->d_rrow = nullptr; }
     if (s->d_rtoff) { s->release(s->d_rtoff); s->d_rtoff = nullptr; }
     if (s->traces) { s->release(s->traces); s->traces = nullptr; }
+    if (s->res_dev) { s->release(s->res_dev); s->res_dev = nullptr; }   // as large as the traces
     loss_status r;
     s->nrec_vel = (int)vel.size();
     s->nrec_str = (int)str.size();

@@ -245,11 +245,25 @@ static void exchanged_receivers(int physics)
     sim.gradient(3);
 }
 
+// a second gradient, of more receivers
+static void added_receivers(int physics)
+{
+    const int n2[3] = {40, 0, 40}, n3[3] = {20, 20, 20}, M[3] = {20, 20, 20};
+    Sim sim(physics, physics == LOSS_ACOUSTIC ? n2 : n3, M, 6, 2, 4);
+    sim.ok(sim.status);
+    for (int nrec : {3, 100}) {
+        sim.receivers(nrec);
+        sim.ok(loss_forward_ckpt(sim.s, 4, 2));
+        sim.gradient(nrec);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     auto arg = [&](int k) { return argc > k ? std::atoi(argv[k]) : 0; };
     if (what == "exchanged_receivers") exchanged_receivers(arg(2));
+    else if (what == "added_receivers") added_receivers(arg(2));
     else check(false, "unknown scenario");
     check(heap.empty(), "%zu allocations left", heap.size());
     if (!fails) std::printf("ok\n");

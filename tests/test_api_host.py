@@ -29,3 +29,9 @@ def test_receivers_exchanged_before_the_adjoint(api_check, physics):
     """The adjoint's recompute records into the traces that exist then: the tiles' receiver
     tables go with them when loss_get_traces has laid them out anew."""
     api_check("exchanged_receivers", physics)
+
+
+@pytest.mark.parametrize("physics", [0, 1])
+def test_gradient_of_more_receivers_than_the_last(api_check, physics):
+    """The device copy of the residuals is as large as the traces of the current receivers."""
+    api_check("added_receivers", physics)
