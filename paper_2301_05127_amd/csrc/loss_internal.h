@@ -217,7 +217,8 @@ enum TileMode : int {
 // carries as sums over the chunks' B and W and the junctions' values around the chunk: p_l at or
 // before its first row, p_r after its last one, p_m inside (l, m, r: 0 the start, 1 the closing
 // right-hand side, 2 .. the junctions inside); transposed: the solution at the row before the
-// chunk likewise (p*), and what each row takes from the values of the piece's junctions
+// chunk likewise (p*; the kernels form it from the chunk's own carry, the host check from
+// these), and what each row takes from the values of the piece's junctions
 struct TileChunk {
     float P[8];                 // products of nf from the chunk's first row on
     float fB[8];                // carry into the elimination
@@ -236,7 +237,7 @@ constexpr int kChunkF = sizeof(TileChunk) / 4;
 constexpr int kLaneF = 52, kLaneInF = 44;
 // Closing row of a piece: w_e = iE E - imE y_{e-1}.  sE: weight of u_e - u_{e-1} in E
 // (slopes: natural end; moments: Hermite row); transposed: 1 at a natural end.
-// cs, ce: moments: sums of the two tap rows; transposed: the transposed taps of y_s and y_e at
+// cs, ce: slopes, moments: sums of the two tap rows; transposed: the transposed taps of y_s and y_e at
 // the closing node; cj: and those of the last junction inside.  m1: transposed: weight of y_s in
 // place of y_{s-1} (-1 at a natural end).
 struct TileEnds {

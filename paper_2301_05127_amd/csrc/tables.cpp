@@ -560,8 +560,6 @@ std::string build_tile(const AxisHost &ax, bool along_x, int op, bool across, Ti
                 sE = -w2;
                 tap_e = [&](int k) { return 6.0 / ax.h * tap(ce, he, e, k); };
             }
-            for (int k = s - kTileHalo; k <= s + kTileHalo; ++k) endc += tap_s(k);
-            for (int k = e - kTileHalo; k <= e + kTileHalo; ++k) endd += tap_e(k);
         } else {
             // T^T on the piece's interior rows; the junction rows follow from the neighbouring
             // interior values: y_J = z_J - y_{J-1} - y_{J+1}, here as taps
@@ -619,6 +617,10 @@ std::string build_tile(const AxisHost &ax, bool along_x, int op, bool across, Ti
             sE = nat_e ? 1.0 : 0.0;
             endc = tap(cs, bh[b], s, e);            // transposed PMBC taps at the closing node
             endd = nat_e ? 0.0 : tap(ce, bh[be], e, e);
+        }
+        if (op != TILE_DT) {            // sums of the tap rows
+            for (int k = s - kTileHalo; k <= s + kTileHalo; ++k) endc += tap_s(k);
+            for (int k = e - kTileHalo; k <= e + kTileHalo; ++k) endd += tap_e(k);
         }
         int hl = std::max(hs, he - m), hr = std::max(he, hs - m), hin = 0;
         for (int j = 0; j < ni; ++j) {

@@ -636,7 +636,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             float B, W;
             Taps tp;
             if (OP == TILE_DT) u[f][0] = u[f][kTileC + 1] = 0.f;
-            rows_local<OP>(rt, u[f], dy[f], B, W);
+            rows_local<OP>(rt, u[f], dy[f], B, W, a.r.s3);
             taps_own<OP, IN>(rt, u[f], 0.f, 0.f, tp);
 #pragma unroll
             for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(pr, hc, w + h * a.nw, yh[f][h], 0.f, 0.f, tp);
@@ -772,7 +772,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     const TileChunk &rt = a.r.chunk[(size_t)lr * kTileWaves + w];
     float B, W;
     Taps tp;
-    rows_local<OP>(rt, u, y, B, W);
+    rows_local<OP>(rt, u, y, B, W, a.r.s3);
     taps_own<OP, IN>(rt, u, 0.f, 0.f, tp);
 #pragma unroll
     for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(p, hc, w + h * a.nw, yh[h], 0.f, 0.f, tp);

@@ -60,10 +60,10 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_axis_rows(AxisArgs a, in
 #pragma unroll
     for (int h = 0; h < kHaloPre; ++h) yh[h] = get(hn[w + h * a.nw]);
     float us = 0.f, ue = 0.f;
-    if constexpr (OP == TILE_D2) {                            // the junctions' own values
+    if constexpr (OP != TILE_DT) {                            // the junctions' own values
         us = get(p.s);
         ue = get(hn[p.hl]);
-        if (w == 0) u[0] = u[1];                              // the first row's one-sided difference
+        if (OP == TILE_D2 && w == 0) u[0] = u[1];             // the first row's one-sided difference
     }
     if (OP == TILE_DT && a.accumulate) {
 #pragma unroll
@@ -73,12 +73,12 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_axis_rows(AxisArgs a, in
     const TileEnds end = a.t.ends[lr];
     float B, W;
     Taps tp;
-    rows_local<OP>(rt, u, y, B, W);
+    rows_local<OP>(rt, u, y, B, W, a.t.s3);
     taps_own<OP, IN>(rt, u, us, ue, tp);
 #pragma unroll
     for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(p, hc, w + h * a.nw, yh[h], us, ue, tp);
     for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) taps_halo<OP, IN>(p, hc, i, get(hn[i]), us, ue, tp);
-    if (OP == TILE_D2 && w == 0) {
+    if (OP != TILE_DT && w == 0) {
         tp.s = fmaf(end.cs, us, tp.s);
         tp.e = fmaf(end.ce, ue, tp.e);
     }

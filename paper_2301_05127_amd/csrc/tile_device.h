@@ -108,21 +108,40 @@ __device__ __forceinline__ float row_rhs(const float (&u)[kTileC + 2], int c)
     else return u[c + 1];
 }
 
-// eliminated rows from a zero carry, B and W of the chunk
+// Taps along x on differences from the junction's own value (see taps_own): slopes but for
+// pieces with junctions inside, where registers are short, and moments.
+template <int OP, bool IN>
+constexpr bool kDiffX = OP == TILE_D2 || (OP == TILE_D1 && !IN);
+
+// In both sweeps of a solve the product that is rounded by itself is the one with the
+// neighbouring row, 0.27 of the sum; the other one is up to 1.3 times it.  (The other way
+// round, slopes along the rows of white noise were 1.04 times as far from 64 bits as those of
+// the passes along one axis, now 0.94, along x 0.96 -> 0.89, of smooth fields 0.96-1.22 ->
+// 0.7-0.9; as many instructions, the same time.)
+__device__ __forceinline__ float sweep(float a, float own, float f, float next) { return fmaf(a, own, f * next); }
+
+// The rows' eliminated values from a zero carry (transposed: their right-hand sides, see
+// rows_finish), B and W of the chunk.
 template <int OP>
 __device__ __forceinline__ void rows_local(const TileChunk &t, const float (&u)[kTileC + 2], float (&y)[kTileC],
-                                           float &B, float &W)
+                                           float &B, float &W, float s3)
 {
-    float v = 0.f;
+    float z[kTileC], v = 0.f;
 #pragma unroll
     for (int c = 0; c < kTileC; ++c) {
-        v = fmaf(t.nf[c], v, t.sc[c] * row_rhs<OP>(u, c));
-        y[c] = v;
+        if constexpr (OP == TILE_DT) {
+            y[c] = t.sc[c] * u[c + 1];          // weights of 1 and 0
+            v = sweep(s3, y[c], t.nf[c], v);
+        } else {
+            v = sweep(t.sc[c], row_rhs<OP>(u, c), t.nf[c], v);
+            y[c] = v;
+        }
+        z[c] = v;
     }
     B = v;
     v = 0.f;
 #pragma unroll
-    for (int c = kTileC - 1; c >= 0; --c) v = fmaf(t.g[c], v, t.fi[c] * y[c]);
+    for (int c = kTileC - 1; c >= 0; --c) v = sweep(t.fi[c], z[c], t.g[c], v);
     W = v;
 }
 
@@ -135,18 +154,21 @@ struct Taps {
     float l = 0.f;              // transposed: the taps left of the piece of its start alone
 };
 
-// from a wave's own rows; moments take the differences from the junction's own value (us, ue),
-// whose share is added once: the taps cancel to the second difference of the field
+// from a wave's own rows.  Single axes take slopes and moments of the differences from the
+// junction's own value (us, ue), whose share is added once: the taps cancel to a difference of
+// the field, and of the values themselves the rounding of the products would remain.  The tile
+// kernels take the values (us = ue = 0): two more loads a field cost them 1-4 %, and their
+// junctions round as those of the passes along one axis do
 template <int OP, bool IN>
 __device__ __forceinline__ void taps_own(const TileChunk &t, const float (&u)[kTileC + 2], float us, float ue, Taps &p)
 {
     if (t.any_ts != 0.f) {          // uniform
 #pragma unroll
-        for (int c = 0; c < kTileC; ++c) p.s = fmaf(t.ts[c], OP == TILE_D2 ? u[c + 1] - us : u[c + 1], p.s);
+        for (int c = kTileC - 1; c >= 0; --c) p.s = fmaf(t.ts[c], u[c + 1] - us, p.s);   // the nearest last
     }
     if (t.any_te != 0.f) {
 #pragma unroll
-        for (int c = 0; c < kTileC; ++c) p.e = fmaf(t.te[c], OP == TILE_D2 ? u[c + 1] - ue : u[c + 1], p.e);
+        for (int c = 0; c < kTileC; ++c) p.e = fmaf(t.te[c], u[c + 1] - ue, p.e);
     }
     if (IN && t.any_in) {
 #pragma unroll
@@ -196,13 +218,18 @@ __device__ __forceinline__ void rows_publish(const Piece &pc, float *ex, int lan
 // row for the last chunk).  Transposed slopes: the rows of G^T y from the solution y, its
 // neighbours and the values y_J of the piece's junctions; the taps left of the piece alone
 // give y at the row before it (`first`: the piece's first chunk); dn = the value at the
-// closing node.
+// closing node.  Differences of y cancel on smooth fields, so its rounding counts: the system
+// is solved for s3 = 3/h times y, the elimination runs again from the carry (adding the carry
+// to the first run's rows rounds each once more), and the row before a chunk follows from this
+// chunk's carry and first row, so that its rounding is theirs (a sum over the chunks' results
+// has its own).  Against 64 bits, error over that of the passes along one axis: white noise
+// 1.06-1.08 -> 0.93, smooth fields 1.16-1.2 -> 0.94 (x_row likewise: 0.96 -> 0.86, 0.98 -> 0.81).
 template <int STRIDE, int OP, bool IN>
 __device__ __forceinline__ float rows_finish(const Piece &pc, const TileChunk &t, const float *ex, int nw, int lane,
                                              float (&y)[kTileC], const TileEnds *end = nullptr, float s3 = 0.f,
                                              bool first = false, int nown = 0, float *dn = nullptr)
 {
-    float ph = 0.f, pe = 0.f, yin = 0.f, win = 0.f, prev = 0.f;
+    float ph = 0.f, pe = 0.f, yin = 0.f, win = 0.f;
     const int ol = IN ? 128 + 64 * t.l : 128, orr = IN ? 128 + 64 * t.r : 192;
 #pragma unroll
     for (int j = 0; j < kTileWaves; ++j) {
@@ -214,10 +241,6 @@ __device__ __forceinline__ float rows_finish(const Piece &pc, const TileChunk &t
             yin = fmaf(t.fB[j], B, yin);
             win = fmaf(t.zB[j], B, win);
             win = fmaf(t.zW[j], W, win);
-            if constexpr (OP == TILE_DT) {
-                prev = fmaf(t.pB[j], B, prev);
-                prev = fmaf(t.pW[j], W, prev);
-            }
         }
     }
     if constexpr (OP != TILE_DT) {
@@ -231,32 +254,43 @@ __device__ __forceinline__ float rows_finish(const Piece &pc, const TileChunk &t
         }
         win = fmaf(t.zph, pm, win);
     }
-    win = fmaf(t.zE, pe, win);
+    win = fmaf(OP == TILE_DT ? s3 * t.zE : t.zE, pe, win);
+    if constexpr (OP == TILE_DT) {
+        float v = yin;
+#pragma unroll
+        for (int c = 0; c < kTileC; ++c) {
+            v = sweep(s3, y[c], t.nf[c], v);
+            y[c] = v;
+        }
+    }
     float v = win;
 #pragma unroll
     for (int c = kTileC - 1; c >= 0; --c) {
-        v = fmaf(t.g[c], v, t.fi[c] * fmaf(t.P[c], yin, y[c]));
+        v = sweep(t.fi[c], OP == TILE_DT ? y[c] : fmaf(t.P[c], yin, y[c]), t.g[c], v);
         y[c] = v;
     }
     if constexpr (OP == TILE_DT) {
-        prev = fmaf(t.pE, pe, prev);
+        float prev = 0.f;
+        if (!first) {               // the last row of the chunk before, by its own factors
+            const TileChunk &b = (&t)[-1];
+            prev = sweep(b.fi[kTileC - 1], yin, b.g[kTileC - 1], y[0]);
+        }
         if (first) {                // the row before the piece; a natural end mirrors y_0
             prev = 0.f;
-            for (int j = 0; j < nw; ++j) prev -= ex[j * STRIDE + kPublish<OP, IN> - 64 + lane];
+            for (int j = 0; j < nw; ++j) prev = fmaf(-s3, ex[j * STRIDE + kPublish<OP, IN> - 64 + lane], prev);
             if (end->m1 != 0.f) prev = -y[0];
         }
         float wl = 0.f;
 #pragma unroll
         for (int c = 0; c < kTileC; ++c)
             if (c == nown - 1) wl = y[c];
-        float d = fmaf(s3, fmaf(end->sE, win, wl), fmaf(end->cs, ph, end->ce * pe));
+        float d = fmaf(end->sE, win, wl) + fmaf(end->cs, ph, end->ce * pe);
         float lo = prev;
 #pragma unroll
         for (int c = 0; c < kTileC; ++c) {
             const float own = y[c];
-            float r = s3 * (lo - (c < kTileC - 1 ? y[c < kTileC - 1 ? c + 1 : c] : win));
+            y[c] = lo - (c < kTileC - 1 ? y[c < kTileC - 1 ? c + 1 : c] : win);
             lo = own;
-            y[c] = r;
         }
         if (t.any_cs != 0.f) {
 #pragma unroll
@@ -327,7 +361,7 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const fl
         if (k + 16 < p.hs) pl = fmaf(cs.y, at(os.y), pl);
         pl = row_sum(pl);
     }
-    const float us = OP == TILE_D2 ? L[kRowOwn] : 0.f, ue = OP == TILE_D2 ? L[kRowRight] : 0.f;
+    const float us = kDiffX<OP, IN> ? L[kRowOwn] : 0.f, ue = kDiffX<OP, IN> ? L[kRowRight] : 0.f;
     float ph = cs.x * (at(os.x) - us), pe = ce.x * (at(oe.x) - ue);
     ph = fmaf(cs.y, at(os.y) - us, ph);
     pe = fmaf(ce.y, at(oe.y) - ue, pe);
@@ -337,7 +371,7 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const fl
     }
     ph = row_sum(ph);
     pe = row_sum(pe);
-    if constexpr (OP == TILE_D2) {
+    if constexpr (kDiffX<OP, IN>) {
         ph = fmaf(p.end.cs, us, ph);
         pe = fmaf(p.end.ce, ue, pe);
     }
@@ -369,28 +403,49 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const fl
         else if constexpr (OP == TILE_D2) return (hi - own) - (own - lo);
         else return own;
     };
-    float y0 = sc.x * rhs(ul, u.x, u.y), y1 = sc.y * rhs(u.x, u.y, u.z);
-    float y2 = sc.z * rhs(u.y, u.z, u.w), y3 = sc.w * rhs(u.z, u.w, ur);
-    if (IN && OP == TILE_D1 && p.ni > 0) {
-        const float4 q = ti[0];
-        y0 = fmaf(q.x, pm, y0);
-        y1 = fmaf(q.y, pm, y1);
-        y2 = fmaf(q.z, pm, y2);
-        y3 = fmaf(q.w, pm, y3);
+    float y0, y1, y2, y3;
+    // (junctions inside: the products with the rows' own values held over the carries; otherwise
+    // the layer's elastic kernels spill 10 registers more and run 6 % longer)
+    constexpr bool kOwn = IN && OP == TILE_D1;
+    if constexpr (kOwn) {
+        y0 = sc.x * rhs(ul, u.x, u.y);
+        y1 = sc.y * rhs(u.x, u.y, u.z);
+        y2 = sc.z * rhs(u.y, u.z, u.w);
+        y3 = sc.w * rhs(u.z, u.w, ur);
+        if (p.ni > 0) {
+            const float4 q = ti[0];
+            y0 = fmaf(q.x, pm, y0);
+            y1 = fmaf(q.y, pm, y1);
+            y2 = fmaf(q.z, pm, y2);
+            y3 = fmaf(q.w, pm, y3);
+        }
+        y1 = fmaf(nf.y, y0, y1);
+        y2 = fmaf(nf.z, y1, y2);
+        y3 = fmaf(nf.w, y2, y3);
+    } else {
+        const float4 k = OP == TILE_DT ? make_float4(p.s3 * sc.x, p.s3 * sc.y, p.s3 * sc.z, p.s3 * sc.w) : sc;
+        y0 = k.x * rhs(ul, u.x, u.y);
+        y1 = sweep(k.y, rhs(u.x, u.y, u.z), nf.y, y0);
+        y2 = sweep(k.z, rhs(u.y, u.z, u.w), nf.z, y1);
+        y3 = sweep(k.w, rhs(u.z, u.w, ur), nf.w, y2);
     }
-    y1 = fmaf(nf.y, y0, y1);
-    y2 = fmaf(nf.z, y1, y2);
-    y3 = fmaf(nf.w, y2, y3);
     float B = fmaf(a.w, ph, y3);
     B = fmaf(a.x, row_shift_up_fill<1>(B, 0.f), B);
     B = fmaf(a.y, row_shift_up_fill<2>(B, 0.f), B);
     B = fmaf(a.z, row_shift_up_fill<4>(B, 0.f), B);
     const float yin = row_shift_up_fill<1>(B, ph);
-    y0 = fmaf(P.x, yin, y0);
-    y1 = fmaf(P.y, yin, y1);
-    y2 = fmaf(P.z, yin, y2);
-    y3 = fmaf(P.w, yin, y3);
-    float we = fmaf(-p.end.imE, y3, p.end.iE * pe);   // of the closing lane
+    if constexpr (OP == TILE_DT) {
+        y0 = sweep(p.s3, sc.x * u.x, nf.x, yin);       // weights of 1 and 0
+        y1 = sweep(p.s3, sc.y * u.y, nf.y, y0);
+        y2 = sweep(p.s3, sc.z * u.z, nf.z, y1);
+        y3 = sweep(p.s3, sc.w * u.w, nf.w, y2);
+    } else {
+        y0 = fmaf(P.x, yin, y0);
+        y1 = fmaf(P.y, yin, y1);
+        y2 = fmaf(P.z, yin, y2);
+        y3 = fmaf(P.w, yin, y3);
+    }
+    float we = fmaf(-p.end.imE, y3, p.end.iE * (OP == TILE_DT ? p.s3 * pe : pe));   // of the closing lane
     we = __shfl(we, p.kc, 16);
     __builtin_amdgcn_sched_barrier(0);
     const float4 fi = t[2], g = t[3], b = t[6];
@@ -404,24 +459,24 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const fl
     W = fmaf(b.z, row_shift_down_fill<4>(W, 0.f), W);
     const float win = row_shift_down_fill<1>(W, we);
     float4 r;
-    r.w = fmaf(g.w, win, t3);
-    r.z = fmaf(g.z, r.w, t2);
-    r.y = fmaf(g.y, r.z, t1);
-    r.x = fmaf(g.x, r.y, t0);
+    r.w = kOwn ? fmaf(g.w, win, t3) : sweep(fi.w, y3, g.w, win);
+    r.z = kOwn ? fmaf(g.z, r.w, t2) : sweep(fi.z, y2, g.z, r.w);
+    r.y = kOwn ? fmaf(g.y, r.z, t1) : sweep(fi.y, y1, g.y, r.z);
+    r.x = kOwn ? fmaf(g.x, r.y, t0) : sweep(fi.x, y0, g.x, r.y);
     float dn = we;                  // the closing node
     if constexpr (OP == TILE_DT) {
         const float4 c1 = t[11], c2 = t[12];
         const int cc = (p.m - 1) & 3;
         const float wl = __shfl(cc == 0 ? r.x : (cc == 1 ? r.y : (cc == 2 ? r.z : r.w)), p.kc, 16);
-        dn = fmaf(p.s3, fmaf(p.end.sE, we, wl), fmaf(p.end.cs, ph, p.end.ce * pe));
-        const float before = p.end.m1 != 0.f ? -r.x : -pl;   // a natural end mirrors y_0
+        dn = fmaf(p.end.sE, we, wl) + fmaf(p.end.cs, ph, p.end.ce * pe);
+        const float before = p.end.m1 != 0.f ? -r.x : -p.s3 * pl;   // a natural end mirrors y_0
         const float lo = row_shift_up_fill<1>(r.w, before);
         const float hi = row_shift_down_fill<1>(r.x, we);
         float4 o;
-        o.x = fmaf(p.s3, lo - r.y, fmaf(c1.x, ph, c2.x * pe));
-        o.y = fmaf(p.s3, r.x - r.z, fmaf(c1.y, ph, c2.y * pe));
-        o.z = fmaf(p.s3, r.y - r.w, fmaf(c1.z, ph, c2.z * pe));
-        o.w = fmaf(p.s3, r.z - hi, fmaf(c1.w, ph, c2.w * pe));
+        o.x = (lo - r.y) + fmaf(c1.x, ph, c2.x * pe);
+        o.y = (r.x - r.z) + fmaf(c1.y, ph, c2.y * pe);
+        o.z = (r.y - r.w) + fmaf(c1.z, ph, c2.z * pe);
+        o.w = (r.z - hi) + fmaf(c1.w, ph, c2.w * pe);
         if (IN && p.ni > 0) {
 #pragma unroll
             for (int j = 0; j < kTileIn; ++j)
