@@ -1499,7 +1499,11 @@ loss_status upload_tiles(loss_sim *s)
                 else if (k == 0 && op != TILE_DT) return LOSS_OK;
             }
         }
-        tiles[k] = planes * built[k][TILE_D1][0].nsub * built[k][TILE_D1][ra].nsub;
+        auto pieces = [&](int axis) {   // an axis without pieces across junctions keeps those between
+            const int n = built[k][TILE_D1][axis].nsub;
+            return n > 0 ? n : built[0][TILE_D1][axis].nsub;
+        };
+        tiles[k] = planes * pieces(0) * pieces(ra);
     }
     // Pieces across junctions hold more nodes, at a tap sum per junction inside.  Tile kernels:
     // they pay when there are tiles enough and clearly fewer of them.  Measured (us per step,
@@ -1508,7 +1512,9 @@ loss_status upload_tiles(loss_sim *s)
     // (9 k) 968 / 898; acoustic 8 x 1025^2, patches of 16 388 / 105, of 32 130 / 100, of 48
     // (3.9 k) 104 / 102; 2049^2, patches of 48 (1.8 k) 59 / 65; 129^2, patches of 16 17 / 21;
     // 16 x 1101 x 706 with layers, patches of 128 (1.1 times as many) 147 / 166.
-    const bool across = tiles[1] > 0 && tiles[0] > 2500 && 2 * tiles[0] >= 3 * tiles[1];
+    // An axis without such pieces counts and keeps those between: 8 x 1025^2, patches of 16 along
+    // x and 64 along z 233 / 96 (line passes 144), of 24 and 96 198 / 126 (154).
+    const bool across = tiles[0] > 2500 && 2 * tiles[0] >= 3 * tiles[1];
     std::vector<char> blob;   // every table, uploaded at once
     std::vector<std::pair<const TileHost *, size_t>> placed;
     std::vector<std::pair<TileAxis *, size_t>> users;

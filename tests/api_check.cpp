@@ -121,6 +121,7 @@ hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t)
             }
     }
     launches["tiles"] = tiles;
+    launches["waves"] = a.nw;
     return count("tile " + std::to_string(mode));
 }
 hipError_t launch_tile_z(int op, const TileZArgs &, hipStream_t) { return count("tile_z " + std::to_string(op)); }
@@ -258,13 +259,29 @@ static void added_receivers(int physics)
     }
 }
 
+// prints the schedule of a grid (0 tiles, 1 line passes), and the tiles of a pass and the waves of
+// a tile when it runs as tiles
+static void route(int physics, const int (&n)[3], const int (&M)[3], int halo, int shots)
+{
+    Sim sim(physics, n, M, halo, shots, 0);
+    sim.ok(sim.status);
+    int32_t schedule = -1;
+    sim.ok(loss_autotune_choice(sim.s, 3, &schedule));
+    sim.ok(loss_set_shape(sim.s, 3, 0));
+    sim.ok(loss_step(sim.s, 1));
+    std::printf("%d %ld %ld\n", (int)schedule, (long)launches["tiles"], (long)launches["waves"]);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     auto arg = [&](int k) { return argc > k ? std::atoi(argv[k]) : 0; };
     if (what == "exchanged_receivers") exchanged_receivers(arg(2));
     else if (what == "added_receivers") added_receivers(arg(2));
-    else check(false, "unknown scenario");
+    else if (what == "route" && argc == 11) {
+        const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
+        route(arg(2), n, M, arg(9), arg(10));
+    } else check(false, "unknown scenario");
     check(heap.empty(), "%zu allocations left", heap.size());
     if (!fails) std::printf("ok\n");
     return fails ? 1 : 0;

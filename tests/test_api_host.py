@@ -35,3 +35,21 @@ def test_receivers_exchanged_before_the_adjoint(api_check, physics):
 def test_gradient_of_more_receivers_than_the_last(api_check, physics):
     """The device copy of the residuals is as large as the traces of the current receivers."""
     api_check("added_receivers", physics)
+
+
+# physics, intervals, patches, halo, shots: tiles of a pass
+TILES = [
+    (0, (1024, 0, 1024), (16, 64, 64), 8, 8, 17 * 16 * 8),    # across junctions along x alone
+    (0, (1024, 0, 1024), (64, 64, 16), 8, 8, 17 * 16 * 8),    # along the rows alone
+    (0, (1024, 0, 1024), (16, 64, 16), 8, 8, 17 * 16 * 8),
+    (0, (1024, 0, 1024), (64, 64, 64), 8, 8, 17 * 16 * 8),    # no patch shorter than a piece
+    (1, (256, 256, 256), (16, 64, 64), 8, 1, 5 * 4 * 257),
+]
+
+
+@pytest.mark.parametrize("case", TILES, ids=["%s_%s" % ("x".join(map(str, c[1])), "x".join(map(str, c[2]))) for c in TILES])
+def test_tiles_of_mixed_patches(api_check, case):
+    """Pieces across junctions are counted, and taken, axis by axis."""
+    physics, n, M, halo, shots, tiles = case
+    out = api_check("route", physics, *n, *M, halo, shots)
+    assert int(out[0].split()[1]) == tiles, out
