@@ -100,8 +100,9 @@ typedef int32_t loss_status;
                                   the x and y derivatives and updates every output).  The
                                   tile schedule applies to halos of at most 20 nodes and
                                   fields of one shot below 2^30 elements; grids of many
-                                  small tiles (patches of less than about 24 intervals)
-                                  keep the line passes unless asked (loss_set_shape) */
+                                  small tiles (patches below 8 intervals on more tiles than
+                                  run at once) keep the line passes unless asked
+                                  (loss_set_shape) */
 
 typedef struct {
     int32_t physics;      /* LOSS_ACOUSTIC (ndim 2) or LOSS_ELASTIC (ndim 3) */

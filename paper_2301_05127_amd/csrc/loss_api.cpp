@@ -1573,14 +1573,25 @@ loss_status upload_tiles(loss_sim *s)
         t.lanes_in = (const float4 *)(d + o[6]);
     }
     s->tile_built = true;
-    // A tile costs its latency however few nodes it holds: patches below kTileInGap, between
-    // whose junctions the pieces stay.  Measured (us per step, tile against line passes at
-    // their default shapes): elastic 129^3, tiles of 8 x 8 972 / 495, of 16 x 16 248 / 409;
-    // acoustic 1025^2 x 8 shots, tiles of 16 x 16 (256 nodes, 33 k tiles) 388 / 166, of 24 x 24
-    // 195 / 172, of 32 x 32 131 / 142.
+    // A tile costs its latency however few nodes it holds, so grids of many small tiles (patches
+    // below kTileInGap, between whose junctions the pieces stay) are left to the line passes.
+    // Estimates of a step in us, without what both share: a round of resident tiles (at most 5
+    // per compute unit by LDS, 24 acoustic or 16 elastic waves by registers) 8, elastic 4 and 0.5
+    // per wave of a tile; the line passes 15, elastic 20, and 10, elastic 30, per million nodes.
+    // They choose the faster schedule (within 3 %) on 536 of 543 grids measured (patches of 2 to
+    // 128, 33^2 to 1025^2 and 33^3 to 201^3, 1 to 8 shots), on the others one up to 1.22 times
+    // slower.
+    // Some of them (us per step, tiles / line passes): acoustic 301^2 x 2, patches of 4 (11 250
+    // tiles) 132 / 37, 201^2 of 7 (841) 22 / 31, 401^2 of 7 (3364) 51 / 35, 401^2 x 8 of 8 (1352
+    // across junctions) 45 / 62, 701^2 x 4 of 4 and 64 (7700) 209 / 98; elastic 65^3 of 5 (11 k)
+    // 336 / 205, 49^3 of 5 (4.9 k) 160 / 171, 129^3 of 4, 64 and 8 (8.3 k) 676 / 490, of 64, 4
+    // and 8 (12.4 k) 413 / 463.
     const int64_t n = std::max<int64_t>(1, planes * s->tax[0].nsub * s->tax[ra].nsub);
-    const int64_t per_tile = planes * s->nx * (ra == 1 ? s->ny : s->nz) / n;
-    s->tile_pays = n < 12000 || per_tile >= 600;
+    const bool ac = ra == 2;
+    const int nw = std::max(1, s->tax[ra].nw);
+    const int64_t resident = 256 * std::min(5, (ac ? 24 : 16) / nw), rounds = (n + resident - 1) / resident;
+    const double nodes = (double)planes * s->nx * (ra == 1 ? s->ny : s->nz);
+    s->tile_pays = rounds * (ac ? 8.0 : 4.0 + 0.5 * nw) <= (ac ? 15.0 + 1e-5 * nodes : 20.0 + 3e-5 * nodes);
     // one launch of each kind has fewer than 2^32 threads, spare workgroups included; else the line passes
     auto threads = [&](int64_t tiles, const TileAxis &t) { return (tiles + 4096) * 64 * t.nw; };
     int64_t most = std::max(threads(n, s->tax[ra]), threads(planes * s->tdt[0].nsub * s->tdt[ra].nsub, s->tdt[ra]));

@@ -53,3 +53,28 @@ def test_tiles_of_mixed_patches(api_check, case):
     physics, n, M, halo, shots, tiles = case
     out = api_check("route", physics, *n, *M, halo, shots)
     assert int(out[0].split()[1]) == tiles, out
+
+
+# physics, intervals, patches, halo, shots: the faster schedule as measured (0 tiles, 1 line passes)
+SCHEDULES = [
+    (0, (300, 0, 300), (4, 1, 4), 8, 2, 1),
+    (0, (400, 0, 400), (7, 1, 7), 8, 1, 1),
+    (0, (200, 0, 200), (7, 1, 7), 8, 1, 0),
+    (0, (64, 0, 64), (2, 1, 2), 8, 2, 1),
+    (0, (64, 0, 64), (2, 1, 2), 8, 1, 0),
+    (0, (700, 0, 700), (4, 1, 64), 8, 4, 1),
+    (0, (400, 0, 400), (8, 1, 8), 8, 8, 0),
+    (0, (2048, 0, 2048), (256, 1, 256), 12, 1, 0),
+    (1, (64, 64, 64), (5, 5, 5), 8, 1, 1),
+    (1, (48, 48, 48), (5, 5, 5), 8, 1, 0),
+    (1, (128, 128, 128), (4, 64, 8), 8, 1, 1),
+    (1, (128, 128, 128), (16, 16, 16), 8, 1, 0),
+]
+
+
+@pytest.mark.parametrize("case", SCHEDULES, ids=["%s_%s_S%d" % ("x".join(map(str, c[1])), "x".join(map(str, c[2])), c[4])
+                                                 for c in SCHEDULES])
+def test_schedule_of_small_tiles(api_check, case):
+    physics, n, M, halo, shots, schedule = case
+    out = api_check("route", physics, *n, *M, halo, shots)
+    assert int(out[0].split()[0]) == schedule, out
