@@ -1602,15 +1602,22 @@ loss_status upload_tiles(loss_sim *s)
     return LOSS_OK;
 }
 
+int deriv_op(int order) { return order == 1 ? TILE_D1 : (order == 2 ? TILE_D2 : TILE_DT); }
+
+// Whether loss_deriv works straight on dense device arrays: tables for the operator and fields
+// below 2^30 nodes (the arrays must not overlap, and a batch must fit a launch, besides).
+bool deriv_direct_ok(const loss_sim *s, int axis, int order)
+{
+    return s->tile_built && s->top[deriv_op(order)][axis].nsub > 0 && s->nodes < (int64_t(1) << 30);
+}
+
 // loss_deriv straight from and to dense device fields, the whole batch in one launch; false
-// in *done where it does not apply (no tile tables for the operator, fields of 2^30 nodes or
-// more, arrays that overlap: the caller then stages the fields).
+// in *done where it does not apply (the caller then stages the fields).
 loss_status deriv_direct(loss_sim *s, int axis, int order, const float *in, float *out, int64_t batch, bool *done)
 {
-    const int op = order == 1 ? TILE_D1 : (order == 2 ? TILE_D2 : TILE_DT);
+    const int op = deriv_op(order);
     const uintptr_t a0 = (uintptr_t)in, b0 = (uintptr_t)out, len = sizeof(float) * (uintptr_t)(batch * s->nodes);
-    *done = s->tile_built && s->top[op][axis].nsub > 0 && s->nodes < (int64_t(1) << 30) &&
-            (a0 + len <= b0 || b0 + len <= a0) && ((a0 | b0) & 3) == 0;
+    *done = deriv_direct_ok(s, axis, order) && (a0 + len <= b0 || b0 + len <= a0) && ((a0 | b0) & 3) == 0;
     if (!*done) return LOSS_OK;
     AxisArgs x{};
     x.in = in;
@@ -2288,7 +2295,7 @@ loss_status loss_deriv(loss_sim *s, int32_t axis, int32_t order, const float *in
     }
     for (int64_t b0 = 0; b0 < batch; b0 += s->S) {
         const int64_t nb = std::min<int64_t>(s->S, batch - b0);
-        if (mem == LOSS_MEM_HOST) {
+        if (mem == LOSS_MEM_HOST && deriv_direct_ok(s, axis, order)) {
             // through dense device copies of the chunk in the temporaries (each holds S padded
             // fields or more)
             bool done = false;

@@ -259,6 +259,22 @@ static void added_receivers(int physics)
     }
 }
 
+// derivatives of host arrays: each field crosses to the device once
+static void host_deriv(int physics, const int (&n)[3], const int (&M)[3], int halo, int end_mode)
+{
+    Sim sim(physics, n, M, halo, 2, 0, end_mode);
+    sim.ok(sim.status);
+    const int batch = 5;
+    std::vector<float> in(batch * sim.nodes, 1.f), out(in);
+    for (int axis = 0; axis < 3; axis += physics == LOSS_ACOUSTIC ? 2 : 1)
+        for (int order : {1, 2, -1}) {
+            bytes_h2d = 0;
+            sim.ok(loss_deriv(sim.s, axis, order, in.data(), out.data(), batch, LOSS_MEM_HOST));
+            check(bytes_h2d == (int64_t)in.size() * 4, "axis %d order %d: %ld bytes of %zu", axis, order, (long)bytes_h2d, in.size() * 4);
+        }
+    for (const auto &l : launches) std::printf("%s %ld\n", l.first.c_str(), (long)l.second);
+}
+
 // prints the schedule of a grid (0 tiles, 1 line passes), and the tiles of a pass and the waves of
 // a tile when it runs as tiles
 static void route(int physics, const int (&n)[3], const int (&M)[3], int halo, int shots)
@@ -281,6 +297,9 @@ int main(int argc, char **argv)
     else if (what == "route" && argc == 11) {
         const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
         route(arg(2), n, M, arg(9), arg(10));
+    } else if (what == "host_deriv" && argc == 11) {
+        const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
+        host_deriv(arg(2), n, M, arg(9), arg(10));
     } else check(false, "unknown scenario");
     check(heap.empty(), "%zu allocations left", heap.size());
     if (!fails) std::printf("ok\n");

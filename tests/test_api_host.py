@@ -78,3 +78,15 @@ def test_schedule_of_small_tiles(api_check, case):
     physics, n, M, halo, shots, schedule = case
     out = api_check("route", physics, *n, *M, halo, shots)
     assert int(out[0].split()[0]) == schedule, out
+
+
+# physics, intervals, patches, halo, end mode: whole calls direct; halos beyond the tile passes;
+# transposes of periodic lines and of halos wider than the patches staged
+HOST_DERIV = [(0, (60, 0, 50), (30, 1, 25), 8, 0), (0, (60, 0, 50), (30, 1, 25), 24, 0), (0, (60, 0, 48), (30, 1, 24), 8, 2),
+              (1, (20, 18, 16), (10, 9, 8), 6, 0), (1, (20, 18, 16), (5, 6, 8), 9, 0)]
+
+
+@pytest.mark.parametrize("case", HOST_DERIV, ids=["p%d_%s_h%de%d" % (c[0], "x".join(map(str, c[2])), c[3], c[4]) for c in HOST_DERIV])
+def test_host_derivatives_upload_once(api_check, case):
+    physics, n, M, halo, end = case
+    api_check("host_deriv", physics, *n, *M, halo, end)
