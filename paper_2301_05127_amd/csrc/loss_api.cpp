@@ -1083,10 +1083,18 @@ loss_status upload_tile_info(loss_sim *s)
 {
     const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
     const int nother = ra == 1 ? s->nz : 1;
-    auto piece = [&](int axis, int node) {   // a piece owns its first node; the last one node N too
+    if (!s->tile_built) {
+        s->info_dirty = false;
+        return LOSS_OK;
+    }
+    // the piece of each node: a piece owns its first node, the last one node N too
+    std::vector<int> of[3];
+    for (int axis : {0, ra}) {
         const std::vector<int> &b = s->tile_sb[axis];
-        return std::max(0, std::min((int)(std::upper_bound(b.begin(), b.end(), node) - b.begin()) - 1, (int)b.size() - 2));
-    };
+        of[axis].resize(b.back() + 1, (int)b.size() - 2);
+        for (int k = 0; k + 1 < (int)b.size(); ++k) std::fill(of[axis].begin() + b[k], of[axis].begin() + b[k + 1], k);
+    }
+    auto piece = [&](int axis, int node) { return of[axis][node]; };
     const int ntx = (int)s->tile_sb[0].size() - 1, ntr = (int)s->tile_sb[ra].size() - 1;
     auto tile = [&](int64_t shot, int o, int lr, int lx) { return ((shot * nother + o) * ntr + lr) * ntx + lx; };
     for (int vel = 0; vel < 2; ++vel) {
@@ -1094,32 +1102,37 @@ loss_status upload_tile_info(loss_sim *s)
         int2 **dinfo = vel ? &s->d_info_vel : &s->d_info_str;
         if (*drec) { s->release(*drec); *drec = nullptr; }
         if (*dinfo) { s->release(*dinfo); *dinfo = nullptr; }
-        std::vector<std::pair<int64_t, RecDev>> list;
-        for (int shot = 0; shot < s->S && s->d.trace_len > 0; ++shot) {
-            const RecHost &rh = s->rec[shot];
-            if (is_velocity(s, rh.comp) != (vel != 0)) continue;
-            for (size_t k = 0; k + 2 < rh.idx.size(); k += 3) {
-                const int x = rh.idx[k], y = rh.idx[k + 1], z = rh.idx[k + 2];
-                RecDev d{};
-                d.shot = shot;
-                d.comp = rh.comp;
-                d.node = (int64_t)z * s->plane + (int64_t)y * s->pitch + x;
-                d.trace_off = s->rec_off[shot] + (int64_t)(k / 3) * s->d.trace_len;
-                list.push_back({tile(shot, ra == 1 ? z : 0, piece(ra, ra == 1 ? y : z), piece(0, x)), d});
-            }
-        }
-        bool any = !list.empty();
+        bool any = false;
         for (const SrcDev &d : s->src_dev) any = any || (d.force != 0) == (vel != 0);
-        if (!any || !s->tile_built) continue;
-        std::stable_sort(list.begin(), list.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
-        std::vector<RecDev> rec;
+        size_t nrec = 0;
+        for (const RecHost &rh : s->rec)
+            if (s->d.trace_len > 0 && is_velocity(s, rh.comp) == (vel != 0)) nrec += rh.idx.size() / 3;
+        if (!any && nrec == 0) continue;
+        // receivers counted, then placed by tile in the order given
         std::vector<int2> info((size_t)s->S * nother * ntr * ntx, make_int2(0, 0));
-        for (const auto &e : list) {
-            int2 &i = info[e.first];
-            if (i.y == 0) i.x = (int)rec.size();
-            i.y += 2;
-            rec.push_back(e.second);
+        std::vector<RecDev> rec(nrec);
+        auto each = [&](auto f) {
+            for (int shot = 0; shot < s->S && nrec > 0; ++shot) {
+                const RecHost &rh = s->rec[shot];
+                if (is_velocity(s, rh.comp) != (vel != 0)) continue;
+                for (size_t k = 0; k + 2 < rh.idx.size(); k += 3) {
+                    const int x = rh.idx[k], y = rh.idx[k + 1], z = rh.idx[k + 2];
+                    f(info[tile(shot, ra == 1 ? z : 0, piece(ra, ra == 1 ? y : z), piece(0, x))], shot, rh.comp, x, y, z, k / 3);
+                }
+            }
+        };
+        each([](int2 &i, int, int, int, int, int, size_t) { i.y++; });
+        int first = 0;
+        for (int2 &i : info) {
+            i.x = first;
+            first += i.y;
+            i.y = 0;
         }
+        each([&](int2 &i, int shot, int comp, int x, int y, int z, size_t k) {
+            rec[i.x + i.y++] = RecDev{shot, comp, (int64_t)z * s->plane + (int64_t)y * s->pitch + x,
+                                      s->rec_off[shot] + (int64_t)k * s->d.trace_len};
+        });
+        for (int2 &i : info) i.y *= 2;
         for (const SrcDev &d : s->src_dev) {
             if ((d.force != 0) != (vel != 0)) continue;
             const int r0 = ra == 1 ? d.y0 : d.z0, nr = ra == 1 ? d.by : d.bz;

@@ -114,11 +114,24 @@ hipError_t launch_tile(int mode, const TileArgs &a, hipStream_t)
     const int64_t tiles = (int64_t)a.S * a.nother * a.x.nsub * a.r.nsub;
     if (a.info) {
         check((size_t)tiles * sizeof(int2) <= room(a.info), "words of the tiles");
-        for (int64_t t = 0; t < tiles && !fails; ++t)
+        launches["receivers"] = 0;
+        for (int64_t t = 0; t < tiles && !fails; ++t) {
+            const int plane = (int)(t / (a.x.nsub * a.r.nsub)), lr = (int)(t / a.x.nsub % a.r.nsub), lx = (int)(t % a.x.nsub);
+            auto owns = [](const TileAxis &x, int l, int64_t node) {   // a piece's nodes; node N with the last one
+                return node >= x.piece[l].x && (node < x.piece[l].y || (node == x.N && x.piece[l].y == x.N));
+            };
             for (int k = a.info[t].x; k < a.info[t].x + a.info[t].y / 2; ++k) {
                 check((size_t)(k + 1) * sizeof(RecDev) <= room(a.rec), "receiver %d of a tile", k);
-                traces_hold(a.traces, a.rec[k].trace_off, a.trace_len);
+                if (fails) break;
+                const RecDev &r = a.rec[k];
+                traces_hold(a.traces, r.trace_off, a.trace_len);
+                const int64_t o = a.nother > 1 ? r.node / a.ostride : 0, in = r.node - o * a.ostride;
+                check(r.shot == plane / a.nother && o == plane % a.nother && owns(a.r, lr, in / a.rstride) &&
+                          owns(a.x, lx, in % a.rstride), "receiver %d in tile %ld", k, (long)t);
+                check(k == a.info[t].x || r.trace_off > a.rec[k - 1].trace_off, "order of the receivers of tile %ld", (long)t);
+                launches["receivers"]++;
             }
+        }
     }
     launches["tiles"] = tiles;
     launches["waves"] = a.nw;
@@ -246,6 +259,23 @@ static void exchanged_receivers(int physics)
     sim.gradient(3);
 }
 
+// receivers on every node of some planes: each is in its tile's list, once
+static void tile_receivers(int physics, const int (&n)[3], const int (&M)[3], int halo, int shots)
+{
+    Sim sim(physics, n, M, halo, shots, 3);
+    sim.ok(sim.status);
+    const int nrec = (int)std::min<int64_t>(sim.nodes, (n[0] + 1) * 40);
+    std::vector<int32_t> idx;
+    for (int i = nrec - 1; i >= 0; --i)
+        for (int v : {i % (n[0] + 1), i * 7 % (n[1] + 1), i * 3 % (n[2] + 1)}) idx.push_back(v);
+    for (int k = 0; k < shots; ++k)
+        sim.ok(loss_add_receivers(sim.s, k, nrec, idx.data(), physics == LOSS_ACOUSTIC ? LOSS_F_SIGMA : LOSS_F_EV1 + 4 * (k % 2)));
+    sim.ok(loss_set_shape(sim.s, 3, 0));
+    sim.ok(loss_step(sim.s, 1));
+    const int64_t last = launches["receivers"], want = (int64_t)nrec * (physics == LOSS_ACOUSTIC ? shots : (shots + 1) / 2);
+    check(last == want, "%ld receivers in tiles, %ld given", (long)last, (long)want);
+}
+
 // a second gradient, of more receivers
 static void added_receivers(int physics)
 {
@@ -297,6 +327,9 @@ int main(int argc, char **argv)
     else if (what == "route" && argc == 11) {
         const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
         route(arg(2), n, M, arg(9), arg(10));
+    } else if (what == "tile_receivers" && argc == 11) {
+        const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
+        tile_receivers(arg(2), n, M, arg(9), arg(10));
     } else if (what == "host_deriv" && argc == 11) {
         const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
         host_deriv(arg(2), n, M, arg(9), arg(10));

@@ -90,3 +90,11 @@ HOST_DERIV = [(0, (60, 0, 50), (30, 1, 25), 8, 0), (0, (60, 0, 50), (30, 1, 25),
 def test_host_derivatives_upload_once(api_check, case):
     physics, n, M, halo, end = case
     api_check("host_deriv", physics, *n, *M, halo, end)
+
+
+@pytest.mark.parametrize("case", [(0, (130, 0, 97), (64, 1, 16), 8, 3), (0, (63, 0, 64), (63, 1, 64), 6, 1),
+                                  (1, (33, 20, 17), (16, 10, 16), 6, 2)], ids=["acoustic", "one_piece", "elastic"])
+def test_receivers_by_tile(api_check, case):
+    """Receivers go to the tile that updates their node, in the order given."""
+    physics, n, M, halo, shots = case
+    api_check("tile_receivers", physics, *n, *M, halo, shots)
