@@ -638,8 +638,8 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             if (OP == TILE_DT) u[f][0] = u[f][kTileC + 1] = 0.f;
             rows_local<OP>(rt, u[f], dy[f], B, W, a.r.s3);
             taps_own<OP, IN>(rt, u[f], 0.f, 0.f, tp);
-#pragma unroll
-            for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(pr, hc, w + h * a.nw, yh[f][h], 0.f, 0.f, tp);
+#pragma unroll                       // right of the closing row the nearest come last
+            for (int h = kHaloPre - 1; h >= 0; --h) taps_halo<OP, IN>(pr, hc, w + h * a.nw, yh[f][h], 0.f, 0.f, tp);
             for (int i = w + kHaloPre * a.nw; i < nhr; i += a.nw)     // few waves, wide taps
                 taps_halo<OP, IN>(pr, hc, i,
                               ld(buf(a.in[f] + pl.fb), (unsigned)hn[i] * pl.rs4, pl.vx) *
@@ -775,7 +775,7 @@ __global__ void __launch_bounds__(kTileWaves * 64, 8) k_tile_z(TileZArgs a, int 
     rows_local<OP>(rt, u, y, B, W, a.r.s3);
     taps_own<OP, IN>(rt, u, 0.f, 0.f, tp);
 #pragma unroll
-    for (int h = 0; h < kHaloPre; ++h) taps_halo<OP, IN>(p, hc, w + h * a.nw, yh[h], 0.f, 0.f, tp);
+    for (int h = kHaloPre - 1; h >= 0; --h) taps_halo<OP, IN>(p, hc, w + h * a.nw, yh[h], 0.f, 0.f, tp);
     for (int i = w + kHaloPre * a.nw; i < nh; i += a.nw) taps_halo<OP, IN>(p, hc, i, get(hn[i]), 0.f, 0.f, tp);
     if (OP == TILE_D1 && clos) {
         float ue = 0.f, ul = 0.f;

@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(kXWaves * 64) k_axis_x(AxisArgs a, int ngrp, i
     const int k = lane & 15;
 #pragma unroll
     for (int it = 0; it < kTileC / 4; ++it)
-        x_row<OP, IN>(xp, tab4 + k * (kLaneF / 4), tabi4 + k * (kLaneInF / 4), L + (4 * it + (lane >> 4)) * kRowPitch, k);
+        x_row<OP, IN, true>(xp, tab4 + k * (kLaneF / 4), tabi4 + k * (kLaneInF / 4), L + (4 * it + (lane >> 4)) * kRowPitch, k);
     wave_sync();
     if (lane >= p.m + (xp.last ? 1 : 0)) return;
 #pragma unroll

@@ -108,16 +108,16 @@ __device__ __forceinline__ float row_rhs(const float (&u)[kTileC + 2], int c)
     else return u[c + 1];
 }
 
-// Taps along x on differences from the junction's own value (see taps_own): slopes but for
-// pieces with junctions inside, where registers are short, and moments.
-template <int OP, bool IN>
-constexpr bool kDiffX = OP == TILE_D2 || (OP == TILE_D1 && !IN);
+// Taps along x on differences from the junction's own value (see taps_own): those of single axes
+// (ALONE), slopes but for pieces with junctions inside, where registers are short, and moments.
+template <int OP, bool IN, bool ALONE>
+constexpr bool kDiffX = OP == TILE_D2 || (OP == TILE_D1 && !IN && ALONE);
 
 // In both sweeps of a solve the product that is rounded by itself is the one with the
 // neighbouring row, 0.27 of the sum; the other one is up to 1.3 times it.  (The other way
 // round, slopes along the rows of white noise were 1.04 times as far from 64 bits as those of
-// the passes along one axis, now 0.94, along x 0.96 -> 0.89, of smooth fields 0.96-1.22 ->
-// 0.7-0.9; as many instructions, the same time.)
+// the passes along one axis, now 0.94, along x 0.96 -> 0.88, of smooth fields 0.96-1.22 ->
+// 0.8-0.95; as many instructions, the same time.)
 __device__ __forceinline__ float sweep(float a, float own, float f, float next) { return fmaf(a, own, f * next); }
 
 // The rows' eliminated values from a zero carry (transposed: their right-hand sides, see
@@ -346,7 +346,7 @@ __device__ __forceinline__ XPiece x_piece(const TileAxis &t, const Piece &p, int
     return x;
 }
 
-template <int OP, bool IN>
+template <int OP, bool IN, bool ALONE = false>
 __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const float4 *ti, float *L, int k)
 {
     __builtin_amdgcn_sched_barrier(0);   // one row group at a time: interleaved they spill
@@ -361,7 +361,7 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const fl
         if (k + 16 < p.hs) pl = fmaf(cs.y, at(os.y), pl);
         pl = row_sum(pl);
     }
-    const float us = kDiffX<OP, IN> ? L[kRowOwn] : 0.f, ue = kDiffX<OP, IN> ? L[kRowRight] : 0.f;
+    const float us = kDiffX<OP, IN, ALONE> ? L[kRowOwn] : 0.f, ue = kDiffX<OP, IN, ALONE> ? L[kRowRight] : 0.f;
     float ph = cs.x * (at(os.x) - us), pe = ce.x * (at(oe.x) - ue);
     ph = fmaf(cs.y, at(os.y) - us, ph);
     pe = fmaf(ce.y, at(oe.y) - ue, pe);
@@ -371,7 +371,7 @@ __device__ __forceinline__ void x_row(const XPiece &p, const float4 *t, const fl
     }
     ph = row_sum(ph);
     pe = row_sum(pe);
-    if constexpr (kDiffX<OP, IN>) {
+    if constexpr (kDiffX<OP, IN, ALONE>) {
         ph = fmaf(p.end.cs, us, ph);
         pe = fmaf(p.end.ce, ue, pe);
     }
