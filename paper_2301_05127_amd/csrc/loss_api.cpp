@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -178,15 +179,31 @@ struct loss_sim {
     int pml_w = 0;
 
     template <class T>
-    loss_status alloc(T **p, size_t count)
+    loss_status alloc(T **p, size_t count, bool spare = true)
     {
         void *q = nullptr;
         if (count == 0) count = 1;
         hipError_t e = hipMalloc(&q, count * sizeof(T));
-        if (e != hipSuccess) return fail(LOSS_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+        if (e != hipSuccess && spare && release_operands()) e = hipMalloc(&q, count * sizeof(T));
+        if (e != hipSuccess) {
+            (void)hipGetLastError();   // a refused allocation is no error of the launches that follow
+            return fail(LOSS_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+        }
         allocs.push_back(q);
         *p = (T *)q;
         return LOSS_OK;
+    }
+    // the operands a gradient keeps for its tile passes, which it can do without; whether there were any
+    bool release_operands()
+    {
+        bool any = false;
+        for (int k = 11; k < 15; ++k)
+            if (adj_el[k]) {
+                release(adj_el[k]);
+                adj_el[k] = nullptr;
+                any = true;
+            }
+        return any;
     }
     void release(void *p)
     {
@@ -1141,8 +1158,10 @@ loss_status upload_tile_info(loss_sim *s)
                 for (int lr = piece(ra, r0); lr <= piece(ra, r0 + nr - 1); ++lr)
                     for (int lx = piece(0, d.x0); lx <= piece(0, d.x0 + d.bx - 1); ++lx) info[tile(d.shot, o, lr, lx)].y |= 1;
         }
-        loss_status r;
-        if ((r = s->alloc(drec, rec.size())) || (r = s->alloc(dinfo, info.size()))) return r;
+        if (s->alloc(drec, rec.size()) || s->alloc(dinfo, info.size())) {   // no room: the line passes
+            s->tile_built = false;
+            break;
+        }
         if (!rec.empty()) HIPCHK(hipMemcpy(*drec, rec.data(), rec.size() * sizeof(RecDev), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(*dinfo, info.data(), info.size() * sizeof(int2), hipMemcpyHostToDevice));
     }
@@ -1492,7 +1511,17 @@ loss_status upload_axis(loss_sim *s, int axis)
     return LOSS_OK;
 }
 
-// Tables of the tile passes; a grid they do not apply to keeps the line passes.
+void drop_tiles(loss_sim *s)
+{
+    s->tile_built = false;
+    for (int axis = 0; axis < 3; ++axis) {
+        s->tax[axis] = s->tdt[axis] = TileAxis();
+        for (auto &op : s->top) op[axis] = TileAxis();
+    }
+}
+
+// Tables of the tile passes; a grid they do not apply to, or a handle without room for them,
+// keeps the line passes.
 loss_status upload_tiles(loss_sim *s)
 {
     if (s->shot_stride >= (int64_t(1) << 30)) return LOSS_OK;   // 32-bit byte offsets within a shot's field
@@ -1571,8 +1600,10 @@ loss_status upload_tiles(loss_sim *s)
         }
     }
     char *d = nullptr;
-    loss_status r = s->alloc(&d, blob.size());
-    if (r) return r;
+    if (s->alloc(&d, blob.size())) {   // no room for the tables: the line passes
+        drop_tiles(s);
+        return LOSS_OK;
+    }
     HIPCHK(hipMemcpy(d, blob.data(), blob.size(), hipMemcpyHostToDevice));
     for (const auto &u : users) {
         TileAxis &t = *u.first;
@@ -1771,12 +1802,8 @@ loss_status elastic_adjoint(loss_sim *s, const double *residual, int32_t param, 
     // passes run one by one)
     bool tiles = tile_adjoint_ok(s);
     for (int k = 11; tiles && k < 15; ++k)
-        if (!s->adj_el[k] && s->alloc(&s->adj_el[k], fe)) tiles = false;
-    if (!tiles) {
-        for (int k = 11; k < 15; ++k)
-            if (s->adj_el[k]) { s->release(s->adj_el[k]); s->adj_el[k] = nullptr; }
-        (void)hipGetLastError();   // a refused allocation is no error of the launches that follow
-    }
+        if (!s->adj_el[k] && s->alloc(&s->adj_el[k], fe, false)) tiles = false;
+    if (!tiles) s->release_operands();
     double *gb = s->grad_pad + 2 * ss;
     float *const *A = s->adj_el;
     float *Y = s->adj_el[9], *Wop = s->adj_el[10];
@@ -1964,14 +1991,21 @@ loss_status loss_create(const loss_desc *desc, void *hip_stream, loss_sim **out)
     s->nx = (int)d.n[0] + 1;
     s->ny = d.ndim == 3 ? (int)d.n[1] + 1 : 1;
     s->nz = (int)d.n[2] + 1;
-    // rows start on 64-byte boundaries (a wave's row of 64 floats then covers whole sectors),
-    // unless that padding would take a field over the size limit below or that of the static
-    // scratch
-    s->pitch = ((int64_t)s->nx + 15) / 16 * 16;
+    // Rows start on 64-byte boundaries (a wave's row of 64 floats then covers whole sectors)
+    // where that padding adds at most a sixteenth to rows padded to 16 bytes, the handle is
+    // small on its device, and no field goes over the size limit below or that of the static
+    // scratch.  us per pass, 16 / 64 bytes: rows of 513 94.1 / 92.0 k, of 257 40.97 / 40.65 k, of
+    // 184 14.26 / 14.06 k, of 1025 (gradient) 257.8 / 254.5 k; but of 129 (9 % more bytes, gradient)
+    // 37.6 / 39.0 k, of 65 (18 %) 1.70 / 1.75 k.
+    const int64_t rows = (int64_t)s->ny * s->nz, p16 = ((int64_t)s->nx + 15) / 16 * 16;
+    s->pitch = ((int64_t)s->nx + 3) / 4 * 4;
     {
-        const int64_t p4 = ((int64_t)s->nx + 3) / 4 * 4, rows = (int64_t)s->ny * s->nz;
-        auto over = [&](int64_t limit) { return s->pitch * rows > limit && p4 * rows <= limit; };
-        if (over((int64_t(1) << 31) - 1) || over(kStaticSlot)) s->pitch = p4;
+        size_t free_mem = 0, total_mem = 0;
+        if (hipMemGetInfo(&free_mem, &total_mem) != hipSuccess) total_mem = 0;
+        const double state = (s->nf + 3.0) * s->S * (double)(p16 * rows) * sizeof(float);
+        auto over = [&](int64_t limit) { return p16 * rows > limit && s->pitch * rows <= limit; };
+        if (p16 - s->pitch <= s->pitch / 16 && state <= total_mem / 16.0 && !over((int64_t(1) << 31) - 1) && !over(kStaticSlot))
+            s->pitch = p16;
     }
     s->plane = s->pitch * s->ny;
     s->shot_stride = s->plane * s->nz;
@@ -2030,7 +2064,11 @@ loss_status loss_create(const loss_desc *desc, void *hip_stream, loss_sim **out)
         if (a == 1 && d.ndim == 2) continue;
         if ((r = upload_axis(s, a))) return bail(r);
     }
-    if ((r = upload_tiles(s))) return bail(r);
+    try {
+        if ((r = upload_tiles(s))) return bail(r);
+    } catch (const std::bad_alloc &) {   // no host memory to build them in
+        drop_tiles(s);
+    }
     if (hipMemcpy(s->d_fields, s->f.data(), sizeof(float *) * s->nf, hipMemcpyHostToDevice) != hipSuccess)
         return bail(fail(LOSS_EHIP, "pointer table upload"));
     if (hipEventCreate(&s->ev0) != hipSuccess || hipEventCreate(&s->ev1) != hipSuccess)

@@ -23,6 +23,7 @@ static void check(bool ok, const char *fmt, ...)
 
 static std::map<char *, size_t> heap;                  // device allocations
 static size_t heap_used = 0, heap_limit = ~size_t(0);
+static int64_t allocations = 0, refused = -1;          // number of the allocation that fails
 static int64_t bytes_h2d = 0;
 static std::map<std::string, int64_t> launches;
 
@@ -39,7 +40,7 @@ static bool on_device(const void *p) { return room(p) != ~size_t(0); }
 extern "C" {
 hipError_t hipMalloc(void **p, size_t n)
 {
-    if (n > heap_limit || heap_used > heap_limit - n) return hipErrorOutOfMemory;
+    if (allocations++ == refused || n > heap_limit || heap_used > heap_limit - n) return hipErrorOutOfMemory;
     *p = std::malloc(n);
     if (!*p) return hipErrorOutOfMemory;
     heap[(char *)*p] = n;
@@ -54,6 +55,12 @@ hipError_t hipFree(void *p)
     heap_used -= it->second;
     heap.erase(it);
     std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemGetInfo(size_t *free_mem, size_t *total)
+{
+    *total = std::min(heap_limit, size_t(288) << 30);
+    *free_mem = *total - heap_used;
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::calloc(1, n); return hipSuccess; }
@@ -276,6 +283,51 @@ static void tile_receivers(int physics, const int (&n)[3], const int (&M)[3], in
     check(last == want, "%ld receivers in tiles, %ld given", (long)last, (long)want);
 }
 
+// the row pitch of a handle, on a device of `gib` GiB
+static void pitch(int nx, int nz, int shots, int gib)
+{
+    heap_limit = size_t(gib) << 30;
+    const int n[3] = {nx - 1, 0, nz - 1}, M[3] = {std::min(nx - 1, 64), 1, std::min(nz - 1, 64)};
+    Sim sim(LOSS_ACOUSTIC, n, M, 6, shots, 0);
+    sim.ok(sim.status);
+    std::printf("%ld\n", sim.s ? (long)sim.s->pitch : 0);
+}
+
+// each allocation of a short run refused in turn: an error or a run without what it was for, and
+// nothing left behind; prints how many runs went through
+static void refusals(int physics)
+{
+    const int n2[3] = {40, 0, 40}, n3[3] = {20, 20, 20}, M[3] = {20, 20, 20};
+    int ran = 0;
+    for (int64_t k = 0;; ++k) {
+        allocations = 0;
+        refused = k;
+        Sim sim(physics, physics == LOSS_ACOUSTIC ? n2 : n3, M, 6, 2, 4);
+        loss_status r = sim.status;
+        if (!r) sim.receivers(5);
+        if (!r) r = loss_step(sim.s, 2);
+        check(r == LOSS_OK || r == LOSS_ENOMEM, "allocation %ld: status %d", (long)k, (int)r);
+        if (allocations <= k) break;
+        ran += r == LOSS_OK;
+    }
+    refused = -1;
+    std::printf("%d\n", ran);
+}
+
+// the operands that a gradient keeps for its tile passes make room for other allocations
+static void operands()
+{
+    const int n[3] = {20, 20, 20}, M[3] = {20, 20, 20};
+    Sim sim(LOSS_ELASTIC, n, M, 6, 2, 8);
+    sim.ok(sim.status);
+    sim.receivers(3);
+    sim.ok(loss_forward_ckpt(sim.s, 8, 4));
+    sim.gradient(3);
+    check(sim.s->adj_el[11] != nullptr, "no operands kept");
+    heap_limit = heap_used + 15 * 4 * field_elems(sim.s);     // the run below needs 18 fields more, less 4
+    sim.ok(loss_forward_ckpt(sim.s, 8, 2));
+}
+
 // a second gradient, of more receivers
 static void added_receivers(int physics)
 {
@@ -327,7 +379,10 @@ int main(int argc, char **argv)
     else if (what == "route" && argc == 11) {
         const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
         route(arg(2), n, M, arg(9), arg(10));
-    } else if (what == "tile_receivers" && argc == 11) {
+    } else if (what == "pitch") pitch(arg(2), arg(3), arg(4), arg(5));
+    else if (what == "refusals") refusals(arg(2));
+    else if (what == "operands") operands();
+    else if (what == "tile_receivers" && argc == 11) {
         const int n[3] = {arg(3), arg(4), arg(5)}, M[3] = {arg(6), arg(7), arg(8)};
         tile_receivers(arg(2), n, M, arg(9), arg(10));
     } else if (what == "host_deriv" && argc == 11) {

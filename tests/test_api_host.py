@@ -98,3 +98,27 @@ def test_receivers_by_tile(api_check, case):
     """Receivers go to the tile that updates their node, in the order given."""
     physics, n, M, halo, shots = case
     api_check("tile_receivers", physics, *n, *M, halo, shots)
+
+
+# nodes along x and z, shots, GiB of the device: floats per row
+PITCH = [(17, 40, 1, 288, 20), (5, 40, 1, 288, 8), (65, 65, 1, 288, 68), (129, 129, 4, 288, 132), (184, 40, 1, 288, 192),
+         (257, 40, 1, 288, 272), (513, 40, 1, 288, 528), (1024, 40, 1, 288, 1024), (513, 2049, 50, 4, 516)]
+
+
+@pytest.mark.parametrize("case", PITCH, ids=["x%d_S%d_%dGiB" % (c[0], c[2], c[3]) for c in PITCH])
+def test_row_padding_is_small(api_check, case):
+    """Rows are padded past 16 bytes where that costs little memory, of a row and of the device."""
+    out = api_check("pitch", *case[:4])
+    assert int(out[0]) == case[4], out
+
+
+@pytest.mark.parametrize("physics", [0, 1])
+def test_runs_without_room_for_the_tiles(api_check, physics):
+    """The tables of the tiles, their receivers and their words are optional: three refusals
+    that a run survives, on the line passes."""
+    out = api_check("refusals", physics)
+    assert int(out[0]) == 3, out
+
+
+def test_gradient_operands_make_room(api_check):
+    api_check("operands")
