@@ -455,9 +455,7 @@ TileArgs tile_args(const loss_sim *s)
     TileArgs t{};
     const int ra = s->d.physics == LOSS_ACOUSTIC ? 2 : 1;
     t.S = s->S;
-    t.nx = s->nx;
     t.row_axis = ra;
-    t.nrow = ra == 1 ? s->ny : s->nz;
     t.nother = ra == 1 ? s->nz : 1;
     t.rstride = ra == 1 ? s->pitch : s->plane;
     t.ostride = ra == 1 ? s->plane : 0;
@@ -527,7 +525,6 @@ loss_status tile_z3(loss_sim *s, int kc, const float *const *in, int var0, float
     z.nf = 3;
     z.S = s->S;
     z.nx = s->nx;
-    z.ny = s->ny;
     z.pitch = s->pitch;
     z.plane = s->plane;
     z.shot_stride = s->shot_stride;
@@ -552,7 +549,8 @@ loss_status tile_z3(loss_sim *s, int kc, const float *const *in, int var0, float
     return timed_end(s, kc);
 }
 
-// stress sub-flow B(dt); `in_step`: part of a step (sources, receivers, step counter)
+// stress sub-flow B(dt) of a step, with its sources, receivers and step counter; keep: the
+// derivatives stored as well (or null)
 loss_status stress_stage_tiles(loss_sim *s, float *keep)
 {
     float *const *F = s->f.data();
@@ -1728,7 +1726,6 @@ loss_status adj_tile_z3(loss_sim *s, const float *const *in, const float *coef)
     z.nf = 3;
     z.S = s->S;
     z.nx = s->nx;
-    z.ny = s->ny;
     z.pitch = s->pitch;
     z.plane = s->plane;
     z.shot_stride = s->shot_stride;

@@ -266,7 +266,7 @@ struct TileArgs {
     int64_t keep_stride;
     const float *c0, *c1, *c2; // media times dt: l2m, lambda, mu / b / K
     float alpha;
-    int S, nx, nrow, nother;   // nodes along x and the rows; planes per shot
+    int S, nother;             // shots; planes per shot
     int64_t rstride, ostride, shot_stride;
     int row_axis;              // 1 or 2
     int nw;                    // waves per workgroup: kTileC rows each
@@ -324,7 +324,7 @@ struct TileZArgs {
     const float *in[3];
     const float *coef;         // transposed slopes: coefficient of the inputs, or null
     float *out[3];
-    int nf, S, nx, ny;
+    int nf, S, nx;
     int64_t pitch, plane, shot_stride;
     int nw;
     TileAxis r;

@@ -47,13 +47,15 @@ __device__ __forceinline__ void st(Buf b, unsigned row, unsigned col, float v)
 // Workgroups are dealt round-robin to the 8 XCDs; each XCD gets runs of `chunk` tiles (x
 // fastest), so that neighbours' halos meet in one L2.  One run per XCD, except where elastic
 // tiles are few (they are in flight at nearly the same time: runs of whole rows, about 16
-// tiles, keep the XCDs' reads close together) and for the z derivatives.  Measured, one run per
-// XCD -> 16: elastic 65^3 1800 -> 1745 us a pass, gradient of 2 x 129^3 (1548 tiles) 39.8 -> 38.9
-// ms; z derivatives of 257^3 x 2 205 -> 200 us; but elastic 257^3 x 2 (12 850 tiles) 685 -> 700
-// us, acoustic 16 x 1101 x 706 with layers 7.65 -> 8.17 ms.  Shots of one tile next to each
-// other (the media read once) lose: 64 x 1025^2 382 -> 410 us a kernel.
-// A single axis: runs of 16 where a field's columns are many (z of 2 x 257^3, second derivative,
-// 77 -> 72 us; 5 column groups, 204 rows, transposed: 90 -> 94).
+// tiles, keep the XCDs' reads close together) and for the z derivatives (of 257^3 x 2 205 / 200
+// us a kernel).  Measured, one run per XCD / runs of 16: elastic us per step 65^3 (260 tiles)
+// 48.4 / 46.5, 193^3 (2316) 393 / 386, 225^3 (3600) 583 / 575, 257 x 257 x 201 (4020) 706 / 695,
+// 257^3 (5140) 842 / 840, x 2 (10 280) 1617 / 1641, 225^3 x 2 (7200) 1118 / 1127; acoustic 16 x
+// 1101 x 706 with layers 7.65 / 8.17 ms a pass.  Shots of one tile next to each other (the media
+// read once) lose: 64 x 1025^2 382 -> 410 us a kernel.
+// A single axis: runs of 16 where a field's columns are many.  Second derivatives along z of
+// 2 x 257^3 (1032 column groups) 77 / 71 us; of 2 to 100 groups within 2 % either way, 128
+// groups 60 / 55, 200 groups 61 / 63, 400 and 1000 the same.
 constexpr int kXcdChunk = 16;
 
 __device__ __forceinline__ int xcd_range() { return (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)); }
