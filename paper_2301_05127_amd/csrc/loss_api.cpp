@@ -1996,13 +1996,12 @@ loss_status loss_create(const loss_desc *desc, void *hip_stream, loss_sim **out)
     // 37.6 / 39.0 k, of 65 (18 %) 1.70 / 1.75 k.
     const int64_t rows = (int64_t)s->ny * s->nz, p16 = ((int64_t)s->nx + 15) / 16 * 16;
     s->pitch = ((int64_t)s->nx + 3) / 4 * 4;
-    {
+    auto over = [&](int64_t limit) { return p16 * rows > limit && s->pitch * rows <= limit; };
+    if (p16 > s->pitch && p16 - s->pitch <= s->pitch / 16 && !over((int64_t(1) << 31) - 1) && !over(kStaticSlot)) {
         size_t free_mem = 0, total_mem = 0;
         if (hipMemGetInfo(&free_mem, &total_mem) != hipSuccess) total_mem = 0;
         const double state = (s->nf + 3.0) * s->S * (double)(p16 * rows) * sizeof(float);
-        auto over = [&](int64_t limit) { return p16 * rows > limit && s->pitch * rows <= limit; };
-        if (p16 - s->pitch <= s->pitch / 16 && state <= total_mem / 16.0 && !over((int64_t(1) << 31) - 1) && !over(kStaticSlot))
-            s->pitch = p16;
+        if (state <= total_mem / 16.0) s->pitch = p16;
     }
     s->plane = s->pitch * s->ny;
     s->shot_stride = s->plane * s->nz;

@@ -638,8 +638,13 @@ __global__ void __launch_bounds__(kTileWaves * 64, kTileWavesPerSimd<MODE>) k_ti
             if (OP == TILE_DT) u[f][0] = u[f][kTileC + 1] = 0.f;
             rows_local<OP>(rt, u[f], dy[f], B, W, a.r.s3);
             taps_own<OP, IN>(rt, u[f], 0.f, 0.f, tp);
-#pragma unroll                       // right of the closing row the nearest come last
-            for (int h = kHaloPre - 1; h >= 0; --h) taps_halo<OP, IN>(pr, hc, w + h * a.nw, yh[f][h], 0.f, 0.f, tp);
+            // Right of the closing row the nearest come last; in the layer's kernels first: there
+            // the other order costs registers (velocities of 16 x 1101 x 706 71 -> 79 us a kernel).
+#pragma unroll
+            for (int g = 0; g < kHaloPre; ++g) {
+                const int h = LAYER ? g : kHaloPre - 1 - g;
+                taps_halo<OP, IN>(pr, hc, w + h * a.nw, yh[f][h], 0.f, 0.f, tp);
+            }
             for (int i = w + kHaloPre * a.nw; i < nhr; i += a.nw)     // few waves, wide taps
                 taps_halo<OP, IN>(pr, hc, i,
                               ld(buf(a.in[f] + pl.fb), (unsigned)hn[i] * pl.rs4, pl.vx) *
